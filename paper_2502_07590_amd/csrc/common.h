@@ -81,6 +81,18 @@ __device__ __forceinline__ float row16_max(float x)
     return x;
 }
 
+// Inclusive prefix sum inside each half-wave (lanes 0..31 and lanes 32..63 separately).
+__device__ __forceinline__ int half_scan(int x)
+{
+    int s = x;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);  // row_shr:1 (rows of 16 lanes, zero fill)
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);  // row_shr:2
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);  // row_shr:4
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);  // row_shr:8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);  // row_bcast15 into rows 1 and 3
+    return s;
+}
+
 // ---- a lane's share of one [d]-row: CH channels, kept as raw 32-bit words --------------------
 template <typename T, int CH> struct RowChunk {
     static constexpr int NW = CH * (int)sizeof(T) / 4;
@@ -406,9 +418,15 @@ dsv_status launch_profile_sparsity(const dsv_problem &p, const void *Q, const vo
 dsv_status launch_idx_validate(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx,
                                unsigned long long *report_dev, int64_t *report_host, hipStream_t st);
 // Stable transposition: every list ascending in the query index, the same result from run to run.
-// cnt: scratch of idx_transpose_bytes(p) bytes (per-key totals, then per-(query chunk, key) counters); col: [B*H, L+1] int64.
+// ws: scratch of idx_transpose_bytes(p) bytes; col: [B*H, L+1] int64.
 size_t idx_transpose_bytes(const dsv_problem &p);
 dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx,
-                                int32_t *idxT, int64_t *col, int32_t *cnt, size_t cnt_bytes, hipStream_t st);
+                                int32_t *idxT, int64_t *col, void *ws, size_t ws_bytes, hipStream_t st);
+// out = the rows of idx in ascending order (same layout); can_sort_rows: whether this L is covered.
+bool can_sort_rows(const dsv_problem &p);
+dsv_status launch_sort_rows(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx, int32_t *out,
+                            hipStream_t st);
+// col[bh, 0 .. L] = exclusive prefix sums of cnt[bh, 0 .. L - 1] for the heads of one table.
+dsv_status launch_col_scan(const int32_t *cnt, int64_t *col, int L, const HeadTable &tab, hipStream_t st);
 
 }  // namespace dsv

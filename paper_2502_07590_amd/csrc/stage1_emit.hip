@@ -67,18 +67,6 @@ struct EmitShared {
     OwnerOut out[32];
 };
 
-// inclusive prefix sum inside each half-wave (lanes 0..31 and lanes 32..63 separately)
-__device__ __forceinline__ int half_scan(int x)
-{
-    int s = x;
-    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);  // row_shr:1 (rows of 16 lanes, zero fill)
-    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);  // row_shr:2
-    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);  // row_shr:4
-    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);  // row_shr:8
-    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);  // row_bcast15 into rows 1 and 3
-    return s;
-}
-
 // Expand the parked masks of tiles tile0 .. tile0 + nfilled - 1 for all 32 owners.
 // (Compacting an owner's entries in LDS first and writing them out with consecutive lanes on consecutive
 // entries was measured slower -- 24.2 against 21.2 ms for the query-major emission at L = 128k, k = 8192 --:
@@ -272,34 +260,6 @@ __global__ __launch_bounds__(64) void emit_t_kernel(const T *__restrict__ Qlr, c
     if (!WRITE && live && half == 0) cnt[(int64_t)bh * L + j] = wpos;
 }
 
-// One block per (b, h): exclusive scan of cnt [L] into col [L+1] (int64).
-__global__ __launch_bounds__(1024) void list_scan_kernel(const int32_t *__restrict__ cnt, int64_t *__restrict__ col,
-                                                         int L)
-{
-    __shared__ int64_t part[1024];
-    const int bh = blockIdx.x;
-    const int32_t *c = cnt + (int64_t)bh * L;
-    int64_t *o = col + (int64_t)bh * (L + 1);
-    const int per = (L + 1023) / 1024;
-    const int lo = min((int)threadIdx.x * per, L), hi = min(lo + per, L);
-    int64_t sum = 0;
-    for (int e = lo; e < hi; ++e) sum += c[e];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int step = 1; step < 1024; step <<= 1) {
-        const int64_t add = threadIdx.x >= (unsigned)step ? part[threadIdx.x - step] : 0;
-        __syncthreads();
-        part[threadIdx.x] += add;
-        __syncthreads();
-    }
-    int64_t run = part[threadIdx.x] - sum;
-    for (int e = lo; e < hi; ++e) {
-        o[e] = run;
-        run += c[e];
-    }
-    if (threadIdx.x == 1023) o[L] = part[1023];
-}
-
 // ------------------------------------------------------------------------------------ host
 template <typename T, int R>
 static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr,
@@ -329,8 +289,10 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
                 DSV_LAUNCH_CHECK();
             }
         }
-        hipLaunchKernelGGL(list_scan_kernel, dim3(p.B * p.H), dim3(1024), 0, st, b.cnt, b.col, p.L);
-        DSV_LAUNCH_CHECK();
+        for (int t = 0; t < n_tabs; ++t) {
+            const dsv_status rc = launch_col_scan(b.cnt, b.col, p.L, tabs[t], st);
+            if (rc != DSV_OK) return rc;
+        }
         KernelSpan span(DSV_KERNEL_EMIT_T_WRITE, st);
         for (int t = 0; t < n_tabs; ++t) {
             dim3 grid(tiles, tabs[t].n);
