@@ -93,6 +93,22 @@ __device__ __forceinline__ int half_scan(int x)
     return s;
 }
 
+// Transposing LDS read (ds_read_b64_tr_b16): inside every block of 16 lanes, lane i receives four halfwords, the
+// e-th being halfword (i % 4) at the address passed by lane 4 e + i / 4 of the block.  So when lane 4 e + q
+// passes the address of channels c0 + 4 q .. + 3 of parked row key(e), lane i ends up with channel c0 + i of rows
+// key(0..3): a quarter of a matrix-core B fragment whose contraction runs over the parked rows.  Two reads
+// (rows key(0..3), key(4..7)) make the 8-element fragment.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+__device__ __forceinline__ bf16x8_t tr_frag(const unsigned char *a0, const unsigned char *a1)
+{
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)a0);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)a1);
+    typedef short s16x8_t __attribute__((ext_vector_type(8)));
+    const s16x8_t f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8_t, f);
+}
+
 // ---- a lane's share of one [d]-row: CH channels, kept as raw 32-bit words --------------------
 template <typename T, int CH> struct RowChunk {
     static constexpr int NW = CH * (int)sizeof(T) / 4;
@@ -401,7 +417,7 @@ dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const float *pa, const
 // ---- predictor side (predictor.hip) ---------------------------------------------------------------------
 struct PredictorLayout {
     int tok_per_block, nblk, nchunk;
-    size_t part, M, T1, T2, qlr, g, ca, ch, terms, dwq, n1, n2, total;
+    size_t part, M, T1, T2, qlr, g, coef, terms, acc, sums, total;
 };
 PredictorLayout predictor_layout(const dsv_problem &p, int n_rows);
 dsv_status launch_predictor_loss(const dsv_problem &p, const void *Q, const void *K, const void *Wq, const void *Wk,

@@ -226,22 +226,6 @@ __device__ __forceinline__ bool decode_group_item(const SplitPlan &pl, int64_t b
 // TOKEN row like the per-query partials.
 constexpr int kVRow = 128 * 2 + 16;  // bytes from one parked row to the next
 
-// Transposing LDS read (ds_read_b64_tr_b16): inside every block of 16 lanes, lane i receives four halfwords, the
-// e-th being halfword (i % 4) at the address passed by lane 4 e + i / 4 of the block.  So when lane 4 e + q
-// passes the address of channels c0 + 4 q .. + 3 of parked row key(e), lane i ends up with channel c0 + i of rows
-// key(0..3): a quarter of a matrix-core B fragment whose contraction runs over the parked rows.  Two reads
-// (rows key(0..3), key(4..7)) make the 8-element fragment.
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-__device__ __forceinline__ bf16x8_t tr_frag(const unsigned char *a0, const unsigned char *a1)
-{
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)a0);
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)a1);
-    typedef short s16x8_t __attribute__((ext_vector_type(8)));
-    const s16x8_t f = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8_t, f);
-}
-
 // Forward, O += P V: lane group g (16 lanes) contracts, in this order, keys fwd_key(g, 0..7); the 32 lanes that
 // one pass of a read serves (two lane groups) then touch 8 rows 2 apart, i.e. 8 disjoint stretches of LDS banks
 // (272-byte rows).  p_slot: place of key n in a row of P, where the 8 keys of a lane group are contiguous.

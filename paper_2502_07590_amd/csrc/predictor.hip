@@ -12,249 +12,397 @@
 // algebra on [d, d], [d, r] and the n sampled rows, done in fp64 (the norm term cancels to a small difference
 // of large sums when the predictor is good).  The paper's point -- no [n, L] intermediate is stored -- holds in
 // the strongest form: none is computed.
+//
+// Both kinds of contraction run on the matrix cores: the Gram matrix in the storage type with fp32 sums over at most
+// 512 tokens (v_mfma_f32_32x32x16_bf16 / 32x32x2_f32), everything behind it in fp64 (v_mfma_f64_16x16x4_f64).
+// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 165 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 46,
+// accum 25 (4.1 ms with the sums over partials in one block per head and the rows' forms on the vector units).
 #include <algorithm>
 
 #include "common.h"
 
 namespace dsv {
 
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double doublex4_t;
+
+// v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16]; element v of the result is
+// C[4 v + l / 16][l % 16].
+__device__ __forceinline__ doublex4_t mfma_f64(double a, double b, doublex4_t c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double sum16(double x)  // over the 16 lanes that share l / 16
+{
+    for (int o = 8; o; o >>= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
 // ---- M = K^T K, partial sums over token blocks ---------------------------------------------------------
-// grid (nblk, B*H); block 256 = 16 x 16 threads, thread (ty, tx) owns the entries of M at rows ty + 16 a,
-// columns tx + 16 b (a, b < D/16: conflict-free LDS reads); tokens pass through LDS 32 at a time as fp32.
+// A block takes tok_per_block tokens, kGramTok at a time through LDS.  The product's two operands are the same: 32
+// channels by some tokens, tokens the contraction, so a fragment is a transposing LDS read of the parked rows (bf16) or
+// a plain one (fp32).  D = 128: wave w forms rows 32 w .. 32 w + 31 of M; D = 64: one 32 x 32 tile per wave.
+// Bound by reading K: 8 bytes per CU and clock against 128 clocks of matrix work per 4 KB.
+constexpr int kGramTok = 64;     // tokens per LDS tile
+constexpr int kGramFlush = 512;  // tokens summed in one chain of fp32 additions
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void gram_partial_kernel(const T *__restrict__ K, int L, int tok_per_block,
                                                            float *__restrict__ part)
 {
-    constexpr int S = D / 16;
-    __shared__ float tile[32][D + 4];
+    constexpr int NB = D / 32;
+    constexpr int TW = NB == 4 ? 4 : 1;                    // tiles per wave
+    constexpr int PITCH = D * (int)sizeof(T) + 16;         // bytes from one parked row to the next
+    constexpr int PPR = D * (int)sizeof(T) / 16;           // 16-byte pieces per row
+    constexpr int NP = kGramTok * PPR / 256;               // pieces per thread and tile
+    __shared__ __align__(16) unsigned char tile[2][kGramTok * PITCH];
     const int bh = blockIdx.y;
     const int t0 = blockIdx.x * tok_per_block, t1 = min(t0 + tok_per_block, L);
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-    const T *Kh = K + (int64_t)bh * L * D;
-    float acc[S][S];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane & 31, half = lane >> 5;
+    const int rb = NB == 4 ? wave : wave >> 1;             // row block of this wave
+    const int cb0 = NB == 4 ? 0 : wave & 1;                // first column block
+    const unsigned char *Kh = reinterpret_cast<const unsigned char *>(K + (int64_t)bh * L * D);
+    uint4 next[NP];
+    auto request = [&](int tb) {
 #pragma unroll
-    for (int a = 0; a < S; ++a)
-#pragma unroll
-        for (int b = 0; b < S; ++b) acc[a][b] = 0.f;
-    for (int tb = t0; tb < t1; tb += 32) {
-        for (int e = threadIdx.x; e < 32 * D; e += 256) {
-            const int t = e / D, c = e % D;
-            tile[t][c] = tb + t < t1 ? to_f32<T>(Kh[(int64_t)(tb + t) * D + c]) : 0.f;
+        for (int i = 0; i < NP; ++i) {
+            const int e = threadIdx.x + 256 * i;
+            const int t = tb + e / PPR;
+            next[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (t < t1) next[i] = *reinterpret_cast<const uint4 *>(Kh + ((int64_t)t * PPR + e % PPR) * 16);
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int t = 0; t < 32; ++t) {
-            float ra[S], rb[S];
+    };
+    floatx16_t acc[TW], sum[TW];
 #pragma unroll
-            for (int a = 0; a < S; ++a) { ra[a] = tile[t][ty + 16 * a]; rb[a] = tile[t][tx + 16 * a]; }
+    for (int j = 0; j < TW; ++j)
 #pragma unroll
-            for (int a = 0; a < S; ++a)
+        for (int i = 0; i < 16; ++i) { acc[j][i] = 0.f; sum[j][i] = 0.f; }
+    request(t0);
+    int buf = 0, since = 0;
+    for (int tb = t0; tb < t1; tb += kGramTok, buf ^= 1) {
+        unsigned char *ts = tile[buf];
 #pragma unroll
-                for (int b = 0; b < S; ++b) acc[a][b] = fmaf(ra[a], rb[b], acc[a][b]);
+        for (int i = 0; i < NP; ++i) {
+            const int e = threadIdx.x + 256 * i;
+            *reinterpret_cast<uint4 *>(ts + (e / PPR) * PITCH + (e % PPR) * 16) = next[i];
         }
-        __syncthreads();
+        __syncthreads();  // two tiles in turn: the one written next was last read before this barrier
+        if (tb + kGramTok < t1) request(tb + kGramTok);
+        if constexpr (sizeof(T) == 2) {
+            const int c16 = lane & 15, g4 = lane >> 4;
+            // rows 4 (c16 / 4) + 2 half (+ 1 in the second read) of 16: 64-byte stretches 16 banks apart
+            const unsigned char *src = ts + (4 * (c16 >> 2) + 2 * half) * PITCH + (g4 & 1) * 32 + (c16 & 3) * 8;
+#pragma unroll
+            for (int s = 0; s < kGramTok / 16; ++s) {
+                const unsigned char *p = src + s * 16 * PITCH;
+                const bf16x8_t a = tr_frag(p + rb * 64, p + PITCH + rb * 64);
+#pragma unroll
+                for (int j = 0; j < TW; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, tr_frag(p + (cb0 + j) * 64, p + PITCH + (cb0 + j) * 64), acc[j], 0, 0, 0);
+            }
+        } else {
+#pragma unroll 8
+            for (int s = 0; s < kGramTok / 2; ++s) {
+                const float *p = reinterpret_cast<const float *>(ts + (2 * s + half) * PITCH) + n;
+                const float a = p[rb * 32];
+#pragma unroll
+                for (int j = 0; j < TW; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, p[(cb0 + j) * 32], acc[j], 0, 0, 0);
+            }
+        }
+        if ((since += kGramTok) >= kGramFlush || tb + kGramTok >= t1) {
+            since = 0;
+#pragma unroll
+            for (int j = 0; j < TW; ++j)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) { sum[j][i] += acc[j][i]; acc[j][i] = 0.f; }
+        }
     }
     float *out = part + ((int64_t)bh * gridDim.x + blockIdx.x) * D * D;
 #pragma unroll
-    for (int a = 0; a < S; ++a)
+    for (int j = 0; j < TW; ++j)
 #pragma unroll
-        for (int b = 0; b < S; ++b) out[(ty + 16 * a) * D + tx + 16 * b] = acc[a][b];
+        for (int v = 0; v < 16; ++v) out[(32 * rb + 8 * (v / 4) + 4 * half + v % 4) * D + 32 * (cb0 + j) + n] = sum[j][v];
 }
 
-// M[bh] = sum of the partials (fp64); then T1 = M Wk [D, R] and T2 = Wk^T T1 [R, R].  One block per head.
-template <typename T>
-__global__ __launch_bounds__(256) void gram_finish_kernel(const float *__restrict__ part, int nblk, const T *__restrict__ Wk,
-                                                          int H, int D, int R, double *__restrict__ M,
-                                                          double *__restrict__ T1, double *__restrict__ T2)
+// M[bh] = sum of the partials, in fp64, in block order.
+__global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ part, int nblk, int DD, double *__restrict__ M)
 {
-    const int bh = blockIdx.x;
-    const T *W = Wk + (int64_t)(bh % H) * D * R;
-    double *Mh = M + (int64_t)bh * D * D, *T1h = T1 + (int64_t)bh * D * R, *T2h = T2 + (int64_t)bh * R * R;
-    for (int e = threadIdx.x; e < D * D; e += 256) {
-        double s = 0.0;
-        for (int b = 0; b < nblk; ++b) s += (double)part[((int64_t)bh * nblk + b) * D * D + e];
-        Mh[e] = s;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < D * R; e += 256) {
-        const int c = e / R, t = e % R;
-        double s = 0.0;
-        for (int c2 = 0; c2 < D; ++c2) s += Mh[c * D + c2] * (double)to_f32<T>(W[c2 * R + t]);
-        T1h[e] = s;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < R * R; e += 256) {
-        const int a = e / R, b = e % R;
-        double s = 0.0;
-        for (int c = 0; c < D; ++c) s += (double)to_f32<T>(W[c * R + a]) * T1h[c * R + b];
-        T2h[e] = s;
-    }
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int64_t bh = blockIdx.y;
+    const float *p = part + bh * nblk * DD + e;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = 0; b < nblk; ++b) s += (double)p[(int64_t)b * DD];
+    M[bh * DD + e] = s;
+}
+
+// T1 = M Wk [D, R], then T2 = Wk^T T1 [R, R]: a thread per entry.
+template <typename T, int D, int R>
+__global__ __launch_bounds__(256) void gram_weights1_kernel(const T *__restrict__ Wk, int H, const double *__restrict__ M,
+                                                            double *__restrict__ T1)
+{
+    const int64_t bh = blockIdx.y;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int c = e / R, t = e % R;
+    const T *W = Wk + (bh % H) * D * R;
+    double s = 0.0;
+#pragma unroll 16
+    for (int c2 = 0; c2 < D; ++c2) s += M[(bh * D + c) * D + c2] * (double)to_f32<T>(W[c2 * R + t]);
+    T1[bh * D * R + e] = s;
+}
+
+template <typename T, int D, int R>
+__global__ __launch_bounds__(256) void gram_weights2_kernel(const T *__restrict__ Wk, int H, const double *__restrict__ T1,
+                                                            double *__restrict__ T2)
+{
+    const int64_t bh = blockIdx.y;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int a = e / R, b = e % R;
+    const T *W = Wk + (bh % H) * D * R;
+    double s = 0.0;
+#pragma unroll 16
+    for (int c = 0; c < D; ++c) s += (double)to_f32<T>(W[c * R + a]) * T1[(bh * D + c) * R + b];
+    T2[bh * R * R + e] = s;
 }
 
 // ---- per sampled row ------------------------------------------------------------------------------------
-// One wave per (head, sampled row).  Writes, per row: qlr [R], G [R] (= dAhat_i Klr), CA = ca_i qlr, CH = ch_i qlr,
-// and the row's loss terms {1 - cos_i, sum_j (ahat_ij - a_ij)^2}.
+// One wave per 16 sampled rows; U = Q_s M, Q_lr = Q_s Wq, V = Q_s T1 and W = Q_lr T2 as fp64 matrix products.  Writes, per
+// row: qlr [R], G [R] (= dAhat_i Klr), the coefficients ca_i, ch_i and the loss terms {1 - cos_i, sum_j (ahat_ij - a_ij)^2}.
 //   ca_i = -0.95 / (n |ahat_i| |a_i|) - 0.1 / (n L),   ch_i = 0.95 <ahat_i, a_i> / (n |ahat_i|^3 |a_i|) + 0.1 / (n L)
-template <typename T>
+// Bound by the D^2 fp64 multiplications per row (64 clocks per 16 x 16 x 4 product).
+template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict__ Q, const T *__restrict__ Wq,
-                                                             const int32_t *__restrict__ rows, int n, int L, int H, int D,
-                                                             int R, const double *__restrict__ M,
-                                                             const double *__restrict__ T1, const double *__restrict__ T2,
-                                                             double *__restrict__ qlr_out, double *__restrict__ g_out,
-                                                             double *__restrict__ ca_out, double *__restrict__ ch_out,
-                                                             double *__restrict__ terms)
+                                                             const int32_t *__restrict__ rows, int n, int L, int H,
+                                                             const double *__restrict__ M, const double *__restrict__ T1,
+                                                             const double *__restrict__ T2, double *__restrict__ qlr_out,
+                                                             double *__restrict__ g_out, double2 *__restrict__ coef,
+                                                             double2 *__restrict__ terms)
 {
-    __shared__ double sh_all[4][128 + 64 + 64 + 64];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + wave;
-    const int bh = blockIdx.y;
-    if (i >= n) return;  // whole wave
-    double *q = sh_all[wave], *ql = q + 128, *v = ql + 64, *w = v + 64;
-    const int row = min(max(rows[i], 0), L - 1);
-    const T *qrow = Q + ((int64_t)bh * L + row) * D;
-    const T *Wh = Wq + (int64_t)(bh % H) * D * R;
-    const double *Mh = M + (int64_t)bh * D * D, *T1h = T1 + (int64_t)bh * D * R, *T2h = T2 + (int64_t)bh * R * R;
-    for (int c = lane; c < D; c += 64) q[c] = (double)to_f32<T>(qrow[c]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); __builtin_amdgcn_wave_barrier(); __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // aa = q^T M q
-    double aa = 0.0;
-    for (int c = lane; c < D; c += 64) {
-        double u = 0.0;
-        for (int c2 = 0; c2 < D; ++c2) u += Mh[c2 * D + c] * q[c2];  // M is symmetric: column c, coalesced
-        aa += q[c] * u;
+    constexpr int CPL = D / 4, RPL = R / 4, NT = R / 16;   // contraction steps: lane group g takes channels g CPL + s
+    __shared__ float xq_all[4][16][D + 1];
+    __shared__ double ql_all[4][16][R + 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int i0 = (blockIdx.x * 4 + wave) * 16;
+    const int64_t bh = blockIdx.y;
+    if (i0 >= n) return;  // whole wave; nothing below synchronises across waves
+    float (*xq)[D + 1] = xq_all[wave];
+    double (*ql)[R + 1] = ql_all[wave];
+    const T *Wh = Wq + (bh % H) * D * R;
+    const double *Mh = M + bh * D * D, *T1h = T1 + bh * D * R, *T2h = T2 + bh * R * R;
+    const int row = min(max(rows[min(i0 + r16, n - 1)], 0), L - 1);
+    const T *qrow = Q + (bh * L + row) * D + g * CPL;
+    double q[CPL];
+#pragma unroll
+    for (int s = 0; s < CPL; ++s) {
+        const float x = to_f32<T>(qrow[s]);
+        xq[r16][g * CPL + s] = x;
+        q[s] = (double)x;
     }
-    for (int o = 32; o; o >>= 1) aa += __shfl_xor(aa, o);
-    // qlr = Wq^T q,  v = T1^T q
-    for (int t = lane; t < R; t += 64) {
-        double a = 0.0, b = 0.0;
-        for (int c = 0; c < D; ++c) { a += (double)to_f32<T>(Wh[c * R + t]) * q[c]; b += T1h[c * R + t] * q[c]; }
-        ql[t] = a;
-        v[t] = b;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double aa[4] = {0.0, 0.0, 0.0, 0.0}, ah[4] = {0.0, 0.0, 0.0, 0.0}, hh[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int nt = 0; nt < D / 16; ++nt) {
+        doublex4_t u = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < CPL; ++s) u = mfma_f64(q[s], Mh[(g * CPL + s) * D + 16 * nt + r16], u);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) aa[v] += u[v] * (double)xq[4 * v + g][16 * nt + r16];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); __builtin_amdgcn_wave_barrier(); __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    double ah = 0.0, hh = 0.0;
-    for (int t = lane; t < R; t += 64) {
-        double ww = 0.0;
-        for (int t2 = 0; t2 < R; ++t2) ww += T2h[t2 * R + t] * ql[t2];  // T2 is symmetric
-        w[t] = ww;
-        ah += ql[t] * v[t];
-        hh += ql[t] * ww;
+    doublex4_t a[NT], b[NT];  // Q_lr and V
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        a[nt] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+        b[nt] = a[nt];
+#pragma unroll
+        for (int s = 0; s < CPL; ++s) {
+            const int e = (g * CPL + s) * R + 16 * nt + r16;
+            a[nt] = mfma_f64(q[s], (double)to_f32<T>(Wh[e]), a[nt]);
+            b[nt] = mfma_f64(q[s], T1h[e], b[nt]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ql[4 * v + g][16 * nt + r16] = a[nt][v];
     }
-    for (int o = 32; o; o >>= 1) { ah += __shfl_xor(ah, o); hh += __shfl_xor(hh, o); }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); __builtin_amdgcn_wave_barrier(); __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const double na = sqrt(aa), nh = sqrt(hh);
-    const double ca = -0.95 / ((double)n * nh * na) - 0.1 / ((double)n * (double)L);
-    const double ch = 0.95 * ah / ((double)n * nh * nh * nh * na) + 0.1 / ((double)n * (double)L);
-    const int64_t o = ((int64_t)bh * n + i) * R;
-    for (int t = lane; t < R; t += 64) {
-        qlr_out[o + t] = ql[t];
-        g_out[o + t] = ca * v[t] + ch * w[t];
-        ca_out[o + t] = ca * ql[t];
-        ch_out[o + t] = ch * ql[t];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    doublex4_t w[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        w[nt] = doublex4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < RPL; ++s) w[nt] = mfma_f64(ql[r16][g * RPL + s], T2h[(g * RPL + s) * R + 16 * nt + r16], w[nt]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            ah[v] += a[nt][v] * b[nt][v];
+            hh[v] += a[nt][v] * w[nt][v];
+        }
     }
-    if (lane == 0) {
-        terms[((int64_t)bh * n + i) * 2 + 0] = 1.0 - ah / (na * nh);
-        terms[((int64_t)bh * n + i) * 2 + 1] = hh - 2.0 * ah + aa;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const double saa = sum16(aa[v]), sah = sum16(ah[v]), shh = sum16(hh[v]);
+        const double na = sqrt(saa), nh = sqrt(shh);
+        const double ca = -0.95 / ((double)n * nh * na) - 0.1 / ((double)n * (double)L);
+        const double ch = 0.95 * sah / ((double)n * nh * nh * nh * na) + 0.1 / ((double)n * (double)L);
+        const int i = i0 + 4 * v + g;
+        if (i < n) {
+            const int64_t o = (bh * n + i) * R + r16;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                qlr_out[o + 16 * nt] = a[nt][v];
+                g_out[o + 16 * nt] = ca * b[nt][v] + ch * w[nt][v];
+            }
+            if (r16 == 0) {
+                coef[bh * n + i] = make_double2(ca, ch);
+                terms[bh * n + i] = make_double2(1.0 - sah / (na * nh), shh - 2.0 * sah + saa);
+            }
+        }
     }
 }
 
 // ---- sums over the sampled rows ---------------------------------------------------------------------------
-// dWq = Q_s^T G [D, R],  N1 = Q_s^T CA [D, R],  N2 = Qlr^T CH [R, R]: every block takes 32 sampled rows (their Q
-// rows and per-row vectors staged in LDS) and writes its partial sums; predictor_finish_kernel adds the partials
-// in block order (deterministic).
-constexpr int kAccRows = 32;
-template <typename T>
+// dWq = Q_s^T G [D, R],  N1 = Q_s^T (ca Q_lr) [D, R],  N2 = Q_lr^T (ch Q_lr) [R, R]: every block takes kAccRows sampled rows
+// (64 Q rows at a time in LDS) and writes its partial sums; predictor_sum_kernel adds them in block order (deterministic).
+// Waves take the 16-channel row tiles of dWq and N1 (and of N2) in turn.
+constexpr int kAccRows = 128;
+template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restrict__ Q, const int32_t *__restrict__ rows,
-                                                              int n, int L, int D, int R, const double *__restrict__ qlr,
-                                                              const double *__restrict__ g, const double *__restrict__ ca,
-                                                              const double *__restrict__ ch, double *__restrict__ p_dwq,
-                                                              double *__restrict__ p_n1, double *__restrict__ p_n2)
+                                                              int n, int L, const double *__restrict__ qlr,
+                                                              const double *__restrict__ gm, const double2 *__restrict__ coef,
+                                                              double *__restrict__ part)
 {
-    __shared__ float xq[kAccRows][128];
-    __shared__ double yg[kAccRows][64], yca[kAccRows][64], ych[kAccRows][64], xl[kAccRows][64];
-    const int bh = blockIdx.y, chunk = blockIdx.x;
-    const int i0 = chunk * kAccRows, ni = min(kAccRows, n - i0);
-    for (int e = threadIdx.x; e < kAccRows * D; e += 256) {
-        const int i = e / D, c = e % D;
-        xq[i][c] = i < ni ? to_f32<T>(Q[((int64_t)bh * L + min(max(rows[i0 + i], 0), L - 1)) * D + c]) : 0.f;
+    constexpr int NT = R / 16, CT = D / 64;                 // column tiles; row tiles of dWq and N1 per wave
+    __shared__ float xq[64][D + 1];
+    const int64_t bh = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    doublex4_t s1[CT][NT], s2[CT][NT], s3[NT];
+    const doublex4_t zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        s3[nt] = zero;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) { s1[ct][nt] = zero; s2[ct][nt] = zero; }
     }
-    for (int e = threadIdx.x; e < kAccRows * R; e += 256) {
-        const int i = e / R, t = e % R;
-        const int64_t o = ((int64_t)bh * n + i0 + i) * R + t;
-        yg[i][t] = i < ni ? g[o] : 0.0;
-        yca[i][t] = i < ni ? ca[o] : 0.0;
-        ych[i][t] = i < ni ? ch[o] : 0.0;
-        xl[i][t] = i < ni ? qlr[o] : 0.0;
+    const int i1 = min((int)(blockIdx.x + 1) * kAccRows, n);
+    for (int i0 = blockIdx.x * kAccRows; i0 < i1; i0 += 64) {
+        __syncthreads();
+        constexpr int EPP = 16 / (int)sizeof(T), PPR = D / EPP;  // elements per 16-byte piece, pieces per row
+#pragma unroll
+        for (int u = 0; u < 64 * PPR / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            const int i = e / PPR, c = e % PPR * EPP;
+            const int row = min(max(rows[min(i0 + i, i1 - 1)], 0), L - 1);
+            const RowChunk<T, EPP> x = load_chunk<T, EPP>(Q + (bh * L + row) * D + c);  // rows past the end meet zero weights
+#pragma unroll
+            for (int m = 0; m < EPP; ++m) {
+                if constexpr (sizeof(T) == 4) xq[i][c + m] = __uint_as_float(x.w[m]);
+                else xq[i][c + m] = __uint_as_float(m & 1 ? x.w[m / 2] & 0xFFFF0000u : x.w[m / 2] << 16);
+            }
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int s = 0; s < 16; ++s) {
+            const int i = i0 + 4 * s + g;
+            const bool ok = i < i1;
+            const int64_t r = bh * n + (ok ? i : i1 - 1);
+            const double2 cf = ok ? coef[r] : make_double2(0.0, 0.0);
+            double vg[NT], vl[NT], x[CT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                vg[nt] = ok ? gm[r * R + 16 * nt + r16] : 0.0;
+                vl[nt] = qlr[r * R + 16 * nt + r16];
+            }
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) x[ct] = (double)xq[4 * s + g][16 * (wave + 4 * ct) + r16];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    s1[ct][nt] = mfma_f64(x[ct], vg[nt], s1[ct][nt]);
+                    s2[ct][nt] = mfma_f64(x[ct], ok ? cf.x * vl[nt] : 0.0, s2[ct][nt]);
+                }
+            if (wave < NT) {  // row tile `wave` of N2
+                const double xl = qlr[r * R + 16 * wave + r16];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) s3[nt] = mfma_f64(xl, ok ? cf.y * vl[nt] : 0.0, s3[nt]);
+            }
+        }
     }
-    __syncthreads();
-    const int64_t pb = (int64_t)bh * gridDim.x + chunk;
-    for (int e = threadIdx.x; e < D * R; e += 256) {
-        const int c = e / R, t = e % R;
-        double s1 = 0.0, s2 = 0.0;
-        for (int i = 0; i < kAccRows; ++i) { s1 += (double)xq[i][c] * yg[i][t]; s2 += (double)xq[i][c] * yca[i][t]; }
-        p_dwq[pb * D * R + e] = s1;
-        p_n1[pb * D * R + e] = s2;
-    }
-    for (int e = threadIdx.x; e < R * R; e += 256) {
-        const int a = e / R, t = e % R;
-        double s = 0.0;
-        for (int i = 0; i < kAccRows; ++i) s += xl[i][a] * ych[i][t];
-        p_n2[pb * R * R + e] = s;
-    }
+    double *o = part + (bh * gridDim.x + blockIdx.x) * (2 * D * R + R * R);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const int e = (16 * (wave + 4 * ct) + 4 * v + g) * R + 16 * nt + r16;
+                o[e] = s1[ct][nt][v];
+                o[D * R + e] = s2[ct][nt][v];
+            }
+            if (wave < NT) o[2 * D * R + (16 * wave + 4 * v + g) * R + 16 * nt + r16] = s3[nt][v];
+        }
 }
 
-// dWk = M (N1 + Wk N2), dWq and N1, N2 from the blocks' partials; loss = {0.95 cos + 0.05 norm, cos, norm}.  One block per head.
-template <typename T>
-__global__ __launch_bounds__(256) void predictor_finish_kernel(const double *__restrict__ M, const T *__restrict__ Wk,
-                                                               const double *__restrict__ p_dwq, const double *__restrict__ p_n1,
-                                                               const double *__restrict__ p_n2, int nchunk,
-                                                               const double *__restrict__ terms, int n, int L, int H, int D,
-                                                               int R, float *__restrict__ loss, float *__restrict__ dWq,
-                                                               float *__restrict__ dWk)
+// sums [2 D R + R R] = dWq, N1, N2 over the blocks' partials; dWq is final.
+__global__ __launch_bounds__(256) void predictor_sum_kernel(const double *__restrict__ part, int nchunk, int DR, int count,
+                                                            double *__restrict__ sums, float *__restrict__ dWq)
 {
-    extern __shared__ double sh[];  // P [D, R] = N1 + Wk N2, then N2 [R, R], then 2 x 256 reduction slots
-    double *P = sh, *N2 = sh + D * R, *red = N2 + R * R;
-    const int bh = blockIdx.x;
-    const T *W = Wk + (int64_t)(bh % H) * D * R;
-    for (int e = threadIdx.x; e < R * R; e += 256) {
-        double s = 0.0;
-        for (int c = 0; c < nchunk; ++c) s += p_n2[((int64_t)bh * nchunk + c) * R * R + e];
-        N2[e] = s;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int64_t bh = blockIdx.y;
+    if (e >= count) return;
+    const double *p = part + bh * nchunk * count + e;
+    double s = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < nchunk; ++c) s += p[(int64_t)c * count];
+    if (e < DR) dWq[bh * DR + e] = (float)s;
+    else sums[bh * count + e] = s;
+}
+
+// dWk = M (N1 + Wk N2) = M N1 + T1 N2; block 0 of a head also forms the loss {0.95 cos + 0.05 norm, cos, norm}.
+template <int D, int R>
+__global__ __launch_bounds__(256) void predictor_finish_kernel(const double *__restrict__ M, const double *__restrict__ T1,
+                                                               const double *__restrict__ sums, const double2 *__restrict__ terms,
+                                                               int n, int L, float *__restrict__ loss, float *__restrict__ dWk)
+{
+    __shared__ double red[2][256];
+    const int64_t bh = blockIdx.y;
+    const double *N1 = sums + bh * (2 * D * R + R * R) + D * R, *N2 = N1 + D * R;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int c = e / R, t = e % R;
+    double s = 0.0;
+#pragma unroll 16
+    for (int c2 = 0; c2 < D; ++c2) s += M[(bh * D + c) * D + c2] * N1[c2 * R + t];
+#pragma unroll 16
+    for (int t2 = 0; t2 < R; ++t2) s += T1[(bh * D + c) * R + t2] * N2[t2 * R + t];
+    dWk[bh * D * R + e] = (float)s;
+    if (blockIdx.x) return;
+    double lc = 0.0, lm = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const double2 x = terms[bh * n + i];
+        lc += x.x;
+        lm += x.y;
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < D * R; e += 256) {
-        const int c = e / R, t = e % R;
-        double s = 0.0, q = 0.0;
-        for (int k = 0; k < nchunk; ++k) {
-            s += p_n1[((int64_t)bh * nchunk + k) * D * R + e];
-            q += p_dwq[((int64_t)bh * nchunk + k) * D * R + e];
-        }
-        for (int t2 = 0; t2 < R; ++t2) s += (double)to_f32<T>(W[c * R + t2]) * N2[t2 * R + t];
-        P[e] = s;
-        dWq[(int64_t)bh * D * R + e] = (float)q;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < D * R; e += 256) {
-        const int c = e / R, t = e % R;
-        double s = 0.0;
-        for (int c2 = 0; c2 < D; ++c2) s += M[(int64_t)bh * D * D + c * D + c2] * P[c2 * R + t];
-        dWk[(int64_t)bh * D * R + e] = (float)s;
-    }
-    double c = 0.0, m = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) { c += terms[((int64_t)bh * n + i) * 2]; m += terms[((int64_t)bh * n + i) * 2 + 1]; }
-    red[threadIdx.x] = c;
-    red[256 + threadIdx.x] = m;
+    red[0][threadIdx.x] = lc;
+    red[1][threadIdx.x] = lm;
     __syncthreads();
     for (int step = 128; step; step >>= 1) {
-        if ((int)threadIdx.x < step) { red[threadIdx.x] += red[threadIdx.x + step]; red[256 + threadIdx.x] += red[256 + threadIdx.x + step]; }
+        if ((int)threadIdx.x < step) {
+            red[0][threadIdx.x] += red[0][threadIdx.x + step];
+            red[1][threadIdx.x] += red[1][threadIdx.x + step];
+        }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        c = red[0] / (double)n;
-        m = red[256] / ((double)n * (double)L);
-        loss[bh * 3 + 0] = (float)(0.95 * c + 0.05 * m);
-        loss[bh * 3 + 1] = (float)c;
-        loss[bh * 3 + 2] = (float)m;
+        lc = red[0][0] / (double)n;
+        lm = red[1][0] / ((double)n * (double)L);
+        loss[bh * 3 + 0] = (float)(0.95 * lc + 0.05 * lm);
+        loss[bh * 3 + 1] = (float)lc;
+        loss[bh * 3 + 2] = (float)lm;
     }
 }
 
@@ -263,8 +411,11 @@ PredictorLayout predictor_layout(const dsv_problem &p, int n)
 {
     const size_t nbh = (size_t)p.B * p.H, D = p.d, R = p.r;
     PredictorLayout w{};
-    w.tok_per_block = 1024;
+    // about three blocks per CU, of 256 to 2048 tokens: every block leaves a [D, D] partial to be written and read again
+    const size_t want = (nbh * p.L + 767) / 768;
+    w.tok_per_block = (int)std::min<size_t>(2048, std::max<size_t>(256, align_up(want, 64)));
     w.nblk = (p.L + w.tok_per_block - 1) / w.tok_per_block;
+    w.nchunk = (n + 127) / 128;   // kAccRows sampled rows per partial sum
     size_t o = 0;
     w.part = o; o = align_up(o + nbh * w.nblk * D * D * 4, 256);
     w.M = o; o = align_up(o + nbh * D * D * 8, 256);
@@ -272,45 +423,37 @@ PredictorLayout predictor_layout(const dsv_problem &p, int n)
     w.T2 = o; o = align_up(o + nbh * R * R * 8, 256);
     w.qlr = o; o = align_up(o + nbh * n * R * 8, 256);
     w.g = o; o = align_up(o + nbh * n * R * 8, 256);
-    w.ca = o; o = align_up(o + nbh * n * R * 8, 256);
-    w.ch = o; o = align_up(o + nbh * n * R * 8, 256);
-    w.terms = o; o = align_up(o + nbh * n * 2 * 8, 256);
-    w.nchunk = (n + 31) / 32;   // kAccRows sampled rows per partial sum
-    w.dwq = o; o = align_up(o + nbh * w.nchunk * D * R * 8, 256);
-    w.n1 = o; o = align_up(o + nbh * w.nchunk * D * R * 8, 256);
-    w.n2 = o; o = align_up(o + nbh * w.nchunk * R * R * 8, 256);
+    w.coef = o; o = align_up(o + nbh * n * 16, 256);
+    w.terms = o; o = align_up(o + nbh * n * 16, 256);
+    w.acc = o; o = align_up(o + nbh * w.nchunk * (2 * D * R + R * R) * 8, 256);
+    w.sums = o; o = align_up(o + nbh * (2 * D * R + R * R) * 8, 256);
     w.total = o;
     return w;
 }
 
-template <typename T>
+template <typename T, int D, int R>
 static dsv_status predictor_t(const dsv_problem &p, const void *Q, const void *K, const void *Wq, const void *Wk,
                               const int32_t *rows, int n, float *loss, float *dWq, float *dWk, char *ws,
                               const PredictorLayout &w, hipStream_t st)
 {
-    const int nbh = p.B * p.H, D = p.d, R = p.r;
+    const int nbh = p.B * p.H;
     float *part = reinterpret_cast<float *>(ws + w.part);
-    double *M = reinterpret_cast<double *>(ws + w.M), *T1 = reinterpret_cast<double *>(ws + w.T1);
-    double *T2 = reinterpret_cast<double *>(ws + w.T2), *qlr = reinterpret_cast<double *>(ws + w.qlr);
-    double *g = reinterpret_cast<double *>(ws + w.g), *ca = reinterpret_cast<double *>(ws + w.ca);
-    double *ch = reinterpret_cast<double *>(ws + w.ch), *terms = reinterpret_cast<double *>(ws + w.terms);
-    double *dwq = reinterpret_cast<double *>(ws + w.dwq), *n1 = reinterpret_cast<double *>(ws + w.n1);
-    double *n2 = reinterpret_cast<double *>(ws + w.n2);
-    if (D == 128)
-        hipLaunchKernelGGL((gram_partial_kernel<T, 128>), dim3(w.nblk, nbh), dim3(256), 0, st, (const T *)K, p.L, w.tok_per_block, part);
-    else
-        hipLaunchKernelGGL((gram_partial_kernel<T, 64>), dim3(w.nblk, nbh), dim3(256), 0, st, (const T *)K, p.L, w.tok_per_block, part);
+    auto f64 = [&](size_t at) { return reinterpret_cast<double *>(ws + at); };
+    double2 *coef = reinterpret_cast<double2 *>(ws + w.coef), *terms = reinterpret_cast<double2 *>(ws + w.terms);
+    constexpr int kSums = 2 * D * R + R * R;
+    hipLaunchKernelGGL((gram_partial_kernel<T, D>), dim3(w.nblk, nbh), dim3(256), 0, st, (const T *)K, p.L, w.tok_per_block, part);
+    hipLaunchKernelGGL(gram_sum_kernel, dim3(D * D / 256, nbh), dim3(256), 0, st, part, w.nblk, D * D, f64(w.M));
+    hipLaunchKernelGGL((gram_weights1_kernel<T, D, R>), dim3(D * R / 256, nbh), dim3(256), 0, st, (const T *)Wk, p.H, f64(w.M), f64(w.T1));
+    hipLaunchKernelGGL((gram_weights2_kernel<T, D, R>), dim3(R * R / 256, nbh), dim3(256), 0, st, (const T *)Wk, p.H, f64(w.T1), f64(w.T2));
     DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((gram_finish_kernel<T>), dim3(nbh), dim3(256), 0, st, part, w.nblk, (const T *)Wk, p.H, D, R, M, T1, T2);
-    DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((predictor_rows_kernel<T>), dim3((n + 3) / 4, nbh), dim3(256), 0, st, (const T *)Q, (const T *)Wq, rows, n,
-                       p.L, p.H, D, R, M, T1, T2, qlr, g, ca, ch, terms);
-    DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((predictor_accum_kernel<T>), dim3(w.nchunk, nbh), dim3(256), 0, st, (const T *)Q, rows, n, p.L, D, R, qlr, g,
-                       ca, ch, dwq, n1, n2);
-    DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((predictor_finish_kernel<T>), dim3(nbh), dim3(256), (size_t)(D * R + R * R + 512) * 8, st, M, (const T *)Wk,
-                       dwq, n1, n2, w.nchunk, terms, n, p.L, p.H, D, R, loss, dWq, dWk);
+    hipLaunchKernelGGL((predictor_rows_kernel<T, D, R>), dim3((n + 63) / 64, nbh), dim3(256), 0, st, (const T *)Q, (const T *)Wq, rows, n,
+                       p.L, p.H, f64(w.M), f64(w.T1), f64(w.T2), f64(w.qlr), f64(w.g), coef, terms);
+    hipLaunchKernelGGL((predictor_accum_kernel<T, D, R>), dim3(w.nchunk, nbh), dim3(256), 0, st, (const T *)Q, rows, n, p.L, f64(w.qlr),
+                       f64(w.g), coef, f64(w.acc));
+    hipLaunchKernelGGL(predictor_sum_kernel, dim3((kSums + 255) / 256, nbh), dim3(256), 0, st, f64(w.acc), w.nchunk, D * R, kSums,
+                       f64(w.sums), dWq);
+    hipLaunchKernelGGL((predictor_finish_kernel<D, R>), dim3(D * R / 256, nbh), dim3(256), 0, st, f64(w.M), f64(w.T1), f64(w.sums), terms,
+                       n, p.L, loss, dWk);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -319,8 +462,17 @@ dsv_status launch_predictor_loss(const dsv_problem &p, const void *Q, const void
                                  const int32_t *rows, int n, float *loss, float *dWq, float *dWk, char *ws,
                                  const PredictorLayout &w, hipStream_t st)
 {
-    if (p.dtype == DSV_BF16) return predictor_t<bf16_t>(p, Q, K, Wq, Wk, rows, n, loss, dWq, dWk, ws, w, st);
-    return predictor_t<float>(p, Q, K, Wq, Wk, rows, n, loss, dWq, dWk, ws, w, st);
+#define DSV_CASE(TT, DD, RR) \
+    if (p.d == DD && p.r == RR) return predictor_t<TT, DD, RR>(p, Q, K, Wq, Wk, rows, n, loss, dWq, dWk, ws, w, st)
+    if (p.dtype == DSV_BF16) {
+        DSV_CASE(bf16_t, 64, 16); DSV_CASE(bf16_t, 64, 32); DSV_CASE(bf16_t, 64, 64);
+        DSV_CASE(bf16_t, 128, 16); DSV_CASE(bf16_t, 128, 32); DSV_CASE(bf16_t, 128, 64);
+    } else if (p.dtype == DSV_F32) {
+        DSV_CASE(float, 64, 16); DSV_CASE(float, 64, 32); DSV_CASE(float, 64, 64);
+        DSV_CASE(float, 128, 16); DSV_CASE(float, 128, 32); DSV_CASE(float, 128, 64);
+    }
+#undef DSV_CASE
+    return DSV_EUNSUPPORTED;
 }
 
 }  // namespace dsv

@@ -1,0 +1,46 @@
+"""dsv_predictor_loss at the edges of its tiles (64 tokens, 16 sampled rows, 128 rows per partial sum) and for every
+d, r and type, against the definition of the loss and its gradients evaluated in 64 bits."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import paper_2502_07590_amd as dsv
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(q, k, wq, wk):
+    n, L = q.shape[0], k.shape[0]
+    ql, kl = q @ wq, k @ wk
+    a, b = q @ k.T, ql @ kl.T
+    na, nb, ab = a.norm(dim=1, keepdim=True), b.norm(dim=1, keepdim=True), (a * b).sum(1, keepdim=True)
+    cos, norm = (1 - ab / (na * nb)).mean(), ((b - a) ** 2).mean()
+    ca, cb = -0.95 / (n * na * nb) - 0.1 / (n * L), 0.95 * ab / (n * na * nb ** 3) + 0.1 / (n * L)
+    db, size = ca * a + cb * b, (ca * a).abs() + (cb * b).abs()
+    want = torch.stack([0.95 * cos + 0.05 * norm, cos, norm]), q.T @ (db @ kl), k.T @ (db.T @ ql)
+    # how far rounding the entries of K^T K reaches: |a_i|^2 and |ahat_i|^2 come from it as quadratic forms, which lose the
+    # factor by which they fall short of |q|^2 |K|^2 (few keys, a row nearly orthogonal to them); the gradients are
+    # differences of terms of the sizes in `size`
+    lost = max(float((q.norm(dim=1) * k.norm() / na[:, 0]).max()), float((ql.norm(dim=1) * kl.norm() / nb[:, 0]).max())) ** 2
+    reach = torch.ones(3, dtype=q.dtype, device=q.device), q.abs().T @ (size @ kl.abs()), k.abs().T @ (size.T @ ql.abs())
+    return want, [2.0 ** -22 * lost * float(x.max()) for x in reach]
+
+
+@pytest.mark.parametrize("L,n", [(1, 1), (63, 15), (64, 16), (65, 17), (257, 127), (600, 129), (2113, 300)])
+@pytest.mark.parametrize("dtype,d,r", [("bf16", 128, 16), ("bf16", 64, 64), ("f32", 128, 64), ("f32", 64, 32), ("bf16", 128, 32)])
+def test_loss_and_gradients_at_tile_edges(L, n, dtype, d, r):
+    g = torch.Generator(device="cuda").manual_seed(L + d)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    H = 2
+    Q, K = (torch.randn(1, H, L, d, generator=g, device="cuda").to(td) for _ in range(2))
+    Wq, Wk = ((torch.randn(H, d, r, generator=g, device="cuda") / d ** 0.5).to(td) for _ in range(2))
+    rows = torch.randperm(L, generator=g, device="cuda")[:n].to(torch.int32)
+    p = dsv.Problem(1, H, L, d, r, dtype, [1] * H, 0.1)
+    got = dsv.predictor_loss(p, Q, K, Wq, Wk, rows)
+    for h in range(H):
+        want, reach = _reference(Q[0, h].double()[rows.long()], K[0, h].double(), Wq[h].double(), Wk[h].double())
+        # fp32 sums of at most 512 tokens: relative 512 * 2^-24 = 3e-5 of the largest entry, and the fp32 result; or what the
+        # rounding of single entries of the Gram matrix reaches, where that is more
+        for x, y, z in zip(got, want, reach):
+            assert (x[h].double() - y).abs().max() <= max(1e-4 * max(float(y.abs().max()), 1e-2), z)
