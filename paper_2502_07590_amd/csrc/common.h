@@ -361,8 +361,14 @@ int window_sample_keys(int L, int k, bool forced);
 // 0: automatic; 1: always the four-pass radix search; 2: the windowed search wherever it fits.  Returns the old mode
 // (mode < 0: only that).
 int set_threshold_search(int mode);
+// Threshold search and query-major emission of short sequences in one launch (stage1_small.hip): every head of an L that
+// small_select(L) accepts.  Leaves the same state behind as the search and launch_emit's first part.
+bool small_select(int L);
+dsv_status launch_select_small(const dsv_problem &p, int Lq, const HeadTable &tab, const void *Qlr, const void *Klr,
+                               const SelectBuffers &b, hipStream_t st);
+// emitted: the query-major index is there already.
 dsv_status launch_emit(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr, const void *Klr,
-                       const SelectBuffers &b, hipStream_t st);
+                       const SelectBuffers &b, bool emitted, hipStream_t st);
 dsv_status launch_sparse_fwd(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
                              const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st);
 dsv_status launch_bwd_dq(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,

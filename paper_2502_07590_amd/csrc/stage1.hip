@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void project_kernel(const T *__restrict__ Q, c
 
 // One 32-query tile (queries q0 .. q0+31 of head slot `slot`); hist: the block's 256 x 32 counters.
 template <typename T, int R, int PASS>
-__device__ __forceinline__ void radix_pass_tile(uint32_t *hist, const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq,
+__device__ __forceinline__ void radix_pass_tile(uint32_t *hist, BucketScratch<64 * kRadixWaves> &scratch, const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq,
                                                 int L, const HeadTable &tab, int slot, int q0, uint32_t *__restrict__ prefix,
                                                 int32_t *__restrict__ krem)
 {
@@ -173,25 +173,17 @@ __device__ __forceinline__ void radix_pass_tile(uint32_t *hist, const T *__restr
     }
     __syncthreads();
 
-    if (threadIdx.x < 32 && q0 + (int)threadIdx.x < Lq) {
-        const int64_t g = (int64_t)bh * padded_len(Lq) + q0 + threadIdx.x;
-        const int kr = PASS == 0 ? tab.k[slot] : krem[g];
-        const uint32_t *hcol = hist + threadIdx.x;
-        int above = 0, digit = 0;
-        // bucket of key digit b: the digit itself, except in pass 0, whose buckets are raw top bytes
-        // (positive floats: key digit = raw ^ 0x80; negative floats: key digit = ~raw)
-        auto bucket_of = [](int b) { return PASS == 0 ? (b >= 128 ? b ^ 0x80 : b ^ 0xFF) : b; };
-        for (int b = 255; b >= 0; --b) {
-            const int c = (int)hcol[32 * bucket_of(b)];
-            if (above + c >= kr) { digit = b; break; }
-            above += c;
-        }
-        const uint32_t mypre = PASS == 0 ? 0u : prefix[g];
-        prefix[g] = mypre | ((uint32_t)digit << SHIFT);
+    const int64_t g = (int64_t)bh * padded_len(Lq) + qi;  // every thread of a query (they share n)
+    const int kr = PASS == 0 ? tab.k[slot] : krem[g];
+    // bucket of key digit b: the digit itself, except in pass 0, whose buckets are raw top bytes
+    // (positive floats: key digit = raw ^ 0x80; negative floats: key digit = ~raw)
+    const Bucket f = find_bucket(hist, scratch, [](int b) { return PASS == 0 ? (b >= 128 ? b ^ 0x80 : b ^ 0xFF) : b; }, kr);
+    if (threadIdx.x < 32 && q0 + n < Lq) {
+        prefix[g] = (PASS == 0 ? 0u : pre) | ((uint32_t)f.digit << SHIFT);
         // after the last digit the bucket holds exactly the keys equal to the threshold: a negative
         // k_rem tells the emission that all of them are taken (then "score >= threshold" decides)
-        const int want = kr - above;
-        krem[g] = (PASS == 3 && want == (int)hcol[32 * bucket_of(digit)]) ? -want : want;
+        const int want = kr - f.above;
+        krem[g] = (PASS == 3 && want == f.count) ? -want : want;
     }
 }
 
@@ -201,7 +193,8 @@ __global__ __launch_bounds__(64 * kRadixWaves) void radix_pass_kernel(const T *_
                                                          int32_t *__restrict__ krem)
 {
     __shared__ uint32_t hist[256 * 32];
-    radix_pass_tile<T, R, PASS>(hist, Qlr, Klr, Lq, L, tab, blockIdx.y, blockIdx.x * 32, prefix, krem);
+    __shared__ BucketScratch<64 * kRadixWaves> scratch;
+    radix_pass_tile<T, R, PASS>(hist, scratch, Qlr, Klr, Lq, L, tab, blockIdx.y, blockIdx.x * 32, prefix, krem);
 }
 
 // The same digit pass for the query tiles on a list (todo[0] = their number, todo[1 + i] = slot * qtiles +
@@ -214,12 +207,13 @@ __global__ __launch_bounds__(64 * kRadixWaves) void radix_pass_list_kernel(const
                                                               int qtiles)
 {
     __shared__ uint32_t hist[256 * 32];
+    __shared__ BucketScratch<64 * kRadixWaves> scratch;
     const int n = min(todo[0], tab.n * qtiles);
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const int id = todo[1 + i];
         const int slot = id / qtiles;
         if (slot >= 0 && slot < tab.n)  // an id outside the table can only come from a corrupted list
-            radix_pass_tile<T, R, PASS>(hist, Qlr, Klr, Lq, L, tab, slot, (id - slot * qtiles) * 32, prefix, krem);
+            radix_pass_tile<T, R, PASS>(hist, scratch, Qlr, Klr, Lq, L, tab, slot, (id - slot * qtiles) * 32, prefix, krem);
         __syncthreads();  // the tile's last readers of hist are done before the next tile clears it
     }
 }
@@ -332,6 +326,16 @@ static dsv_status select_t(const dsv_problem &p, int Lq, const HeadTable *tabs, 
     const T *Kl = (const T *)Klr;
     const int qtiles = (Lq + 31) / 32;
     const int mode = b.win && b.todo ? g_threshold_search.load() : 1;
+    if (small_select(p.L)) {
+        {
+            KernelSpan search(DSV_KERNEL_THRESHOLD, st), emission(DSV_KERNEL_EMIT, st);  // one kernel does both
+            for (int t = 0; t < n_tabs; ++t) {
+                const dsv_status rc = launch_select_small(p, Lq, tabs[t], Qlr, Klr, b, st);
+                if (rc != DSV_OK) return rc;
+            }
+        }
+        return launch_emit(p, Lq, tabs, n_tabs, Qlr, Klr, b, true, st);
+    }
     {
         KernelSpan span(DSV_KERNEL_THRESHOLD, st);
         for (int t = 0; t < n_tabs; ++t) {
@@ -365,7 +369,7 @@ static dsv_status select_t(const dsv_problem &p, int Lq, const HeadTable *tabs, 
             }
         }
     }
-    return launch_emit(p, Lq, tabs, n_tabs, Qlr, Klr, b, st);
+    return launch_emit(p, Lq, tabs, n_tabs, Qlr, Klr, b, false, st);
 }
 
 dsv_status launch_select(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr, const void *Klr,

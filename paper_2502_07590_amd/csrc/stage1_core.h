@@ -75,12 +75,85 @@ __device__ __forceinline__ float key_score(uint32_t key)
     return __uint_as_float((key & 0x80000000u) ? (key ^ 0x80000000u) : ~key);
 }
 
+// 16 predicate bits of a lane, bit tile_pos(v) <- pred(v); the caller shifts by 4*half and merges.
+#define DSV_MASK16(m, pred_expr)                                   \
+    do {                                                           \
+        (m) = 0u;                                                  \
+        _Pragma("unroll") for (int v = 0; v < 16; ++v)             \
+            (m) |= (uint32_t)(pred_expr) << tile_pos(v);           \
+    } while (0)
+
+// Same, for predicates of the form "d(v) < 0" with d a float expression (NaN-free): the sign bits
+// are shifted into a register with one v_alignbit each (no compare, no condition-code traffic),
+// then put in tile order: bit-reverse, and spread the four nibbles to the low nibbles of four bytes.
+#define DSV_SIGNMASK16(m, d_expr)                                                          \
+    do {                                                                                   \
+        uint32_t acc_ = 0u;                                                                \
+        _Pragma("unroll") for (int v = 0; v < 16; ++v)                                     \
+            acc_ = __builtin_amdgcn_alignbit(acc_, __float_as_uint(d_expr), 31);           \
+        acc_ = __builtin_bitreverse32(acc_) >> 16; /* bit v = sign of d(v) */              \
+        acc_ = (acc_ | (acc_ << 8)) & 0x00FF00FFu;                                         \
+        (m) = (acc_ | (acc_ << 4)) & 0x0F0F0F0Fu;  /* bit tile_pos(v) */                   \
+    } while (0)
+
+__device__ __forceinline__ uint32_t merge_halves(uint32_t m, int half)
+{
+    m <<= 4 * half;
+    return m | (uint32_t)__shfl_xor((int)m, 32);
+}
+
 // Waves per block of the threshold-search kernels (one block = 32 queries, the waves stride over the key
 // tiles); their 32 KB histogram allows 4 blocks per CU.
 #ifndef DSV_RADIX_WAVES
 #define DSV_RADIX_WAVES 8
 #endif
 constexpr int kRadixWaves = DSV_RADIX_WAVES;
+
+// The bucket of an LDS histogram that holds each query's want-th largest count.  hist: [256 buckets][32 queries]; bucket_of
+// maps key order (0 = smallest) to buckets.  All THREADS threads of the block call it, thread t with the `want` of query
+// t % 32; each sums 256 / (THREADS / 32) buckets of its query, so that the search is a few dozen LDS reads deep instead
+// of 256 (the four radix passes over two heads of L = 20280, r = 32: 355 -> 301 us; the sample of four heads: 236 -> 157 us).  digit: in key order, -1 when the query's counts do not reach want;
+// above: counts in higher buckets; count: in the bucket itself.
+struct Bucket {
+    int digit, above, count;
+};
+template <int THREADS> struct BucketScratch {
+    int part[THREADS / 32][32];
+    Bucket found[32];
+};
+template <int THREADS, typename F>
+__device__ __forceinline__ Bucket find_bucket(const uint32_t *hist, BucketScratch<THREADS> &sh, F bucket_of, int want)
+{
+    constexpr int G = THREADS / 32, C = 256 / G;
+    const int q = threadIdx.x & 31, t = threadIdx.x >> 5;
+    int c[C], sum = 0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        c[i] = (int)hist[32 * bucket_of(t * C + i) + q];
+        sum += c[i];
+    }
+    sh.part[t][q] = sum;
+    if (t == 0) sh.found[q] = Bucket{-1, 0, 0};
+    __syncthreads();
+    int above = 0;
+#pragma unroll
+    for (int u = 1; u < G; ++u) above += u > t ? sh.part[u][q] : 0;
+    if (above < want && want <= above + sum) {
+        int digit = -1, count = 0;
+#pragma unroll
+        for (int i = C - 1; i >= 0; --i) {
+            if (digit < 0) {
+                if (above + c[i] >= want) { digit = t * C + i; count = c[i]; }
+                else above += c[i];
+            }
+        }
+        sh.found[q] = Bucket{digit, above, count};
+    }
+    __syncthreads();
+    const Bucket found = sh.found[q];
+    __syncthreads();  // the scratch and the histogram are free again
+    return found;
+}
 
 // Per-query selection state (threshold, tie budget, jcut) is stored [B*H, padded_len(L)]: rows padded
 // to whole 32-query tiles, so that a tile's 32 values can be fetched with aligned vector loads.

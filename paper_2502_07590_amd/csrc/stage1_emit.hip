@@ -15,33 +15,6 @@
 
 namespace dsv {
 
-// 16 predicate bits of a lane, bit tile_pos(v) <- pred(v); the caller shifts by 4*half and merges.
-#define DSV_MASK16(m, pred_expr)                                   \
-    do {                                                           \
-        (m) = 0u;                                                  \
-        _Pragma("unroll") for (int v = 0; v < 16; ++v)             \
-            (m) |= (uint32_t)(pred_expr) << tile_pos(v);           \
-    } while (0)
-
-// Same, for predicates of the form "d(v) < 0" with d a float expression (NaN-free): the sign bits
-// are shifted into a register with one v_alignbit each (no compare, no condition-code traffic),
-// then put in tile order: bit-reverse, and spread the four nibbles to the low nibbles of four bytes.
-#define DSV_SIGNMASK16(m, d_expr)                                                          \
-    do {                                                                                   \
-        uint32_t acc_ = 0u;                                                                \
-        _Pragma("unroll") for (int v = 0; v < 16; ++v)                                     \
-            acc_ = __builtin_amdgcn_alignbit(acc_, __float_as_uint(d_expr), 31);           \
-        acc_ = __builtin_bitreverse32(acc_) >> 16; /* bit v = sign of d(v) */              \
-        acc_ = (acc_ | (acc_ << 8)) & 0x00FF00FFu;                                         \
-        (m) = (acc_ | (acc_ << 4)) & 0x0F0F0F0Fu;  /* bit tile_pos(v) */                   \
-    } while (0)
-
-__device__ __forceinline__ uint32_t merge_halves(uint32_t m, int half)
-{
-    m <<= 4 * half;
-    return m | (uint32_t)__shfl_xor((int)m, 32);
-}
-
 // ---- output: masks parked per tile, expanded in batches -------------------------------------------
 // A selected entry is 4 bytes and consecutive entries of one owner are produced ~16 tiles apart, so
 // writing them as they appear makes every store a partial cache line (measured: 5x write
@@ -263,14 +236,14 @@ __global__ __launch_bounds__(64) void emit_t_kernel(const T *__restrict__ Qlr, c
 // ------------------------------------------------------------------------------------ host
 template <typename T, int R>
 static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr,
-                             const void *Klr, const SelectBuffers &b, hipStream_t st)
+                             const void *Klr, const SelectBuffers &b, bool emitted, hipStream_t st)
 {
     const T *Ql = (const T *)Qlr;
     const T *Kl = (const T *)Klr;
     const int tiles = (p.L + 31) / 32;    // key tiles
     const int qtiles = (Lq + 31) / 32;    // query (or query-group) tiles
     const float *tau_f = reinterpret_cast<const float *>(b.prefix);
-    {
+    if (!emitted) {
         KernelSpan span(DSV_KERNEL_EMIT, st);
         for (int t = 0; t < n_tabs; ++t) {
             dim3 grid(qtiles, tabs[t].n);
@@ -305,9 +278,9 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
 }
 
 dsv_status launch_emit(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr, const void *Klr,
-                       const SelectBuffers &b, hipStream_t st)
+                       const SelectBuffers &b, bool emitted, hipStream_t st)
 {
-#define DSV_CASE(TT, RR) return emit_all_t<TT, RR>(p, Lq, tabs, n_tabs, Qlr, Klr, b, st)
+#define DSV_CASE(TT, RR) return emit_all_t<TT, RR>(p, Lq, tabs, n_tabs, Qlr, Klr, b, emitted, st)
     if (p.dtype == DSV_BF16) {
         if (p.r == 16) DSV_CASE(bf16_t, 16);
         if (p.r == 32) DSV_CASE(bf16_t, 32);

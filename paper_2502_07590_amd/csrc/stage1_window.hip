@@ -71,7 +71,7 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_sample_kernel(const T
                                                             uint32_t *__restrict__ hi_out, int32_t *__restrict__ todo)
 {
     __shared__ uint32_t hA[256 * 32], hB[256 * 32];  // [digit][query]
-    __shared__ int32_t dig[2][32], abv[2][32];
+    __shared__ BucketScratch<64 * kRadixWaves> scratch;
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
     const int q0 = blockIdx.x * 32;
@@ -83,7 +83,6 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_sample_kernel(const T
     const Frag<T, R> qf = load_frag<T, R>(Qb, q0, Lq, lane);
     const int rank[2] = {wr.hi[slot], wr.lo[slot]};
     const int kTiles = wr.tiles[slot], stride = wr.stride[slot];
-    const int n_keys = kTiles * 32;
 
     for (int e = threadIdx.x; e < 256 * 32; e += 64 * kRadixWaves) hA[e] = 0;
     __syncthreads();
@@ -94,23 +93,12 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_sample_kernel(const T
         for (int v = 0; v < 16; ++v) atomicAdd(&hA[(score_key(acc[v]) >> 24) * 32 + n], 1u);
     }
     __syncthreads();
-    if (threadIdx.x < 64) {
-        const int q = threadIdx.x & 31, w = threadIdx.x >> 5;
-        int d = -1, above = 0;
-        if (rank[w] >= 1 && rank[w] <= n_keys) {
-            for (int b = 255; b >= 0; --b) {
-                const int c = (int)hA[b * 32 + q];
-                if (above + c >= rank[w]) { d = b; break; }
-                above += c;
-            }
-        }
-        dig[w][q] = d;
-        abv[w][q] = above;
-    }
-    __syncthreads();
+    const auto digit_order = [](int b) { return b; };
+    const Bucket f_hi = find_bucket(hA, scratch, digit_order, rank[0]);  // -1 for a rank outside 1 .. n_keys
+    const Bucket f_lo = find_bucket(hA, scratch, digit_order, rank[1]);
     for (int e = threadIdx.x; e < 256 * 32; e += 64 * kRadixWaves) { hA[e] = 0; hB[e] = 0; }
     __syncthreads();
-    const uint32_t d_hi = (uint32_t)dig[0][n], d_lo = (uint32_t)dig[1][n];  // -1 matches no top byte
+    const uint32_t d_hi = (uint32_t)f_hi.digit, d_lo = (uint32_t)f_lo.digit;  // -1 matches no top byte
     for (int tile = wave; tile < kTiles; tile += kRadixWaves) {
         const int64_t row = (int64_t)(tile * 32 + n) * stride + stride / 2;
         const floatx16_t acc = score_tile<T, R>(load_frag_row<T, R>(Kb, row, lane), qf);
@@ -122,23 +110,13 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_sample_kernel(const T
         }
     }
     __syncthreads();
-    if (threadIdx.x < 64) {
-        const int q = threadIdx.x & 31, w = threadIdx.x >> 5;
-        const int d0 = dig[w][q];
-        uint32_t out = w ? 0u : 0xFFFFFFFFu;  // no bound on this side
-        if (d0 >= 0) {
-            const uint32_t *h = w ? hB : hA;
-            const int rem = rank[w] - abv[w][q];
-            int above = 0, d1 = 0;
-            for (int b = 255; b >= 0; --b) {
-                const int c = (int)h[b * 32 + q];
-                if (above + c >= rem) { d1 = b; break; }
-                above += c;
-            }
-            const uint32_t key16 = ((uint32_t)d0 << 8) | (uint32_t)d1;
-            out = w ? (key16 << 16) : ((key16 << 16) | 0xFFFFu);  // rounded outward
-        }
-        if (q0 + q < Lq) (w ? lo_out : hi_out)[(int64_t)bh * padded_len(Lq) + q0 + q] = out;
+    const Bucket g_hi = find_bucket(hA, scratch, digit_order, rank[0] - f_hi.above);
+    const Bucket g_lo = find_bucket(hB, scratch, digit_order, rank[1] - f_lo.above);
+    if (threadIdx.x < 32 && q0 + n < Lq) {
+        const int64_t g = (int64_t)bh * padded_len(Lq) + q0 + n;
+        // rounded outward; no bound on a side whose order statistic lies outside the sample
+        hi_out[g] = f_hi.digit < 0 ? 0xFFFFFFFFu : ((uint32_t)f_hi.digit << 24 | (uint32_t)g_hi.digit << 16 | 0xFFFFu);
+        lo_out[g] = f_lo.digit < 0 ? 0u : ((uint32_t)f_lo.digit << 24 | (uint32_t)g_lo.digit << 16);
     }
 }
 
@@ -153,6 +131,7 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_hist_kernel(const T *
                                                                       int32_t *__restrict__ todo, int qtiles)
 {
     __shared__ uint32_t hist[256 * 32];
+    __shared__ BucketScratch<64 * kRadixWaves> scratch;
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
     const int q0 = blockIdx.x * 32;
@@ -216,24 +195,16 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_hist_kernel(const T *
     }
     __syncthreads();
 
+    const int kr = tab.k[slot];
+    const Bucket f = find_bucket(hist, scratch, [](int b) { return b; }, kr);
     if (threadIdx.x < 32) {  // lane t of wave 0 holds lo and s of query q0 + t
         bool fail = false;
-        if (q0 + (int)threadIdx.x < Lq) {
-            const int kr = tab.k[slot];
-            const uint32_t *hcol = hist + threadIdx.x;
-            int cum = (int)hcol[32 * 255], b = -1, cnt = 0;
-            if (cum < kr) {
-                for (int bb = 254; bb >= 0; --bb) {
-                    const int c = (int)hcol[32 * bb];
-                    if (cum + c >= kr) { b = bb; cnt = c; break; }
-                    cum += c;
-                }
-            }
-            if (b < 0) {
-                fail = true;  // the k-th largest score lies above the bins or below lo
+        if (q0 + n < Lq) {
+            const int want = kr - f.above, cnt = f.count;
+            if (f.digit < 0 || f.digit == 255) {
+                fail = true;  // the k-th largest score lies below lo or above the bins
             } else {
-                const int want = kr - cum;
-                prefix[g] = lo + ((uint32_t)b << s);
+                prefix[g] = lo + ((uint32_t)f.digit << s);
                 if (s == 0) {  // the bin is a single score value: settled
                     krem[g] = want == cnt ? -want : want;
                     win[g] = 0u;
