@@ -77,7 +77,7 @@ typedef struct dsv_problem {
 /* The caller promises that every idx row, and every idx_t list, is in ascending order -- which is
  * how dsv_lowrank_topk / dsv_lowrank_topk_t write them.  Stage 2 then runs its L2-blocked kernels
  * (the key axis cut into cache-sized ranges, one contiguous segment of each row per range), which
- * need more workspace and are several times faster on long sequences.  Without the flag stage 2
+ * need more workspace and are several times faster on long sequences, wherever the problem is large enough for them.  Without the flag stage 2
  * makes no assumption on the order.  Setting it for unsorted indices gives wrong results. */
 #define DSV_FLAG_SORTED_INDEX 1u
 
@@ -122,7 +122,7 @@ DSV_API dsv_status dsv_lowrank_topk_t(const dsv_problem *p, const void *Q, const
  *     O_i = sum_j p_j v_j;     lse_i = log sum_j exp(s_j).
  * O is written in `dtype`, lse in float.  Workspace: none without DSV_FLAG_SORTED_INDEX (the query
  * returns 0 and a null workspace is accepted); with it, the segment pointers and the per-range
- * partial results. */
+ * partial results, or none where the problem is too small for ranges to pay. */
 DSV_API size_t dsv_sparse_attn_fwd_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                const int32_t *idx, void *O, float *lse,
@@ -140,7 +140,7 @@ DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, cons
  * rounding alone would cost more than the output tolerance; O only serves as a centring value
  * (dO . O is within rounding of Delta) that keeps the accumulated weights small.  The workspace holds Delta, the transposed index
  * (as large as idx), its column pointers and the counters of dsv_idx_transpose.  The transposed index built here has
- * ascending lists whatever the order inside the rows of idx is, so the dkdv step always runs its L2-blocked kernel
+ * ascending lists whatever the order inside the rows of idx is, so the dkdv step may run its L2-blocked kernel
  * and the results are identical, bit for bit, to dsv_sparse_attn_bwd_t on dsv_idx_transpose's output and from run to
  * run.  Without DSV_FLAG_SORTED_INDEX the rows of larger problems are first copied in ascending order (same workspace), so
  * that the dq step is L2-blocked as well; the result is then that of the ascending rows.  Building the transposed index is a
@@ -183,7 +183,7 @@ DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, co
  *   keys with an empty list get zeros.
  *
  * Workspace of dq and dkdv: none without DSV_FLAG_SORTED_INDEX (query returns 0, null accepted);
- * with it, segment pointers and per-range partial sums. */
+ * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked. */
 DSV_API size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                           const int32_t *idx, const void *O, const float *lse, const void *dO,

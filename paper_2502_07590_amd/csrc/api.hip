@@ -120,8 +120,37 @@ dsv_status check_grouping(const dsv_problem &p, const dsv_grouping *g)
 }
 int group_size(const dsv_grouping &g) { return g.gf * g.gh * g.gw; }
 
-// Whether stage 2 runs its L2-blocked kernels: sorted indices promised and more than one range.
+// Whether the grouped kernels run L2-blocked: sorted indices promised and more than one range.
 bool use_split(const dsv_problem &p, const SplitPlan &pl) { return (p.flags & DSV_FLAG_SORTED_INDEX) && pl.S > 1; }
+
+size_t kv_bytes(const dsv_problem &p) { return (size_t)p.L * 2 * p.d * esize(p.dtype); }  // K and V rows of a head
+int64_t mean_k(const dsv_problem &p)
+{
+    int64_t s = 0;
+    for (int h = 0; h < p.H; ++h) s += p.k_per_head[h];
+    return s / p.H;
+}
+
+// Whether the per-query forward and dq step run L2-blocked: sorted indices promised, and enough to gather from enough rows.
+// Blocking costs about 0.5 ns per (row, range) -- partial results written and merged, segments, row order -- and wins
+// back what the gathers lose to L2 misses, which ascending rows walked side by side already keep few.  Measured at bf16,
+// d = 128, four heads, blocked against not, forward / dq in us: L = 4096, k = 40: 75 : 24 / 106 : 23; 8192, k = 512: 387 : 331 /
+// 474 : 328; 16000 (7.8 MB), k = 1000: 1295 : 1296 / 1500 : 1351, k = 3200: 3472 : 3484 / 4003 : 4122; 20280, k = 202: 556 : 375 /
+// 700 : 346, k = 1267: 1992 : 2200 / 2276 : 2257; 32768 (16 MB), k = 327: 1241 : 921 / 1436 : 979, k = 2048: 4962 : 5804 /
+// 5574 : 6924; two heads of 65536 (32 MB), k = 655: 2438 : 2067 / 2449 : 2172, k = 1310: 3956 : 4132 / 4158 : 5057; of 131072
+// (64 MB), k = 327: 4747 : 2473 / 4666 : 3727, k = 655: 6150 : 6167 / 6186 : 7390, k = 1310: 9356 : 14269 / 9630 : 16269.
+bool split_rows(const dsv_problem &p, const SplitPlan &pl)
+{
+    return use_split(p, pl) && kv_bytes(p) >= ((size_t)8 << 20) && mean_k(p) >= (kv_bytes(p) > ((size_t)48 << 20) ? 512 : 768);
+}
+
+// The same for the key-major step, whose lists differ in length: the blocked form also sorts them by it.  Measured as above:
+// L = 4096, k = 40: 114 : 61, k = 256: 191 : 178, k = 819: 359 : 411; 8192, k = 81: 240 : 166, k = 512: 519 : 624; 12000, k = 120:
+// 408 : 333, k = 750: 985 : 1396; 16000, k = 160: 569 : 559; one head of 4096, k = 256: 96 : 62.
+bool split_lists(const dsv_problem &p, const SplitPlan &pl)
+{
+    return use_split(p, pl) && kv_bytes(p) > ((size_t)1 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
+}
 
 // Whether a whole backward on rows in any order sorts them first, so that the dq step runs L2-blocked: once a head's K and
 // V rows no longer share an XCD's 4 MB L2 with everything else.  Measured, bf16, d = 128, k = L / 12, the whole backward
@@ -142,7 +171,7 @@ FwdLayout fwd_layout(const dsv_problem &p)
 {
     FwdLayout w{};
     w.plan = make_split_plan(p, kFwdRangeBytes);
-    w.split = use_split(p, w.plan);
+    w.split = split_rows(p, w.plan);
     if (!w.split) return w;
     const size_t rows = (size_t)p.B * p.H * p.L;
     size_t o = 0;
@@ -159,7 +188,7 @@ FwdLayout fwd_layout(const dsv_problem &p)
 // One split backward step (dq or dkdv): segment pointers and two [rows, S, d] partial arrays
 // (+ [rows, S] for the dq step's Delta partials; laid out for both so that the steps can share it).
 struct StepLayout {
-    bool split;
+    bool split_dq, split_dkdv;
     SplitPlan plan;
     size_t seg, pa, pb, pdelta, hist, order, rowstat, total;
 };
@@ -168,8 +197,9 @@ StepLayout step_layout(const dsv_problem &p)
 {
     StepLayout w{};
     w.plan = make_split_plan(p, kBwdRangeBytes);
-    w.split = use_split(p, w.plan);
-    if (!w.split) return w;
+    w.split_dq = split_rows(p, w.plan);
+    w.split_dkdv = split_lists(p, w.plan);
+    if (!w.split_dq && !w.split_dkdv) return w;
     const size_t nbh = (size_t)p.B * p.H;
     const size_t rows = nbh * p.L;
     size_t o = 0;
@@ -414,7 +444,7 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     if (st != DSV_OK) return st;
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.split) return launch_bwd_dq(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, stream);
+    if (!w.split_dq) return launch_bwd_dq(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, stream);
     return launch_bwd_dq_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, w.plan,
                                step_buffers(static_cast<char *>(workspace), w), stream);
 }
@@ -458,7 +488,7 @@ dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const v
     if (st != DSV_OK) return st;
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.split)
+    if (!w.split_dkdv)
         return launch_bwd_dkdv(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
                                stream);
     return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
@@ -624,7 +654,7 @@ GroupedBwdLayout grouped_bwd_layout(const dsv_problem &p, const dsv_grouping &g)
     GroupedBwdLayout w{};
     // the L2-blocked sweep expands a list of groups while it stages it; the plain sweep (a single range) and the
     // general path take the per-query form written out
-    w.lists_of_groups = native && step_layout(sorted).split && (uint64_t)p.L * (uint64_t)group_size(g) < (1ull << 32);
+    w.lists_of_groups = native && step_layout(sorted).split_dkdv && (uint64_t)p.L * (uint64_t)group_size(g) < (1ull << 32);
     size_t o = 0;
     w.delta = o; o = align_up(o + nbh * p.L * 4, 256);
     w.qp = o; o = align_up(o + rows, 256);

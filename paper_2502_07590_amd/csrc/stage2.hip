@@ -2,7 +2,8 @@
 // backward (paper Sec. "Sparse Attention with Query Grouping", per-query form; attention formula
 // of Sec. "Various Self-Attention Paradigms"), for index rows in ANY order.  The inner loops live in stage2_core.h.
 //
-// A wave handles 4 rows (one per 16-lane group), a block 16 consecutive rows of one head.
+// Two layouts: a lane group per row (a wave handles 64 / lanes rows side by side), and a wave per row for small problems and
+// for the key-major step, whose lists differ in length.
 #include <algorithm>
 
 #include "stage2_core.h"
@@ -53,7 +54,8 @@ __global__ __launch_bounds__(256) void sparse_fwd_kernel(const T *__restrict__ Q
 // Two gather passes with no floating-point atomics:
 //   dq pass    query-major over idx: dQ and the row term Delta_i;
 //   dkdv pass  key-major over the transposed index (for each key, the queries that selected it):
-//              dK and dV, each output row owned by one lane group.
+//              dK and dV, each output row owned by one wave; keys with an empty list get zeros.
+//                dK_j = scale * sum_i dS_ij q_i,  dV_j = sum_i p_ij dO_i,  dS_ij = p_ij (dO_i . v_j - Delta_i)
 // Delta_i = dO_i . O_i equals sum_j p_ij dP_ij over the selected keys (dP_ij = dO_i . v_j); the dq
 // pass forms it from that sum in fp32, because the stored O is rounded to the storage type and the
 // error of dO . O_stored alone would exceed the output tolerance.  One sweep yields both Delta and dQ:
@@ -103,59 +105,178 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_kernel(const T *__restrict_
     }
 }
 
-// dkdv pass: a group of 16 lanes owns key j and walks the queries that selected it.
-//   dK_j = scale * sum_i dS_ij q_i,  dV_j = sum_i p_ij dO_i,  dS_ij = p_ij (dO_i . v_j - Delta_i).
-// Keys with an empty list get zeros; every output row is written exactly once.
+// ------------------------------------------------------------------------------------ a wave per row
+// Forms for heads whose K and V rows an L2 holds: the 64 / LPR lane groups of a wave share ONE row (or key), each walks an
+// equal part of its index row (or list), and the parts' sums meet in a butterfly over the groups.  No ranges, no partial
+// results in memory, no row order: one launch, and 64 / LPR times the waves of the forms above, which is what a short
+// sequence lacks (L = 1024, two heads, fp32, k = 128: the forward 33.6 -> 12.7 us, the backward 72.9 -> 25.5 us against the blocked
+// forms).  The key-major step takes this form wherever it does not run blocked: lists differ in length by an order of
+// magnitude, and a wave that owns 16 of them waits for the longest (L = 32768, four heads, k = 2048, lists as stage 1 makes
+// them: 19.8 ms by lane groups, 14.4 by waves).
+template <int LPR> __device__ __forceinline__ float group_sum(float x)  // over the 64 / LPR groups of the wave
+{
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
+// This group's part of n positions: whole steps of 4.
+template <int LPR> __device__ __forceinline__ void group_part(int n, int grp, int &tb, int &te)
+{
+    const int per = ((n + 64 / LPR - 1) / (64 / LPR) + 3) & ~3;
+    tb = min(grp * per, n);
+    te = min(tb + per, n);
+}
+
 template <typename T, int D, int LPR>
-__global__ __launch_bounds__(256) void sparse_bwd_dkdv_kernel(const T *__restrict__ Q, const T *__restrict__ K,
-                                                              const T *__restrict__ V,
-                                                              const int32_t *__restrict__ idxT,
-                                                              const int64_t *__restrict__ col,
-                                                              const float *__restrict__ lse,
-                                                              const float *__restrict__ delta,
-                                                              const T *__restrict__ dO, T *__restrict__ dK,
-                                                              T *__restrict__ dV, int L, float scale, HeadTable tab)
+__global__ __launch_bounds__(256) void sparse_fwd_wave_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                              const T *__restrict__ V, const int32_t *__restrict__ idx,
+                                                              T *__restrict__ O, float *__restrict__ lse, int L, float scale,
+                                                              HeadTable tab)
 {
     typedef LaneLayout<T, D, LPR> LL;
     constexpr int CH = D / LPR;
-    constexpr int RPW = 64 / LPR;  // rows per wave
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = tab.k[slot];
+    const int lane = threadIdx.x & 63;
     const int grp = lane / LPR, s = lane % LPR;
-    const int64_t jq = (int64_t)blockIdx.x * (4 * RPW) + wave * RPW + grp;
-    const bool live = jq < L;
-    const int64_t j = live ? jq : L - 1;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= L) return;  // whole wave; nothing synchronises across waves
+    const int64_t head_base = (int64_t)bh * L * D;
+    const int32_t *row = idx + tab.off[slot] + i * k;
+    const RowChunk<T, CH> q = load_chunk<T, CH, LL::PSB>(Q + head_base + i * D + LL::off(s));
+    FwdState<CH> st;
+    st.m = -INFINITY;
+    st.l = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) st.acc[c] = 0.f;
+    __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
+    int tb, te;
+    group_part<LPR>(k, grp, tb, te);
+    fwd_sweep<T, D, LPR>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+                         stage_all[threadIdx.x / LPR], s);
+    float m = st.m;
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+    const float f = fast_exp2(st.m - m);  // a group without positions: 2^(-inf) = 0
+    const float l = group_sum<LPR>(st.l * f);
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) st.acc[c] = group_sum<LPR>(st.acc[c] * f) * inv;
+    if (grp == 0) {
+        store_chunk<T, CH, LL::PSB>(O + head_base + i * D + LL::off(s), st.acc);
+        if (s == 0) lse[(int64_t)bh * L + i] = (m + log2f(l)) * kLn2;
+    }
+}
+
+template <typename T, int D, int LPR>
+__global__ __launch_bounds__(256) void sparse_bwd_dq_wave_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                                 const T *__restrict__ V, const int32_t *__restrict__ idx,
+                                                                 const T *__restrict__ O, const float *__restrict__ lse,
+                                                                 const T *__restrict__ dO, T *__restrict__ dQ,
+                                                                 float *__restrict__ delta_out, int L, float scale,
+                                                                 HeadTable tab)
+{
+    typedef LaneLayout<T, D, LPR> LL;
+    constexpr int CH = D / LPR;
+    const int slot = blockIdx.y;
+    const int bh = tab.bh[slot];
+    const int k = tab.k[slot];
+    const int lane = threadIdx.x & 63;
+    const int grp = lane / LPR, s = lane % LPR;
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= L) return;
+    const int64_t head_base = (int64_t)bh * L * D;
+    const int32_t *row = idx + tab.off[slot] + i * k;
+    const RowChunk<T, CH> q = load_chunk<T, CH, LL::PSB>(Q + head_base + i * D + LL::off(s));
+    const RowChunk<T, CH> go = load_chunk<T, CH, LL::PSB>(dO + head_base + i * D + LL::off(s));
+    const RowChunk<T, CH> o = load_chunk<T, CH, LL::PSB>(O + head_base + i * D + LL::off(s));
+    const float delta0 = row_sum<LPR>(dot_chunk<T, CH>(go, o));
+    DqState<CH> st;
+    st.delta = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) { st.a[c] = 0.f; st.b[c] = 0.f; }
+    __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
+    int tb, te;
+    group_part<LPR>(k, grp, tb, te);
+    dq_sweep<T, D, LPR>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+                        lse[(int64_t)bh * L + i] * kLog2e, delta0, stage_all[threadIdx.x / LPR], s);
+    const float delta = group_sum<LPR>(st.delta);
+    float dq[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) dq[c] = scale * group_sum<LPR>(st.a[c] - (delta - delta0) * st.b[c]);
+    if (grp == 0) {
+        store_chunk<T, CH, LL::PSB>(dQ + head_base + i * D + LL::off(s), dq);
+        if (s == 0) delta_out[(int64_t)bh * L + i] = delta;
+    }
+}
+
+template <typename T, int D, int LPR>
+__global__ __launch_bounds__(256) void sparse_bwd_dkdv_wave_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                                   const T *__restrict__ V, const int32_t *__restrict__ idxT,
+                                                                   const int64_t *__restrict__ col,
+                                                                   const float *__restrict__ lse,
+                                                                   const float *__restrict__ delta, const T *__restrict__ dO,
+                                                                   T *__restrict__ dK, T *__restrict__ dV, int L, float scale,
+                                                                   HeadTable tab)
+{
+    typedef LaneLayout<T, D, LPR> LL;
+    constexpr int CH = D / LPR;
+    const int slot = blockIdx.y;
+    const int bh = tab.bh[slot];
+    const int lane = threadIdx.x & 63;
+    const int grp = lane / LPR, s = lane % LPR;
+    const int64_t j = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= L) return;
     const int64_t head_base = (int64_t)bh * L * D;
     const int64_t *cp = col + (int64_t)bh * (L + 1);
     const int64_t beg = cp[j];
-    const int n = live ? (int)(cp[j + 1] - beg) : 0;
-    const int32_t *list = idxT + tab.off[slot] + beg;
-
+    const int n = (int)(cp[j + 1] - beg);
     const RowChunk<T, CH> kc = load_chunk<T, CH, LL::PSB>(K + head_base + j * D + LL::off(s));
     const RowChunk<T, CH> vc = load_chunk<T, CH, LL::PSB>(V + head_base + j * D + LL::off(s));
     DkdvState<CH> st;
 #pragma unroll
     for (int c = 0; c < CH; ++c) { st.dk[c] = 0.f; st.dv[c] = 0.f; }
-    __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
-    int32_t *stage = stage_all[threadIdx.x / LPR];
+    __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
+    int tb, te;
+    group_part<LPR>(n, grp, tb, te);
     dkdv_sweep<T, D, LPR>(st, kc, vc, Q + head_base, dO + head_base, lse + (int64_t)bh * L, delta + (int64_t)bh * L,
-                     (uint32_t)LL::off(s), list, 0, n, scale * kLog2e, stage, s);
-    if (live) {
+                          (uint32_t)LL::off(s), idxT + tab.off[slot] + beg, tb, te, scale * kLog2e,
+                          stage_all[threadIdx.x / LPR], s);
 #pragma unroll
-        for (int c = 0; c < CH; ++c) st.dk[c] *= scale;
+    for (int c = 0; c < CH; ++c) {
+        st.dk[c] = scale * group_sum<LPR>(st.dk[c]);
+        st.dv[c] = group_sum<LPR>(st.dv[c]);
+    }
+    if (grp == 0) {
         store_chunk<T, CH, LL::PSB>(dK + head_base + j * D + LL::off(s), st.dk);
         store_chunk<T, CH, LL::PSB>(dV + head_base + j * D + LL::off(s), st.dv);
     }
 }
 
 // ------------------------------------------------------------------------------------ host
+// Whether rows get a wave each instead of a lane group: when the groups' waves (rows * lanes / 64) would be fewer than
+// `enough`.  Measured, lane groups against waves: bf16, d = 128, one head, k = L / 16, forward: L = 4096 (256 waves): 90 : 32 us,
+// 8192: 190 : 100, 12000: 268 : 255, 16000: 363 : 454; dq: 4096 (512 waves): 55 : 29, 8192: 132 : 88, 12000: 252 : 200,
+// 16000: 349 : 393.  d = 64: forward 12000 (750 waves): 120 : 95, 16000: 160 : 185; dq 16000 (1000 waves): 242 : 185.
+static bool wave_per_row(const dsv_problem &p, int lanes, int64_t enough)
+{
+    return (int64_t)p.B * p.H * p.L * lanes / 64 < enough;
+}
+
 template <typename T, int D>
 static dsv_status fwd_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
                         const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st)
 {
     KernelSpan span(DSV_KERNEL_FWD_SWEEP, st);
     for (int t = 0; t < n_tabs; ++t) {
+        if (wave_per_row(p, SweepLanes<T, D>::fwd, 800)) {
+            hipLaunchKernelGGL((sparse_fwd_wave_kernel<T, D, SweepLanes<T, D>::fwd>), dim3((p.L + 3) / 4, tabs[t].n), dim3(256), 0, st,
+                               (const T *)Q, (const T *)K, (const T *)V, idx, (T *)O, lse, p.L, p.scale, tabs[t]);
+            DSV_LAUNCH_CHECK();
+            continue;
+        }
         dim3 grid((p.L + 256 / SweepLanes<T, D>::fwd - 1) / (256 / SweepLanes<T, D>::fwd), tabs[t].n);
         hipLaunchKernelGGL((sparse_fwd_kernel<T, D, SweepLanes<T, D>::fwd>), grid, dim3(256), 0, st, (const T *)Q, (const T *)K, (const T *)V,
                            idx, (T *)O, lse, p.L, p.scale, tabs[t]);
@@ -171,6 +292,13 @@ static dsv_status bwd_dq_t(const dsv_problem &p, const HeadTable *tabs, int n_ta
 {
     KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
     for (int t = 0; t < n_tabs; ++t) {
+        if (wave_per_row(p, SweepLanes<T, D>::dq, 1600)) {
+            hipLaunchKernelGGL((sparse_bwd_dq_wave_kernel<T, D, SweepLanes<T, D>::dq>), dim3((p.L + 3) / 4, tabs[t].n), dim3(256), 0, st,
+                               (const T *)Q, (const T *)K, (const T *)V, idx, (const T *)O, lse, (const T *)dO, (T *)dQ, delta, p.L,
+                               p.scale, tabs[t]);
+            DSV_LAUNCH_CHECK();
+            continue;
+        }
         dim3 qgrid((p.L + 256 / SweepLanes<T, D>::dq - 1) / (256 / SweepLanes<T, D>::dq), tabs[t].n);
         hipLaunchKernelGGL((sparse_bwd_dq_kernel<T, D, SweepLanes<T, D>::dq>), qgrid, dim3(256), 0, st, (const T *)Q, (const T *)K,
                            (const T *)V, idx, (const T *)O, lse, (const T *)dO, (T *)dQ, delta, p.L, p.scale, tabs[t]);
@@ -186,9 +314,9 @@ static dsv_status bwd_dkdv_t(const dsv_problem &p, const HeadTable *tabs, int n_
 {
     KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
     for (int t = 0; t < n_tabs; ++t) {
-        dim3 kgrid((p.L + 256 / SweepLanes<T, D>::dkdv - 1) / (256 / SweepLanes<T, D>::dkdv), tabs[t].n);
-        hipLaunchKernelGGL((sparse_bwd_dkdv_kernel<T, D, SweepLanes<T, D>::dkdv>), kgrid, dim3(256), 0, st, (const T *)Q, (const T *)K,
-                           (const T *)V, idxT, col, lse, delta, (const T *)dO, (T *)dK, (T *)dV, p.L, p.scale, tabs[t]);
+        hipLaunchKernelGGL((sparse_bwd_dkdv_wave_kernel<T, D, SweepLanes<T, D>::dq>), dim3((p.L + 3) / 4, tabs[t].n), dim3(256), 0, st,
+                           (const T *)Q, (const T *)K, (const T *)V, idxT, col, lse, delta, (const T *)dO, (T *)dK, (T *)dV, p.L,
+                           p.scale, tabs[t]);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;

@@ -380,13 +380,9 @@ __device__ __forceinline__ void dkdv_step(DkdvState<D / LPR> &st, const RowChunk
             const float2 rs = stat_s[iq[u] - stat_base];
             l2[u] = rs.x;
             dl[u] = rs.y;
-        } else if (delta_h) {
+        } else {
             l2[u] = lse_h[iq[u]] * kLog2e;
             dl[u] = delta_h[iq[u]];
-        } else {  // lse_h is a packed array {lse * log2(e), Delta} per query: one 8-byte load
-            const float2 rs = reinterpret_cast<const float2 *>(lse_h)[iq[u]];
-            l2[u] = rs.x;
-            dl[u] = rs.y;
         }
     }
     float p[U], ds[U];
