@@ -1,0 +1,346 @@
+// Query grouping, backward: dK and dV of the grouped attention (paper Sec. "Sparse Attention with Query Grouping"), bf16,
+// d = 128, groups of up to 32 queries.
+//
+// Key-major, and dense where the selection is: a wave owns 16 consecutive keys and walks the UNION of their lists of groups;
+// every group of the union brings its G queries' Q and dO rows once, and all four products of 32 queries x 16 keys run on
+// the matrix cores with a mask for the (group, key) pairs that are not selected.  Neighbouring keys of the token grid are
+// selected by much the same groups -- on spatially smooth inputs the union of 16 keys is 3.2 times a single list, so that
+// a step of 512 (query, key) pairs holds 160 selected ones --, and even with unrelated keys (10 times, at 6 % kept) the
+// matrix cores form the pairs faster than the vector units the selected ones alone.
+//
+//   S^T = Q_u K^T, dP^T = dO_u V^T   v_mfma_f32_16x16x32_bf16, A = 16 gathered rows as they come from memory (lane = row
+//        l % 16, channels 32 m + 8 (l / 16): one load instruction touches whole 64-byte sectors), B = the keys' K and V rows,
+//        kept in registers.  Lane l then holds key l % 16 against queries 4 (l / 16) + 0..3 of either half of the step.
+//   dK += dS^T Q_u, dV += P^T dO_u   A = the weights, which those lanes hold in the A layout already (which queries a lane
+//        group contracts is free: slots 16 (e / 4) + 4 (l / 16) + e % 4), as bf16 head + tail -- 16 significant bits of every
+//        fp32 weight, as in the per-query sweep --, B = the gathered rows transposed out of LDS (tr_frag).
+//
+// Work item = (head, query range, 4 x 16 keys): the rows of a range (at most 8192 queries, 4 MB) stay in an XCD's L2, and
+// every XCD walks its ranges one after the other.  A range leaves partial sums for the per-query merge; a single range
+// writes the result.  L = 32768, four heads, k = 2048, 2 x 2 x 2 cubes, smooth inputs: 3.5 ms, with the
+// merge 3.6 (the per-query key-major sweep on the lists written out: 5.75 + 0.45), a sixth of it matrix work: a step is a
+// chain of loads, LDS, two products and the queue that eight waves per CU only partly hide.  One wave per block instead of
+// four neighbouring ones measured 7 % slower (neighbours share rows in the L1).
+#include <algorithm>
+
+#include "stage2_core.h"
+
+namespace dsv {
+
+typedef uint32_t __attribute__((may_alias)) u32m;
+
+constexpr int kUnionKeys = 16;        // keys per wave
+constexpr int kUnionGroups = 1024;    // groups whose key masks a wave holds at a time
+constexpr int kUnionRow = 128 * 2 + 16;  // bytes from one parked row to the next
+constexpr int kUnionQueue = 128;      // queued (group, mask) entries, a power of two
+
+struct UnionWave {
+    unsigned char q[32 * kUnionRow], g[32 * kUnionRow];  // the step's 32 Q and dO rows
+    uint32_t mask[kUnionGroups / 2];                     // 16-bit key masks of the groups in the window, two per word
+    uint32_t queue[kUnionQueue];                         // group - first of the range << 16 | mask
+    float2 stat[32];                                     // {lse log2 e, Delta} of the step's queries
+    uint32_t smask[32];                                  // key mask of every slot
+};
+static_assert(4 * sizeof(UnionWave) <= 80 * 1024, "two blocks per CU");
+
+struct UnionPlan {
+    int S;             // ranges: 1, 2, 4 or a multiple of 8
+    int groups;        // groups per range
+    int nkb;           // blocks of 64 keys
+};
+
+// Place of slot s among the parked rows: the eight rows that one pass of a transposing read serves (two lane groups) lie
+// two apart, i.e. in disjoint LDS banks.
+__device__ __forceinline__ int union_row(int s) { return (s & 16) + 2 * (s & 7) + ((s >> 3) & 1); }
+
+__device__ __forceinline__ void union_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Q, dO, rowstat: queries in group-major order (group g = queries g G .. g G + G - 1).
+__global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                              const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
+                                                              const int32_t *__restrict__ lists, const int64_t *__restrict__ col,
+                                                              const float2 *__restrict__ rowstat, bf16_t *__restrict__ dK,
+                                                              bf16_t *__restrict__ dV, float *__restrict__ pdk,
+                                                              float *__restrict__ pdv, int L, int G, float scale, HeadTable tab,
+                                                              UnionPlan pl)
+{
+    constexpr int D = 128;
+    __shared__ __align__(16) UnionWave sh_all[4];
+    // block -> (head, range, key block): consecutive ids on consecutive XCDs, an XCD stays inside one range
+    int slot, range, kb;
+    {
+        const int share = pl.S < 8 ? 8 / pl.S : 1;           // XCDs that work on the same range
+        const int per_xcd = pl.S < 8 ? (pl.nkb + share - 1) / share : pl.nkb * (pl.S / 8);
+        const int64_t b = blockIdx.x;
+        slot = (int)(b / (8 * per_xcd));
+        const int rem = (int)(b - (int64_t)slot * 8 * per_xcd);
+        const int xcd = rem & 7, local = rem >> 3;
+        if (pl.S < 8) {
+            range = xcd % pl.S;
+            kb = local * share + xcd / pl.S;
+        } else {
+            range = local / pl.nkb * 8 + xcd;
+            kb = local % pl.nkb;
+        }
+        if (kb >= pl.nkb) return;
+    }
+    const int bh = tab.bh[slot];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c16 = lane & 15, g4 = lane >> 4;
+    UnionWave &sh = sh_all[wave];
+    const int j0 = (kb * 4 + wave) * kUnionKeys;
+    if (j0 >= L) return;  // whole wave; nothing below synchronises across waves
+    const int Lq = L / G;
+    const int gb = min(range * pl.groups, Lq), ge = min(gb + pl.groups, Lq);  // this range's groups
+    const int64_t hb = (int64_t)bh * L * D;
+    const bf16_t *Qr = Q + hb + (int64_t)gb * G * D, *Gr = dO + hb + (int64_t)gb * G * D;  // rows of the range
+    const float2 *stat = rowstat + (int64_t)bh * L + (int64_t)gb * G;
+
+    // B operands: the keys' rows (past the end: the last key, never selected)
+    bf16x8_t kf[4], vf[4];
+    {
+        const int64_t row = hb + (int64_t)min(j0 + c16, L - 1) * D + g4 * 8;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            kf[m] = *reinterpret_cast<const bf16x8_t *>(K + row + m * 32);
+            vf[m] = *reinterpret_cast<const bf16x8_t *>(V + row + m * 32);
+        }
+    }
+    // list pointers: four lanes per key, each takes every fourth entry from its first on
+    const int32_t *list;
+    int pos, end;
+    {
+        const int j = j0 + (lane >> 2);
+        const int64_t *cp = col + (int64_t)bh * (L + 1) + min(j, L - 1);
+        const int64_t first = cp[0];
+        end = j < L ? (int)(cp[1] - first) : 0;
+        list = lists + tab.off[slot] + first;
+        int lo = 0, hi = end;  // first entry of this range
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (list[mid] < gb) lo = mid + 1; else hi = mid;
+        }
+        pos = lo + (lane & 3);
+    }
+    floatx4_t dk[8], dv[8];  // [channel block]: channel 16 nb + l % 16, keys 4 (l / 16) + v
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) { dk[nb] = floatx4_t{0.f, 0.f, 0.f, 0.f}; dv[nb] = dk[nb]; }
+    const float c2 = scale * kLog2e;
+    const int NG = 32 / G;                                   // groups per step
+    const int ga = c16 / G, gc = (16 + c16) / G;             // this lane's two load slots: group of the step ...
+    const int ma = c16 - ga * G, mc = 16 + c16 - gc * G;     // ... and member (a group >= NG: an unused slot)
+    const int gs = (lane & 31) / G, ms = (lane & 31) - gs * G;  // slot lane % 32, for row statistics and mask
+    const int rowa = union_row(c16) * kUnionRow + g4 * 16, rowc = union_row(16 + c16) * kUnionRow + g4 * 16;
+    const int tr0 = union_row(4 * g4 + (c16 >> 2)) * kUnionRow + (c16 & 3) * 8, tr1 = tr0 + 16 * kUnionRow;
+
+    int head = 0, count = 0;          // queue: ring positions head .. head + count - 1
+    int win = gb, scan = kUnionGroups;  // window of masks [win, win + kUnionGroups); groups of it already queued
+    bool fresh = false;               // no window built yet
+    // Fills the queue up to a step's groups, or as far as the range goes.
+    auto refill = [&]() {
+        while (count < NG) {
+            if (scan >= kUnionGroups) {
+                if (fresh) win += kUnionGroups;
+                fresh = true;
+                if (win >= ge) { win = ge; scan = kUnionGroups; fresh = false; return; }
+                const int lim = min(win + kUnionGroups, ge);
+#pragma unroll
+                for (int e = 0; e < kUnionGroups / 2 / 64; ++e) sh.mask[lane + 64 * e] = 0u;
+                union_sync();
+                const uint32_t bit = 1u << (lane >> 2);
+                bool more = true;
+                while (more) {
+                    int e[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) e[u] = pos + 4 * u < end ? list[pos + 4 * u] : 0x7FFFFFFF;
+                    int took = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e[u] < lim) {  // ascending: a prefix of the four
+                            const int r = max(e[u] - win, 0);
+                            atomicOr(&sh.mask[r >> 1], bit << (16 * (r & 1)));
+                            ++took;
+                        }
+                    pos += 4 * took;
+                    more = __any(took == 4);
+                }
+                union_sync();
+                scan = 0;
+            }
+            const uint32_t w = sh.mask[(scan + lane) >> 1];
+            const uint32_t m = (w >> (16 * (lane & 1))) & 0xFFFFu;
+            const unsigned long long some = __ballot(m != 0u);
+            if (m) {
+                const int at = head + count + __popcll(some & ((1ull << lane) - 1ull));
+                sh.queue[at & (kUnionQueue - 1)] = (uint32_t)(win - gb + scan + lane) << 16 | m;
+            }
+            count += __popcll(some);
+            scan += 64;
+        }
+    };
+    bf16x8_t qa[2][4], oa[2][4];  // A operands: rows of slots l % 16 and 16 + l % 16
+    float2 st = make_float2(0.f, 0.f);
+    uint32_t sm = 0u;
+    // Takes the next step's groups off the queue and requests their rows; false at the end of the range.
+    auto fetch = [&]() -> bool {
+        refill();
+        if (count == 0) return false;
+        union_sync();
+        const int n = min(NG, count);
+        const uint32_t first = sh.queue[head & (kUnionQueue - 1)];
+        auto entry = [&](int gi) { return gi < n ? sh.queue[(head + gi) & (kUnionQueue - 1)] : (first & 0xFFFF0000u); };
+        const uint32_t ea = entry(ga), ec = entry(gc), es = entry(gs);
+        const int64_t ra = (int64_t)((int)(ea >> 16) * G + ma) * D + g4 * 8;
+        const int64_t rc = (int64_t)((int)(ec >> 16) * G + mc) * D + g4 * 8;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            qa[0][m] = *reinterpret_cast<const bf16x8_t *>(Qr + ra + m * 32);
+            qa[1][m] = *reinterpret_cast<const bf16x8_t *>(Qr + rc + m * 32);
+            oa[0][m] = *reinterpret_cast<const bf16x8_t *>(Gr + ra + m * 32);
+            oa[1][m] = *reinterpret_cast<const bf16x8_t *>(Gr + rc + m * 32);
+        }
+        st = stat[(int)(es >> 16) * G + ms];
+        sm = es & 0xFFFFu;
+        head += n;
+        count -= n;
+        return true;
+    };
+    bool have = fetch();
+    while (have) {  // wave-uniform
+        // park the rows, the row statistics and the masks
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            *reinterpret_cast<bf16x8_t *>(sh.q + rowa + m * 64) = qa[0][m];
+            *reinterpret_cast<bf16x8_t *>(sh.q + rowc + m * 64) = qa[1][m];
+            *reinterpret_cast<bf16x8_t *>(sh.g + rowa + m * 64) = oa[0][m];
+            *reinterpret_cast<bf16x8_t *>(sh.g + rowc + m * 64) = oa[1][m];
+        }
+        if (lane < 32) {
+            sh.stat[lane] = st;
+            sh.smask[lane] = sm;
+        }
+        floatx4_t as[2], ap[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            as[t] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+            ap[t] = as[t];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                as[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[t][m], kf[m], as[t], 0, 0, 0);
+                ap[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(oa[t][m], vf[m], ap[t], 0, 0, 0);
+            }
+        }
+        union_sync();
+        have = fetch();  // the next step's rows travel while this one is finished
+        uint32_t ph[4], pt[4], sh_[4], st_[4];  // A operands of the second products: two queries per word
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint4 mk = *reinterpret_cast<const uint4 *>(&sh.smask[16 * t + 4 * g4]);
+            const float4 s01 = *reinterpret_cast<const float4 *>(&sh.stat[16 * t + 4 * g4]);
+            const float4 s23 = *reinterpret_cast<const float4 *>(&sh.stat[16 * t + 4 * g4 + 2]);
+            const uint32_t mm[4] = {mk.x, mk.y, mk.z, mk.w};
+            const float l2[4] = {s01.x, s01.z, s23.x, s23.z}, dl[4] = {s01.y, s01.w, s23.y, s23.w};
+            float p[4], ds[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                p[v] = (mm[v] >> c16) & 1u ? fast_exp2(as[t][v] * c2 - l2[v]) : 0.f;
+                ds[v] = p[v] * (ap[t][v] - dl[v]);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; v += 2) {
+                const SplitWeights wp = split_weights(p[v], p[v + 1]), ws = split_weights(ds[v], ds[v + 1]);
+                ph[2 * t + v / 2] = wp.head; pt[2 * t + v / 2] = wp.tail;
+                sh_[2 * t + v / 2] = ws.head; st_[2 * t + v / 2] = ws.tail;
+            }
+        }
+        auto frag = [](const uint32_t (&w)[4]) { return __builtin_bit_cast(bf16x8_t, make_uint4(w[0], w[1], w[2], w[3])); };
+        const bf16x8_t fph = frag(ph), fpt = frag(pt), fsh = frag(sh_), fst = frag(st_);
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) {
+            const bf16x8_t qt = tr_frag(sh.q + tr0 + nb * 32, sh.q + tr1 + nb * 32);
+            const bf16x8_t ot = tr_frag(sh.g + tr0 + nb * 32, sh.g + tr1 + nb * 32);
+            dk[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fst, qt, dk[nb], 0, 0, 0);
+            dv[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fpt, ot, dv[nb], 0, 0, 0);
+            dk[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fsh, qt, dk[nb], 0, 0, 0);
+            dv[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fph, ot, dv[nb], 0, 0, 0);
+        }
+        union_sync();  // the next step overwrites the parked rows
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int j = j0 + 4 * g4 + v;
+        if (j < L) {
+            if (pl.S == 1) {
+                bf16_t *ok = dK + hb + (int64_t)j * D + c16, *ov = dV + hb + (int64_t)j * D + c16;
+#pragma unroll
+                for (int nb = 0; nb < 8; ++nb) {
+                    ok[16 * nb] = f32_to_bf16(scale * dk[nb][v]);
+                    ov[16 * nb] = f32_to_bf16(dv[nb][v]);
+                }
+            } else {
+                const int64_t o = (((int64_t)bh * L + j) * pl.S + range) * D + c16;
+#pragma unroll
+                for (int nb = 0; nb < 8; ++nb) {
+                    pdk[o + 16 * nb] = dk[nb][v];
+                    pdv[o + 16 * nb] = dv[nb][v];
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------ host
+static UnionPlan union_plan(int L, int G)
+{
+    UnionPlan pl;
+    const int want = (int)((L + kMaxRangeRows - 1) / kMaxRangeRows);  // ranges of at most 8192 queries
+    const int S = want <= 1 ? 1 : want <= 2 ? 2 : want <= 4 ? 4 : (want + 7) / 8 * 8;
+    const int Lq = L / G;
+    pl.S = S;
+    pl.groups = (Lq + S - 1) / S;  // at most 8192 + 32 queries: group numbers inside a range fit 16 bits
+    pl.nkb = (L + 4 * kUnionKeys - 1) / (4 * kUnionKeys);
+    return pl;
+}
+
+size_t grouped_dkdv_bytes(const dsv_problem &p, int G)
+{
+    const size_t rows = (size_t)p.B * p.H * p.L;
+    const int S = union_plan(p.L, G).S;
+    return align_up(rows * 8, 256) + (S > 1 ? 2 * align_up(rows * S * p.d * 4, 256) : 0);
+}
+
+dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+                               const void *V, const int32_t *lists, const int64_t *col, const float *lse, const float *delta,
+                               const void *dO, void *dK, void *dV, char *ws, hipStream_t st)
+{
+    if (p.dtype != DSV_BF16 || p.d != 128 || G > 32) return DSV_EUNSUPPORTED;
+    const UnionPlan pl = union_plan(p.L, G);
+    const size_t rows = (size_t)p.B * p.H * p.L;
+    float2 *rowstat = reinterpret_cast<float2 *>(ws);
+    float *pdk = reinterpret_cast<float *>(ws + align_up(rows * 8, 256));
+    float *pdv = reinterpret_cast<float *>(ws + align_up(rows * 8, 256) + align_up(rows * pl.S * p.d * 4, 256));
+    dsv_status rc = launch_pack_rowstat(lse, delta, rowstat, (int64_t)rows, st);
+    if (rc != DSV_OK) return rc;
+    {
+        KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
+        const int share = pl.S < 8 ? 8 / pl.S : 1;
+        const int64_t per_xcd = pl.S < 8 ? (pl.nkb + share - 1) / share : (int64_t)pl.nkb * (pl.S / 8);
+        for (int t = 0; t < n_tabs; ++t) {
+            const int64_t blocks = tabs[t].n * per_xcd * 8;
+            if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
+            hipLaunchKernelGGL(grouped_dkdv_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)Q, (const bf16_t *)K,
+                               (const bf16_t *)V, (const bf16_t *)dO, lists, col, (const float2 *)rowstat, (bf16_t *)dK, (bf16_t *)dV,
+                               pdk, pdv, p.L, G, p.scale, tabs[t], pl);
+            DSV_LAUNCH_CHECK();
+        }
+    }
+    if (pl.S == 1) return DSV_OK;
+    return launch_dkdv_merge_bf16_128(p, pdk, pdv, dK, dV, pl.S, st);
+}
+
+}  // namespace dsv

@@ -40,7 +40,7 @@ __device__ __forceinline__ bool decode_item(const SplitPlan &pl, int64_t b, int 
 // from col_ptr), cut by QUERY ranges.
 __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restrict__ index,
                                                           const int64_t *__restrict__ col, int L, HeadTable tab,
-                                                          SplitPlan pl, int32_t *__restrict__ seg, GroupExpand ge)
+                                                          SplitPlan pl, int32_t *__restrict__ seg)
 {
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
     if (col) {
         const int64_t *cp = col + (int64_t)bh * (L + 1);
         base = index + tab.off[slot] + cp[row];
-        len = (int)(cp[row + 1] - cp[row]) * ge.G;  // lists of groups: positions of the expanded list
+        len = (int)(cp[row + 1] - cp[row]);
     } else {
         len = tab.k[slot];
         base = index + tab.off[slot] + (int64_t)row * len;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
     int lo = 0, hi = len;  // first position with value >= target
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if ((int64_t)expanded_entry(base, mid, ge) < target) lo = mid + 1; else hi = mid;
+        if ((int64_t)base[mid] < target) lo = mid + 1; else hi = mid;
     }
     seg[((int64_t)bh * L + row) * np + s] = lo;
 }
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
                                                                     const float2 *__restrict__ rowstat,
                                                                     const T *__restrict__ dO, float *__restrict__ pdk,
                                                                     float *__restrict__ pdv, int L, float scale,
-                                                                    HeadTable tab, SplitPlan pl, GroupExpand ge)
+                                                                    HeadTable tab, SplitPlan pl)
 {
     typedef LaneLayout<T, D, LPR> LL;
     constexpr int CH = D / LPR;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
         __syncthreads();
     }
     dkdv_sweep<T, D, LPR, true>(st, kc, vc, Q + head_base, dO + head_base, nullptr, nullptr, (uint32_t)LL::off(s), list, tb,
-                                te, scale * kLog2e, stage, s, stat_s, q_first, ge);
+                                te, scale * kLog2e, stage, s, stat_s, q_first);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + j) * pl.S + range;
         store_acc<T, D, LPR>(pdk + slot_id * D, s, st.dk);
@@ -439,13 +439,12 @@ SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes)
 }
 
 static dsv_status launch_segments(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const SplitPlan &pl,
-                                  const int32_t *index, const int64_t *col, int32_t *seg, hipStream_t st,
-                                  GroupExpand ge = no_expand())
+                                  const int32_t *index, const int64_t *col, int32_t *seg, hipStream_t st)
 {
     const int64_t n = (int64_t)p.L * (pl.S + 1);
     for (int t = 0; t < n_tabs; ++t) {
         dim3 grid((unsigned)((n + 255) / 256), tabs[t].n);
-        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, col, p.L, tabs[t], pl, seg, ge);
+        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, col, p.L, tabs[t], pl, seg);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
@@ -466,6 +465,13 @@ static dsv_status launch_row_order(const dsv_problem &p, const SplitPlan &pl, co
     hipLaunchKernelGGL(seglen_hist_kernel, grid, dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, hist);
     hipLaunchKernelGGL(seglen_scan_kernel, dim3(nbh * pl.S), dim3(1024), 0, st, hist, nbins);
     hipLaunchKernelGGL(seglen_scatter_kernel, grid, dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, hist, order);
+    DSV_LAUNCH_CHECK();
+    return DSV_OK;
+}
+
+dsv_status launch_pack_rowstat(const float *lse, const float *delta, float2 *out, int64_t n, hipStream_t st)
+{
+    hipLaunchKernelGGL(pack_rowstat_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, lse, delta, out, n);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -532,17 +538,14 @@ template <typename T, int D>
 static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                    const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                    const float *lse, const float *delta, const void *dO, void *dK, void *dV,
-                                   const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G)
+                                   const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st)
 {
     const int nbh = p.B * p.H;
-    if (expand_G < 1 || (uint64_t)p.L * (uint64_t)expand_G >= (1ull << 32)) return DSV_EUNSUPPORTED;
-    const GroupExpand ge = expand_G > 1 ? make_expand(expand_G) : no_expand();
-    dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idxT, col, w.seg, st, ge);
+    dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idxT, col, w.seg, st);
     if (rc != DSV_OK) return rc;
     const int64_t nrows = (int64_t)nbh * p.L;
-    hipLaunchKernelGGL(pack_rowstat_kernel, dim3((unsigned)((nrows + 255) / 256)), dim3(256), 0, st, lse, delta,
-                       w.rowstat, nrows);
-    DSV_LAUNCH_CHECK();
+    rc = launch_pack_rowstat(lse, delta, w.rowstat, nrows, st);
+    if (rc != DSV_OK) return rc;
     rc = launch_row_order(p, pl, w.seg, w.hist, w.order, st);
     if (rc != DSV_OK) return rc;
     {
@@ -558,7 +561,7 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
                                               (int)(kMaxRangeRows * sizeof(float2))));
             hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), stat_bytes, st, (const T *)Q, (const T *)K,
                                (const T *)V, idxT, col, w.seg, w.order, (const float2 *)w.rowstat, (const T *)dO, w.pa, w.pb,
-                               p.L, p.scale, tabs[t], lp, ge);
+                               p.L, p.scale, tabs[t], lp);
             DSV_LAUNCH_CHECK();
         }
     }
@@ -577,7 +580,7 @@ dsv_status launch_row_segments(const dsv_problem &p, int rows, const HeadTable *
     const int64_t n = (int64_t)rows * (pl.S + 1);
     for (int t = 0; t < n_tabs; ++t) {
         dim3 grid((unsigned)((n + 255) / 256), tabs[t].n);
-        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, (const int64_t *)nullptr, rows, tabs[t], pl, seg, no_expand());
+        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, (const int64_t *)nullptr, rows, tabs[t], pl, seg);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
@@ -590,6 +593,16 @@ dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const float *pm, cons
     const int64_t n_rows = (int64_t)p.B * p.H * p.L;
     hipLaunchKernelGGL((sparse_fwd_merge_kernel<bf16_t, 128>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, pm, pl_,
                        pacc, (bf16_t *)O, lse, n_rows, S);
+    DSV_LAUNCH_CHECK();
+    return DSV_OK;
+}
+
+dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const float *pdk, const float *pdv, void *dK, void *dV, int S,
+                                      hipStream_t st)
+{
+    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
+    hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<bf16_t, 128>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, pdk, pdv,
+                       (bf16_t *)dK, (bf16_t *)dV, n_rows, S, p.scale);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -633,9 +646,9 @@ dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int 
 dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                  const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                  const float *lse, const float *delta, const void *dO, void *dK, void *dV,
-                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G)
+                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st)
 {
-    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st, expand_G);
+    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st);
 }
 
 }  // namespace dsv

@@ -1,0 +1,46 @@
+"""dK and dV of the grouped backward at the edges of its tiles (16 keys, 32 queries per step, 1024 groups per window, ranges
+of 8192 queries), against the per-query backward of the same selection with the group's row given to every member."""
+from __future__ import annotations
+
+import math
+
+import pytest
+import torch
+
+import paper_2502_07590_amd as dsv
+
+pytestmark = pytest.mark.gpu
+
+
+# cubes of 1, 2, 3, 8, 12 and 32 queries; 1, 2, 4 and 8 ranges; more than one window of groups; keys nobody selects
+@pytest.mark.parametrize("grid,cube,ks", [((1, 1, 17), (1, 1, 1), [5]), ((3, 5, 7), (3, 1, 1), [1, 40]), ((2, 6, 30), (2, 1, 1), [77]),
+                                          ((4, 48, 48), (1, 3, 4), [300, 64]), ((8, 32, 48), (2, 2, 2), [700]), ((4, 72, 72), (2, 1, 1), [90]),
+                                          ((8, 64, 72), (2, 4, 4), [500])])
+def test_grouped_gradients_of_keys_and_values(grid, cube, ks):
+    L, G, H = math.prod(grid), math.prod(cube), len(ks)
+    (F, Hh, Ww), (gf, gh, gw) = grid, cube
+    g = torch.Generator(device="cuda").manual_seed(L)
+    Q, K, V, dO = (torch.randn(1, H, L, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
+    tokens = torch.arange(L, device="cuda").reshape(F // gf, gf, Hh // gh, gh, Ww // gw, gw).permute(0, 2, 4, 1, 3, 5).reshape(-1, G)
+    idx_g, idx, lists, cols = [], [], [], []
+    for k in ks:
+        # evenly spread from a start of the group's own, never the last 7 keys (L > 8): distinct, lists of uneven length
+        n = max(L - 7, k)
+        first = (torch.rand(L // G, 1, generator=g, device="cuda") ** 2 * n).long()
+        rows = ((first + torch.arange(k, device="cuda")[None] * (n // k)) % n).sort(1).values
+        rows = rows.to(torch.int32)
+        full = torch.empty(L, k, dtype=torch.int32, device="cuda")
+        full[tokens.reshape(-1)] = rows.repeat_interleave(G, 0)
+        order = torch.sort(rows.reshape(-1), stable=True).indices
+        col = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+        col[1:] = torch.bincount(rows.reshape(-1), minlength=L).cumsum(0)
+        idx_g.append(rows.reshape(-1)); idx.append(full.reshape(-1)); lists.append((order // k).to(torch.int32)); cols.append(col)
+    p = dsv.Problem(1, H, L, 128, 16, "bf16", ks, 128 ** -0.5, sorted_index=True)
+    grp = dsv.Grouping(grid, cube)
+    O, lse = dsv.sparse_attn_fwd(p, Q, K, V, torch.cat(idx))
+    want = dsv.sparse_attn_bwd(p, Q, K, V, torch.cat(idx), O, lse, dO)
+    got = dsv.sparse_attn_bwd_grouped(p, grp, Q, K, V, torch.cat(idx_g), torch.cat(lists), torch.stack(cols), O, lse, dO)
+    # both are fp32 sums rounded to bf16 once: the parity bound of the tests against the oracle
+    for a, b in zip(got, want):
+        a, b = a.float(), b.float()
+        assert ((a - b).abs() <= torch.clamp_min(b.abs() * 2.0 ** -7, 2e-2)).all()
