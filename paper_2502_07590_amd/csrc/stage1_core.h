@@ -162,4 +162,57 @@ __host__ __device__ __forceinline__ constexpr int padded_len(int L) { return (L 
 // jcut value of a query all of whose threshold-equal keys are selected: "score >= tau" decides.
 constexpr int32_t kAllTies = 0x7FFFFFFF;
 
+// Block-wide emission: a half-wave per query, its lanes a word (32 keys) each, in ascending order.  gt: the lane's keys above
+// the threshold (all_simple: at or above it); eq: its keys equal to it, of which the query takes the lowest `room`.
+struct RowOut {
+    int at, room, last_tie;  // entries written, ties still to take, highest tie taken (the same in the half-wave)
+};
+__device__ __forceinline__ void emit_row_words(RowOut &ro, uint32_t gt, uint32_t eq, bool all_simple, int tile, int half, bool live,
+                                               int32_t *__restrict__ row, int k)
+{
+    uint32_t m = gt;
+    if (!all_simple) {
+        const int c = __popc(eq);
+        const int incl = half_scan(c);
+        const int take = max(0, min(c, ro.room - (incl - c)));
+        while (__popc(eq) > take) eq &= ~(0x80000000u >> __clz(eq));
+        int tie = eq ? tile * 32 + 31 - __clz(eq) : -1;
+        for (int o = 16; o; o >>= 1) tie = max(tie, __shfl_xor(tie, o));
+        ro.last_tie = max(ro.last_tie, tie);
+        ro.room = max(0, ro.room - __shfl(incl, 31 + 32 * half));
+        m |= eq;
+    }
+    const int c = __popc(m);
+    const int incl = half_scan(c);
+    const int pos = ro.at + incl - c;
+    ro.at += __shfl(incl, 31 + 32 * half);
+    if (live) {
+        if (pos + c > k) {  // a correct threshold fills the row exactly
+            const int fits = max(k - pos, 0);
+            while (__popc(m) > fits) m &= ~(0x80000000u >> __clz(m));
+        }
+        int32_t *dst = row + pos;
+        while (m) {
+            *dst++ = tile * 32 + (__ffs(m) - 1);
+            m &= m - 1;
+        }
+    }
+}
+
+// The two words of a 32 x 32 score tile for this lane's query (both lanes of a query get them).
+__device__ __forceinline__ void threshold_words(const floatx16_t &acc, float tau, bool all_simple, uint32_t valid, int half,
+                                                uint32_t &gt, uint32_t &eq)
+{
+    eq = 0u;
+    if (all_simple) {
+        DSV_SIGNMASK16(gt, acc[v] - tau);
+        gt = ~merge_halves(gt, half) & valid;
+    } else {
+        DSV_MASK16(gt, acc[v] > tau);
+        DSV_MASK16(eq, acc[v] == tau);
+        gt = merge_halves(gt, half) & valid;
+        eq = merge_halves(eq, half) & valid;
+    }
+}
+
 }  // namespace dsv

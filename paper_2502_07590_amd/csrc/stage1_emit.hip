@@ -140,6 +140,58 @@ __global__ __launch_bounds__(64) void emit_kernel(const T *__restrict__ Qlr, con
     if (tile_flag && lane == 0) tile_flag[(int64_t)bh * gridDim.x + blockIdx.x] = all_simple ? 1 : 0;
 }
 
+// The same by blocks of 16 waves per 32 queries, which form the words of 32 key tiles together and expand two queries each:
+// for few queries, whose single waves (one per 32 of them, the whole key axis in turn) would leave most of the chip idle.
+constexpr int kEmitWaves = 16;
+template <typename T, int R>
+__global__ __launch_bounds__(64 * kEmitWaves) void emit_block_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq,
+                                                                     int L, HeadTable tab, uint32_t *__restrict__ prefix,
+                                                                     const int32_t *__restrict__ krem, int32_t *__restrict__ idx,
+                                                                     int32_t *__restrict__ jcut, int32_t *__restrict__ tile_flag)
+{
+    constexpr int TPW = kBatch / kEmitWaves;       // tiles per wave and round
+    __shared__ uint32_t gt[2][kBatch][33], eq[2][kBatch][33];
+    const int slot = blockIdx.y;
+    const int bh = tab.bh[slot];
+    const int k = tab.k[slot];
+    const int q0 = blockIdx.x * 32;
+    const T *Qb = Qlr + (int64_t)bh * Lq * R;
+    const T *Kb = Klr + (int64_t)bh * L * R;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane & 31, half = lane >> 5;
+    const int64_t g0 = (int64_t)bh * padded_len(Lq) + q0;
+    const int last = Lq - 1 - q0;                  // queries past the end repeat the last one
+    const float tau = key_score(prefix[g0 + min(n, last)]);
+    const bool all_simple = __all(krem[g0 + min(n, last)] < 0);
+    const int q = 2 * wave + half;                 // the query this half-wave expands
+    const bool live = q <= last;
+    const int kr = krem[g0 + min(q, last)];
+    RowOut ro{0, kr < 0 ? -kr : kr, -1};
+    int32_t *row = idx + tab.off[slot] + (int64_t)(q0 + min(q, last)) * k;
+    const Frag<T, R> qf = load_frag<T, R>(Qb, q0, Lq, lane);
+    const int ntiles = (L + 31) >> 5;
+    int buf = 0;
+    for (int t0 = 0; t0 < ntiles; t0 += kBatch, buf ^= 1) {
+#pragma unroll
+        for (int i = 0; i < TPW; ++i) {
+            const int at = TPW * wave + i, j0 = (t0 + at) * 32;
+            const uint32_t valid = j0 + 32 <= L ? 0xFFFFFFFFu : (j0 < L ? (1u << (L - j0)) - 1u : 0u);
+            uint32_t g, e;
+            threshold_words(score_tile<T, R>(load_frag<T, R>(Kb, j0, L, lane), qf), tau, all_simple, valid, half, g, e);
+            if (half == 0) {
+                gt[buf][at][n] = g;
+                if (!all_simple) eq[buf][at][n] = e;
+            }
+        }
+        __syncthreads();  // two buffers in turn: the one written next was last read before this barrier
+        emit_row_words(ro, gt[buf][n][q], all_simple ? 0u : eq[buf][n][q], all_simple, t0 + n, half, live, row, k);
+    }
+    __syncthreads();      // every wave has read the thresholds
+    if (threadIdx.x < 32 && (int)threadIdx.x <= last) prefix[g0 + n] = __float_as_uint(tau);
+    if (jcut && live && n == 0) jcut[g0 + q] = kr < 0 ? kAllTies : ro.last_tie;
+    if (tile_flag && threadIdx.x == 0) tile_flag[(int64_t)bh * gridDim.x + blockIdx.x] = all_simple ? 1 : 0;
+}
+
 // ------------------------------------------------------------------------------------ key-major
 // tau_f: the fp32 thresholds left in `prefix` by emit_kernel.  The tile is computed with the query
 // fragment as the row operand and the key fragment as the column operand, so lane l owns key
@@ -234,6 +286,11 @@ __global__ __launch_bounds__(64) void emit_t_kernel(const T *__restrict__ Qlr, c
 }
 
 // ------------------------------------------------------------------------------------ host
+// Whether the query-major emission takes a block per 32 queries instead of a wave: below two waves per SIMD.  Measured, waves
+// against blocks: 512 query tiles (the groups of four heads of L = 32768), 691 : 180 us; 3804 tiles of r = 32, 813 : 842; 4096
+// tiles of r = 16, 1135 : 1090.
+static bool emit_by_blocks(int64_t tiles) { return tiles < 2048; }
+
 template <typename T, int R>
 static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr,
                              const void *Klr, const SelectBuffers &b, bool emitted, hipStream_t st)
@@ -247,8 +304,12 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
         KernelSpan span(DSV_KERNEL_EMIT, st);
         for (int t = 0; t < n_tabs; ++t) {
             dim3 grid(qtiles, tabs[t].n);
-            hipLaunchKernelGGL((emit_kernel<T, R>), grid, dim3(64), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem, b.idx,
-                               b.jcut, b.tile_flag);
+            if (emit_by_blocks((int64_t)qtiles * tabs[t].n))
+                hipLaunchKernelGGL((emit_block_kernel<T, R>), grid, dim3(64 * kEmitWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem,
+                                   b.idx, b.jcut, b.tile_flag);
+            else
+                hipLaunchKernelGGL((emit_kernel<T, R>), grid, dim3(64), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem, b.idx,
+                                   b.jcut, b.tile_flag);
             DSV_LAUNCH_CHECK();
         }
     }

@@ -71,61 +71,26 @@ __global__ __launch_bounds__(64 * kSmallWaves) void select_small_kernel(const T 
         const int tile = wave + kSmallWaves * i;
         const int j0 = tile * 32;
         const uint32_t valid = j0 + 32 <= L ? 0xFFFFFFFFu : (j0 < L ? (1u << (L - j0)) - 1u : 0u);
-        uint32_t m;
-        if (all_simple) {
-            DSV_SIGNMASK16(m, acc[i][v] - tau);
-            m = ~merge_halves(m, half) & valid;
-        } else {
-            uint32_t e;
-            DSV_MASK16(m, acc[i][v] > tau);
-            DSV_MASK16(e, acc[i][v] == tau);
-            m = merge_halves(m, half) & valid;
-            e = merge_halves(e, half) & valid;
-            if (half == 0) eq[tile][n] = e;
+        uint32_t g, e;
+        threshold_words(acc[i], tau, all_simple, valid, half, g, e);
+        if (half == 0) {
+            gt[tile][n] = g;
+            eq[tile][n] = e;
         }
-        if (half == 0) gt[tile][n] = m;
     }
     __syncthreads();
 
-    // emission: a half-wave per query, its lanes a word (32 keys) each, in ascending order
     const int q = 2 * wave + half;
     const bool live = q0 + q < Lq;
-    int32_t *row = idx + tab.off[slot] + (int64_t)min(q0 + q, Lq - 1) * k;
-    int at = 0, room = ties[q], last_tie = -1;
+    RowOut ro{0, ties[q], -1};
     for (int t0 = 0; t0 < ntiles; t0 += 32) {
-        const int tile = t0 + n;
-        uint32_t m = tile < ntiles ? gt[tile][q] : 0u;
-        if (!all_simple) {  // the lowest `room` ties of the query
-            uint32_t e = tile < ntiles ? eq[tile][q] : 0u;
-            const int c = __popc(e);
-            const int incl = half_scan(c);
-            const int take = max(0, min(c, room - (incl - c)));
-            while (__popc(e) > take) e &= ~(0x80000000u >> __clz(e));
-            int tie = e ? tile * 32 + 31 - __clz(e) : -1;
-            for (int o = 16; o; o >>= 1) tie = max(tie, __shfl_xor(tie, o));
-            last_tie = max(last_tie, tie);
-            room = max(0, room - __shfl(incl, 31 + 32 * half));
-            m |= e;
-        }
-        const int c = __popc(m);
-        const int incl = half_scan(c);
-        const int pos = at + incl - c;
-        at += __shfl(incl, 31 + 32 * half);
-        if (live) {
-            if (pos + c > k) {  // a correct threshold fills the row exactly
-                const int fits = max(k - pos, 0);
-                while (__popc(m) > fits) m &= ~(0x80000000u >> __clz(m));
-            }
-            int32_t *dst = row + pos;
-            while (m) {
-                *dst++ = tile * 32 + (__ffs(m) - 1);
-                m &= m - 1;
-            }
-        }
+        const bool in = t0 + n < ntiles;
+        emit_row_words(ro, in ? gt[t0 + n][q] : 0u, in ? eq[t0 + n][q] : 0u, all_simple, t0 + n, half, live,
+                       idx + tab.off[slot] + (int64_t)min(q0 + q, Lq - 1) * k, k);
     }
     const int64_t g0 = (int64_t)bh * padded_len(Lq) + q0;
     if (threadIdx.x < 32 && q0 + n < Lq) prefix[g0 + n] = __float_as_uint(tau);
-    if (jcut && live && n == 0) jcut[g0 + q] = all_simple ? kAllTies : last_tie;
+    if (jcut && live && n == 0) jcut[g0 + q] = all_simple ? kAllTies : ro.last_tie;
     if (tile_flag && threadIdx.x == 0) tile_flag[(int64_t)bh * gridDim.x + blockIdx.x] = all_simple ? 1 : 0;
 }
 

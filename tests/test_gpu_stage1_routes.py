@@ -42,3 +42,26 @@ def _check(p, Q, K, Wq, Wk):
 def test_short_sequences(L, ks, dtype, d, r, ties):
     Q, K, Wq, Wk = _inputs(2, L, d, r, dtype, ties, L + r)
     _check(dsv.Problem(1, 2, L, d, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+
+
+# above 2048 keys: radix passes, from 16384 on the windowed search; the emission by blocks below 2048 query tiles (65536
+# queries), by waves from there on
+@pytest.mark.parametrize("H,L,ks,r,ties", [(1, 2080, [2080], 16, False), (2, 5001, [5, 900], 64, True), (1, 16411, [1500], 16, False),
+                                           (3, 22000, [1100, 2, 5000], 16, False)])
+def test_longer_sequences(H, L, ks, r, ties):
+    Q, K, Wq, Wk = _inputs(H, L, 64, r, "bf16", ties, L)
+    _check(dsv.Problem(1, H, L, 64, r, "bf16", ks, 0.1), Q, K, Wq, Wk)
+
+
+def test_smooth_inputs_keep_the_windowed_search():
+    """Keys that vary slowly along the token grid, whose width the sample's stride divides: the scrambled sample brackets
+    the thresholds, and the result is the radix search's."""
+    L, k = 16384, 1024
+    g = torch.Generator(device="cuda").manual_seed(1)
+    t = torch.arange(L, device="cuda", dtype=torch.float32)
+    wave = torch.stack([torch.cos(2 * torch.pi * t / period + phase) for period in (64.0, 32.0, 4096.0, 1500.0)
+                        for phase in (0.0, 1.0, 2.0, 3.0)], 1)
+    mix = torch.randn(16, 64, generator=g, device="cuda")
+    Q, K = ((wave @ mix + 0.1 * torch.randn(L, 64, generator=g, device="cuda")).bfloat16()[None, None].contiguous() for _ in range(2))
+    Wq, Wk = ((torch.randn(1, 64, 16, generator=g, device="cuda") / 8).bfloat16() for _ in range(2))
+    _check(dsv.Problem(1, 1, L, 64, 16, "bf16", [k], 0.1), Q, K, Wq, Wk)
