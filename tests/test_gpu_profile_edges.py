@@ -1,0 +1,37 @@
+"""dsv_profile_sparsity where its counters and searches have edges: few keys, keys past the last whole tile, equal scores,
+one key that holds the whole mass; counts against the definition in 64 bits, and the same from run to run."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import paper_2502_07590_amd as dsv
+
+pytestmark = pytest.mark.gpu
+
+
+def _counts(q, k, scale, mass):
+    p = torch.softmax(q.double() @ k.double().T * scale, 1).sort(1, descending=True).values
+    return ((p.cumsum(1) < mass).sum(1) + 1).clamp_max(k.shape[0]), p
+
+
+@pytest.mark.parametrize("L,n", [(1, 1), (31, 5), (33, 33), (512, 31), (1000, 32), (4097, 65)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("scale_mul", [0.0, 1.0, 40.0])   # all keys alike; ordinary; one key takes all
+def test_counts_at_the_edges(L, n, dtype, d, scale_mul):
+    g = torch.Generator(device="cuda").manual_seed(L + n)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(1, 2, L, d, generator=g, device="cuda").to(td) for _ in range(2))
+    rows = torch.randperm(L, generator=g, device="cuda")[:n].to(torch.int32)
+    p = dsv.Problem(1, 2, L, d, 16, dtype, [1, 1], scale_mul / d ** 0.5)
+    sparsity, counts = dsv.profile_sparsity(p, Q, K, rows, mass=0.9)
+    again = dsv.profile_sparsity(p, Q, K, rows, mass=0.9)
+    assert torch.equal(counts, again[1]) and torch.equal(sparsity, again[0])
+    for h in range(2):
+        want, prob = _counts(Q[0, h][rows.long()], K[0, h], p.scale, 0.9)
+        off = counts[h].long() - want
+        # fp32 scores and normaliser: the cumulative mass is right to about 4e-6 (d * 2^-24 in the exponent, summed), so a
+        # count may be off by the keys that such a mass holds where it crosses 0.9
+        edge = torch.gather(prob, 1, (want[:, None] - 1)).squeeze(1)
+        assert (off.abs() <= torch.ceil(8e-6 * max(1.0, scale_mul) / edge).clamp_min(1)).all()
+        assert torch.isclose(sparsity[h].double(), (1 - counts[h].double() / L).mean(), atol=1e-6)
