@@ -161,9 +161,62 @@ bool sort_rows_first(const dsv_problem &p)
     return !(p.flags & DSV_FLAG_SORTED_INDEX) && can_sort_rows(p) && (size_t)p.L * 2 * p.d * esize(p.dtype) > ((size_t)3 << 20);
 }
 
+// Smallest k whose heads run the forward over dense tiles with a mask (dense.hip), INT32_MAX if none should.  (The mask needs
+// a workspace, which calls without the flag do not have.)
+// Costs measured on bf16, in us.  Gathering: 18.5e-6 per pair at d = 128, 10.4e-6 at d = 64, once the chip is full.  Dense: per
+// 64-key tile a round of blocks takes 1.6 (1.2) with at most one block of 128 queries per CU and 2.5 (2.1) when the CUs
+// hold two (three), and a last round that is partly empty costs a fifth of a full one.  Estimated and measured, d = 128:
+// 12 heads of 2048, 51 : 71; 4 of 4096, 102 : 116; 1 of 8192, 205 : 202; 12 of 8192, 544 : 580; 4 of 16384, 768 : 755; 4 of 32768,
+// 2816 : 2900; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.
+int32_t dense_fwd_min_k(const dsv_problem &p)
+{
+    if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
+    const bool wide = p.d == 128;
+    const double pair = wide ? 18.5e-6 : 10.4e-6, light = wide ? 1.6 : 1.2, full = wide ? 2.5 : 2.1, slots = wide ? 512 : 768;
+    std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
+    std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
+    int32_t best_k = INT32_MAX;
+    double best = 0.0, gathered = 0.0;  // us saved by the heads with the largest k
+    for (int m = 1; m <= p.H; ++m) {
+        gathered += pair * (double)p.B * p.L * ks[m - 1];
+        if (m < p.H && ks[m] == ks[m - 1]) continue;
+        const double blocks = (double)p.B * m * ((p.L + 127) / 128), tiles = (p.L + 63) / 64;
+        const double dense = tiles * (blocks <= 256 ? light : full * std::max(1.0, blocks / slots + 0.2));
+        if (gathered - 1.1 * dense > best) {
+            best = gathered - 1.1 * dense;
+            best_k = ks[m - 1];
+        }
+    }
+    return best_k;
+}
+
+// tabs cut in two: heads of at least min_k, and the others
+void cut_tables(const std::vector<HeadTable> &tabs, int32_t min_k, std::vector<HeadTable> &yes, std::vector<HeadTable> &no)
+{
+    for (const HeadTable &t : tabs) {
+        HeadTable a{}, b{};
+        for (int s = 0; s < t.n; ++s) {
+            HeadTable &d = t.k[s] >= min_k ? a : b;
+            d.bh[d.n] = t.bh[s];
+            d.k[d.n] = t.k[s];
+            d.off[d.n++] = t.off[s];
+        }
+        if (a.n) yes.push_back(a);
+        if (b.n) no.push_back(b);
+    }
+}
+
+// Scratch for masks: all of them, at most 1 GB at a time (of one head 128 rows at least).
+size_t mask_bytes(const dsv_problem &p, int heads)
+{
+    const size_t row = (size_t)bits_pitch(p.L) * 4;
+    return align_up(std::max(std::min((size_t)p.B * heads * p.L * row, (size_t)1 << 30), kDenseMinRows * row), 256);
+}
+
 struct FwdLayout {
     bool split;
     SplitPlan plan;
+    int32_t dense_k;  // heads that keep at least so many keys run over dense tiles
     size_t seg, pm, pl, pacc, hist, order, total;
 };
 
@@ -172,6 +225,10 @@ FwdLayout fwd_layout(const dsv_problem &p)
     FwdLayout w{};
     w.plan = make_split_plan(p, kFwdRangeBytes);
     w.split = split_rows(p, w.plan);
+    w.dense_k = dense_fwd_min_k(p);
+    int dense = 0;
+    for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= w.dense_k;
+    if (dense) w.total = mask_bytes(p, dense);
     if (!w.split) return w;
     const size_t rows = (size_t)p.B * p.H * p.L;
     size_t o = 0;
@@ -181,7 +238,7 @@ FwdLayout fwd_layout(const dsv_problem &p)
     w.pacc = o; o = align_up(o + rows * w.plan.S * p.d * 4, 256);
     w.hist = o; o = align_up(o + (size_t)p.B * p.H * w.plan.S * ((size_t)w.plan.range_len + 1) * 4, 256);
     w.order = o; o = align_up(o + rows * w.plan.S * 4, 256);
-    w.total = o;
+    w.total = std::max(w.total, o);  // the mask takes the place of the partial results
     return w;
 }
 
@@ -413,8 +470,15 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
     if (st != DSV_OK) return st;
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.split) return launch_sparse_fwd(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, stream);
     char *ws = static_cast<char *>(workspace);
+    std::vector<HeadTable> dense, rest;
+    cut_tables(tabs, w.dense_k, dense, rest);
+    for (const HeadTable &t : dense) {
+        st = launch_dense_fwd(*p, t, Q, K, V, idx, O, lse, ws, w.total, stream);
+        if (st != DSV_OK) return st;
+    }
+    if (rest.empty()) return DSV_OK;
+    if (!w.split) return launch_sparse_fwd(*p, rest.data(), (int)rest.size(), Q, K, V, idx, O, lse, stream);
     FwdSplitWorkspace b;
     b.seg = reinterpret_cast<int32_t *>(ws + w.seg);
     b.pm = reinterpret_cast<float *>(ws + w.pm);
@@ -422,7 +486,7 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
     b.pacc = reinterpret_cast<float *>(ws + w.pacc);
     b.hist = reinterpret_cast<int32_t *>(ws + w.hist);
     b.order = reinterpret_cast<int32_t *>(ws + w.order);
-    return launch_sparse_fwd_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, w.plan, b, stream);
+    return launch_sparse_fwd_split(*p, rest.data(), (int)rest.size(), Q, K, V, idx, O, lse, w.plan, b, stream);
 }
 
 // ------------------------------------------------------------------------------------ stage 2 backward

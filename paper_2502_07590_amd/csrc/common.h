@@ -397,7 +397,7 @@ dsv_status launch_grouped_dq(const dsv_problem &p, const dsv_grouping &gr, const
                              hipStream_t st);
 dsv_status launch_row_segments(const dsv_problem &p, int rows, const HeadTable *tabs, int n_tabs, const SplitPlan &pl,
                                const int32_t *index, int32_t *seg, hipStream_t st);
-dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const float *pm, const float *pl_, const float *pacc, void *O,
+dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const float *pm, const float *pl_, const float *pacc, void *O,
                                      float *lse, int S, hipStream_t st);
 dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const float *pdk, const float *pdv, void *dK, void *dV, int S,
                                       hipStream_t st);
@@ -435,6 +435,16 @@ dsv_status launch_idx_validate(const dsv_problem &p, const HeadTable *tabs, int 
 size_t idx_transpose_bytes(const dsv_problem &p);
 dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx,
                                 int32_t *idxT, int64_t *col, void *ws, size_t ws_bytes, hipStream_t st);
+// Rows row0 .. row0 + nrows - 1 of `heads` head slots as a bit matrix [heads, nrows, bits_pitch(L) words]; L <= kBitsMaxKeys.
+constexpr int kBitsMaxKeys = 524288;  // a row's bitmap fits 64 KB of LDS
+int bits_pitch(int L);
+dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
+                             int nrows, uint32_t *bits, hipStream_t st);
+// Forward of some heads over dense tiles with a mask (dense.hip; bf16, scale > 0, L <= kBitsMaxKeys); ws: scratch for the
+// mask, at least kDenseMinRows rows of it.
+constexpr int kDenseMinRows = 128;
+dsv_status launch_dense_fwd(const dsv_problem &p, const HeadTable &tab, const void *Q, const void *K, const void *V,
+                            const int32_t *idx, void *O, float *lse, char *ws, size_t ws_bytes, hipStream_t st);
 // out = the rows of idx in ascending order (same layout); can_sort_rows: whether this L is covered.
 bool can_sort_rows(const dsv_problem &p);
 dsv_status launch_sort_rows(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx, int32_t *out,

@@ -833,7 +833,7 @@ dsv_status launch_grouped_fwd(const dsv_problem &p, const dsv_grouping &gr, cons
             DSV_LAUNCH_CHECK();
         }
     }
-    return launch_fwd_merge_bf16_128(p, split->pa, split->pb, split->pc, O, lse, pl.S, st);
+    return launch_fwd_merge_bf16_128(p, tabs, n_tabs, split->pa, split->pb, split->pc, O, lse, pl.S, st);
 }
 
 dsv_status launch_grouped_dq(const dsv_problem &p, const dsv_grouping &gr, const HeadTable *tabs, int n_tabs,

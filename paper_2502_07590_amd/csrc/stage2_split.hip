@@ -117,13 +117,14 @@ __global__ __launch_bounds__(256) void sparse_fwd_split_kernel(const T *__restri
 template <typename T, int D>
 __global__ __launch_bounds__(256) void sparse_fwd_merge_kernel(const float *__restrict__ pm, const float *__restrict__ pl_,
                                                                const float *__restrict__ pacc, T *__restrict__ O,
-                                                               float *__restrict__ lse, int64_t n_rows, int S)
+                                                               float *__restrict__ lse, int L, HeadTable tab, int S)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
-    const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;  // b*H*L + i
-    if (row >= n_rows) return;
+    const int64_t i = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
+    if (i >= L) return;
+    const int64_t row = (int64_t)tab.bh[blockIdx.y] * L + i;
     const float *m_r = pm + row * S;
     const float *l_r = pl_ + row * S;
     float M = -INFINITY;
@@ -346,12 +347,12 @@ __device__ __forceinline__ int seg_len(const int32_t *__restrict__ seg, int64_t 
 }
 
 __global__ __launch_bounds__(256) void seglen_hist_kernel(const int32_t *__restrict__ seg, int L, int S, int nbins,
-                                                          int32_t *__restrict__ hist)
+                                                          HeadTable tab, int32_t *__restrict__ hist)
 {
     extern __shared__ int32_t lh[];  // [nbins]
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
-    const int bh = unit / S, r = unit % S;
+    const int bh = tab.bh[unit / S], r = unit % S;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk;
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -389,12 +390,13 @@ __global__ __launch_bounds__(1024) void seglen_scan_kernel(int32_t *__restrict__
 }
 
 __global__ __launch_bounds__(256) void seglen_scatter_kernel(const int32_t *__restrict__ seg, int L, int S, int nbins,
-                                                             int32_t *__restrict__ hist, int32_t *__restrict__ order)
+                                                             HeadTable tab, int32_t *__restrict__ hist,
+                                                             int32_t *__restrict__ order)
 {
     extern __shared__ int32_t lh[];  // [nbins]: this chunk's count per class, then its next free slot in `order`
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
-    const int bh = unit / S, r = unit % S;
+    const int bh = tab.bh[unit / S], r = unit % S;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk, row1 = min(row0 + kSeglenChunk, L);
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -450,8 +452,8 @@ static dsv_status launch_segments(const dsv_problem &p, const HeadTable *tabs, i
     return DSV_OK;
 }
 
-// order[bh, r, :] = the rows of head bh by descending segment length in range r (from seg).
-static dsv_status launch_row_order(const dsv_problem &p, const SplitPlan &pl, const int32_t *seg, int32_t *hist,
+// order[bh, r, :] = the rows of the tables' heads by descending segment length in range r (from seg).
+static dsv_status launch_row_order(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const SplitPlan &pl, const int32_t *seg, int32_t *hist,
                                    int32_t *order, hipStream_t st)
 {
     const int nbh = p.B * p.H;
@@ -459,12 +461,17 @@ static dsv_status launch_row_order(const dsv_problem &p, const SplitPlan &pl, co
     const int nbins = std::min(pl.range_len + 1, 8193);
     const int64_t nh = (int64_t)nbh * pl.S * nbins;
     hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)std::min<int64_t>((nh + 255) / 256, 4096)), dim3(256), 0, st, hist, nh);
-    const int64_t nblocks = (int64_t)((p.L + kSeglenChunk - 1) / kSeglenChunk) * nbh * pl.S;
-    if (nblocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
-    dim3 grid((unsigned)nblocks);
-    hipLaunchKernelGGL(seglen_hist_kernel, grid, dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, hist);
+    const int64_t chunks = (p.L + kSeglenChunk - 1) / kSeglenChunk;
+    for (int t = 0; t < n_tabs; ++t) {
+        const int64_t nblocks = chunks * tabs[t].n * pl.S;
+        if (nblocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
+        hipLaunchKernelGGL(seglen_hist_kernel, dim3((unsigned)nblocks), dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, tabs[t],
+                           hist);
+    }
     hipLaunchKernelGGL(seglen_scan_kernel, dim3(nbh * pl.S), dim3(1024), 0, st, hist, nbins);
-    hipLaunchKernelGGL(seglen_scatter_kernel, grid, dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, hist, order);
+    for (int t = 0; t < n_tabs; ++t)
+        hipLaunchKernelGGL(seglen_scatter_kernel, dim3((unsigned)(chunks * tabs[t].n * pl.S)), dim3(256), (size_t)nbins * 4, st, seg, p.L,
+                           pl.S, nbins, tabs[t], hist, order);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -483,7 +490,7 @@ static dsv_status fwd_split_t(const dsv_problem &p, const HeadTable *tabs, int n
 {
     dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idx, nullptr, w.seg, st);
     if (rc != DSV_OK) return rc;
-    rc = launch_row_order(p, pl, w.seg, w.hist, w.order, st);
+    rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st);
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_FWD_SWEEP, st);
@@ -497,10 +504,11 @@ static dsv_status fwd_split_t(const dsv_problem &p, const HeadTable *tabs, int n
             DSV_LAUNCH_CHECK();
         }
     }
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_fwd_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, w.pm,
-                       w.pl, w.pacc, (T *)O, lse, n_rows, pl.S);
-    DSV_LAUNCH_CHECK();
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL((sparse_fwd_merge_kernel<T, D>), dim3((p.L + 15) / 16, tabs[t].n), dim3(256), 0, st, w.pm, w.pl, w.pacc,
+                           (T *)O, lse, p.L, tabs[t], pl.S);
+        DSV_LAUNCH_CHECK();
+    }
     return DSV_OK;
 }
 
@@ -512,7 +520,7 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
 {
     dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idx, nullptr, w.seg, st);
     if (rc != DSV_OK) return rc;
-    rc = launch_row_order(p, pl, w.seg, w.hist, w.order, st);
+    rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st);
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
@@ -546,7 +554,7 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
     const int64_t nrows = (int64_t)nbh * p.L;
     rc = launch_pack_rowstat(lse, delta, w.rowstat, nrows, st);
     if (rc != DSV_OK) return rc;
-    rc = launch_row_order(p, pl, w.seg, w.hist, w.order, st);
+    rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st);
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
@@ -587,13 +595,14 @@ dsv_status launch_row_segments(const dsv_problem &p, int rows, const HeadTable *
 }
 
 // Merges of per-(token row, range) partials, bf16 d = 128 (the grouped kernels' case).
-dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const float *pm, const float *pl_, const float *pacc, void *O,
+dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const float *pm, const float *pl_, const float *pacc, void *O,
                                      float *lse, int S, hipStream_t st)
 {
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_fwd_merge_kernel<bf16_t, 128>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, pm, pl_,
-                       pacc, (bf16_t *)O, lse, n_rows, S);
-    DSV_LAUNCH_CHECK();
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL((sparse_fwd_merge_kernel<bf16_t, 128>), dim3((p.L + 15) / 16, tabs[t].n), dim3(256), 0, st, pm, pl_, pacc,
+                           (bf16_t *)O, lse, p.L, tabs[t], S);
+        DSV_LAUNCH_CHECK();
+    }
     return DSV_OK;
 }
 

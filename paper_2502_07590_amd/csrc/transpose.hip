@@ -19,7 +19,6 @@ namespace dsv {
 // that the 512 keys of a block are whole 64-byte pieces of every row.
 constexpr int kBitsKeys = 512;               // keys per block of the counting and filling kernels (16 words)
 constexpr int kBitsRows = 1024;              // queries per block of those kernels: one segment of every list
-constexpr int kBitsMaxKeys = 524288;         // a row's bitmap fits 64 KB of LDS
 constexpr size_t kBitsBytes = (size_t)2 << 30;  // scratch for the bit matrix: larger problems go through it piece by piece
 
 // One block per row at a time: its entries are OR-ed into an LDS bitmap, which is then written out and cleared.
@@ -427,6 +426,18 @@ __global__ __launch_bounds__(256) void fill_zero_i32_kernel(int4 *__restrict__ p
 }
 
 // ------------------------------------------------------------------------------------ host
+int bits_pitch(int L) { return (L + kBitsKeys - 1) / kBitsKeys * 16; }
+
+dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
+                             int nrows, uint32_t *bits, hipStream_t st)
+{
+    const int pitch = bits_pitch(p.L);
+    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min(nrows, 4096), heads), dim3(256), (size_t)pitch * 4, st, idx, p.L, tab, slot0,
+                       row0, nrows, pitch, bits);
+    DSV_LAUNCH_CHECK();
+    return DSV_OK;
+}
+
 struct TransposePlan {
     bool bits;
     int n_chunks;       // segments (bit matrix) or chunks (entry sort) of queries per head
@@ -452,7 +463,7 @@ static TransposePlan transpose_plan(const dsv_problem &p)
     w.cnt2 = o; o = align_up(o + nbh * w.n_chunks * p.L * 4, 256);
     w.mat = o;
     if (w.bits) {
-        w.pitch = (p.L + kBitsKeys - 1) / kBitsKeys * 16;
+        w.pitch = bits_pitch(p.L);
         const size_t row = (size_t)w.pitch * 4;
         const size_t fit = kBitsBytes / row;  // rows
         if (fit >= (size_t)p.L) {
@@ -475,7 +486,6 @@ static dsv_status transpose_bits(const dsv_problem &p, const HeadTable &tab, con
 {
     int32_t *tot = reinterpret_cast<int32_t *>(ws + w.tot), *cnt2 = reinterpret_cast<int32_t *>(ws + w.cnt2);
     uint32_t *bits = reinterpret_cast<uint32_t *>(ws + w.mat);
-    const size_t lds = (size_t)w.pitch * 4;  // at most 64 KB
     const unsigned kb = w.pitch / 16;
     const bool whole = w.rows >= p.L;        // the piece built for counting still stands when the lists are filled
     for (int s0 = 0; s0 < tab.n; s0 += w.heads) {
@@ -484,9 +494,10 @@ static dsv_status transpose_bits(const dsv_problem &p, const HeadTable &tab, con
             for (int r0 = 0; r0 < p.L; r0 += w.rows) {
                 const int nr = std::min(w.rows, p.L - r0);
                 const dim3 grid(kb, (nr + kBitsRows - 1) / kBitsRows, nh);
-                if (!fill || !whole)
-                    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min(nr, 4096), nh), dim3(256), lds, st, idx, p.L, tab, s0, r0, nr,
-                                       w.pitch, bits);
+                if (!fill || !whole) {
+                    const dsv_status rc = launch_bits_build(p, tab, s0, nh, idx, r0, nr, bits, st);
+                    if (rc != DSV_OK) return rc;
+                }
                 if (!fill)
                     hipLaunchKernelGGL(bits_count_kernel, grid, dim3(256), 0, st, bits, w.pitch, p.L, tab, s0, r0, nr, w.n_chunks, cnt2);
                 else

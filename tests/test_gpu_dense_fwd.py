@@ -1,0 +1,54 @@
+"""The forward over dense tiles with a mask, next to gathered heads in one call, at the edges of its tiles (128 queries,
+64 keys), on rows that leave whole tiles out, and where the mask goes piece by piece; against attention in 64 bits."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+import paper_2502_07590_amd as dsv
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(p, Q, K, V, heads, at):
+    O, lse = dsv.sparse_attn_fwd(p, Q, K, V, torch.cat([x.reshape(-1) for x in heads]))
+    for bh, rows in enumerate(heads):
+        b, h = divmod(bh, p.H)
+        q, k, v = Q[b, h].double()[at], K[b, h].double(), V[b, h].double()
+        s = torch.gather(q @ k.T * p.scale, 1, rows[at].long())
+        want = torch.logsumexp(s, 1)
+        prob = (s - want[:, None]).exp()
+        out = torch.stack([prob[i] @ v[rows[at[i]].long()] for i in range(len(at))])
+        # the parity bounds of the tests against the oracle
+        assert ((O[b, h][at].double() - out).abs() <= torch.clamp_min(out.abs() * 2.0 ** -7, 2e-2)).all()
+        assert ((lse[b, h][at].double() - want).abs() <= torch.clamp_min(want.abs() * 2.0 ** -20, 1e-4)).all()
+
+
+def _rows(L, k, g, near=False):
+    if near:   # a run of k keys round the query's own place: most tiles hold nothing for it
+        first = (torch.arange(L, device="cuda") - k // 2).clamp(0, L - k)
+        return (first[:, None] + torch.arange(k, device="cuda")[None]).to(torch.int32)
+    edge = (torch.arange(k + 1, device="cuda") * L) // k
+    width = edge[1:] - edge[:-1]
+    return (edge[:-1] + (torch.rand(L, k, generator=g, device="cuda") * width).long().clamp_max(width - 1)).to(torch.int32)
+
+
+# 12 heads fill the chip: those that keep L / 5 run over tiles, those that keep 9 are gathered
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,L,near", [(1, 2047, False), (2, 2177, False), (1, 4159, True), (1, 4096, False)])
+def test_dense_and_gathered_heads(d, B, L, near):
+    g = torch.Generator(device="cuda").manual_seed(L + d)
+    ks = [L // 5, 9, L // 4, L // 5, L, 9, L // 3, L // 5, L // 4, L // 5, L // 4, L // 3]
+    Q, K, V = (3 * torch.randn(B, 12, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(B, 12, L, d, 16, "bf16", ks, d ** -0.5, sorted_index=True)
+    assert dsv.sparse_attn_fwd_workspace(p) > 0
+    heads = [_rows(L, k, g, near) for _ in range(B) for k in ks]
+    _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 61, device="cuda"), torch.arange(L - 70, L, device="cuda")]))
+
+
+def test_mask_in_pieces():
+    L, k = 98309, 4000
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Q, K, V = (torch.randn(1, 1, L, 128, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(1, 1, L, 128, 16, "bf16", [k], 128 ** -0.5, sorted_index=True)
+    _check(p, Q, K, V, [_rows(L, k, g)], torch.randint(0, L, (200,), generator=g, device="cuda"))
