@@ -65,3 +65,16 @@ def test_smooth_inputs_keep_the_windowed_search():
     Q, K = ((wave @ mix + 0.1 * torch.randn(L, 64, generator=g, device="cuda")).bfloat16()[None, None].contiguous() for _ in range(2))
     Wq, Wk = ((torch.randn(1, 64, 16, generator=g, device="cuda") / 8).bfloat16() for _ in range(2))
     _check(dsv.Problem(1, 1, L, 64, 16, "bf16", [k], 0.1), Q, K, Wq, Wk)
+
+
+# 64 tokens per wave, 256 per block; 4 outputs per lane below 32768 tokens, 16 or 32 from there on
+@pytest.mark.parametrize("L", [1, 65, 321, 16385])
+@pytest.mark.parametrize("dtype,d,r", [("f32", 64, 16), ("f32", 128, 64), ("bf16", 128, 32), ("bf16", 64, 64), ("bf16", 128, 16)])
+def test_projection(L, dtype, d, r):
+    Q, K, Wq, Wk = _inputs(2, L, d, r, dtype, False, L + d)
+    p = dsv.Problem(1, 2, L, d, r, dtype, [1, 1], 0.1)
+    for X, W, got in zip((Q, K), (Wq, Wk), dsv.lowrank_project(p, Q, K, Wq, Wk)):
+        want = X.double() @ W.double()
+        # a chain of d fp32 multiply-adds, rounded to the storage type once
+        bound = d * 2.0 ** -24 * (X.double().abs() @ W.double().abs()) + want.abs() * (2.0 ** -8 if dtype == "bf16" else 0.0)
+        assert ((got.double() - want).abs() <= bound).all()
