@@ -1,16 +1,23 @@
 // Stage 1 for short sequences: threshold search and query-major emission in one kernel (paper Sec. "Critical KV Estimation
 // with Kernel Fusion").  A block of 16 waves takes 32 queries of one head; its waves score up to NT key tiles each ONCE and
-// keep the scores in registers through the four digits of the radix search (stage1.hip) and the emission, so that a
-// call is two launches -- projection and this -- instead of six, and no score is formed five times by blocks that the
-// few tiles of a short sequence leave waiting for one another.  What bounds it: the barriers and LDS round trips of the
-// four digits -- 10 us of the first, whose counters are few and hot, 3 us of each of the others.  L = 1024, two heads, fp32:
-// 128 -> 32 us per call.  Outputs are those of the radix search and of the emission (stage1_emit.hip), bit for bit.
+// keep the scores in registers through the search and the emission, so that a call is two launches -- projection and
+// this -- instead of six, and no score is formed five times by blocks that the few tiles of a short sequence leave waiting
+// for one another.
+//   search   256 equal bins between each query's smallest and largest score (bins of equal width in the VALUE: a few scores
+//            each, where the leading bits of the float patterns put hundreds into each of a handful of counters); the
+//            scores of the bin that holds the k-th largest go to LDS and are ranked against each other.  Exact: the map
+//            from score to bin is monotone.  If a query of the block finds more than kSmallCap scores in its bin (massive
+//            ties), the block takes the four 8-bit digits of the radix search (stage1.hip) instead.
+//// What bounds it: barriers and LDS round trips, about ten in a row.  L = 1024, two heads, fp32, per call with the projection:
+// 128 us in six launches, 32 with the digits, 28.6 with the bins.  Outputs are those of the radix search and of the
+// emission (stage1_emit.hip), bit for bit.
 #include "stage1_core.h"
 
 namespace dsv {
 
 constexpr int kSmallWaves = 16;
 constexpr int kSmallMaxTiles = 4;  // score tiles a wave keeps: 64 accumulators of the 128 registers that 16 waves leave it
+constexpr int kSmallCap = 64;      // scores of a query's bin that are ranked in LDS
 constexpr int kSmallMaxKeys = kSmallWaves * kSmallMaxTiles * 32;
 
 template <typename T, int R, int NT>
@@ -23,7 +30,11 @@ __global__ __launch_bounds__(64 * kSmallWaves) void select_small_kernel(const T 
     __shared__ uint32_t hist[256 * 32];
     __shared__ uint32_t gt[TILES][33], eq[TILES][33];  // per key tile and query: scores above (or at) the threshold, ties
     __shared__ BucketScratch<64 * kSmallWaves> scratch;
-    __shared__ int32_t ties[32];
+    __shared__ uint32_t cand[32][kSmallCap + 1];
+    __shared__ uint32_t lo_s[32], hi_s[32];            // smallest and largest score of every query (order-preserving keys)
+    __shared__ int32_t ccnt[32], rem[32], ties[32];
+    __shared__ uint32_t tau_s[32];
+    __shared__ int32_t eq_s[32];
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
     const int k = tab.k[slot];
@@ -41,27 +52,98 @@ __global__ __launch_bounds__(64 * kSmallWaves) void select_small_kernel(const T 
 
     uint32_t pre = 0;
     int want = k, count = 0;
-#pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 24 - 8 * pass;
+    auto valid_key = [&](int i, int v) { return tile_pos(v) < L - (wave + kSmallWaves * i) * 32 - 4 * half; };
+    auto clear_hist = [&]() {
 #pragma unroll
         for (int e = 0; e < 256 * 32 / (64 * kSmallWaves); ++e) hist[threadIdx.x + e * 64 * kSmallWaves] = 0u;
-        __syncthreads();
+    };
+    if (threadIdx.x < 32) {
+        lo_s[n] = 0xFFFFFFFFu;
+        hi_s[n] = 0u;
+        ccnt[n] = 0;
+    }
+    clear_hist();
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            const int left = L - (wave + kSmallWaves * i) * 32 - 4 * half;  // keys of the tile from this half's first on
+    for (int i = 0; i < NT; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < 16; ++v)
+            if (valid_key(i, v)) {
                 const uint32_t key = score_key(acc[i][v]);
-                if (tile_pos(v) < left && (pass == 0 || (key >> ((shift + 8) & 31)) == (pre >> ((shift + 8) & 31))))
-                    atomicAdd(&hist[((key >> shift) & 255u) * 32 + n], 1u);
+                lo = min(lo, key);
+                hi = max(hi, key);
+            }
+    __syncthreads();
+    if (lo <= hi) {
+        atomicMin(&lo_s[n], lo);
+        atomicMax(&hi_s[n], hi);
+    }
+    __syncthreads();
+    const float least = key_score(lo_s[n]);
+    const float span = key_score(hi_s[n]) - least;
+    const float per = span > 0.f ? 255.9f / span : 0.f;  // all alike (or a span beyond the floats): one bin
+    auto bin = [&](float x) { return (uint32_t)fminf(fmaxf((x - least) * per, 0.f), 255.f); };  // not a number (infinite scores): 0
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (valid_key(i, v)) atomicAdd(&hist[bin(acc[i][v]) * 32 + n], 1u);
+    __syncthreads();
+    const Bucket top = find_bucket(hist, scratch, [](int b) { return b; }, k);
+    if (__all(top.count <= kSmallCap)) {  // the same 32 queries in every wave: the whole block
+        if (threadIdx.x < 32) rem[n] = k - top.above;
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (valid_key(i, v) && (int)bin(acc[i][v]) == top.digit) {
+                    const int at = atomicAdd(&ccnt[n], 1);
+                    if (at < kSmallCap) cand[n][at] = score_key(acc[i][v]);
+                }
+        __syncthreads();
+        // the r-th largest of a query's scores in the bin: the key x with #(y > x) < r <= #(y >= x)
+        const int q = threadIdx.x >> 5, c = min(ccnt[q], kSmallCap), r = rem[q];
+        for (int i = n; i < c; i += 32) {
+            const uint32_t x = cand[q][i];
+            int above = 0, same = 0;
+            for (int y = 0; y < c; ++y) {
+                const uint32_t other = cand[q][y];
+                above += other > x;
+                same += other == x;
+            }
+            if (above < r && r <= above + same) {  // every thread that finds it writes the same values
+                tau_s[q] = x;
+                ties[q] = r - above;
+                eq_s[q] = same;
             }
         }
         __syncthreads();
-        const Bucket f = find_bucket(hist, scratch, [](int b) { return b; }, want);
-        pre |= (uint32_t)f.digit << shift;
-        want -= f.above;
-        count = f.count;
+        pre = tau_s[n];
+        want = ties[n];
+        count = eq_s[n];
+    } else {
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass) {
+            const int shift = 24 - 8 * pass;
+#pragma unroll
+            for (int e = 0; e < 256 * 32 / (64 * kSmallWaves); ++e) hist[threadIdx.x + e * 64 * kSmallWaves] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                const int left = L - (wave + kSmallWaves * i) * 32 - 4 * half;  // keys of the tile from this half's first on
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const uint32_t key = score_key(acc[i][v]);
+                    if (tile_pos(v) < left && (pass == 0 || (key >> ((shift + 8) & 31)) == (pre >> ((shift + 8) & 31))))
+                        atomicAdd(&hist[((key >> shift) & 255u) * 32 + n], 1u);
+                }
+            }
+            __syncthreads();
+            const Bucket f = find_bucket(hist, scratch, [](int b) { return b; }, want);
+            pre |= (uint32_t)f.digit << shift;
+            want -= f.above;
+            count = f.count;
+        }
     }
     const float tau = key_score(pre);
     const bool all_simple = __all(want == count);  // every query takes all its ties: "score >= tau" decides
