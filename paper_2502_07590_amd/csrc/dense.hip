@@ -32,6 +32,34 @@ __device__ __forceinline__ float mask_or_neg_inf(float s, uint32_t word, int bit
     return __uint_as_float((__float_as_uint(s) & keep) | (0xFF800000u & ~keep));
 }
 
+// A masked pair has weight zero, and zero times a row of V that is not finite is no number: a query whose sum came out not
+// finite is formed once more, by its wave, from its selected keys alone.
+template <int D>
+__device__ __forceinline__ void dense_fwd_exact(const bf16_t *__restrict__ qrow, const bf16_t *__restrict__ Kh, const bf16_t *__restrict__ Vh,
+                                             const uint32_t *__restrict__ mrow, bf16_t *__restrict__ orow, int L, float c2, float mc, float l)
+{
+    constexpr int CH = D / 64;
+    const int lane = threadIdx.x & 63;
+    float acc[CH], q[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        acc[c] = 0.f;
+        q[c] = bf16_to_f32(qrow[lane * CH + c]);
+    }
+    for (int wd = 0; wd * 32 < L; ++wd)
+        for (uint32_t word = mrow[wd]; word; word &= word - 1) {
+            const int64_t at = (int64_t)(wd * 32 + __ffs(word) - 1) * D + lane * CH;
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) s = fmaf(q[c], bf16_to_f32(Kh[at + c]), s);
+            const float p = fast_exp2(fmaf(group_sum<1>(s), c2, -mc));
+#pragma unroll
+            for (int c = 0; c < CH; ++c) acc[c] = fmaf(p, bf16_to_f32(Vh[at + c]), acc[c]);
+        }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) orow[lane * CH + c] = f32_to_bf16(acc[c] / l);
+}
+
 template <int D>
 __global__ __launch_bounds__(256, 2) void dense_fwd_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                            const bf16_t *__restrict__ V, const uint32_t *__restrict__ bits,
@@ -142,7 +170,19 @@ __global__ __launch_bounds__(256, 2) void dense_fwd_kernel(const bf16_t *__restr
             }
     }
     l += __shfl_xor(l, 32);
-    if (!live) return;
+    float zero = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) zero = fmaf(o[nb][v], 0.f, zero);
+    const bool finite = zero + __shfl_xor(zero, 32) == 0.f;
+    for (unsigned long long todo = __ballot(live && !finite && half == 0); todo; todo &= todo - 1) {
+        const int q = __ffsll(todo) - 1, rq = blockIdx.x * kDenseQueries + wave * 32 + q;
+        const int64_t at = hb + (int64_t)(row0 + rq) * D;
+        dense_fwd_exact<D>(Q + at, K + hb, V + hb, bits + ((int64_t)blockIdx.y * nrows + rq) * pitch, O + at, L, c2, __shfl(mc, q), __shfl(l, q));
+    }
+    if (half == 0 && live) lse[(int64_t)bh * L + qi] = (mc + log2f(l)) * kLn2;
+    if (!live || !finite) return;
     const float inv = 1.f / l;
     bf16_t *orow = O + hb + qi * D + 4 * half;
 #pragma unroll
@@ -151,7 +191,6 @@ __global__ __launch_bounds__(256, 2) void dense_fwd_kernel(const bf16_t *__restr
         for (int g = 0; g < 4; ++g)
             *reinterpret_cast<uint2 *>(orow + 32 * nb + 8 * g) =
                 make_uint2(pack_bf16x2(o[nb][4 * g] * inv, o[nb][4 * g + 1] * inv), pack_bf16x2(o[nb][4 * g + 2] * inv, o[nb][4 * g + 3] * inv));
-    if (half == 0) lse[(int64_t)bh * L + qi] = (mc + log2f(l)) * kLn2;
 }
 
 // ------------------------------------------------------------------------------------ host

@@ -60,6 +60,44 @@ __device__ __forceinline__ void union_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A pair that is not selected has weight zero, and zero times a row of Q or dO that is not finite is no number: a key whose
+// sums came out not finite is formed once more, by its wave, from its own list (n groups of G queries) alone.  A lane takes
+// channels 2 lane and 2 lane + 1.
+__device__ __forceinline__ void grouped_dkdv_exact(const bf16_t *__restrict__ Qr, const bf16_t *__restrict__ Gr, const float2 *__restrict__ stat,
+                                                const bf16_t *__restrict__ krow, const bf16_t *__restrict__ vrow,
+                                                const int32_t *__restrict__ list, int n, int gb, int ge, int G, float c2,
+                                                float (&dk)[2], float (&dv)[2])
+{
+    const int lane = threadIdx.x & 63;
+    auto pair = [&](const bf16_t *row, float (&x)[2]) {
+        const uint32_t w = *reinterpret_cast<const uint32_t *>(row + 2 * lane);
+        x[0] = __uint_as_float(w << 16);
+        x[1] = __uint_as_float(w & 0xFFFF0000u);
+    };
+    float k[2], v[2];
+    pair(krow, k);
+    pair(vrow, v);
+    dk[0] = dk[1] = dv[0] = dv[1] = 0.f;
+    for (int t = 0; t < n; ++t) {
+        const int g = list[t];
+        if (g < gb || g >= ge) continue;
+        for (int m = 0; m < G; ++m) {
+            const int64_t row = (int64_t)(g - gb) * G + m;
+            float q[2], o[2];
+            pair(Qr + row * 128, q);
+            pair(Gr + row * 128, o);
+            const float s = group_sum<1>(fmaf(q[0], k[0], q[1] * k[1])), dp = group_sum<1>(fmaf(o[0], v[0], o[1] * v[1]));
+            const float2 st = stat[row];
+            const float p = fast_exp2(s * c2 - st.x), ds = p * (dp - st.y);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                dk[c] = fmaf(ds, q[c], dk[c]);
+                dv[c] = fmaf(p, o[c], dv[c]);
+            }
+        }
+    }
+}
+
 // Q, dO, rowstat: queries in group-major order (group g = queries g G .. g G + G - 1).
 __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                               const bf16_t *__restrict__ V, const bf16_t *__restrict__ dO,
@@ -271,10 +309,38 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
         }
         union_sync();  // the next step overwrites the parked rows
     }
+    unsigned finite = 0u;  // bit v: key 4 g4 + v
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float zero = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) zero = fmaf(dk[nb][v], 0.f, fmaf(dv[nb][v], 0.f, zero));
+        const unsigned long long bad = __ballot(!(zero == 0.f));
+        finite |= (((bad >> (16 * g4)) & 0xFFFFull) == 0ull) << v;
+        for (int g = 0; g < 4; ++g) {
+            const int j = j0 + 4 * g + v;
+            if (((bad >> (16 * g)) & 0xFFFFull) == 0ull || j >= L) continue;
+            const int64_t *cp = col + (int64_t)bh * (L + 1) + j;
+            const int64_t row = hb + (int64_t)j * D;
+            float xk[2], xv[2];
+            grouped_dkdv_exact(Qr, Gr, stat, K + row, V + row, lists + tab.off[slot] + cp[0], (int)(cp[1] - cp[0]), gb, ge, G, c2, xk, xv);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                if (pl.S == 1) {
+                    dK[row + 2 * lane + c] = f32_to_bf16(scale * xk[c]);
+                    dV[row + 2 * lane + c] = f32_to_bf16(xv[c]);
+                } else {
+                    const int64_t o = (((int64_t)bh * L + j) * pl.S + range) * D + 2 * lane + c;
+                    pdk[o] = xk[c];
+                    pdv[o] = xv[c];
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int j = j0 + 4 * g4 + v;
-        if (j < L) {
+        if (j < L && (finite >> v & 1u)) {
             if (pl.S == 1) {
                 bf16_t *ok = dK + hb + (int64_t)j * D + c16, *ov = dV + hb + (int64_t)j * D + c16;
 #pragma unroll

@@ -8,7 +8,8 @@
 //            scores of the bin that holds the k-th largest go to LDS and are ranked against each other.  Exact: the map
 //            from score to bin is monotone.  If a query of the block finds more than kSmallCap scores in its bin (massive
 //            ties), the block takes the four 8-bit digits of the radix search (stage1.hip) instead.
-//// What bounds it: barriers and LDS round trips, about ten in a row.  L = 1024, two heads, fp32, per call with the projection:
+//
+// What bounds it: barriers and LDS round trips, about ten in a row.  L = 1024, two heads, fp32, per call with the projection:
 // 128 us in six launches, 32 with the digits, 28.6 with the bins.  Outputs are those of the radix search and of the
 // emission (stage1_emit.hip), bit for bit.
 #include "stage1_core.h"

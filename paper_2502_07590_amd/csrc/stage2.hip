@@ -113,13 +113,6 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_kernel(const T *__restrict_
 // forms).  The key-major step takes this form wherever it does not run blocked: lists differ in length by an order of
 // magnitude, and a wave that owns 16 of them waits for the longest (L = 32768, four heads, k = 2048, lists as stage 1 makes
 // them: 19.8 ms by lane groups, 14.4 by waves).
-template <int LPR> __device__ __forceinline__ float group_sum(float x)  // over the 64 / LPR groups of the wave
-{
-#pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
 // This group's part of n positions: whole steps of 4.
 template <int LPR> __device__ __forceinline__ void group_part(int n, int grp, int &tb, int &te)
 {

@@ -237,6 +237,14 @@ __device__ __forceinline__ void fwd_step(FwdState<D / LPR> &st, const RowChunk<T
         axpy_pair<T, CH>(st.acc, vc[u], vc[u + 1], p[u], p[u + 1], sizeof(T) == 2 ? pack_bf16x2(p[u], p[u + 1]) : 0u);
 }
 
+// Sum over the 64 / LPR lane groups of the wave (LPR = 1: over its lanes).
+template <int LPR> __device__ __forceinline__ float group_sum(float x)
+{
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
 // ---- index staging ------------------------------------------------------------------------------
 // The lanes of a group all need the same index entries.  Reading them straight from memory costs one
 // full-width vector-memory instruction per step (as much address-path time as a whole gathered row)

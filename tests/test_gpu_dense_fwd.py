@@ -52,3 +52,26 @@ def test_mask_in_pieces():
     Q, K, V = (torch.randn(1, 1, L, 128, generator=g, device="cuda").bfloat16() for _ in range(3))
     p = dsv.Problem(1, 1, L, 128, 16, "bf16", [k], 128 ** -0.5, sorted_index=True)
     _check(p, Q, K, V, [_rows(L, k, g)], torch.randint(0, L, (200,), generator=g, device="cuda"))
+
+
+# a value row that is not finite belongs to the queries that keep its key, and to no others
+@pytest.mark.parametrize("d,bad", [(64, float("inf")), (128, float("nan"))])
+def test_rows_that_are_not_finite(d, bad):
+    L, k = 2113, 400
+    g = torch.Generator(device="cuda").manual_seed(d)
+    Q, K, V = (torch.randn(1, 12, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    V[0, :, 700] = bad
+    K[0, :, 1500] = bad
+    rows = _rows(L, k, g, near=True)
+    idx = torch.cat([rows.reshape(-1)] * 12)
+    p = dsv.Problem(1, 12, L, d, 16, "bf16", [k] * 12, d ** -0.5, sorted_index=True)
+    assert dsv.sparse_attn_fwd_workspace(p) > 0
+    O, _ = dsv.sparse_attn_fwd(p, Q, K, V, idx)
+    V[0, :, 700], K[0, :, 1500] = 0, 0
+    keeps = ((rows == 700) | (rows == 1500)).any(1)
+    assert not O[0][:, keeps].isfinite().all(-1).any() and O[0][:, ~keeps].isfinite().all()
+    want, _ = dsv.sparse_attn_fwd(p, Q, K, V, idx)
+    # queries whose tiles held the row are formed once more, with probabilities of 24 instead of 8 bits: the two differ by
+    # 2^-9 sum p |v| < 2^-9 max |v| and the roundings of both outputs
+    a, b = O[0][:, ~keeps].float(), want[0][:, ~keeps].float()
+    assert ((a - b).abs() <= 2.0 ** -9 * V.float().abs().max() + 2.0 ** -8 * b.abs()).all()

@@ -44,3 +44,32 @@ def test_grouped_gradients_of_keys_and_values(grid, cube, ks):
     for a, b in zip(got, want):
         a, b = a.float(), b.float()
         assert ((a - b).abs() <= torch.clamp_min(b.abs() * 2.0 ** -7, 2e-2)).all()
+
+
+# a gradient row that is not finite belongs to the keys that its group keeps, and to no others; 1 and 2 ranges
+@pytest.mark.parametrize("grid,bad", [((4, 16, 16), float("inf")), ((4, 48, 48), float("nan"))])
+def test_gradient_rows_that_are_not_finite(grid, bad):
+    L, k, cube = math.prod(grid), 200, (2, 2, 2)
+    g = torch.Generator(device="cuda").manual_seed(L)
+    Q, K, V, dO = (torch.randn(1, 1, L, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
+    ids = torch.arange(L, device="cuda").reshape(grid[0] // 2, 2, grid[1] // 2, 2, grid[2] // 2, 2).permute(0, 2, 4, 1, 3, 5).reshape(-1, 8)
+    rows = torch.rand(L // 8, L, generator=g, device="cuda").topk(k, 1).indices.sort(1).values.to(torch.int32)
+    order = torch.sort(rows.reshape(-1), stable=True).indices
+    col = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+    col[1:] = torch.bincount(rows.reshape(-1), minlength=L).cumsum(0)
+    full = torch.empty(L, k, dtype=torch.int32, device="cuda")
+    full[ids.reshape(-1)] = rows.repeat_interleave(8, 0)
+    p = dsv.Problem(1, 1, L, 128, 16, "bf16", [k], 128 ** -0.5, sorted_index=True)
+    grp = dsv.Grouping(grid, cube)
+    O, lse = dsv.sparse_attn_fwd(p, Q, K, V, full.reshape(-1))
+    args = (rows.reshape(-1), (order // k).to(torch.int32), col[None], O, lse)
+    clean = dsv.sparse_attn_bwd_grouped(p, grp, Q, K, V, *args, dO)
+    group = 5
+    dO[0, 0, ids[group, 3]] = bad
+    got = dsv.sparse_attn_bwd_grouped(p, grp, Q, K, V, *args, dO)
+    keeps = torch.zeros(L, dtype=torch.bool, device="cuda")
+    keeps[rows[group].long()] = True
+    for a, b in zip(got[1:], clean[1:]):
+        assert not a[0, 0, keeps].isfinite().all(-1).any() and a[0, 0, ~keeps].isfinite().all()
+        a, b = a[0, 0, ~keeps].float(), b[0, 0, ~keeps].float()
+        assert ((a - b).abs() <= torch.clamp_min(b.abs() * 2.0 ** -7, 2e-2)).all()  # sums of another order: the bound above
