@@ -503,6 +503,15 @@ def main():
                                              "frac_of_it": round(gbs / GATHER_CEILING_GBS[n], 4)},
                      "note": "achieved = algorithmic gather bytes (K row + V row + index entry per pair) / kernel time; the ranges "
                              "of the split-K plan stay in each XCD's L2, so the bytes cross the L2 -> L1 path, not HBM"}
+        if n == "sparse_attn_fwd" and gbs > L1_PEAK_GBS:
+            # more than gathers could bring: the heads ran over dense tiles with a mask, on the matrix cores
+            formed, kept = (4.0 * cfg.d * pairs / (k_ms * 1e-3) / 1e12 for pairs in (n_scores, nnz))
+            stage2[n] = {"bound": "mfma", "bound_name": "matrix cores, dense bf16", "achieved": round(kept, 1),
+                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(kept / MFMA_BF16_PEAK_TFLOPS, 4),
+                         "traffic": traffic, "kernel": "mask and dense tile kernels of " + n, "kernel_ms": round(k_ms, 3),
+                         "call_ms": round(call_ms[n], 3),
+                         "formed": {"achieved": round(formed, 1), "frac": round(formed / MFMA_BF16_PEAK_TFLOPS, 4)},
+                         "note": "achieved = 4 d flops per selected pair / kernel time; formed counts every pair of the tiles"}
     dominant = max(pair_bytes, key=lambda n: kern_ms[SWEEP_OF_CALL[n]])
     roofline = dict(stage2[dominant])
     # Stage 1 is selection work on the plain vector ALUs.  Algorithmic work: per score one compare against the

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <initializer_list>
 #include <mutex>
+#include <optional>
 #include <vector>
 
 #include "common.h"
@@ -473,6 +474,8 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
     char *ws = static_cast<char *>(workspace);
     std::vector<HeadTable> dense, rest;
     cut_tables(tabs, w.dense_k, dense, rest);
+    std::optional<KernelSpan> span;
+    if (!dense.empty()) span.emplace(DSV_KERNEL_FWD_SWEEP, stream);  // both parts together
     for (const HeadTable &t : dense) {
         st = launch_dense_fwd(*p, t, Q, K, V, idx, O, lse, ws, w.total, stream);
         if (st != DSV_OK) return st;

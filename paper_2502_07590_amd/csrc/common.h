@@ -246,18 +246,24 @@ struct KernelTimer {
     bool on = false;
     hipEvent_t ev[DSV_KERNEL_COUNT][2] = {};
     bool recorded[DSV_KERNEL_COUNT] = {};
+    bool open[DSV_KERNEL_COUNT] = {};  // inside a span of that kind: a nested one is part of it
 };
 extern KernelTimer g_kernel_timer;
 struct KernelSpan {
     int id;
     hipStream_t st;
-    KernelSpan(int id_, hipStream_t st_) : id(id_), st(st_)
+    bool outer;
+    KernelSpan(int id_, hipStream_t st_) : id(id_), st(st_), outer(g_kernel_timer.on && !g_kernel_timer.open[id_])
     {
-        if (g_kernel_timer.on) (void)hipEventRecord(g_kernel_timer.ev[id][0], st);
+        if (!outer) return;
+        g_kernel_timer.open[id] = true;
+        (void)hipEventRecord(g_kernel_timer.ev[id][0], st);
     }
     ~KernelSpan()
     {
-        if (g_kernel_timer.on) g_kernel_timer.recorded[id] = hipEventRecord(g_kernel_timer.ev[id][1], st) == hipSuccess;
+        if (!outer) return;
+        g_kernel_timer.open[id] = false;
+        g_kernel_timer.recorded[id] = hipEventRecord(g_kernel_timer.ev[id][1], st) == hipSuccess;
     }
 };
 
