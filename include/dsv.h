@@ -297,7 +297,8 @@ DSV_API dsv_status dsv_predictor_loss(const dsv_problem *p, const void *Q, const
  * counts: DEVICE int32 [B*H, n_rows], the number of critical keys of every sampled query;
  * sparsity: DEVICE float [B*H] = mean_i (1 - counts_i / L);
  * ema: DEVICE float [B*H] or NULL: updated in place, ema = alpha * sparsity + (1 - alpha) * ema.
- * Scores are recomputed in each of five sweeps on the matrix cores, never stored.  Probability mass is summed in integers
+ * Scores are recomputed in each of three sweeps on the matrix cores (up to eight where very many are nearly alike), never
+ * stored.  No workspace: the query returns 0, and a null one is accepted.  Probability mass is summed in integers
  * (units of 2^-38): the same counts from run to run. */
 DSV_API size_t dsv_profile_sparsity_workspace(const dsv_problem *p, int32_t n_rows);
 DSV_API dsv_status dsv_profile_sparsity(const dsv_problem *p, const void *Q, const void *K, const int32_t *rows,

@@ -2,16 +2,21 @@
 // "Exploiting Dynamic Sparsity"): on a sample of query rows, how many of the highest-probability keys hold
 // `mass` (the paper: 90 %) of each query's softmax; the head's sparsity is the mean fraction of the other keys.
 //
-// Same machinery as the selection of stage 1, on the TRUE scores (contraction over all d channels, matrix
-// cores) and with probability MASS in place of counts: a first sweep gives every sampled query its softmax
-// normaliser (running maximum and sum); four sweeps then find, digit by digit on the order-preserving bit
-// pattern of the score, the score at which the cumulative probability -- taken from the top -- reaches the
-// target, histogramming count and mass per digit in LDS; the last bucket holds keys of one score, of which
-// ceil(missing mass / their probability) are needed.  Scores are recomputed in every sweep, never stored.
+// One kernel, a block per 32 sampled queries of a head; the TRUE scores (contraction over all d channels, matrix cores) are
+// recomputed in every sweep over the keys, never stored:
+//   sweep 1   smallest and largest score and the sum of the exponentials of every query;
+//   sweep 2   count and probability mass in 256 bins of equal width between the smallest and the largest score: the bin in
+//             which the cumulative mass, from the top, reaches the target (equal widths in the VALUE: the bin holds L / 100
+//             scores or so, where the leading eight bits of the float pattern name an octave and a sign);
+//   sweep 3   the scores of that bin go to LDS, where one more histogram and a comparison of the few that share its bin find
+//             the score that crosses; of keys with that very score, ceil(missing mass / their probability) are needed.
+// A bin of more than kProfCap scores is divided again by 256 (a sweep each, twice at most); what is then still too many
+// are ties or nearly so, and four sweeps over the order-preserving bit pattern of the score decide.
 // Count and mass share one 64-bit integer counter, the mass in units of 2^-38: one LDS atomic per score instead of two,
-// and integer ones -- LDS float additions retire about one wave per 44 clocks and CU, which was half of the whole call
-// (L = 32768, four heads, 2048 rows each: the first digit's sweep 1364 us, 270 now; the call 2660 -> 1230) --, and sums that
-// do not depend on the order of arrival.  Every sweep requests a wave's next key tile before it scores this one.
+// and integer ones -- LDS float additions retire about one wave per 44 clocks and CU --, and sums that do not depend on the
+// order of arrival.  Every sweep requests a wave's next key tile before it scores this one; fragment loads bound the sweeps (32 rows
+// x 32 bytes each).  L = 32768, four heads, 2048 rows each: 2660 us with float counters and five sweeps, 1176 with
+// integer ones, 796 with three sweeps.
 #include <algorithm>
 
 #include "stage1_core.h"
@@ -41,34 +46,89 @@ __device__ __forceinline__ Frag<T, D> load_query_frag(const T *__restrict__ Qh, 
     return load_frag_row<T, D>(Qh, (int64_t)min(max(rows[i], 0), L - 1), lane);
 }
 
-// ---- sweep 0: softmax normaliser of every sampled query -------------------------------------------------
-// stat[bh, i] = {m2, 1 / z}: m2 = max_j (s_ij * c2) (log2 domain, c2 = scale * log2 e), z = sum_j 2^(s_ij c2 - m2).
-template <typename T, int D>
-__global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_norm_kernel(const T *__restrict__ Q, const T *__restrict__ K,
-                                                                       const int32_t *__restrict__ rows, int n, int L,
-                                                                       float c2, float2 *__restrict__ stat)
+constexpr int kProfCap = 512;  // scores of a query's bin that fit LDS
+
+template <int G> struct ProfShared {
+    unsigned long long hist[256 * 32];   // [bin][query]
+    unsigned long long part[G * 32];     // the search's partial sums
+    float cand[32][kProfCap + 1];
+    int ncand[32];
+    float lo[32], hi[32], m2[32], rz[32];
+    struct { uint32_t digit; int count; unsigned long long above; } found[32];
+};
+
+// The bin in which the cumulative mass, from the top, reaches `want`: above0 (count and mass) lies above all of them.  All
+// threads of the block; thread t of a query (32 t + query) adds up C bins.
+template <int G>
+__device__ __forceinline__ void cross_bin(ProfShared<G> &sh, unsigned long long above0, unsigned long long want)
 {
-    constexpr int kProfWaves = ProfWaves<T, D>::n;
-    __shared__ float red_m[kProfWaves][64], red_z[kProfWaves][64];
+    constexpr int C = 256 / G;
+    const int q = threadIdx.x & 31, t = threadIdx.x >> 5;
+    __syncthreads();
+    unsigned long long c[C], sum = 0ull;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        c[i] = sh.hist[(t * C + i) * 32 + q];
+        sum += c[i];                                   // counts and masses add up side by side
+    }
+    sh.part[t * 32 + q] = sum;
+    __syncthreads();
+    unsigned long long above = above0;
+    for (int u = t + 1; u < G; ++u) above += sh.part[u * 32 + q];
+    // the thread whose bins cross the target; the lowest one also where rounding left the total a hair short
+    if (mass_of(above) < want && (mass_of(above + sum) >= want || t == 0)) {
+        int digit = t * C;
+        unsigned long long mine = c[0];
+#pragma unroll
+        for (int i = C - 1; i > 0; --i) {
+            if (digit == t * C) {
+                if (mass_of(above + c[i]) >= want) { digit = t * C + i; mine = c[i]; }
+                else above += c[i];
+            }
+        }
+        sh.found[q].digit = (uint32_t)digit;
+        sh.found[q].count = count_of(mine);
+        sh.found[q].above = above;
+    }
+    __syncthreads();
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                                  const int32_t *__restrict__ rows, int n, int L,
+                                                                  float c2, float target, int32_t *__restrict__ counts)
+{
+    constexpr int WAVES = ProfWaves<T, D>::n, THREADS = 64 * WAVES, G = THREADS / 32;
+    extern __shared__ __align__(16) unsigned char lds[];
+    ProfShared<G> &sh = *reinterpret_cast<ProfShared<G> *>(lds);
     const int bh = blockIdx.y;
     const int q0 = blockIdx.x * 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5;
-    const T *Qh = Q + (int64_t)bh * L * D;
+    const int nq = lane & 31, half = lane >> 5;      // in the sweeps; the searches below take query threadIdx.x % 32 too
     const T *Kh = K + (int64_t)bh * L * D;
-    const Frag<T, D> qf = load_query_frag<T, D>(Qh, rows, q0, n, L, lane);
+    const Frag<T, D> qf = load_query_frag<T, D>(Q + (int64_t)bh * L * D, rows, q0, n, L, lane);
     const int ntiles = (L + 31) >> 5;
-    float m = -INFINITY, z = 0.f;
-    Frag<T, D> kf_next = load_frag<T, D>(Kh, wave * 32, L, lane);
-    for (int tile = wave; tile < ntiles; tile += kProfWaves) {
-        const int j0 = tile * 32;
-        const Frag<T, D> kf = kf_next;
-        kf_next = load_frag<T, D>(Kh, (tile + kProfWaves) * 32, L, lane);
-        const floatx16_t acc = score_tile<T, D>(kf, qf);
+    // f(score of key j0 + tile_pos(v), whether there is such a key), 16 a tile
+    auto sweep = [&](auto f) {
+        Frag<T, D> kf_next = load_frag<T, D>(Kh, wave * 32, L, lane);
+        for (int tile = wave; tile < ntiles; tile += WAVES) {
+            const int left = L - tile * 32 - 4 * half;  // keys from this half's first on
+            const Frag<T, D> kf = kf_next;
+            kf_next = load_frag<T, D>(Kh, (tile + WAVES) * 32, L, lane);
+            f(score_tile<T, D>(kf, qf), left);
+        }
+    };
+
+    // ---- softmax normaliser (log2 domain: m2 = max_j s_ij c2, z = sum_j 2^(s_ij c2 - m2)) and range of the scores
+    float lo = INFINITY, hi = -INFINITY, m = -INFINITY, z = 0.f;
+    sweep([&](const floatx16_t &acc, int left) {
         float s[16], mt = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            s[v] = j0 + tile_pos(v) + 4 * half < L ? acc[v] * c2 : -INFINITY;
+            const bool ok = tile_pos(v) < left;
+            lo = fminf(lo, ok ? acc[v] : INFINITY);
+            hi = fmaxf(hi, ok ? acc[v] : -INFINITY);
+            s[v] = ok ? acc[v] * c2 : -INFINITY;
             mt = fmaxf(mt, s[v]);
         }
         const float mn = fmaxf(m, mt);
@@ -79,110 +139,126 @@ __global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_norm_kernel
             z = z * __builtin_amdgcn_exp2f(m - mn) + add;   // m = -inf on the first tile: factor 0
             m = mn;
         }
-    }
-    red_m[wave][lane] = m;
-    red_z[wave][lane] = z;
-    __syncthreads();
-    if (threadIdx.x < 32 && q0 + (int)threadIdx.x < n) {
-        float mm = -INFINITY;
-        for (int w = 0; w < kProfWaves; ++w) mm = fmaxf(mm, fmaxf(red_m[w][threadIdx.x], red_m[w][threadIdx.x + 32]));
-        float zz = 0.f;
-        for (int w = 0; w < kProfWaves; ++w)
-            for (int h = 0; h < 2; ++h) {
-                const float mw = red_m[w][threadIdx.x + 32 * h];
-                if (mw > -INFINITY) zz += red_z[w][threadIdx.x + 32 * h] * __builtin_amdgcn_exp2f(mw - mm);
-            }
-        stat[(int64_t)bh * padded_len(n) + q0 + threadIdx.x] = make_float2(mm, 1.f / zz);
-    }
-}
-
-// ---- sweeps 1-4: one digit of the threshold score ---------------------------------------------------------
-// Per sampled query: prefix (digits found so far), mass_above (units of 2^-38) / count_above (probability and number of keys
-// in the buckets above the prefix's).  PASS 3 also writes the count of critical keys.
-template <typename T, int D, int PASS>
-__global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_pass_kernel(const T *__restrict__ Q, const T *__restrict__ K,
-                                                                       const int32_t *__restrict__ rows, int n, int L,
-                                                                       float c2, float target,
-                                                                       const float2 *__restrict__ stat,
-                                                                       uint32_t *__restrict__ prefix,
-                                                                       unsigned long long *__restrict__ mass_above,
-                                                                       int32_t *__restrict__ count_above,
-                                                                       int32_t *__restrict__ counts)
-{
-    constexpr int SHIFT = 24 - 8 * PASS;
-    constexpr int kProfWaves = ProfWaves<T, D>::n, THREADS = 64 * kProfWaves;
-    constexpr int G = THREADS / 32, C = 256 / G;       // threads per query in the search, buckets of each
-    extern __shared__ unsigned long long hist[];       // [256 digits][32 queries], then the search's scratch [G][32]
-    unsigned long long *part = hist + 256 * 32;
-    const int bh = blockIdx.y;
-    const int q0 = blockIdx.x * 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nq = lane & 31, half = lane >> 5;
-    const T *Qh = Q + (int64_t)bh * L * D;
-    const T *Kh = K + (int64_t)bh * L * D;
-    for (int e = threadIdx.x; e < 256 * 32; e += THREADS) hist[e] = 0ull;
-    __syncthreads();
-    const int64_t g = (int64_t)bh * padded_len(n) + min(q0 + nq, n - 1);
-    const float2 st = stat[g];
-    uint32_t pre = 0;
-    if constexpr (PASS > 0) pre = prefix[g];
-    const Frag<T, D> qf = load_query_frag<T, D>(Qh, rows, q0, n, L, lane);
-    const int ntiles = (L + 31) >> 5;
-    Frag<T, D> kf_next = load_frag<T, D>(Kh, wave * 32, L, lane);
-    for (int tile = wave; tile < ntiles; tile += kProfWaves) {
-        const int left = L - tile * 32 - 4 * half;     // keys from this half's first on
-        const Frag<T, D> kf = kf_next;
-        kf_next = load_frag<T, D>(Kh, (tile + kProfWaves) * 32, L, lane);
-        const floatx16_t acc = score_tile<T, D>(kf, qf);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t key = score_key(acc[v]);
-            bool ok = tile_pos(v) < left;
-            if constexpr (PASS > 0) ok = ok && ((key >> (SHIFT + 8)) == (pre >> (SHIFT + 8)));
-            if (ok) atomicAdd(&hist[((key >> SHIFT) & 255u) * 32 + nq], count_and_mass(__builtin_amdgcn_exp2f(acc[v] * c2 - st.x) * st.y));
+    });
+    {
+        float (*red)[4][64] = reinterpret_cast<float (*)[4][64]>(sh.hist);
+        red[wave][0][lane] = m;
+        red[wave][1][lane] = z;
+        red[wave][2][lane] = lo;
+        red[wave][3][lane] = hi;
+        __syncthreads();
+        if (threadIdx.x < 32) {
+            float mm = -INFINITY, l = INFINITY, h = -INFINITY;
+            for (int w = 0; w < WAVES; ++w)
+                for (int x = 0; x < 64; x += 32) {
+                    mm = fmaxf(mm, red[w][0][nq + x]);
+                    l = fminf(l, red[w][2][nq + x]);
+                    h = fmaxf(h, red[w][3][nq + x]);
+                }
+            float zz = 0.f;
+            for (int w = 0; w < WAVES; ++w)
+                for (int x = 0; x < 64; x += 32) {
+                    const float mw = red[w][0][nq + x];
+                    if (mw > -INFINITY) zz += red[w][1][nq + x] * __builtin_amdgcn_exp2f(mw - mm);
+                }
+            sh.m2[nq] = mm;
+            sh.rz[nq] = 1.f / zz;
+            sh.lo[nq] = l;
+            sh.hi[nq] = h;
+            sh.ncand[nq] = 0;
         }
+        __syncthreads();
     }
-    __syncthreads();
-    // the bucket in which the cumulative mass, from the top, reaches the target; thread t of a query adds up C buckets
+    const float m2 = sh.m2[nq], rz = sh.rz[nq], least = sh.lo[nq], span = sh.hi[nq] - least;
+    const float per = span > 0.f ? 0x1p32f / span : 0.f;
     const unsigned long long want = (unsigned long long)((double)target * 0x1p38);
-    const unsigned long long above0 = PASS == 0 ? 0ull : mass_above[g];
-    const int t = threadIdx.x >> 5;
-    unsigned long long c[C], sum = 0ull;
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-        c[i] = hist[(t * C + i) * 32 + nq];
-        sum += c[i];                                   // counts and masses add up side by side
-    }
-    part[t * 32 + nq] = sum;
-    __syncthreads();
+    auto mass = [&](float x) { return count_and_mass(__builtin_amdgcn_exp2f(x * c2 - m2) * rz); };
+    // the score's place between the smallest and the largest, in 2^-32 (not a number: 0), or its order-preserving pattern
+    auto code = [&](float x, bool pattern) {
+        return pattern ? score_key(x) : (uint32_t)fminf(fmaxf((x - least) * per, 0.f), 0x1.fffffep31f);
+    };
+    auto clear = [&]() {
+        for (int e = threadIdx.x; e < 256 * 32; e += THREADS) sh.hist[e] = 0ull;
+        __syncthreads();
+    };
+
+    // ---- bins, by eight bits of the code at a time, until the crossing bin of every query fits LDS
+    bool pattern = false;
+    uint32_t pre = 0u;
     unsigned long long above = 0ull;
-    for (int u = t + 1; u < G; ++u) above += part[u * 32 + nq];
-    // the thread whose buckets cross the target; the lowest one also where rounding left the total a hair short
-    const bool reached = above0 + mass_of(above) + mass_of(sum) >= want, before = above0 + mass_of(above) >= want;
-    if (!before && (reached || t == 0) && q0 + nq < n) {
-        int digit = t * C;
+    int known = 0, count = 0;  // leading bits found; scores that share them
+    for (;;) {
+        clear();
+        const int shift = 24 - known;
+        sweep([&](const floatx16_t &acc, int left) {
 #pragma unroll
-        for (int i = C - 1; i > 0; --i) {
-            if (digit == t * C) {
-                if (above0 + mass_of(above + c[i]) >= want) digit = t * C + i;
-                else above += c[i];
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t x = code(acc[v], pattern);
+                if (tile_pos(v) < left && (known == 0 || (x ^ pre) >> (shift + 8) == 0u))
+                    atomicAdd(&sh.hist[((x >> shift) & 255u) * 32 + nq], mass(acc[v]));
             }
+        });
+        cross_bin(sh, above, want);
+        pre |= sh.found[nq].digit << shift;
+        above = sh.found[nq].above;
+        count = sh.found[nq].count;
+        known += 8;
+        if (!pattern && __all(count <= kProfCap)) break;  // the same 32 queries in every wave: the whole block
+        if (known == 32) break;
+        if (!pattern && known == 24) {
+            pattern = true;
+            pre = 0u;
+            above = 0ull;
+            known = 0;
         }
-        const int64_t gq = (int64_t)bh * padded_len(n) + q0 + nq;
-        const unsigned long long ma = above0 + mass_of(above);
-        const int ca = (PASS == 0 ? 0 : count_above[gq]) + count_of(above);
-        const uint32_t full = pre | ((uint32_t)digit << SHIFT);
-        prefix[gq] = full;
-        mass_above[gq] = ma;
-        count_above[gq] = ca;
-        if constexpr (PASS == 3) {
-            // every key of this bucket has the score `full` decodes to, hence the same probability
-            const int cb = max(count_of(hist[digit * 32 + nq]), 1);
-            const float p = __builtin_amdgcn_exp2f(key_score(full) * c2 - st.x) * st.y;
-            const float missing = (float)((double)(want > ma ? want - ma : 0ull) * 0x1p-38);
-            const int need = p > 0.f ? (int)fminf(ceilf(missing / p), (float)cb) : cb;
-            counts[(int64_t)bh * n + q0 + nq] = ca + min(max(need, 1), cb);
+    }
+    const bool mine = q0 + nq < n;
+    int32_t *out = counts + (int64_t)bh * n + q0 + nq;
+    // of `same` keys of score x, below `above`, as many as the missing mass takes
+    auto write = [&](float x, unsigned long long over, int same) {
+        const float p = __builtin_amdgcn_exp2f(x * c2 - m2) * rz;
+        const float missing = (float)((double)(want > mass_of(over) ? want - mass_of(over) : 0ull) * 0x1p-38);
+        const int need = p > 0.f ? (int)fminf(ceilf(missing / p), (float)same) : same;
+        *out = count_of(over) + min(max(need, 1), same);
+    };
+    if (pattern) {  // every key of the bin has the score that `pre` decodes to
+        if (threadIdx.x < 32 && mine) write(key_score(pre), above, max(count, 1));
+        return;
+    }
+    // ---- the crossing bin's scores, in LDS
+    clear();
+    sweep([&](const floatx16_t &acc, int left) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (tile_pos(v) < left && (code(acc[v], false) ^ pre) >> (32 - known) == 0u) {
+                const int at = atomicAdd(&sh.ncand[nq], 1);
+                if (at < kProfCap) sh.cand[nq][at] = acc[v];
+            }
+    });
+    __syncthreads();
+    const int t = threadIdx.x >> 5, c = min(sh.ncand[nq], kProfCap);
+    const int shift = 24 - known;
+    auto bin = [&](float x) { return (code(x, false) >> shift) & 255u; };
+    for (int i = t; i < c; i += G) atomicAdd(&sh.hist[bin(sh.cand[nq][i]) * 32 + nq], mass(sh.cand[nq][i]));
+    cross_bin(sh, above, want);
+    above = sh.found[nq].above;
+    const uint32_t digit = sh.found[nq].digit;
+    for (int i = t; i < c; i += G) {
+        const float x = sh.cand[nq][i];
+        if (bin(x) != digit) continue;
+        const uint32_t key = score_key(x);
+        unsigned long long over = above, with = 0ull;
+        bool lowest = true;
+        for (int j = 0; j < c; ++j) {
+            const float y = sh.cand[nq][j];
+            if (bin(y) != digit) continue;
+            const uint32_t other = score_key(y);
+            if (other > key) over += mass(y);
+            else if (other == key) with += mass(y);
+            else lowest = false;
         }
+        // every thread that finds the crossing score writes the same count
+        if (mine && mass_of(over) < want && (mass_of(over + with) >= want || lowest)) write(x, over, count_of(with));
     }
 }
 
@@ -211,49 +287,30 @@ __global__ __launch_bounds__(256) void profile_finish_kernel(const int32_t *__re
 // ------------------------------------------------------------------------------------ host
 template <typename T, int D>
 static dsv_status profile_t(const dsv_problem &p, const void *Q, const void *K, const int32_t *rows, int n, float mass,
-                            int32_t *counts, float *sparsity, float *ema, float alpha, char *ws, hipStream_t st)
+                            int32_t *counts, float *sparsity, float *ema, float alpha, hipStream_t st)
 {
     const int nbh = p.B * p.H;
-    const size_t np_ = (size_t)nbh * padded_len(n);
-    float2 *stat = reinterpret_cast<float2 *>(ws);
-    uint32_t *prefix = reinterpret_cast<uint32_t *>(ws + align_up(np_ * 8, 256));
-    unsigned long long *mabove = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(prefix) + align_up(np_ * 4, 256));
-    int32_t *cabove = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(mabove) + align_up(np_ * 8, 256));
-    const float c2 = p.scale * 1.4426950408889634f;
     constexpr int threads = 64 * ProfWaves<T, D>::n;
-    const size_t lds = (256 * 32 + threads / 32 * 32) * 8;  // counters and the search's scratch: above the default of 64 KB
-    const void *kernels[] = {reinterpret_cast<const void *>(&profile_pass_kernel<T, D, 0>), reinterpret_cast<const void *>(&profile_pass_kernel<T, D, 1>),
-                             reinterpret_cast<const void *>(&profile_pass_kernel<T, D, 2>), reinterpret_cast<const void *>(&profile_pass_kernel<T, D, 3>)};
-    for (const void *k : kernels) DSV_HIP_CHECK(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    dim3 grid((n + 31) / 32, nbh), block(threads);
-    hipLaunchKernelGGL((profile_norm_kernel<T, D>), grid, block, 0, st, (const T *)Q, (const T *)K, rows, n, p.L, c2, stat);
-    DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((profile_pass_kernel<T, D, 0>), grid, block, lds, st, (const T *)Q, (const T *)K, rows, n, p.L, c2, mass, stat, prefix, mabove, cabove, counts);
-    hipLaunchKernelGGL((profile_pass_kernel<T, D, 1>), grid, block, lds, st, (const T *)Q, (const T *)K, rows, n, p.L, c2, mass, stat, prefix, mabove, cabove, counts);
-    hipLaunchKernelGGL((profile_pass_kernel<T, D, 2>), grid, block, lds, st, (const T *)Q, (const T *)K, rows, n, p.L, c2, mass, stat, prefix, mabove, cabove, counts);
-    hipLaunchKernelGGL((profile_pass_kernel<T, D, 3>), grid, block, lds, st, (const T *)Q, (const T *)K, rows, n, p.L, c2, mass, stat, prefix, mabove, cabove, counts);
+    constexpr size_t lds = sizeof(ProfShared<threads / 32>);  // above the default of 64 KB
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    DSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&profile_kernel<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((profile_kernel<T, D>), dim3((n + 31) / 32, nbh), dim3(threads), lds, st, (const T *)Q, (const T *)K, rows, n, p.L,
+                       p.scale * 1.4426950408889634f, mass, counts);
     DSV_LAUNCH_CHECK();
     hipLaunchKernelGGL(profile_finish_kernel, dim3(nbh), dim3(256), 0, st, counts, n, p.L, sparsity, ema, alpha);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
 
-size_t profile_workspace_bytes(const dsv_problem &p, int n)
-{
-    const size_t np_ = (size_t)p.B * p.H * padded_len(n);
-    return 2 * align_up(np_ * 8, 256) + 2 * align_up(np_ * 4, 256);
-}
-
 dsv_status launch_profile_sparsity(const dsv_problem &p, const void *Q, const void *K, const int32_t *rows, int n,
-                                   float mass, int32_t *counts, float *sparsity, float *ema, float alpha, char *ws,
-                                   hipStream_t st)
+                                   float mass, int32_t *counts, float *sparsity, float *ema, float alpha, hipStream_t st)
 {
     if (p.dtype == DSV_BF16) {
-        if (p.d == 64) return profile_t<bf16_t, 64>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, ws, st);
-        if (p.d == 128) return profile_t<bf16_t, 128>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, ws, st);
+        if (p.d == 64) return profile_t<bf16_t, 64>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, st);
+        if (p.d == 128) return profile_t<bf16_t, 128>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, st);
     } else if (p.dtype == DSV_F32) {
-        if (p.d == 64) return profile_t<float, 64>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, ws, st);
-        if (p.d == 128) return profile_t<float, 128>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, ws, st);
+        if (p.d == 64) return profile_t<float, 64>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, st);
+        if (p.d == 128) return profile_t<float, 128>(p, Q, K, rows, n, mass, counts, sparsity, ema, alpha, st);
     }
     return DSV_EUNSUPPORTED;
 }

@@ -35,3 +35,20 @@ def test_counts_at_the_edges(L, n, dtype, d, scale_mul):
         edge = torch.gather(prob, 1, (want[:, None] - 1)).squeeze(1)
         assert (off.abs() <= torch.ceil(8e-6 * max(1.0, scale_mul) / edge).clamp_min(1)).all()
         assert torch.isclose(sparsity[h].double(), (1 - counts[h].double() / L).mean(), atol=1e-6)
+
+
+# the crossing bin: some keys (ranked in LDS), more than 512 nearly alike (divided again), more than 512 of one score
+@pytest.mark.parametrize("noise", [None, 1e-3, 0.0])
+def test_counts_in_crowded_bins(noise):
+    L, d, n = 6000, 64, 40
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q = torch.randn(1, 1, L, d, generator=g, device="cuda")
+    K = torch.randn(1, 1, L, d, generator=g, device="cuda")
+    if noise is not None:
+        K[0, 0, 100:5500] = K[0, 0, 100] + noise * torch.randn(5400, d, generator=g, device="cuda")
+    rows = torch.randperm(L, generator=g, device="cuda")[:n].to(torch.int32)
+    p = dsv.Problem(1, 1, L, d, 16, "f32", [1], 0.2)
+    _, counts = dsv.profile_sparsity(p, Q, K, rows, mass=0.9)
+    want, prob = _counts(Q[0, 0][rows.long()], K[0, 0], p.scale, 0.9)
+    edge = torch.gather(prob, 1, (want[:, None] - 1)).squeeze(1)
+    assert ((counts[0].long() - want).abs() <= torch.ceil(8e-6 / edge).clamp_min(1)).all()  # as above
