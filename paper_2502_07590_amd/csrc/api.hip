@@ -132,6 +132,13 @@ int64_t mean_k(const dsv_problem &p)
     return s / p.H;
 }
 
+// Whether sequences of less than eight full ranges are cut in two or four instead of eight: every range leaves partial results,
+// segment pointers and a row order, smaller ones stay in the L2 with the index that streams past them.  Measured, bf16, d = 128, four
+// heads, eight ranges against two or four: dkdv at L = 8192, k = 512: 496 : 415 us; 12000, k = 750: 946 : 832; 16000, k = 160: 539 : 346;
+// 32768, k = 327: 1598 : 1365, k = 1000: 3294 : 3119 and dq 2899 : 2692; on lists as stage 1 makes them, 32768, k = 2048, the whole backward
+// 11284 : 11302; 20280, k = 507 .. 4056: 7641 : 7725.
+bool few_ranges(const dsv_problem &p) { return mean_k(p) <= 1280; }
+
 // Whether the per-query forward and dq step run L2-blocked: sorted indices promised, and enough to gather from enough rows.
 // Blocking costs about 0.5 ns per (row, range) -- partial results written and merged, segments, row order -- and wins
 // back what the gathers lose to L2 misses, which ascending rows walked side by side already keep few.  Measured at bf16,
@@ -145,12 +152,14 @@ bool split_rows(const dsv_problem &p, const SplitPlan &pl)
     return use_split(p, pl) && kv_bytes(p) >= ((size_t)8 << 20) && mean_k(p) >= (kv_bytes(p) > ((size_t)48 << 20) ? 512 : 768);
 }
 
-// The same for the key-major step, whose lists differ in length: the blocked form also sorts them by it.  Measured as above:
-// L = 4096, k = 40: 114 : 61, k = 256: 191 : 178, k = 819: 359 : 411; 8192, k = 81: 240 : 166, k = 512: 519 : 624; 12000, k = 120:
-// 408 : 333, k = 750: 985 : 1396; 16000, k = 160: 569 : 559; one head of 4096, k = 256: 96 : 62.
+// The same for the key-major step, whose lists differ in length: the blocked form also sorts them by it, the other one gives
+// every list a wave.  Blocked against not, us, lists of even length: L = 4096, k = 40: 72 : 47, k = 256: 155 : 134, k = 819: 338 : 360;
+// 8192, k = 81: 135 : 128, k = 512: 410 : 521; 12000, k = 120: 217 : 259, k = 750: 833 : 1179; 16384, k = 160: 349 : 458; lists as stage 1
+// makes them: 4096, k = 819: 489 : 428; 8192, k = 512: 707 : 717; 16384, k = 1000: 2012 : 3004; three heads of 6000, d = 64 (1.5 MB),
+// k = 600: 371 : 222; one of 4096, k = 256, even: 103 : 38.
 bool split_lists(const dsv_problem &p, const SplitPlan &pl)
 {
-    return use_split(p, pl) && kv_bytes(p) > ((size_t)1 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
+    return use_split(p, pl) && kv_bytes(p) > ((size_t)3 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
 }
 
 // Whether a whole backward on rows in any order sorts them first, so that the dq step runs L2-blocked: once a head's K and
@@ -224,7 +233,7 @@ struct FwdLayout {
 FwdLayout fwd_layout(const dsv_problem &p)
 {
     FwdLayout w{};
-    w.plan = make_split_plan(p, kFwdRangeBytes);
+    w.plan = make_split_plan(p, kFwdRangeBytes, few_ranges(p));
     w.split = split_rows(p, w.plan);
     w.dense_k = dense_fwd_min_k(p);
     int dense = 0;
@@ -254,7 +263,7 @@ struct StepLayout {
 StepLayout step_layout(const dsv_problem &p)
 {
     StepLayout w{};
-    w.plan = make_split_plan(p, kBwdRangeBytes);
+    w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
     w.split_dq = split_rows(p, w.plan);
     w.split_dkdv = split_lists(p, w.plan);
     if (!w.split_dq && !w.split_dkdv) return w;
@@ -655,7 +664,8 @@ struct GroupedStepLayout {
 GroupedStepLayout grouped_step_layout(const dsv_problem &p, const dsv_grouping &g, bool dq)
 {
     GroupedStepLayout w{};
-    w.plan = make_split_plan(p, kBwdRangeBytes);
+    // few: a group's partial results are its members' (four heads of 32768, k = 2048, 2 x 2 x 2, the layer: 8058 -> 7612 us)
+    w.plan = make_split_plan(p, kBwdRangeBytes, true);
     w.split = use_split(p, w.plan);
     if (!w.split) return w;
     const size_t nbh = (size_t)p.B * p.H, rows = nbh * p.L, Lq = p.L / group_size(g);

@@ -286,10 +286,35 @@ constexpr size_t kMaxRangeRows = 8192;  // rows of a range: 8 bytes of row stati
 struct SplitPlan {
     int range_len;  // keys (queries) per range
     int S;          // ranges
-    int S_pad;      // S rounded up to a multiple of 8 (one XCD per residue class)
+    int S_pad;      // ranges as laid out over the XCDs: 2, 4 or a multiple of 8, at least S
     int nqb;        // row blocks per range (each kernel sets it from its own rows per block)
 };
-SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes);
+SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes, bool few);
+
+// Work items (row block, range) of a head: linear id -> range and row block, consecutive ids on consecutive XCDs.  Eight ranges or
+// more: an XCD (one of eight) walks the blocks of its own ranges one range after the other.  One, two or four: the XCDs that
+// share a range take its blocks in turn.
+__host__ __device__ __forceinline__ int64_t range_items(int S_pad, int nqb)
+{
+    return S_pad < 8 ? 8ll * ((nqb * S_pad + 7) / 8) : (int64_t)S_pad * nqb;
+}
+__device__ __forceinline__ bool decode_range_item(int S, int S_pad, int nqb, int64_t b, int &slot, int &range, int &rb)
+{
+    const int64_t per_head = range_items(S_pad, nqb);
+    slot = (int)(b / per_head);
+    const int rem = (int)(b - (int64_t)slot * per_head);
+    const int xcd = rem & 7, local = rem >> 3;
+    if (S_pad < 8) {
+        const int share = 8 / S_pad;
+        range = xcd % S_pad;
+        rb = local * share + xcd / S_pad;
+    } else {
+        const int t = local / nqb;
+        rb = local - t * nqb;
+        range = t * 8 + xcd;
+    }
+    return range < S && rb < nqb;
+}
 
 struct FwdSplitWorkspace {
     int32_t *seg;  // [B*H, L, S+1] segment pointers into every idx row

@@ -195,21 +195,6 @@ __global__ void group_overlap_finish_kernel(const unsigned long long *__restrict
     if (slot < tab.n) overlap[tab.bh[slot]] = (float)((double)count[tab.bh[slot]] / ((double)L * tab.k[slot]));
 }
 
-// Linear block id -> (head slot, key range, block of 4 groups), consecutive ids on consecutive XCDs, every XCD
-// walking its own ranges one after the other (the order of the per-query L2-blocked sweeps).
-__device__ __forceinline__ bool decode_group_item(const SplitPlan &pl, int64_t b, int &slot, int &range, int &gb)
-{
-    const int64_t per_head = (int64_t)pl.S_pad * pl.nqb;
-    slot = (int)(b / per_head);
-    const int64_t rem = b - (int64_t)slot * per_head;
-    const int xcd = (int)(rem & 7);
-    const int64_t local = rem >> 3;
-    const int t = (int)(local / pl.nqb);
-    gb = (int)(local - (int64_t)t * pl.nqb);
-    range = t * 8 + xcd;
-    return range < pl.S;
-}
-
 // ---- grouped forward ------------------------------------------------------------------------------------
 // Both products of a tile run on the matrix cores.
 //   S = Q_g K^T   v_mfma_f32_32x32x16_bf16 per 16 channels: A = the group's query rows (rows >= G zero), B = the 32
@@ -249,7 +234,7 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
     constexpr int NM = D / 16;
     int slot, range = 0, gb;
     if (SPLIT) {
-        if (!decode_group_item(pl, blockIdx.x, slot, range, gb)) return;
+        if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, gb)) return;
     } else {
         slot = blockIdx.y;
         gb = blockIdx.x;
@@ -488,7 +473,7 @@ __global__ __launch_bounds__(256) void grouped_dq_kernel(const bf16_t *__restric
     constexpr int NC = D / 32;
     int slot, range = 0, gb;
     if (SPLIT) {
-        if (!decode_group_item(pl, blockIdx.x, slot, range, gb)) return;
+        if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, gb)) return;
     } else {
         slot = blockIdx.y;
         gb = blockIdx.x;
@@ -824,7 +809,7 @@ dsv_status launch_grouped_fwd(const dsv_problem &p, const dsv_grouping &gr, cons
     {
         KernelSpan span(DSV_KERNEL_FWD_SWEEP, st);
         for (int t = 0; t < n_tabs; ++t) {
-            const int64_t blocks = (int64_t)tabs[t].n * pl.S_pad * pl.nqb;
+            const int64_t blocks = tabs[t].n * range_items(pl.S_pad, pl.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             dim3 grid((unsigned)blocks);
             launch_fwd_variant<true>(nsub, grid, st, (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, idx_g, (bf16_t *)O, lse,
@@ -865,7 +850,7 @@ dsv_status launch_grouped_dq(const dsv_problem &p, const dsv_grouping &gr, const
     {
         KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
         for (int t = 0; t < n_tabs; ++t) {
-            const int64_t blocks = (int64_t)tabs[t].n * pl.S_pad * pl.nqb;
+            const int64_t blocks = tabs[t].n * range_items(pl.S_pad, pl.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             dim3 grid((unsigned)blocks);
             launch_dq_variant<true>(nsub, grid, st, (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, idx_g, (const bf16_t *)O, lse,

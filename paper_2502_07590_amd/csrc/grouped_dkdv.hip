@@ -109,24 +109,8 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
 {
     constexpr int D = 128;
     __shared__ __align__(16) UnionWave sh_all[4];
-    // block -> (head, range, key block): consecutive ids on consecutive XCDs, an XCD stays inside one range
     int slot, range, kb;
-    {
-        const int share = pl.S < 8 ? 8 / pl.S : 1;           // XCDs that work on the same range
-        const int per_xcd = pl.S < 8 ? (pl.nkb + share - 1) / share : pl.nkb * (pl.S / 8);
-        const int64_t b = blockIdx.x;
-        slot = (int)(b / (8 * per_xcd));
-        const int rem = (int)(b - (int64_t)slot * 8 * per_xcd);
-        const int xcd = rem & 7, local = rem >> 3;
-        if (pl.S < 8) {
-            range = xcd % pl.S;
-            kb = local * share + xcd / pl.S;
-        } else {
-            range = local / pl.nkb * 8 + xcd;
-            kb = local % pl.nkb;
-        }
-        if (kb >= pl.nkb) return;
-    }
+    if (!decode_range_item(pl.S, pl.S, pl.nkb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, g4 = lane >> 4;
@@ -394,10 +378,8 @@ dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tab
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
-        const int share = pl.S < 8 ? 8 / pl.S : 1;
-        const int64_t per_xcd = pl.S < 8 ? (pl.nkb + share - 1) / share : (int64_t)pl.nkb * (pl.S / 8);
         for (int t = 0; t < n_tabs; ++t) {
-            const int64_t blocks = tabs[t].n * per_xcd * 8;
+            const int64_t blocks = tabs[t].n * range_items(pl.S, pl.nkb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             hipLaunchKernelGGL(grouped_dkdv_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)Q, (const bf16_t *)K,
                                (const bf16_t *)V, (const bf16_t *)dO, lists, col, (const float2 *)rowstat, (bf16_t *)dK, (bf16_t *)dV,

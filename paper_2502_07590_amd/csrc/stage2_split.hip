@@ -18,22 +18,6 @@
 
 namespace dsv {
 
-// Decode a linear block id into (head slot, range, row block).  Consecutive ids go to
-// consecutive XCDs; ids b, b+8, b+16, ... (one XCD) walk the row blocks of one range, then the
-// next range of that XCD.  Ranges are padded to a multiple of 8; padded ranges return false.
-__device__ __forceinline__ bool decode_item(const SplitPlan &pl, int64_t b, int &slot, int &range, int &rb)
-{
-    const int64_t per_head = (int64_t)pl.S_pad * pl.nqb;
-    slot = (int)(b / per_head);
-    const int64_t rem = b - (int64_t)slot * per_head;
-    const int xcd = (int)(rem & 7);
-    const int64_t local = rem >> 3;
-    const int t = (int)(local / pl.nqb);
-    rb = (int)(local - (int64_t)t * pl.nqb);
-    range = t * 8 + xcd;
-    return range < pl.S;
-}
-
 // ---- segment pointers -----------------------------------------------------------------------
 // seg[bh, row, s] = first position in the (ascending) row whose value is >= s * range_len, for
 // s = 0 .. S.  Query-major: rows of idx (length k).  Key-major: lists of idx_t (start and length
@@ -84,7 +68,7 @@ __global__ __launch_bounds__(256) void sparse_fwd_split_kernel(const T *__restri
     constexpr int CH = D / LPR;
     constexpr int RPW = 64 / LPR;  // rows per wave
     int slot, range, qb;
-    if (!decode_item(pl, blockIdx.x, slot, range, qb)) return;
+    if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, qb)) return;
     const int bh = tab.bh[slot];
     const int k = tab.k[slot];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -166,7 +150,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_split_kernel(const T *__res
     constexpr int CH = D / LPR;
     constexpr int RPW = 64 / LPR;  // rows per wave
     int slot, range, qb;
-    if (!decode_item(pl, blockIdx.x, slot, range, qb)) return;
+    if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, qb)) return;
     const int bh = tab.bh[slot];
     const int k = tab.k[slot];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -257,7 +241,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
     constexpr int CH = D / LPR;
     constexpr int RPW = 64 / LPR;  // rows per wave
     int slot, range, kb;
-    if (!decode_item(pl, blockIdx.x, slot, range, kb)) return;
+    if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / LPR, s = lane % LPR;
@@ -423,19 +407,19 @@ __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t *__restrict__ p, 
 }
 
 // ------------------------------------------------------------------------------------ host
-SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes)
+SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes, bool few)
 {
     const size_t esz = p.dtype == DSV_BF16 ? 2 : 4;
     const size_t row_pair_bytes = 2 * (size_t)p.d * esz;  // one K row + one V row (or Q + dO)
     SplitPlan pl;
-    // ranges of about range_bytes, their number a multiple of 8 so that every XCD gets the same
-    // number of ranges (a 6-5 split of ranges over XCDs costs ~10 %)
-    // at most kMaxRangeRows rows per range: the dkdv sweep parks the range's row statistics in LDS
+    // ranges of at most range_bytes and kMaxRangeRows rows (the dkdv sweep parks the range's row statistics in LDS), their
+    // number a multiple of 8, so that every XCD gets the same number (a 6-5 split of ranges over XCDs costs ~10 %).  few: two
+    // or four where the size asks for no more
     const size_t target = std::min<size_t>(kMaxRangeRows, std::max<size_t>(256, range_bytes / row_pair_bytes));
-    int S = (int)((p.L + 8 * target - 1) / (8 * target)) * 8;
-    pl.range_len = (p.L + S - 1) / S;
+    const int want = (int)((p.L + target - 1) / target);
+    pl.S_pad = few && want <= 2 ? 2 : few && want <= 4 ? 4 : (want + 7) / 8 * 8;
+    pl.range_len = (p.L + pl.S_pad - 1) / pl.S_pad;
     pl.S = (p.L + pl.range_len - 1) / pl.range_len;
-    pl.S_pad = (pl.S + 7) / 8 * 8;
     pl.nqb = (p.L + 15) / 16;
     return pl;
 }
@@ -497,7 +481,7 @@ static dsv_status fwd_split_t(const dsv_problem &p, const HeadTable *tabs, int n
         for (int t = 0; t < n_tabs; ++t) {
             SplitPlan lp = pl;
             lp.nqb = (p.L + 256 / SweepLanes<T, D>::fwd - 1) / (256 / SweepLanes<T, D>::fwd);  // row blocks of this kernel's layout
-            const int64_t blocks = (int64_t)tabs[t].n * lp.S_pad * lp.nqb;
+            const int64_t blocks = tabs[t].n * range_items(lp.S_pad, lp.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             hipLaunchKernelGGL((sparse_fwd_split_kernel<T, D, SweepLanes<T, D>::fwd>), dim3((unsigned)blocks), dim3(256), 0, st, (const T *)Q,
                                (const T *)K, (const T *)V, idx, w.seg, w.order, w.pm, w.pl, w.pacc, p.L, p.scale, tabs[t], lp);
@@ -527,7 +511,7 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
         for (int t = 0; t < n_tabs; ++t) {
             SplitPlan lp = pl;
             lp.nqb = (p.L + 256 / SweepLanes<T, D>::dq - 1) / (256 / SweepLanes<T, D>::dq);  // row blocks of this kernel's layout
-            const int64_t blocks = (int64_t)tabs[t].n * lp.S_pad * lp.nqb;
+            const int64_t blocks = tabs[t].n * range_items(lp.S_pad, lp.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             hipLaunchKernelGGL((sparse_bwd_dq_split_kernel<T, D, SweepLanes<T, D>::dq>), dim3((unsigned)blocks), dim3(256), 0, st, (const T *)Q,
                                (const T *)K, (const T *)V, idx, w.seg, w.order, (const T *)O, lse, (const T *)dO, w.pa, w.pb,
@@ -561,7 +545,7 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
         for (int t = 0; t < n_tabs; ++t) {
             SplitPlan lp = pl;
             lp.nqb = (p.L + 256 / SweepLanes<T, D>::dkdv - 1) / (256 / SweepLanes<T, D>::dkdv);  // row blocks of this kernel's layout
-            const int64_t blocks = (int64_t)tabs[t].n * lp.S_pad * lp.nqb;
+            const int64_t blocks = tabs[t].n * range_items(lp.S_pad, lp.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
             const size_t stat_bytes = (size_t)lp.range_len * sizeof(float2);  // <= kMaxRangeRows * 8
             auto kern = &sparse_bwd_dkdv_split_kernel<T, D, SweepLanes<T, D>::dkdv>;
