@@ -541,7 +541,7 @@ dsv_status dsv_idx_transpose(const dsv_problem *p, const int32_t *idx, int32_t *
     st = check_workspace(workspace, ws_bytes, need);
     if (st != DSV_OK) return st;
     const std::vector<HeadTable> tabs = make_tables(*p);
-    return launch_idx_transpose(*p, tabs.data(), (int)tabs.size(), idx, idx_t, col_ptr,
+    return launch_idx_transpose(*p, tabs.data(), (int)tabs.size(), idx, false, idx_t, col_ptr,
                                 workspace, need, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -595,18 +595,21 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
     // step may run the L2-blocked kernel
     dsv_problem sorted = *p;
     sorted.flags |= DSV_FLAG_SORTED_INDEX;
+    const std::vector<HeadTable> tabs = make_tables(*p);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    uint32_t *bits = nullptr;
     if (sort_rows_first(*p)) {
         // rows in any order: an ascending copy (in the place of the lists, which are built after the dq step) lets the
-        // dq step run L2-blocked too
-        const std::vector<HeadTable> tabs = make_tables(*p);
-        st = launch_sort_rows(*p, tabs.data(), (int)tabs.size(), idx, idx_t, static_cast<hipStream_t>(hip_stream));
+        // dq step run L2-blocked too; its bitmaps serve the transposition
+        bits = transpose_matrix(*p, ws + w.cnt);
+        st = launch_sort_rows(*p, tabs.data(), (int)tabs.size(), idx, idx_t, bits, stream);
         if (st != DSV_OK) return st;
         st = dsv_sparse_attn_bwd_dq(&sorted, Q, K, V, idx_t, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
     } else {
         st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
     }
     if (st != DSV_OK) return st;
-    st = dsv_idx_transpose(p, idx, idx_t, col, ws + w.cnt, w.cnt_bytes, hip_stream);
+    st = launch_idx_transpose(*p, tabs.data(), (int)tabs.size(), idx, bits != nullptr, idx_t, col, ws + w.cnt, w.cnt_bytes, stream);
     if (st != DSV_OK) return st;
     return dsv_sparse_attn_bwd_dkdv(&sorted, Q, K, V, idx_t, col, lse, delta, dO, dK, dV, ws + w.step, w.step_bytes, hip_stream);
 }

@@ -462,7 +462,7 @@ dsv_status launch_idx_validate(const dsv_problem &p, const HeadTable *tabs, int 
 // Stable transposition: every list ascending in the query index, the same result from run to run.
 // ws: scratch of idx_transpose_bytes(p) bytes; col: [B*H, L+1] int64.
 size_t idx_transpose_bytes(const dsv_problem &p);
-dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx,
+dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx, bool built,
                                 int32_t *idxT, int64_t *col, void *ws, size_t ws_bytes, hipStream_t st);
 // Rows row0 .. row0 + nrows - 1 of `heads` head slots as a bit matrix [heads, nrows, bits_pitch(L) words]; L <= kBitsMaxKeys.
 constexpr int kBitsMaxKeys = 524288;  // a row's bitmap fits 64 KB of LDS
@@ -474,10 +474,13 @@ dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slo
 constexpr int kDenseMinRows = 128;
 dsv_status launch_dense_fwd(const dsv_problem &p, const HeadTable &tab, const void *Q, const void *K, const void *V,
                             const int32_t *idx, void *O, float *lse, char *ws, size_t ws_bytes, hipStream_t st);
-// out = the rows of idx in ascending order (same layout); can_sort_rows: whether this L is covered.
+// The bit matrix in the workspace of launch_idx_transpose if it holds all heads at once, else null: a caller that has filled it
+// (launch_sort_rows) says `built`.
+uint32_t *transpose_matrix(const dsv_problem &p, void *ws);
+// out = the rows of idx in ascending order (same layout), and their bitmaps if bits is given; can_sort_rows: whether this L is covered.
 bool can_sort_rows(const dsv_problem &p);
 dsv_status launch_sort_rows(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx, int32_t *out,
-                            hipStream_t st);
+                            uint32_t *bits, hipStream_t st);
 // col[bh, 0 .. L] = exclusive prefix sums of cnt[bh, 0 .. L - 1] for the heads of one table.
 dsv_status launch_col_scan(const int32_t *cnt, int64_t *col, int L, const HeadTable &tab, hipStream_t st);
 
