@@ -260,13 +260,8 @@ struct StepLayout {
     size_t seg, pa, pb, pdelta, hist, order, rowstat, total;
 };
 
-StepLayout step_layout(const dsv_problem &p)
+void place_step(const dsv_problem &p, StepLayout &w)
 {
-    StepLayout w{};
-    w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
-    w.split_dq = split_rows(p, w.plan);
-    w.split_dkdv = split_lists(p, w.plan);
-    if (!w.split_dq && !w.split_dkdv) return w;
     const size_t nbh = (size_t)p.B * p.H;
     const size_t rows = nbh * p.L;
     size_t o = 0;
@@ -278,6 +273,15 @@ StepLayout step_layout(const dsv_problem &p)
     w.order = o; o = align_up(o + rows * w.plan.S * 4, 256);
     w.rowstat = o; o = align_up(o + rows * 8, 256);
     w.total = o;
+}
+
+StepLayout step_layout(const dsv_problem &p)
+{
+    StepLayout w{};
+    w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
+    w.split_dq = split_rows(p, w.plan);
+    w.split_dkdv = split_lists(p, w.plan);
+    if (w.split_dq || w.split_dkdv) place_step(p, w);
     return w;
 }
 
@@ -700,7 +704,10 @@ GroupedSplit grouped_split(char *ws, const GroupedStepLayout &w)
 // The group kernels proper exist for bf16, d = 128 and groups of at most 32 queries.  Every other case (fp32, d = 64,
 // larger cubes) runs the per-query kernels on the queries reordered group by group, with the group index expanded to
 // one row per query: the same results, without the saving.
-bool grouped_native(const dsv_problem &p, const dsv_grouping &g) { return p.dtype == DSV_BF16 && p.d == 128 && group_size(g) <= 32; }
+bool grouped_native(const dsv_problem &p, const dsv_grouping &g)
+{
+    return p.dtype == DSV_BF16 && p.d == 128 && group_size(g) <= 32 && (uint64_t)p.L * (uint64_t)group_size(g) < (1ull << 32);
+}
 
 struct GroupedFwdGeneral {
     size_t qp, op, lsep, idxx, step, step_bytes, total;
@@ -717,6 +724,26 @@ GroupedFwdGeneral grouped_fwd_general(const dsv_problem &p)
     w.idxx = o; o = align_up(o + total_pairs(p) * 4, 256);
     w.step = o; w.step_bytes = fwd_layout(p).total; o += w.step_bytes;
     w.total = o;
+    return w;
+}
+
+// The key-major step of the group kernels' cases: heads by unions or by the per-query sweep on the lists of groups, as the device
+// finds (launch_union_choice), both with the same ranges of queries -- one where 8192 rows hold them all.
+struct GroupedKeyLayout {
+    StepLayout step;
+    size_t use, total;
+};
+GroupedKeyLayout grouped_key_layout(const dsv_problem &p)
+{
+    GroupedKeyLayout w{};
+    w.step.plan = make_split_plan(p, kBwdRangeBytes, true);
+    if ((size_t)p.L <= kMaxRangeRows) {
+        w.step.plan.S = w.step.plan.S_pad = 1;
+        w.step.plan.range_len = p.L;
+    }
+    place_step(p, w.step);
+    w.use = w.step.total;
+    w.total = align_up(w.use + (size_t)p.B * p.H * 4, 256);
     return w;
 }
 
@@ -746,7 +773,7 @@ GroupedBwdLayout grouped_bwd_layout(const dsv_problem &p, const dsv_grouping &g)
     }
     // the dq step's scratch and the dkdv step's are never live together
     w.step = o;
-    w.step_bytes = native ? std::max(grouped_step_layout(p, g, true).total, grouped_dkdv_bytes(p, group_size(g)))
+    w.step_bytes = native ? std::max(grouped_step_layout(p, g, true).total, grouped_key_layout(p).total)
                           : std::max(step_layout(p).total, step_layout(sorted).total);
     o += w.step_bytes;
     w.total = o;
@@ -846,9 +873,22 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
         if (st != DSV_OK) return st;
         if ((st = launch_group_rows(*p, *g, 2, ws + w.dqp, dQ, stream)) != DSV_OK) return st;
     }
-    if (native)
-        return launch_grouped_dkdv(*p, group_size(*g), tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, lsep, deltap,
-                                   ws + w.gop, dK, dV, ws + w.step, stream);
+    if (native) {
+        const int G = group_size(*g);
+        const GroupedKeyLayout kw = grouped_key_layout(*p);
+        const BwdSplitWorkspace b = step_buffers(ws + w.step, kw.step);
+        int32_t *use = reinterpret_cast<int32_t *>(ws + w.step + kw.use);
+        KernelSpan span(DSV_KERNEL_DKDV_SWEEP, stream);  // both forms together
+        st = launch_pack_rowstat(lsep, deltap, b.rowstat, (int64_t)p->B * p->H * p->L, stream);
+        if (st != DSV_OK) return st;
+        st = launch_union_choice(*p, G, tabs.data(), (int)tabs.size(), idx_t_g, col_ptr, use, stream);
+        if (st != DSV_OK) return st;
+        st = launch_grouped_dkdv(*p, G, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, ws + w.gop, dK, dV, kw.step.plan, b,
+                                 use, stream);
+        if (st != DSV_OK) return st;
+        return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, lsep, deltap, ws + w.gop, dK, dV,
+                                     kw.step.plan, b, stream, G, use);
+    }
     // dK, dV step: the per-query key-major sweep on the reordered queries
     st = launch_group_expand(*p, *g, tabs.data(), (int)tabs.size(), idx_g, idx_t_g, col_ptr, nullptr,
                              reinterpret_cast<int32_t *>(ws + w.idxtx), reinterpret_cast<int64_t *>(ws + w.colx), stream);

@@ -283,6 +283,22 @@ constexpr size_t kFwdRangeBytes = 2u << 20;
 constexpr size_t kBwdRangeBytes = 4u << 20;
 constexpr size_t kMaxRangeRows = 8192;  // rows of a range: 8 bytes of row statistics each fit 64 KB of LDS
 
+// A key-major list of GROUPS standing for the per-query list it expands to (queries in group-major order: group g
+// holds queries g G .. g G + G - 1): position pos of the expanded list is entry pos / G of the stored one, times G,
+// plus pos % G.  G = 1: a plain list.  magic = floor(2^32 / G) + 1 divides positions below 2^32 / G exactly.
+struct GroupExpand {
+    int32_t G;
+    uint32_t magic;
+};
+__host__ __device__ __forceinline__ GroupExpand no_expand() { return GroupExpand{1, 0u}; }
+__host__ __forceinline__ GroupExpand make_expand(int G) { return GroupExpand{G, (uint32_t)((1ull << 32) / (uint64_t)G) + 1u}; }
+__device__ __forceinline__ int32_t expanded_entry(const int32_t *__restrict__ list, int pos, const GroupExpand &ge)
+{
+    if (ge.G == 1) return list[pos];
+    const int q = (int)__umulhi((uint32_t)pos, ge.magic);
+    return list[q] * ge.G + (pos - q * ge.G);
+}
+
 struct SplitPlan {
     int range_len;  // keys (queries) per range
     int S;          // ranges
@@ -344,7 +360,11 @@ dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int 
 dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                  const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                  const float *lse, const float *delta, const void *dO, void *dK, void *dV,
-                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st);
+                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G = 1,
+                                 const int32_t *skip = nullptr);
+// expand_G > 1: idxT / col hold lists of groups of expand_G queries (tabs[].off the offsets of those lists); the sweep
+// runs on the per-query lists they stand for.  Needs p.L < 2^32 / expand_G.  skip (device, [B*H], or null): heads that something else has
+// swept, into the partial results (with a single range, into dK and dV); w.rowstat is then filled already.
 
 // Device buffers of the selection.  idx_t == nullptr skips the key-major emission (then jcut, cnt,
 // col may be null as well).
@@ -430,15 +450,15 @@ dsv_status launch_row_segments(const dsv_problem &p, int rows, const HeadTable *
                                const int32_t *index, int32_t *seg, hipStream_t st);
 dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const float *pm, const float *pl_, const float *pacc, void *O,
                                      float *lse, int S, hipStream_t st);
-dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const float *pdk, const float *pdv, void *dK, void *dV, int S,
-                                      hipStream_t st);
 dsv_status launch_pack_rowstat(const float *lse, const float *delta, float2 *out, int64_t n, hipStream_t st);
-// dK, dV of the group kernels' cases (grouped_dkdv.hip): Q, dO, lse, delta in group-major order, lists of groups (tabs built
-// for L / G rows per head); ws: grouped_dkdv_bytes.
-size_t grouped_dkdv_bytes(const dsv_problem &p, int G);
+// dK, dV of the group kernels' cases over unions of lists (grouped_dkdv.hip): Q, dO, w.rowstat in group-major order, lists of groups
+// (tabs built for L / G rows per head).  Heads with use[bh] == 0 are left out.  Writes the partial results of every range, or,
+// with a single range, dK and dV.  launch_union_choice sets use.
+dsv_status launch_union_choice(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
+                               int32_t *use, hipStream_t st);
 dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
-                               const void *V, const int32_t *lists, const int64_t *col, const float *lse, const float *delta,
-                               const void *dO, void *dK, void *dV, char *ws, hipStream_t st);
+                               const void *V, const int32_t *lists, const int64_t *col, const void *dO, void *dK, void *dV,
+                               const SplitPlan &plan, const BwdSplitWorkspace &w, const int32_t *use, hipStream_t st);
 dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const float *pa, const float *pb, const float *pdelta,
                                     const void *O, const void *dO, void *dQ, float *delta, int S, hipStream_t st);
 

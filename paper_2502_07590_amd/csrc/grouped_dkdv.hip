@@ -4,9 +4,9 @@
 // Key-major, and dense where the selection is: a wave owns 16 consecutive keys and walks the UNION of their lists of groups;
 // every group of the union brings its G queries' Q and dO rows once, and all four products of 32 queries x 16 keys run on
 // the matrix cores with a mask for the (group, key) pairs that are not selected.  Neighbouring keys of the token grid are
-// selected by much the same groups -- on spatially smooth inputs the union of 16 keys is 3.2 times a single list, so that
-// a step of 512 (query, key) pairs holds 160 selected ones --, and even with unrelated keys (10 times, at 6 % kept) the
-// matrix cores form the pairs faster than the vector units the selected ones alone.
+// selected by much the same groups: on spatially smooth inputs the union of 16 keys is 3.2 times a single list, so that
+// a step of 512 (query, key) pairs holds 160 selected ones.  Keys chosen independently of their neighbours (10 times at 6 % kept)
+// are better served by the per-query sweep on the lists of groups; union_choice_kernel looks, head by head.
 //
 //   S^T = Q_u K^T, dP^T = dO_u V^T   v_mfma_f32_16x16x32_bf16, A = 16 gathered rows as they come from memory (lane = row
 //        l % 16, channels 32 m + 8 (l / 16): one load instruction touches whole 64-byte sectors), B = the keys' K and V rows,
@@ -18,7 +18,7 @@
 // Work item = (head, query range, 4 x 16 keys): the rows of a range (at most 8192 queries, 4 MB) stay in an XCD's L2, and
 // every XCD walks its ranges one after the other.  A range leaves partial sums for the per-query merge; a single range
 // writes the result.  L = 32768, four heads, k = 2048, 2 x 2 x 2 cubes, smooth inputs: 3.5 ms, with the
-// merge 3.6 (the per-query key-major sweep on the lists written out: 5.75 + 0.45), a sixth of it matrix work: a step is a
+// merge 3.6 (the per-query key-major sweep on the lists of groups: 5.75 + 0.45), a sixth of it matrix work: a step is a
 // chain of loads, LDS, two products and the queue that eight waves per CU only partly hide.  One wave per block instead of
 // four neighbouring ones measured 7 % slower (neighbours share rows in the L1).
 #include <algorithm>
@@ -44,7 +44,7 @@ struct UnionWave {
 static_assert(4 * sizeof(UnionWave) <= 80 * 1024, "two blocks per CU");
 
 struct UnionPlan {
-    int S;             // ranges: 1, 2, 4 or a multiple of 8
+    int S, S_pad;      // ranges, as the gathering sweep has them
     int groups;        // groups per range
     int nkb;           // blocks of 64 keys
 };
@@ -105,13 +105,14 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
                                                               const float2 *__restrict__ rowstat, bf16_t *__restrict__ dK,
                                                               bf16_t *__restrict__ dV, float *__restrict__ pdk,
                                                               float *__restrict__ pdv, int L, int G, float scale, HeadTable tab,
-                                                              UnionPlan pl)
+                                                              UnionPlan pl, const int32_t *__restrict__ use)
 {
     constexpr int D = 128;
     __shared__ __align__(16) UnionWave sh_all[4];
     int slot, range, kb;
-    if (!decode_range_item(pl.S, pl.S, pl.nkb, blockIdx.x, slot, range, kb)) return;
+    if (!decode_range_item(pl.S, pl.S_pad, pl.nkb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
+    if (!use[bh]) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, g4 = lane >> 4;
     UnionWave &sh = sh_all[wave];
@@ -344,51 +345,85 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
     }
 }
 
-// ------------------------------------------------------------------------------------ host
-static UnionPlan union_plan(int L, int G)
+// Whether the keys of a head go by unions: use[bh] = 1 where the union of 16 neighbouring lists, measured on kChoiceSamples blocks of
+// 16 keys (of long lists the groups of one window), is at most 5.5 times a list -- in queries per step, of which a group
+// size that does not divide 32 leaves some unused.  Measured, L = 32768, k = 2048, 2 x 2 x 2, per four heads: union 3.2 times a
+// list: 3.5 ms by unions, 5.8 by the per-query sweep on the lists of groups; 10 times (keys chosen independently): 9.5, 5.6.
+constexpr int kChoiceSamples = 16;
+constexpr int kChoiceGroups = 32768;
+__global__ __launch_bounds__(1024) void union_choice_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col, int L,
+                                                            int G, HeadTable tab, int32_t *__restrict__ use)
 {
-    UnionPlan pl;
-    const int want = (int)((L + kMaxRangeRows - 1) / kMaxRangeRows);  // ranges of at most 8192 queries
-    const int S = want <= 1 ? 1 : want <= 2 ? 2 : want <= 4 ? 4 : (want + 7) / 8 * 8;
-    const int Lq = L / G;
-    pl.S = S;
-    pl.groups = (Lq + S - 1) / S;  // at most 8192 + 32 queries: group numbers inside a range fit 16 bits
-    pl.nkb = (L + 4 * kUnionKeys - 1) / (4 * kUnionKeys);
-    return pl;
+    __shared__ uint32_t bm[kChoiceGroups / 32];  // a word per thread
+    __shared__ int32_t sums[2];                  // entries, groups in the unions
+    const int slot = blockIdx.x, bh = tab.bh[slot];
+    const int Lq = L / G, blocks = (L + kUnionKeys - 1) / kUnionKeys;
+    bm[threadIdx.x] = 0u;
+    if (threadIdx.x < 2) sums[threadIdx.x] = 0;
+    __syncthreads();
+    for (int s = 0; s < kChoiceSamples; ++s) {
+        const int j = (int)((int64_t)s * blocks / kChoiceSamples) * kUnionKeys + (threadIdx.x >> 6);  // 64 threads per key
+        const int w0 = Lq > kChoiceGroups ? (int)((int64_t)(Lq - kChoiceGroups) * s / (kChoiceSamples - 1)) : 0;
+        int entries = 0;
+        if (j < L) {
+            const int64_t *cp = col + (int64_t)bh * (L + 1) + j;
+            const int32_t *list = lists + tab.off[slot] + cp[0];
+            const int n = (int)(cp[1] - cp[0]);
+            int lo = 0, hi = n;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (list[mid] < w0) lo = mid + 1; else hi = mid;
+            }
+            for (int t = lo + (threadIdx.x & 63); t < n; t += 64) {
+                const int e = list[t] - w0;
+                if (e < 0 || e >= kChoiceGroups) break;
+                atomicOr(&bm[e >> 5], 1u << (e & 31));
+                ++entries;
+            }
+        }
+        if (entries) atomicAdd(&sums[0], entries);
+        __syncthreads();
+        const int c = __popc(bm[threadIdx.x]);
+        if (c) atomicAdd(&sums[1], c);
+        bm[threadIdx.x] = 0u;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        const int64_t slots = 32 / G * G;  // queries of a step that are used
+        use[bh] = (int64_t)sums[1] * 16 * 32 * 2 <= 11 * (int64_t)sums[0] * slots;
+    }
 }
 
-size_t grouped_dkdv_bytes(const dsv_problem &p, int G)
+// ------------------------------------------------------------------------------------ host
+dsv_status launch_union_choice(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
+                               int32_t *use, hipStream_t st)
 {
-    const size_t rows = (size_t)p.B * p.H * p.L;
-    const int S = union_plan(p.L, G).S;
-    return align_up(rows * 8, 256) + (S > 1 ? 2 * align_up(rows * S * p.d * 4, 256) : 0);
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL(union_choice_kernel, dim3(tabs[t].n), dim3(1024), 0, st, lists, col, p.L, G, tabs[t], use);
+        DSV_LAUNCH_CHECK();
+    }
+    return DSV_OK;
 }
 
 dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
-                               const void *V, const int32_t *lists, const int64_t *col, const float *lse, const float *delta,
-                               const void *dO, void *dK, void *dV, char *ws, hipStream_t st)
+                               const void *V, const int32_t *lists, const int64_t *col, const void *dO, void *dK, void *dV,
+                               const SplitPlan &plan, const BwdSplitWorkspace &w, const int32_t *use, hipStream_t st)
 {
     if (p.dtype != DSV_BF16 || p.d != 128 || G > 32) return DSV_EUNSUPPORTED;
-    const UnionPlan pl = union_plan(p.L, G);
-    const size_t rows = (size_t)p.B * p.H * p.L;
-    float2 *rowstat = reinterpret_cast<float2 *>(ws);
-    float *pdk = reinterpret_cast<float *>(ws + align_up(rows * 8, 256));
-    float *pdv = reinterpret_cast<float *>(ws + align_up(rows * 8, 256) + align_up(rows * pl.S * p.d * 4, 256));
-    dsv_status rc = launch_pack_rowstat(lse, delta, rowstat, (int64_t)rows, st);
-    if (rc != DSV_OK) return rc;
-    {
-        KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
-        for (int t = 0; t < n_tabs; ++t) {
-            const int64_t blocks = tabs[t].n * range_items(pl.S, pl.nkb);
-            if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
-            hipLaunchKernelGGL(grouped_dkdv_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)Q, (const bf16_t *)K,
-                               (const bf16_t *)V, (const bf16_t *)dO, lists, col, (const float2 *)rowstat, (bf16_t *)dK, (bf16_t *)dV,
-                               pdk, pdv, p.L, G, p.scale, tabs[t], pl);
-            DSV_LAUNCH_CHECK();
-        }
+    UnionPlan pl;
+    pl.S = plan.S;
+    pl.S_pad = plan.S_pad;
+    pl.groups = (p.L / G + pl.S - 1) / pl.S;  // of at most 8192 queries and a group: group numbers inside a range fit 16 bits
+    pl.nkb = (p.L + 4 * kUnionKeys - 1) / (4 * kUnionKeys);
+    for (int t = 0; t < n_tabs; ++t) {
+        const int64_t blocks = tabs[t].n * range_items(pl.S_pad, pl.nkb);
+        if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
+        hipLaunchKernelGGL(grouped_dkdv_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)Q, (const bf16_t *)K,
+                           (const bf16_t *)V, (const bf16_t *)dO, lists, col, (const float2 *)w.rowstat, (bf16_t *)dK, (bf16_t *)dV,
+                           w.pa, w.pb, p.L, G, p.scale, tabs[t], pl, use);
+        DSV_LAUNCH_CHECK();
     }
-    if (pl.S == 1) return DSV_OK;
-    return launch_dkdv_merge_bf16_128(p, pdk, pdv, dK, dV, pl.S, st);
+    return DSV_OK;
 }
 
 }  // namespace dsv

@@ -24,10 +24,12 @@ namespace dsv {
 // from col_ptr), cut by QUERY ranges.
 __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restrict__ index,
                                                           const int64_t *__restrict__ col, int L, HeadTable tab,
-                                                          SplitPlan pl, int32_t *__restrict__ seg)
+                                                          SplitPlan pl, int32_t *__restrict__ seg, GroupExpand ge,
+                                                          const int32_t *__restrict__ skip)
 {
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
+    if (skip && skip[bh]) return;
     const int np = pl.S + 1;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (int64_t)L * np) return;
@@ -38,7 +40,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
     if (col) {
         const int64_t *cp = col + (int64_t)bh * (L + 1);
         base = index + tab.off[slot] + cp[row];
-        len = (int)(cp[row + 1] - cp[row]);
+        len = (int)(cp[row + 1] - cp[row]) * ge.G;  // lists of groups: positions of the expanded list
     } else {
         len = tab.k[slot];
         base = index + tab.off[slot] + (int64_t)row * len;
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
     int lo = 0, hi = len;  // first position with value >= target
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if ((int64_t)base[mid] < target) lo = mid + 1; else hi = mid;
+        if ((int64_t)expanded_entry(base, mid, ge) < target) lo = mid + 1; else hi = mid;
     }
     seg[((int64_t)bh * L + row) * np + s] = lo;
 }
@@ -235,7 +237,8 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
                                                                     const float2 *__restrict__ rowstat,
                                                                     const T *__restrict__ dO, float *__restrict__ pdk,
                                                                     float *__restrict__ pdv, int L, float scale,
-                                                                    HeadTable tab, SplitPlan pl)
+                                                                    HeadTable tab, SplitPlan pl, GroupExpand ge,
+                                                                    const int32_t *__restrict__ skip)
 {
     typedef LaneLayout<T, D, LPR> LL;
     constexpr int CH = D / LPR;
@@ -243,6 +246,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
     int slot, range, kb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
+    if (skip && skip[bh]) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / LPR, s = lane % LPR;
     const int64_t jpos = (int64_t)kb * (4 * RPW) + wave * RPW + grp;
@@ -270,7 +274,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
         __syncthreads();
     }
     dkdv_sweep<T, D, LPR, true>(st, kc, vc, Q + head_base, dO + head_base, nullptr, nullptr, (uint32_t)LL::off(s), list, tb,
-                                te, scale * kLog2e, stage, s, stat_s, q_first);
+                                te, scale * kLog2e, stage, s, stat_s, q_first, ge);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + j) * pl.S + range;
         store_acc<T, D, LPR>(pdk + slot_id * D, s, st.dk);
@@ -282,13 +286,14 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void sparse_bwd_dkdv_merge_kernel(const float *__restrict__ pdk,
                                                                     const float *__restrict__ pdv,
                                                                     T *__restrict__ dK, T *__restrict__ dV,
-                                                                    int64_t n_rows, int S, float scale)
+                                                                    int64_t n_rows, int S, float scale, int L,
+                                                                    const int32_t *__restrict__ skip)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
     const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
-    if (row >= n_rows) return;
+    if (row >= n_rows || (skip && skip[row / L])) return;
     float a[CH], b[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) { a[c] = 0.f; b[c] = 0.f; }
@@ -331,12 +336,14 @@ __device__ __forceinline__ int seg_len(const int32_t *__restrict__ seg, int64_t 
 }
 
 __global__ __launch_bounds__(256) void seglen_hist_kernel(const int32_t *__restrict__ seg, int L, int S, int nbins,
-                                                          HeadTable tab, int32_t *__restrict__ hist)
+                                                          HeadTable tab, int32_t *__restrict__ hist,
+                                                          const int32_t *__restrict__ skip)
 {
     extern __shared__ int32_t lh[];  // [nbins]
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
+    if (skip && skip[bh]) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk;
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -375,12 +382,13 @@ __global__ __launch_bounds__(1024) void seglen_scan_kernel(int32_t *__restrict__
 
 __global__ __launch_bounds__(256) void seglen_scatter_kernel(const int32_t *__restrict__ seg, int L, int S, int nbins,
                                                              HeadTable tab, int32_t *__restrict__ hist,
-                                                             int32_t *__restrict__ order)
+                                                             int32_t *__restrict__ order, const int32_t *__restrict__ skip)
 {
     extern __shared__ int32_t lh[];  // [nbins]: this chunk's count per class, then its next free slot in `order`
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
+    if (skip && skip[bh]) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk, row1 = min(row0 + kSeglenChunk, L);
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -425,12 +433,13 @@ SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes, bool few)
 }
 
 static dsv_status launch_segments(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const SplitPlan &pl,
-                                  const int32_t *index, const int64_t *col, int32_t *seg, hipStream_t st)
+                                  const int32_t *index, const int64_t *col, int32_t *seg, hipStream_t st,
+                                  GroupExpand ge = no_expand(), const int32_t *skip = nullptr)
 {
     const int64_t n = (int64_t)p.L * (pl.S + 1);
     for (int t = 0; t < n_tabs; ++t) {
         dim3 grid((unsigned)((n + 255) / 256), tabs[t].n);
-        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, col, p.L, tabs[t], pl, seg);
+        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, col, p.L, tabs[t], pl, seg, ge, skip);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
@@ -438,7 +447,7 @@ static dsv_status launch_segments(const dsv_problem &p, const HeadTable *tabs, i
 
 // order[bh, r, :] = the rows of the tables' heads by descending segment length in range r (from seg).
 static dsv_status launch_row_order(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const SplitPlan &pl, const int32_t *seg, int32_t *hist,
-                                   int32_t *order, hipStream_t st)
+                                   int32_t *order, hipStream_t st, const int32_t *skip = nullptr)
 {
     const int nbh = p.B * p.H;
     // length classes; longer segments (possible only with ranges above 8192 rows) share the last class
@@ -450,12 +459,12 @@ static dsv_status launch_row_order(const dsv_problem &p, const HeadTable *tabs, 
         const int64_t nblocks = chunks * tabs[t].n * pl.S;
         if (nblocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
         hipLaunchKernelGGL(seglen_hist_kernel, dim3((unsigned)nblocks), dim3(256), (size_t)nbins * 4, st, seg, p.L, pl.S, nbins, tabs[t],
-                           hist);
+                           hist, skip);
     }
     hipLaunchKernelGGL(seglen_scan_kernel, dim3(nbh * pl.S), dim3(1024), 0, st, hist, nbins);
     for (int t = 0; t < n_tabs; ++t)
         hipLaunchKernelGGL(seglen_scatter_kernel, dim3((unsigned)(chunks * tabs[t].n * pl.S)), dim3(256), (size_t)nbins * 4, st, seg, p.L,
-                           pl.S, nbins, tabs[t], hist, order);
+                           pl.S, nbins, tabs[t], hist, order, skip);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -530,15 +539,18 @@ template <typename T, int D>
 static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                    const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                    const float *lse, const float *delta, const void *dO, void *dK, void *dV,
-                                   const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st)
+                                   const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G,
+                                   const int32_t *skip)
 {
     const int nbh = p.B * p.H;
-    dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idxT, col, w.seg, st);
+    if (expand_G < 1 || (uint64_t)p.L * (uint64_t)expand_G >= (1ull << 32)) return DSV_EUNSUPPORTED;
+    const GroupExpand ge = expand_G > 1 ? make_expand(expand_G) : no_expand();
+    dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idxT, col, w.seg, st, ge, skip);
     if (rc != DSV_OK) return rc;
     const int64_t nrows = (int64_t)nbh * p.L;
-    rc = launch_pack_rowstat(lse, delta, w.rowstat, nrows, st);
+    if (!skip) rc = launch_pack_rowstat(lse, delta, w.rowstat, nrows, st);
     if (rc != DSV_OK) return rc;
-    rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st);
+    rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st, skip);
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
@@ -553,13 +565,13 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
                                               (int)(kMaxRangeRows * sizeof(float2))));
             hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), stat_bytes, st, (const T *)Q, (const T *)K,
                                (const T *)V, idxT, col, w.seg, w.order, (const float2 *)w.rowstat, (const T *)dO, w.pa, w.pb,
-                               p.L, p.scale, tabs[t], lp);
+                               p.L, p.scale, tabs[t], lp, ge, skip);
             DSV_LAUNCH_CHECK();
         }
     }
     const int64_t n_rows = (int64_t)p.B * p.H * p.L;
     hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st,
-                       w.pa, w.pb, (T *)dK, (T *)dV, n_rows, pl.S, p.scale);
+                       w.pa, w.pb, (T *)dK, (T *)dV, n_rows, pl.S, p.scale, p.L, pl.S > 1 ? nullptr : skip);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
@@ -572,7 +584,8 @@ dsv_status launch_row_segments(const dsv_problem &p, int rows, const HeadTable *
     const int64_t n = (int64_t)rows * (pl.S + 1);
     for (int t = 0; t < n_tabs; ++t) {
         dim3 grid((unsigned)((n + 255) / 256), tabs[t].n);
-        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, (const int64_t *)nullptr, rows, tabs[t], pl, seg);
+        hipLaunchKernelGGL(segment_ptr_kernel, grid, dim3(256), 0, st, index, (const int64_t *)nullptr, rows, tabs[t], pl, seg,
+                           no_expand(), (const int32_t *)nullptr);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
@@ -587,16 +600,6 @@ dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs
                            (bf16_t *)O, lse, p.L, tabs[t], S);
         DSV_LAUNCH_CHECK();
     }
-    return DSV_OK;
-}
-
-dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const float *pdk, const float *pdv, void *dK, void *dV, int S,
-                                      hipStream_t st)
-{
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<bf16_t, 128>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, pdk, pdv,
-                       (bf16_t *)dK, (bf16_t *)dV, n_rows, S, p.scale);
-    DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
 
@@ -639,9 +642,10 @@ dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int 
 dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                  const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                  const float *lse, const float *delta, const void *dO, void *dK, void *dV,
-                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st)
+                                 const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G,
+                                 const int32_t *skip)
 {
-    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st);
+    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st, expand_G, skip);
 }
 
 }  // namespace dsv

@@ -12,22 +12,24 @@ import paper_2502_07590_amd as dsv
 pytestmark = pytest.mark.gpu
 
 
+# keys that neighbours share (every head goes by unions of lists), that they do not (by the per-query sweep), one head of each;
 # cubes of 1, 2, 3, 8, 12 and 32 queries; 1, 2, 4 and 8 ranges; more than one window of groups; keys nobody selects
 @pytest.mark.parametrize("grid,cube,ks", [((1, 1, 17), (1, 1, 1), [5]), ((3, 5, 7), (3, 1, 1), [1, 40]), ((2, 6, 30), (2, 1, 1), [77]),
                                           ((4, 48, 48), (1, 3, 4), [300, 64]), ((8, 32, 48), (2, 2, 2), [700]), ((4, 72, 72), (2, 1, 1), [90]),
                                           ((8, 64, 72), (2, 4, 4), [500])])
-def test_grouped_gradients_of_keys_and_values(grid, cube, ks):
+@pytest.mark.parametrize("near", [(True, True), (False, False), (True, False)])
+def test_grouped_gradients_of_keys_and_values(grid, cube, ks, near):
     L, G, H = math.prod(grid), math.prod(cube), len(ks)
     (F, Hh, Ww), (gf, gh, gw) = grid, cube
     g = torch.Generator(device="cuda").manual_seed(L)
     Q, K, V, dO = (torch.randn(1, H, L, 128, generator=g, device="cuda").bfloat16() for _ in range(4))
     tokens = torch.arange(L, device="cuda").reshape(F // gf, gf, Hh // gh, gh, Ww // gw, gw).permute(0, 2, 4, 1, 3, 5).reshape(-1, G)
     idx_g, idx, lists, cols = [], [], [], []
-    for k in ks:
-        # evenly spread from a start of the group's own, never the last 7 keys (L > 8): distinct, lists of uneven length
+    for h, k in enumerate(ks):
+        # evenly spread, or one after the other, from a start of the group's own, never the last 7 keys (L > 8): distinct, lists of uneven length
         n = max(L - 7, k)
         first = (torch.rand(L // G, 1, generator=g, device="cuda") ** 2 * n).long()
-        rows = ((first + torch.arange(k, device="cuda")[None] * (n // k)) % n).sort(1).values
+        rows = ((first + torch.arange(k, device="cuda")[None] * (1 if near[h] else n // k)) % n).sort(1).values
         rows = rows.to(torch.int32)
         full = torch.empty(L, k, dtype=torch.int32, device="cuda")
         full[tokens.reshape(-1)] = rows.repeat_interleave(G, 0)
