@@ -349,57 +349,64 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
 // 16 keys (of long lists the groups of one window), is at most 5.5 times a list -- in queries per step, of which a group
 // size that does not divide 32 leaves some unused.  Measured, L = 32768, k = 2048, 2 x 2 x 2, per four heads: union 3.2 times a
 // list: 3.5 ms by unions, 5.8 by the per-query sweep on the lists of groups; 10 times (keys chosen independently): 9.5, 5.6.
+// A wave per sample, four lanes per key.
 constexpr int kChoiceSamples = 16;
-constexpr int kChoiceGroups = 32768;
-__global__ __launch_bounds__(1024) void union_choice_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col, int L,
-                                                            int G, HeadTable tab, int32_t *__restrict__ use)
+constexpr int kChoiceGroups = 8192;
+__global__ __launch_bounds__(64 * kChoiceSamples) void union_choice_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col,
+                                                                           int L, int G, HeadTable tab, int32_t *__restrict__ use)
 {
-    __shared__ uint32_t bm[kChoiceGroups / 32];  // a word per thread
-    __shared__ int32_t sums[2];                  // entries, groups in the unions
+    __shared__ uint32_t bm_all[kChoiceSamples][kChoiceGroups / 32];
+    __shared__ int32_t sums[2];  // entries, groups in the unions
     const int slot = blockIdx.x, bh = tab.bh[slot];
+    const int lane = threadIdx.x & 63, sample = threadIdx.x >> 6;
     const int Lq = L / G, blocks = (L + kUnionKeys - 1) / kUnionKeys;
-    bm[threadIdx.x] = 0u;
+    uint32_t *bm = bm_all[sample];
+    for (int w = lane; w < kChoiceGroups / 32; w += 64) bm[w] = 0u;
     if (threadIdx.x < 2) sums[threadIdx.x] = 0;
     __syncthreads();
-    for (int s = 0; s < kChoiceSamples; ++s) {
-        const int j = (int)((int64_t)s * blocks / kChoiceSamples) * kUnionKeys + (threadIdx.x >> 6);  // 64 threads per key
-        const int w0 = Lq > kChoiceGroups ? (int)((int64_t)(Lq - kChoiceGroups) * s / (kChoiceSamples - 1)) : 0;
-        int entries = 0;
-        if (j < L) {
-            const int64_t *cp = col + (int64_t)bh * (L + 1) + j;
-            const int32_t *list = lists + tab.off[slot] + cp[0];
-            const int n = (int)(cp[1] - cp[0]);
-            int lo = 0, hi = n;
-            while (lo < hi) {
+    const int j = (int)((int64_t)sample * blocks / kChoiceSamples) * kUnionKeys + (lane >> 2);
+    const int w0 = Lq > kChoiceGroups ? (int)((int64_t)(Lq - kChoiceGroups) * sample / (kChoiceSamples - 1)) : 0;
+    int entries = 0;
+    if (j < L) {
+        const int64_t *cp = col + (int64_t)bh * (L + 1) + j;
+        const int32_t *list = lists + tab.off[slot] + cp[0];
+        const int n = (int)(cp[1] - cp[0]);
+        int lo = 0;
+        if (w0 > 0)
+            for (int hi = n; lo < hi;) {
                 const int mid = (lo + hi) >> 1;
                 if (list[mid] < w0) lo = mid + 1; else hi = mid;
             }
-            for (int t = lo + (threadIdx.x & 63); t < n; t += 64) {
-                const int e = list[t] - w0;
-                if (e < 0 || e >= kChoiceGroups) break;
-                atomicOr(&bm[e >> 5], 1u << (e & 31));
-                ++entries;
-            }
+        for (int t = lo + (lane & 3); t < n; t += 32) {
+            int e[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) e[u] = list[min(t + 4 * u, n - 1)] - w0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (t + 4 * u < n && e[u] >= 0 && e[u] < kChoiceGroups) {
+                    atomicOr(&bm[e[u] >> 5], 1u << (e[u] & 31));
+                    ++entries;
+                }
+            if (e[7] >= kChoiceGroups) break;  // ascending
         }
-        if (entries) atomicAdd(&sums[0], entries);
-        __syncthreads();
-        const int c = __popc(bm[threadIdx.x]);
-        if (c) atomicAdd(&sums[1], c);
-        bm[threadIdx.x] = 0u;
-        __syncthreads();
     }
+    union_sync();
+    int groups = 0;
+    for (int w = lane; w < kChoiceGroups / 32; w += 64) groups += __popc(bm[w]);
+    if (entries) atomicAdd(&sums[0], entries);
+    if (groups) atomicAdd(&sums[1], groups);
+    __syncthreads();
     if (threadIdx.x == 0) {
         const int64_t slots = 32 / G * G;  // queries of a step that are used
         use[bh] = (int64_t)sums[1] * 16 * 32 * 2 <= 11 * (int64_t)sums[0] * slots;
     }
 }
 
-// ------------------------------------------------------------------------------------ host
 dsv_status launch_union_choice(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
                                int32_t *use, hipStream_t st)
 {
     for (int t = 0; t < n_tabs; ++t) {
-        hipLaunchKernelGGL(union_choice_kernel, dim3(tabs[t].n), dim3(1024), 0, st, lists, col, p.L, G, tabs[t], use);
+        hipLaunchKernelGGL(union_choice_kernel, dim3(tabs[t].n), dim3(64 * kChoiceSamples), 0, st, lists, col, p.L, G, tabs[t], use);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
