@@ -32,11 +32,11 @@ VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9   # 256 CUs x 64 fp32 lanes x 2.4 GHz, on
 # (FETCH_SIZE reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0), and the L2 hit rate from
 # TCC_HIT_sum / (TCC_HIT_sum + TCC_MISS_sum).  Source: profiles/config2_pmc_counters.md.  The figures belong to ONE
 # build of the kernels: they are reported only while the library still names that version.
-PMC_LIBRARY_VERSION = "dsv 0.4 (gfx950)"
+PMC_LIBRARY_VERSION = "dsv 0.5 (gfx950)"
 PMC_CONFIG2 = {
-    "sparse_attn_fwd": {"fetch_kib": 31042322, "write_kib": 14155844, "l2_hit_rate": 0.9693},
-    "sparse_attn_bwd_dq": {"fetch_kib": 48468979, "write_kib": 12976401, "l2_hit_rate": 0.9644},
-    "sparse_attn_bwd_dkdv": {"fetch_kib": 33568648, "write_kib": 12582918, "l2_hit_rate": 0.9739},
+    "sparse_attn_fwd": {"fetch_kib": 85484433, "write_kib": 12786373, "l2_hit_rate": 0.7156},  # mask and dense tiles
+    "sparse_attn_bwd_dq": {"fetch_kib": 48450877, "write_kib": 12976385, "l2_hit_rate": 0.9644},
+    "sparse_attn_bwd_dkdv": {"fetch_kib": 33413195, "write_kib": 12582914, "l2_hit_rate": 0.9740},
 }
 # the gather sweep inside each stage-2 call (the kernel the roofline object is about)
 SWEEP_OF_CALL = {"sparse_attn_fwd": "fwd_sweep", "sparse_attn_bwd_dq": "dq_sweep", "sparse_attn_bwd_dkdv": "dkdv_sweep"}
@@ -350,8 +350,8 @@ def predictor_report(dsv, torch, cfg, ks, g, Wq, Wk):
                                "note": "one pass over K (Gram matrix K^T K), the rest is [d, d] / [d, r] algebra in fp64",
                                "k_bytes": k_bytes},
             "profile_sparsity": {"ms": round(ms[1], 3), "sparsity_per_head": [round(float(x), 4) for x in res["prof"][0].tolist()],
-                                 "scores_per_sweep": n_scores, "sweeps": 5,
-                                 "mfma_tflops": round(5 * 2.0 * cfg.d * n_scores / (ms[1] * 1e-3) / 1e12, 1)}}
+                                 "scores_per_sweep": n_scores, "sweeps": 3,
+                                 "mfma_tflops": round(3 * 2.0 * cfg.d * n_scores / (ms[1] * 1e-3) / 1e12, 1)}}
 
 
 def grouping_accuracy(dsv, torch, np, wl, cfg, seed):

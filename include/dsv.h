@@ -145,7 +145,7 @@ DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, cons
  * and the results are identical, bit for bit, to dsv_sparse_attn_bwd_t on dsv_idx_transpose's output and from run to
  * run.  Without DSV_FLAG_SORTED_INDEX the rows of larger problems are first copied in ascending order (same workspace), so
  * that the dq step is L2-blocked as well; the result is then that of the ascending rows.  Building the transposed index is a
- * tenth of the call (L = 20280, four heads keeping 507 .. 4056 keys: 0.75 ms of 7.8); callers that run stage 1 here can take
+ * tenth of the call (L = 20280, four heads keeping 507 .. 4056 keys: 0.55 ms of 7.6); callers that run stage 1 here can take
  * its transposed index (dsv_lowrank_topk_t) and call dsv_sparse_attn_bwd_t. */
 DSV_API size_t dsv_sparse_attn_bwd_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *K, const void *V,
@@ -225,8 +225,8 @@ DSV_API dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q,
  *   workspace (segment pointers, per-range partials); without the flag the group kernels need none (the
  *   query returns 0).
  * dsv_sparse_attn_bwd_grouped: gradients of the above (selection held constant).  dQ group by group with
- *   the forward's tiling (K and V rows gathered once per group); dK and dV key tile by key tile over the union of 16
- *   keys' lists of groups, on queries reordered group by group: the workspace holds the reordered Q, dO, lse, Delta
+ *   the forward's tiling (K and V rows gathered once per group); dK and dV on queries reordered group by group,
+ *   16 keys at a time over the union of their lists of groups where neighbouring keys share them, else key by key: the workspace holds the reordered Q, dO, lse, Delta
  *   besides the steps' scratch.  Needs idx_t_g and col_ptr.  The flag selects the L2-blocked dQ step as in the forward.
  *   Cases outside bf16, d = 128, G <= 32: the per-query kernels as described for the forward, with the per-query form of
  *   both indices in the workspace. */
