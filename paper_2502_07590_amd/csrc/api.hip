@@ -737,7 +737,7 @@ GroupedKeyLayout grouped_key_layout(const dsv_problem &p)
 {
     GroupedKeyLayout w{};
     w.step.plan = make_split_plan(p, kBwdRangeBytes, true);
-    if ((size_t)p.L <= kMaxRangeRows) {
+    if ((size_t)p.L <= kMaxRangeRows && row_blocks(p) >= kFewRangesBlocks) {
         w.step.plan.S = w.step.plan.S_pad = 1;
         w.step.plan.range_len = p.L;
     }

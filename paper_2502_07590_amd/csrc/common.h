@@ -306,6 +306,8 @@ struct SplitPlan {
     int nqb;        // row blocks per range (each kernel sets it from its own rows per block)
 };
 SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes, bool few);
+constexpr int64_t kFewRangesBlocks = 4096;
+__host__ __forceinline__ int64_t row_blocks(const dsv_problem &p) { return (int64_t)p.B * p.H * ((p.L + 63) / 64); }
 
 // Work items (row block, range) of a head: linear id -> range and row block, consecutive ids on consecutive XCDs.  Eight ranges or
 // more: an XCD (one of eight) walks the blocks of its own ranges one range after the other.  One, two or four: the XCDs that
