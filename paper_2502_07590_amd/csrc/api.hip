@@ -132,11 +132,11 @@ int64_t mean_k(const dsv_problem &p)
     return s / p.H;
 }
 
-// Whether sequences of less than eight full ranges are cut in two or four instead of eight: every range leaves partial results,
-// segment pointers and a row order, smaller ones stay in the L2 with the index that streams past them.  Measured, bf16, d = 128, four
-// heads, eight ranges against two or four: dkdv at L = 8192, k = 512: 496 : 415 us; 12000, k = 750: 946 : 832; 16000, k = 160: 539 : 346;
-// 32768, k = 327: 1598 : 1365, k = 1000: 3294 : 3119 and dq 2899 : 2692; on lists as stage 1 makes them, 32768, k = 2048, the whole backward
-// 11284 : 11302; 20280, k = 507 .. 4056: 7641 : 7725.
+// Whether sequences of less than eight full ranges are cut in two or four instead of eight, given blocks enough (make_split_plan):
+// every range leaves partial results, segment pointers and a row order, smaller ones stay in the L2 with the index that
+// streams past them.  Measured, bf16, d = 128, four heads, eight ranges against four: dkdv at L = 32768, k = 327: 1598 : 1365 us,
+// k = 1000: 3294 : 3119 and dq 2899 : 2692; on lists as stage 1 makes them, 32768, k = 2048, the whole backward 11284 : 11302; 20280,
+// k = 507 .. 4056: 7641 : 7725.
 bool few_ranges(const dsv_problem &p) { return mean_k(p) <= 1280; }
 
 // Whether the per-query forward and dq step run L2-blocked: sorted indices promised, and enough to gather from enough rows.
@@ -153,13 +153,12 @@ bool split_rows(const dsv_problem &p, const SplitPlan &pl)
 }
 
 // The same for the key-major step, whose lists differ in length: the blocked form also sorts them by it, the other one gives
-// every list a wave.  Blocked against not, us, lists of even length: L = 4096, k = 40: 72 : 47, k = 256: 155 : 134, k = 819: 338 : 360;
-// 8192, k = 81: 135 : 128, k = 512: 410 : 521; 12000, k = 120: 217 : 259, k = 750: 833 : 1179; 16384, k = 160: 349 : 458; lists as stage 1
-// makes them: 4096, k = 819: 489 : 428; 8192, k = 512: 707 : 717; 16384, k = 1000: 2012 : 3004; three heads of 6000, d = 64 (1.5 MB),
-// k = 600: 371 : 222; one of 4096, k = 256, even: 103 : 38.
+// every list a wave.  Blocked (eight ranges) against not, us, bf16, d = 128, lists as stage 1 makes them: four heads of 2048, k = 200:
+// 102 : 82, k = 500: 155 : 146; 4096, k = 150: 160 : 139, k = 400: 240 : 260, k = 819: 357 : 431; 8192, k = 200: 334 : 370, k = 512:
+// 512 : 721; 16384, k = 1000: 1619 : 3004; one head of 4096, k = 256: 105 : 74; three of 6000, d = 64, k = 200: 157 : 101, k = 600: 221 : 222.
 bool split_lists(const dsv_problem &p, const SplitPlan &pl)
 {
-    return use_split(p, pl) && kv_bytes(p) > ((size_t)3 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
+    return use_split(p, pl) && kv_bytes(p) > ((size_t)1 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
 }
 
 // Whether a whole backward on rows in any order sorts them first, so that the dq step runs L2-blocked: once a head's K and
