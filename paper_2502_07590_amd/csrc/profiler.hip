@@ -171,7 +171,8 @@ __global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_kernel(cons
     }
     const float m2 = sh.m2[nq], rz = sh.rz[nq], least = sh.lo[nq], span = sh.hi[nq] - least;
     const float per = span > 0.f ? 0x1p32f / span : 0.f;
-    const unsigned long long want = (unsigned long long)((double)target * 0x1p38);
+    // at least one unit: a target below 2^-38 is met by the most probable key (nothing would reach a target of zero)
+    const unsigned long long want = max((unsigned long long)((double)target * 0x1p38), 1ull);
     auto mass = [&](float x) { return count_and_mass(__builtin_amdgcn_exp2f(x * c2 - m2) * rz); };
     // the score's place between the smallest and the largest, in 2^-32 (not a number: 0), or its order-preserving pattern
     auto code = [&](float x, bool pattern) {

@@ -52,3 +52,18 @@ def test_counts_in_crowded_bins(noise):
     want, prob = _counts(Q[0, 0][rows.long()], K[0, 0], p.scale, 0.9)
     edge = torch.gather(prob, 1, (want[:, None] - 1)).squeeze(1)
     assert ((counts[0].long() - want).abs() <= torch.ceil(8e-6 / edge).clamp_min(1)).all()  # as above
+
+
+# targets below one unit of the counters (2^-38), and of a few units: the most probable key holds that much; without ties, one
+@pytest.mark.parametrize("mass", [1e-30, 1e-12, 3.6e-12, 1e-11])
+@pytest.mark.parametrize("dtype,d,L", [("bf16", 128, 1000), ("f32", 64, 33), ("f32", 128, 4097)])
+def test_a_tiny_mass_needs_one_key(mass, dtype, d, L):
+    n = 33
+    g = torch.Generator(device="cuda").manual_seed(L)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(1, 2, L, d, generator=g, device="cuda").to(td) for _ in range(2))
+    rows = torch.randperm(L, generator=g, device="cuda")[:n].to(torch.int32)
+    p = dsv.Problem(1, 2, L, d, 16, dtype, [1, 1], 1.0 / d ** 0.5)
+    sparsity, counts = dsv.profile_sparsity(p, Q, K, rows, mass=mass)
+    assert (counts == 1).all()
+    assert torch.allclose(sparsity.double(), torch.full((2,), 1 - 1 / L, dtype=torch.float64, device="cuda"), atol=1e-6)
