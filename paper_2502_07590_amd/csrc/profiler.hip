@@ -220,7 +220,8 @@ __global__ __launch_bounds__((64 * ProfWaves<T, D>::n)) void profile_kernel(cons
         const float p = __builtin_amdgcn_exp2f(x * c2 - m2) * rz;
         const float missing = (float)((double)(want > mass_of(over) ? want - mass_of(over) : 0ull) * 0x1p-38);
         const int need = p > 0.f ? (int)fminf(ceilf(missing / p), (float)same) : same;
-        *out = count_of(over) + min(max(need, 1), same);
+        // the total may fall short of a target next to 1: then every key counts, and no more
+        *out = min(count_of(over) + min(max(need, 1), same), L);
     };
     if (pattern) {  // every key of the bin has the score that `pre` decodes to
         if (threadIdx.x < 32 && mine) write(key_score(pre), above, max(count, 1));

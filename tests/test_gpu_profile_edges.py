@@ -67,3 +67,19 @@ def test_a_tiny_mass_needs_one_key(mass, dtype, d, L):
     sparsity, counts = dsv.profile_sparsity(p, Q, K, rows, mass=mass)
     assert (counts == 1).all()
     assert torch.allclose(sparsity.double(), torch.full((2,), 1 - 1 / L, dtype=torch.float64, device="cuda"), atol=1e-6)
+
+
+# a target next to 1, most of the keys alike and hardly probable: where the fp32 sum of all probabilities is short of the
+# target, every key counts
+def test_a_mass_next_to_one_counts_no_key_twice():
+    L, d, n, mass = 6000, 64, 64, 1 - 2.0 ** -24
+    g = torch.Generator(device="cuda").manual_seed(5)
+    u = torch.nn.functional.normalize(torch.randn(d, generator=g, device="cuda"), dim=0)
+    Q = (1 + torch.rand(1, 1, L, 1, generator=g, device="cuda")) * u
+    K = torch.randn(1, 1, L, d, generator=g, device="cuda")
+    K[0, 0, 100:5500] = -4 * u
+    rows = torch.arange(n, dtype=torch.int32, device="cuda")
+    p = dsv.Problem(1, 1, L, d, 16, "f32", [1], 1.0)
+    _, counts = dsv.profile_sparsity(p, Q, K, rows, mass=mass)
+    least, _ = _counts(Q[0, 0, :n], K[0, 0], p.scale, mass - 8e-6)  # the bound on the cumulative mass above
+    assert (counts[0] <= L).all() and (counts[0] >= least).all()
