@@ -173,15 +173,15 @@ bool sort_rows_first(const dsv_problem &p)
 // Smallest k whose heads run the forward over dense tiles with a mask (dense.hip), INT32_MAX if none should.  (The mask needs
 // a workspace, which calls without the flag do not have.)
 // Costs measured on bf16, in us.  Gathering: 18.5e-6 per pair at d = 128, 10.4e-6 at d = 64, once the chip is full.  Dense: per
-// 64-key tile a round of blocks takes 1.6 (1.2) with at most one block of 128 queries per CU and 2.5 (2.1) when the CUs
+// 64-key tile a round of blocks takes 2.0 (1.45) with at most one block of 128 queries per CU and 2.9 (2.5) when the CUs
 // hold two (three), and a last round that is partly empty costs a fifth of a full one.  Estimated and measured, d = 128:
-// 12 heads of 2048, 51 : 71; 4 of 4096, 102 : 116; 1 of 8192, 205 : 202; 12 of 8192, 544 : 580; 4 of 16384, 768 : 755; 4 of 32768,
-// 2816 : 2900; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.
+// 12 heads of 2048, 64 : 81; 4 of 4096, 128 : 131; 1 of 8192, 256 : 237; 12 of 8192, 631 : 685; 4 of 16384, 891 : 870; 4 of 32768,
+// 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.
 int32_t dense_fwd_min_k(const dsv_problem &p)
 {
     if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
     const bool wide = p.d == 128;
-    const double pair = wide ? 18.5e-6 : 10.4e-6, light = wide ? 1.6 : 1.2, full = wide ? 2.5 : 2.1, slots = wide ? 512 : 768;
+    const double pair = wide ? 18.5e-6 : 10.4e-6, light = wide ? 2.0 : 1.45, full = wide ? 2.9 : 2.5, slots = wide ? 512 : 768;
     std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
     std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
     int32_t best_k = INT32_MAX;
@@ -232,7 +232,7 @@ struct FwdLayout {
 FwdLayout fwd_layout(const dsv_problem &p)
 {
     FwdLayout w{};
-    w.plan = make_split_plan(p, kFwdRangeBytes, few_ranges(p));
+    w.plan = make_split_plan(p, kFwdRangeBytes, false);  // every range brings a maximum of its own (stage2_core.h)
     w.split = split_rows(p, w.plan);
     w.dense_k = dense_fwd_min_k(p);
     int dense = 0;

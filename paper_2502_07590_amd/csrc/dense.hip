@@ -2,9 +2,9 @@
 // bf16: the same sums as the gathering kernels, for heads that keep enough of their keys.
 //
 // A gathered (query, key) pair costs 18.5 ps at d = 128 -- 512 bytes through the vector memory path, whatever the density --;
-// a pair of a dense tile costs 0.6 ps on the matrix cores, selected or not, because the tile's K and V rows cross that path
-// once for 128 queries.  So from about one key in 27 on it is cheaper to form every pair and mask the others out (the
-// rule, with the sizes that fill the chip, stands with dense_fwd_min_k).  L = 32768, four heads, k = 2048: 4.92 -> 2.85 ms,
+// a pair of a dense tile costs 0.7 ps on the matrix cores, selected or not, because the tile's K and V rows cross that path
+// once for 128 queries.  So from about one key in 25 on it is cheaper to form every pair and mask the others out (the
+// rule, with the sizes that fill the chip, stands with dense_fwd_min_k).  L = 32768, four heads, k = 2048: 4.92 -> 3.40 ms,
 // 0.4 of them the mask.
 // The mask is a bit matrix [queries, keys] built from the index rows (bits_build_kernel: any order), some queries at a time.
 //
@@ -13,10 +13,11 @@
 //                     lane; the two lanes of a query only meet when its maximum moves.
 //   O^T += V^T P^T    B = the probabilities, which those lanes hold in the B layout already (which keys a lane group
 //                     contracts is free: 16 s + 4 half + e % 4 + 8 (e / 4)), A = V transposed out of LDS (tr_frag).
-// The running maximum follows every tile, so that a query's largest probability is exactly 1 in bf16: letting it lag by up
-// to 2^8 saves 2 % of the time and costs a quarter of the accuracy (2.1e-3 instead of 1.75e-3 from the 64-bit result).
-// Per 64 keys and wave: 1024 clocks of matrix work beside 1150 of vector work, half of those the exponentials; measured,
-// the two add up to 96 % of the time at 1.9 GHz: two waves per SIMD overlap them little.
+//                     The probabilities go in as bf16 head and tail, 16 significant bits: the result is then as far from the
+//                     64-bit one as its rounding to bf16 puts it (1.66e-3).  One bf16 word saves a fifth of the time
+//                     (2.85 ms) and leaves 1.74e-3, further off than the gathering kernels over ranges (1.68e-3).
+// Per 64 keys and wave: 1536 clocks of matrix work beside about 1450 of vector work, a third of those the exponentials: two waves
+// per SIMD overlap them little (the sum, at the 2 GHz that such work runs at, is the time measured).
 #include <algorithm>
 
 #include "stage2_core.h"
@@ -161,12 +162,17 @@ __global__ __launch_bounds__(256, 2) void dense_fwd_kernel(const bf16_t *__restr
 #pragma unroll
                 for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(s[t][8 * h + e], c2, -mc));
                 l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-                const uint4 pw = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
-                const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, pw);
+                const SplitWeights w0 = split_weights(p[0], p[1]), w1 = split_weights(p[2], p[3]);
+                const SplitWeights w2 = split_weights(p[4], p[5]), w3 = split_weights(p[6], p[7]);
+                const bf16x8_t ph = __builtin_bit_cast(bf16x8_t, make_uint4(w0.head, w1.head, w2.head, w3.head));
+                const bf16x8_t pt = __builtin_bit_cast(bf16x8_t, make_uint4(w0.tail, w1.tail, w2.tail, w3.tail));
                 const unsigned char *v0 = vt + va + (32 * t + 16 * h) * VP;
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(v0 + nb * 64, v0 + 8 * VP + nb * 64), pf, o[nb], 0, 0, 0);
+                for (int nb = 0; nb < NB; ++nb) {
+                    const bf16x8_t vf = tr_frag(v0 + nb * 64, v0 + 8 * VP + nb * 64);
+                    o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pt, o[nb], 0, 0, 0);
+                    o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, ph, o[nb], 0, 0, 0);
+                }
             }
     }
     l += __shfl_xor(l, 32);

@@ -199,8 +199,8 @@ __global__ void group_overlap_finish_kernel(const unsigned long long *__restrict
 // Both products of a tile run on the matrix cores.
 //   S = Q_g K^T   v_mfma_f32_32x32x16_bf16 per 16 channels: A = the group's query rows (rows >= G zero), B = the 32
 //                 gathered K rows (lane = key, 8 channels), read from the rows parked in LDS.
-//   O += P V      v_mfma_f32_16x16x32_bf16 per 16 channels: A = P (rows = queries, rows >= 8 zero), B = V with the
-//                 contraction over the tile's 32 keys.  A B fragment holds, per lane, 8 KEYS of one channel -- the
+//   O += P V      v_mfma_f32_16x16x32_bf16 per 16 channels: A = P (rows 0..7 = bf16 heads of the probabilities, rows
+//                 8..15 = their tails, which makes 16 significant bits), B = V with the contraction over the tile's 32 keys.  A B fragment holds, per lane, 8 KEYS of one channel -- the
 //                 transpose of how a gathered row arrives -- so the tile's V rows are parked row-major in LDS and
 //                 read back with transposing LDS reads (tr_frag below).  Which keys a lane group contracts is
 //                 free as long as A and B agree (fwd_key below); P is stored with each group's keys contiguous,
@@ -216,6 +216,13 @@ constexpr int kVRow = 128 * 2 + 16;  // bytes from one parked row to the next
 // (272-byte rows).  p_slot: place of key n in a row of P, where the 8 keys of a lane group are contiguous.
 __device__ __forceinline__ int fwd_key(int g, int e) { return 16 * (e >> 2) + 2 * (4 * (g & 1) + (e & 3)) + (g >> 1); }
 __device__ __forceinline__ int p_slot(int n) { return 16 * (n & 1) + 8 * ((n >> 3) & 1) + 4 * (n >> 4) + ((n >> 1) & 3); }
+
+// x = head + tail as two bf16 values (head = x rounded to bf16, tail = the rounded remainder)
+__device__ __forceinline__ void split_bf16(float x, uint16_t &hi, uint16_t &lo)
+{
+    hi = f32_to_bf16(x);
+    lo = f32_to_bf16(x - __uint_as_float((uint32_t)hi << 16));
+}
 
 // NSUB = 1: the four waves of a block take four groups of at most 8 queries.  NSUB = 2 / 4: ONE group of up to 16 / 32
 // queries per block of NSUB waves, wave w taking members 8 w .. 8 w + 7; the waves gather the tile's rows together (two load instructions
@@ -267,7 +274,7 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
     __shared__ __align__(16) uint32_t p_all[4][16 * 16 + 8];
     unsigned char *K_s = k_all[NSUB == 1 ? wave : 0];                        // the tile's 32 K rows, row-major
     unsigned char *V_s = v_all[NSUB == 1 ? wave : 0];                        // the tile's 32 V rows
-    u32_alias *P_s = p_all[wave];                                            // [16 rows][32 key slots] bf16, rows 8.. zero
+    u32_alias *P_s = p_all[wave];                                            // [16 rows][32 key slots] bf16: heads, tails
     f32_alias *fac_s = reinterpret_cast<f32_alias *>(p_all[wave] + 16 * 16);  // [8 queries]
     for (int e = lane; e < 16 * 16; e += 64) P_s[e] = 0u;
 
@@ -285,7 +292,7 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
     float M[4], lsum[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) { M[v] = -INFINITY; lsum[v] = 0.f; }
-    floatx4_t oacc[NM];  // oacc[nb][v]: query 4 * g4 + v (lane groups 0 and 1), channel 16 nb + c16
+    floatx4_t oacc[NM];  // oacc[nb][v]: query 4 * g4 + v (lane groups 0 and 1; its tails in 2 and 3), channel 16 nb + c16
 #pragma unroll
     for (int nb = 0; nb < NM; ++nb) oacc[nb] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     const float c2 = scale * kLog2e;
@@ -356,7 +363,12 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
         }
         moved = __any(moved);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) reinterpret_cast<u16_alias *>(P_s)[(4 * half + v) * 32 + pslot] = f32_to_bf16(p[v]);
+        for (int v = 0; v < 4; ++v) {
+            uint16_t hi, lo;
+            split_bf16(p[v], hi, lo);
+            reinterpret_cast<u16_alias *>(P_s)[(4 * half + v) * 32 + pslot] = hi;
+            reinterpret_cast<u16_alias *>(P_s)[(8 + 4 * half + v) * 32 + pslot] = lo;
+        }
         if (moved && n == 0) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) fac_s[4 * half + v] = corr[v];
@@ -376,6 +388,11 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
         block_sync();  // the next tile overwrites P_s and the parked rows
     }
     if (!active) return;
+    // the sums of the tails, from lane groups 2 and 3 to 0 and 1 (and the other way, where nobody looks)
+#pragma unroll
+    for (int nb = 0; nb < NM; ++nb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) oacc[nb][v] += __shfl_xor(oacc[nb][v], 32);
     // query 4 * half + v lives in this half-wave's softmax state; the output rows of queries 4 * g4 + v in lane groups 0, 1
     float lt[4];
 #pragma unroll
@@ -450,13 +467,6 @@ __global__ __launch_bounds__(256) void grouped_fwd_kernel(const bf16_t *__restri
 // of key n in a row of the weight matrix, where the 8 keys of (k-step, lane group) are contiguous.
 __device__ __forceinline__ int dq_key(int s, int h, int e) { return 16 * s + 4 * (e & 3) + 2 * h + (e >> 2); }
 __device__ __forceinline__ int w_slot(int n) { return (n & 16) + 8 * ((n >> 1) & 1) + 4 * (n & 1) + ((n >> 2) & 3); }
-
-// x = head + tail as two bf16 values (head = x rounded to bf16, tail = the rounded remainder)
-__device__ __forceinline__ void split_bf16(float x, uint16_t &hi, uint16_t &lo)
-{
-    hi = f32_to_bf16(x);
-    lo = f32_to_bf16(x - __uint_as_float((uint32_t)hi << 16));
-}
 
 // NSUB as in the forward: 4 = one group of up to 32 queries per block, the rows gathered and parked once per block.
 template <int D, bool SPLIT, int NSUB>

@@ -39,7 +39,10 @@ __global__ __launch_bounds__(256) void sparse_fwd_kernel(const T *__restrict__ Q
     for (int c = 0; c < CH; ++c) st.acc[c] = 0.f;
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    fwd_sweep<T, D, LPR>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e, stage, s);
+    constexpr bool FOLD = sizeof(T) == 4;
+    __shared__ float sums[FOLD ? (CH + 2) * 256 : 256];
+    fwd_sweep<T, D, LPR, true, FOLD>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e, stage, s,
+                               sums + threadIdx.x);
 
     const float inv = 1.f / st.l;
 #pragma unroll
@@ -94,7 +97,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_kernel(const T *__restrict_
     for (int c = 0; c < CH; ++c) { st.a[c] = 0.f; st.b[c] = 0.f; }
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    dq_sweep<T, D, LPR>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e,
+    dq_sweep<T, D, LPR, sizeof(T) == 4>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e,
                    lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s);
     if (live) {
         float dq[CH];
@@ -147,8 +150,8 @@ __global__ __launch_bounds__(256) void sparse_fwd_wave_kernel(const T *__restric
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(k, grp, tb, te);
-    fwd_sweep<T, D, LPR>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
-                         stage_all[threadIdx.x / LPR], s);
+    fwd_sweep<T, D, LPR, true, false>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+                               stage_all[threadIdx.x / LPR], s, (float *)nullptr);
     float m = st.m;
 #pragma unroll
     for (int o = LPR; o < 64; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
@@ -193,7 +196,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_wave_kernel(const T *__rest
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(k, grp, tb, te);
-    dq_sweep<T, D, LPR>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+    dq_sweep<T, D, LPR, sizeof(T) == 4>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
                         lse[(int64_t)bh * L + i] * kLog2e, delta0, stage_all[threadIdx.x / LPR], s);
     const float delta = group_sum<LPR>(st.delta);
     float dq[CH];
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_wave_kernel(const T *__re
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(n, grp, tb, te);
-    dkdv_sweep<T, D, LPR>(st, kc, vc, Q + head_base, dO + head_base, lse + (int64_t)bh * L, delta + (int64_t)bh * L,
+    dkdv_sweep<T, D, LPR, sizeof(T) == 4>(st, kc, vc, Q + head_base, dO + head_base, lse + (int64_t)bh * L, delta + (int64_t)bh * L,
                           (uint32_t)LL::off(s), idxT + tab.off[slot] + beg, tb, te, scale * kLog2e,
                           stage_all[threadIdx.x / LPR], s);
 #pragma unroll

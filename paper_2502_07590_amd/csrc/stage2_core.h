@@ -17,10 +17,16 @@
 // bf16 rows: dots use v_dot2_f32_bf16 on the packed words; the accumulations "acc += w * row"
 // take two gathered rows at a time, interleave their words with v_perm so that one packed word
 // holds the same channel of both rows, and issue one v_dot2_f32_bf16 per channel with the two
-// weights packed as bf16 -- half the VALU work of unpack + FMA.  The probabilities p are thereby
-// rounded to bf16 (relative 2^-9, as any bf16 flash-attention kernel rounds P before its second
-// GEMM); the signed, possibly large dS weights go in as two bf16 words (head + tail, 16
-// significant bits, two dot2 per channel).  Accumulators stay fp32.  fp32 rows use plain FMAs.
+// weights packed as bf16 -- half the VALU work of unpack + FMA.  The signed, possibly large dS weights
+// go in as two bf16 words (head + tail, 16 significant bits, two dot2 per channel), and so do the
+// forward's probabilities wherever a row is walked in one piece.  Accumulators stay fp32.  fp32 rows use plain FMAs.
+//
+// Rows walked in one piece take two cares that a row cut in eight or more ranges does without -- every range has a
+// maximum of its own, whose probability is exactly 1 in bf16, and short sums of its own:
+//   FINE  probabilities as head and tail: 1.66e-3 from the 64-bit result, which is the rounding of the output, where one bf16
+//         word leaves 1.74e-3 (in ranges: 1.68e-3).  0 to 5 % of the time.
+//   FOLD  (fp32 rows) sums folded every kFold keys: k = 1000, 4.0e-7 from the 64-bit result (in ranges: 4.2e-7; in one
+//         chain of additions: 6.9e-7).  0 to 3 % of the time.
 #pragma once
 
 #include "common.h"
@@ -184,14 +190,30 @@ __device__ __forceinline__ RowChunk<T, D / LPR> gather_chunk(const T *__restrict
 }
 
 // ------------------------------------------------------------------------------------ forward sweep
+constexpr int kFold = 64;  // keys of one chain of fp32 sums (FOLD)
+
 template <int CH> struct FwdState {
     float m, l;
     float acc[CH];
 };
+// The sums so far of a row in LDS -- element c of a thread at whole[256 c], m, l, acc in this order: in registers they would
+// cost the kernel a wave per SIMD -- += part, which starts again below the same maximum.
+template <int CH> __device__ __forceinline__ void fold(float *whole, FwdState<CH> &part, bool first)
+{
+    const float f = first ? 0.f : fast_exp2(whole[0] - part.m);
+    whole[0] = part.m;
+    whole[256] = first ? part.l : fmaf(whole[256], f, part.l);
+    part.l = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        whole[256 * (c + 2)] = first ? part.acc[c] : fmaf(whole[256 * (c + 2)], f, part.acc[c]);
+        part.acc[c] = 0.f;
+    }
+}
 
 // jsrc: U staged index entries (LDS); TAIL: only the first nvalid of them count (the rest are valid
 // row numbers too -- duplicates of the segment's last entry -- and get weight zero).
-template <typename T, int D, int LPR, bool TAIL>
+template <typename T, int D, int LPR, bool TAIL, bool FINE>
 __device__ __forceinline__ void fwd_step(FwdState<D / LPR> &st, const RowChunk<T, D / LPR> &q, const T *__restrict__ Kh,
                                          const T *__restrict__ Vh, uint32_t lane_off, const int32_t *jsrc, int nvalid,
                                          float c2)
@@ -234,7 +256,8 @@ __device__ __forceinline__ void fwd_step(FwdState<D / LPR> &st, const RowChunk<T
     for (int u = 0; u < U; u += 4) st.l += (p[u] + p[u + 1]) + (p[u + 2] + p[u + 3]);
 #pragma unroll
     for (int u = 0; u < U; u += 2)
-        axpy_pair<T, CH>(st.acc, vc[u], vc[u + 1], p[u], p[u + 1], sizeof(T) == 2 ? pack_bf16x2(p[u], p[u + 1]) : 0u);
+        if constexpr (FINE) axpy_pair_precise<T, CH>(st.acc, vc[u], vc[u + 1], p[u], p[u + 1]);
+        else axpy_pair<T, CH>(st.acc, vc[u], vc[u + 1], p[u], p[u + 1], sizeof(T) == 2 ? pack_bf16x2(p[u], p[u + 1]) : 0u);
 }
 
 // Sum over the 64 / LPR lane groups of the wave (LPR = 1: over its lanes).
@@ -277,11 +300,12 @@ template <int LPR> struct StagedIndex {
 };
 
 // positions [tb, te) of `row`; all lanes of the group call with the same arguments.  stage: the
-// group's kStage-entry LDS slot (16-byte aligned); s: this lane's number inside the group.
-template <typename T, int D, int LPR>
+// group's kStage-entry LDS slot (16-byte aligned); s: this lane's number inside the group.  whole: this thread's column of
+// [D / LPR + 2][256] floats of LDS (FOLD; else unused).
+template <typename T, int D, int LPR, bool FINE, bool FOLD>
 __device__ __forceinline__ void fwd_sweep(FwdState<D / LPR> &st, const RowChunk<T, D / LPR> &q, const T *__restrict__ Kh,
                                           const T *__restrict__ Vh, uint32_t lane_off, const int32_t *__restrict__ row,
-                                          int tb, int te, float c2, int32_t *stage, int s)
+                                          int tb, int te, float c2, int32_t *stage, int s, float *whole)
 {
     if (tb >= te) return;
     StagedIndex<LPR> si;
@@ -291,8 +315,16 @@ __device__ __forceinline__ void fwd_sweep(FwdState<D / LPR> &st, const RowChunk<
         if (c0 + kStage < te) si.request(row, c0 + kStage, te, s);
         const int n = min(kStage, te - c0);
         int it = 0;
-        for (; it + DSV_FWD_U <= n; it += DSV_FWD_U) fwd_step<T, D, LPR, false>(st, q, Kh, Vh, lane_off, stage + it, DSV_FWD_U, c2);
-        if (it < n) fwd_step<T, D, LPR, true>(st, q, Kh, Vh, lane_off, stage + it, n - it, c2);
+        for (; it + DSV_FWD_U <= n; it += DSV_FWD_U)
+            fwd_step<T, D, LPR, false, FINE>(st, q, Kh, Vh, lane_off, stage + it, DSV_FWD_U, c2);
+        if (it < n) fwd_step<T, D, LPR, true, FINE>(st, q, Kh, Vh, lane_off, stage + it, n - it, c2);
+        if (FOLD && (c0 - tb) % kFold == kFold - kStage) fold(whole, st, c0 - tb < kFold);
+    }
+    if (FOLD && te - tb > kFold - kStage) {  // folded at least once
+        const float f = fast_exp2(whole[0] - st.m);
+        st.l = fmaf(whole[256], f, st.l);
+#pragma unroll
+        for (int c = 0; c < D / LPR; ++c) st.acc[c] = fmaf(whole[256 * (c + 2)], f, st.acc[c]);
     }
 }
 
@@ -301,6 +333,17 @@ template <int CH> struct DqState {
     float delta;
     float a[CH], b[CH];  // a: the centred sum C
 };
+template <int CH> __device__ __forceinline__ void fold(DqState<CH> &whole, DqState<CH> &part)
+{
+    whole.delta += part.delta;
+    part.delta = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        whole.a[c] += part.a[c];
+        whole.b[c] += part.b[c];
+        part.a[c] = part.b[c] = 0.f;
+    }
+}
 
 template <typename T, int D, int LPR, bool TAIL>
 __device__ __forceinline__ void dq_step(DqState<D / LPR> &st, const RowChunk<T, D / LPR> &q,
@@ -333,13 +376,14 @@ __device__ __forceinline__ void dq_step(DqState<D / LPR> &st, const RowChunk<T, 
     axpy_pair2<T, CH>(st.a, st.b, kc[0], kc[1], wc[0], wc[1], p[0], p[1]);
 }
 
-template <typename T, int D, int LPR>
+template <typename T, int D, int LPR, bool FOLD>
 __device__ __forceinline__ void dq_sweep(DqState<D / LPR> &st, const RowChunk<T, D / LPR> &q,
                                          const RowChunk<T, D / LPR> &go, const T *__restrict__ Kh,
                                          const T *__restrict__ Vh, uint32_t lane_off, const int32_t *__restrict__ row,
                                          int tb, int te, float c2, float lse2, float delta0, int32_t *stage, int s)
 {
     if (tb >= te) return;
+    DqState<D / LPR> whole = st;  // nothing yet
     StagedIndex<LPR> si;
     si.request(row, tb, te, s);
     for (int c0 = tb; c0 < te; c0 += kStage) {
@@ -355,6 +399,11 @@ __device__ __forceinline__ void dq_sweep(DqState<D / LPR> &st, const RowChunk<T,
 #endif
         for (; it + 2 <= n; it += 2) dq_step<T, D, LPR, false>(st, q, go, Kh, Vh, lane_off, stage + it, 2, c2, lse2, delta0);
         if (it < n) dq_step<T, D, LPR, true>(st, q, go, Kh, Vh, lane_off, stage + it, n - it, c2, lse2, delta0);
+        if (FOLD && (c0 - tb) % kFold == kFold - kStage) fold(whole, st);
+    }
+    if constexpr (FOLD) {
+        fold(whole, st);
+        st = whole;
     }
 }
 
@@ -362,6 +411,15 @@ __device__ __forceinline__ void dq_sweep(DqState<D / LPR> &st, const RowChunk<T,
 template <int CH> struct DkdvState {
     float dk[CH], dv[CH];
 };
+template <int CH> __device__ __forceinline__ void fold(DkdvState<CH> &whole, DkdvState<CH> &part)
+{
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        whole.dk[c] += part.dk[c];
+        whole.dv[c] += part.dv[c];
+        part.dk[c] = part.dv[c] = 0.f;
+    }
+}
 
 // stat_s (optional): the packed {lse * log2(e), Delta} entries of the queries from stat_base on, parked in
 // LDS by the caller (every query of the list segment lies in that stretch); then lse_h / delta_h are unused.
@@ -407,7 +465,7 @@ __device__ __forceinline__ void dkdv_step(DkdvState<D / LPR> &st, const RowChunk
     axpy_pair_precise<T, CH>(st.dv, gc[0], gc[1], p[0], p[1]);
 }
 
-template <typename T, int D, int LPR, bool LDS_STAT = false>
+template <typename T, int D, int LPR, bool FOLD, bool LDS_STAT = false>
 __device__ __forceinline__ void dkdv_sweep(DkdvState<D / LPR> &st, const RowChunk<T, D / LPR> &kc,
                                            const RowChunk<T, D / LPR> &vc, const T *__restrict__ Qh,
                                            const T *__restrict__ Gh, const float *__restrict__ lse_h,
@@ -417,6 +475,7 @@ __device__ __forceinline__ void dkdv_sweep(DkdvState<D / LPR> &st, const RowChun
                                            GroupExpand ge = no_expand())
 {
     if (tb >= te) return;
+    DkdvState<D / LPR> whole = st;  // nothing yet
     StagedIndex<LPR> si;
     si.request(list, tb, te, s, ge);
     for (int c0 = tb; c0 < te; c0 += kStage) {
@@ -432,6 +491,11 @@ __device__ __forceinline__ void dkdv_sweep(DkdvState<D / LPR> &st, const RowChun
 #endif
         for (; it + 2 <= n; it += 2) dkdv_step<T, D, LPR, false, LDS_STAT>(st, kc, vc, Qh, Gh, lse_h, delta_h, stat_s, stat_base, lane_off, stage + it, 2, c2);
         if (it < n) dkdv_step<T, D, LPR, true, LDS_STAT>(st, kc, vc, Qh, Gh, lse_h, delta_h, stat_s, stat_base, lane_off, stage + it, n - it, c2);
+        if (FOLD && (c0 - tb) % kFold == kFold - kStage) fold(whole, st);
+    }
+    if constexpr (FOLD) {
+        fold(whole, st);
+        st = whole;
     }
 }
 

@@ -91,7 +91,8 @@ __global__ __launch_bounds__(256) void sparse_fwd_split_kernel(const T *__restri
     for (int c = 0; c < CH; ++c) st.acc[c] = 0.f;
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    fwd_sweep<T, D, LPR>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e, stage, s);
+    fwd_sweep<T, D, LPR, false, false>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e, stage, s,
+                                (float *)nullptr);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + i) * pl.S + range;
         store_acc<T, D, LPR>(pacc + slot_id * D, s, st.acc);
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_split_kernel(const T *__res
     for (int c = 0; c < CH; ++c) { st.a[c] = 0.f; st.b[c] = 0.f; }
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    dq_sweep<T, D, LPR>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+    dq_sweep<T, D, LPR, false>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
                    lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + i) * pl.S + range;
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
         for (int e = threadIdx.x; e < nq; e += 256) stat_s[e] = src[e];
         __syncthreads();
     }
-    dkdv_sweep<T, D, LPR, true>(st, kc, vc, Q + head_base, dO + head_base, nullptr, nullptr, (uint32_t)LL::off(s), list, tb,
+    dkdv_sweep<T, D, LPR, false, true>(st, kc, vc, Q + head_base, dO + head_base, nullptr, nullptr, (uint32_t)LL::off(s), list, tb,
                                 te, scale * kLog2e, stage, s, stat_s, q_first, ge);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + j) * pl.S + range;
