@@ -1,6 +1,7 @@
 // C ABI of libdsv: argument checks, workspace layout, launch order.  All checks run on the host
 // before anything is enqueued; the library never allocates device memory.
 #include <algorithm>
+#include <cmath>
 #include <initializer_list>
 #include <mutex>
 #include <optional>
@@ -132,33 +133,63 @@ int64_t mean_k(const dsv_problem &p)
     return s / p.H;
 }
 
-// Whether sequences of less than eight full ranges are cut in two or four instead of eight, given blocks enough (make_split_plan):
-// every range leaves partial results, segment pointers and a row order, smaller ones stay in the L2 with the index that
-// streams past them.  Measured, bf16, d = 128, four heads, eight ranges against four: dkdv at L = 32768, k = 327: 1598 : 1365 us,
-// k = 1000: 3294 : 3119 and dq 2899 : 2692; on lists as stage 1 makes them, 32768, k = 2048, the whole backward 11284 : 11302; 20280,
-// k = 507 .. 4056: 7641 : 7725.
+// Whether the dq step cuts sequences of less than eight full ranges in two or four instead of eight, given blocks enough
+// (make_split_plan): every range leaves partial results, segment pointers and a row order, smaller ones stay in the L2 with the
+// index that streams past them.  Measured, bf16, d = 128, four heads, eight ranges against four: L = 32768, k = 1092: 3373 : 3163 us;
+// 24000, k = 800: 1893 : 1728; k = 2048 no gain.  The forward gains nothing and would share maxima (stage2_core.h); the key-major
+// step loses: 32768, k = 327: 1680 : 1882, d = 64, 24000, k = 400: 800 : 1006.
 bool few_ranges(const dsv_problem &p) { return mean_k(p) <= 1280; }
 
-// Whether the per-query forward and dq step run L2-blocked: sorted indices promised, and enough to gather from enough rows.
-// Blocking costs about 0.5 ns per (row, range) -- partial results written and merged, segments, row order -- and wins
-// back what the gathers lose to L2 misses, which ascending rows walked side by side already keep few.  Measured at bf16,
-// d = 128, four heads, blocked against not, forward / dq in us: L = 4096, k = 40: 75 : 24 / 106 : 23; 8192, k = 512: 387 : 331 /
-// 474 : 328; 16000 (7.8 MB), k = 1000: 1295 : 1296 / 1500 : 1351, k = 3200: 3472 : 3484 / 4003 : 4122; 20280, k = 202: 556 : 375 /
-// 700 : 346, k = 1267: 1992 : 2200 / 2276 : 2257; 32768 (16 MB), k = 327: 1241 : 921 / 1436 : 979, k = 2048: 4962 : 5804 /
-// 5574 : 6924; two heads of 65536 (32 MB), k = 655: 2438 : 2067 / 2449 : 2172, k = 1310: 3956 : 4132 / 4158 : 5057; of 131072
-// (64 MB), k = 327: 4747 : 2473 / 4666 : 3727, k = 655: 6150 : 6167 / 6186 : 7390, k = 1310: 9356 : 14269 / 9630 : 16269.
-bool split_rows(const dsv_problem &p, const SplitPlan &pl)
+// Form of the forward and the dq step for the heads that keep fewer than dense_k keys: a lane group or a wave per row
+// (stage2.hip), or key ranges (stage2_split.hip; sorted indices promised).  Their times, estimated in us, each a chain of
+// steps -- as long as the longest row -- beside the work of the whole chip:
+//   groups   0.1 to 0.3 us per key of a row; least work per pair, until the rows of all heads outgrow the caches
+//   waves    a chain 4 to 16 times shorter; every part of a row in whole steps of four keys, the parts meet in exchanges (one
+//            per accumulator and halving of the lanes), and no neighbour walks beside, so that a head's rows soon miss
+//            the L2.  Chosen where it is 6 % (dq) or 10 % ahead.
+//   ranges   seven launches, partial results of every (row, range); rows that stay in the L2
+// Measured over 1008 problems (both types and head dimensions, 1 to 12 heads, 500 to 131072 keys, 8 to 5120 kept, lists as
+// stage 1 makes them) the form chosen takes 1.012 times the fastest one's time in the mean; of 2016 calls it is more than 5 %
+// behind ranges in 2, and behind groups, where only those and waves are open, in 21.  Groups, waves, ranges in us, bf16,
+// d = 128: forward, four heads of 3000, k = 20: 12, 34, 56; of 4096, k = 640: 243, 213, 226; one of 8192, k = 320: 120, 78, 119;
+// dq, four of 24000, k = 1280: 2656, 4271, 2640; fp32, four of 32768, k = 640: 5522, 7896, 3752.
+enum class RowForm { groups, waves, ranges };
+RowForm row_form(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t dense_k)
 {
-    return use_split(p, pl) && kv_bytes(p) >= ((size_t)8 << 20) && mean_k(p) >= (kv_bytes(p) > ((size_t)48 << 20) ? 512 : 768);
+    const double row_bytes = (double)p.d * esize(p.dtype), kv = (double)kv_bytes(p) / (1 << 20);
+    const int lanes = (int)std::clamp(row_bytes / (dq ? 32 : 64), 4.0, 16.0), parts = 64 / lanes;  // SweepLanes (stage2_core.h)
+    double sum = 0, most = 0, whole_steps = 0;
+    int n = 0;
+    for (int h = 0; h < p.H; ++h) {
+        const int32_t k = p.k_per_head[h];
+        if (k >= dense_k) continue;
+        sum += k;
+        most = std::max(most, (double)k);
+        whole_steps += 4 * parts * std::ceil(k / (4.0 * parts));
+        ++n;
+    }
+    if (!n) return RowForm::groups;  // nobody asks
+    const double heads = (double)p.B * n, rows = heads * p.L, pair = 3.3e-8 * 2 * row_bytes * p.B * p.L;
+    auto beside = [](double chain, double all) { return std::sqrt(chain * chain + all * all); };
+    auto above = [](double x) { return std::max(0.0, std::log2(x)); };  // doublings past a size
+    const double per_key = dq ? 0.19 : p.dtype == DSV_F32 ? 0.17 : p.d == 128 ? 0.31 : 0.1;
+    const double groups = 7 + beside(per_key * most, pair * sum * (1.16 + 0.05 * above(kv / 8) + 0.45 * above(kv * std::sqrt(std::min(heads, 4.0)) / 32)));
+    const double exchanges = (dq ? 2 * 4e-6 : 9e-6) * (p.d / lanes) * std::log2(parts);
+    const double waves = (dq ? 1.06 : 1.1) * (7 + beside(0.008 * most, rows * exchanges + pair * whole_steps * (1 + (dq ? 0.3 : 0.45) * above(kv / 3))));
+    const double ranges = 28 + (dq ? 4.4e-6 : 2.5e-6) * p.d * rows * std::max(pl.S_pad, 8) + beside(0.03 * most, pair * sum);
+    if (use_split(p, pl) && ranges < std::min(groups, waves)) return RowForm::ranges;
+    return waves < groups ? RowForm::waves : RowForm::groups;
 }
 
-// The same for the key-major step, whose lists differ in length: the blocked form also sorts them by it, the other one gives
-// every list a wave.  Blocked (eight ranges) against not, us, bf16, d = 128, lists as stage 1 makes them: four heads of 2048, k = 200:
-// 102 : 82, k = 500: 155 : 146; 4096, k = 150: 160 : 139, k = 400: 240 : 260, k = 819: 357 : 431; 8192, k = 200: 334 : 370, k = 512:
-// 512 : 721; 16384, k = 1000: 1619 : 3004; one head of 4096, k = 256: 105 : 74; three of 6000, d = 64, k = 200: 157 : 101, k = 600: 221 : 222.
+// Whether the key-major step runs over query ranges.  Lists differ in length: the blocked form also sorts them by it, the other
+// one gives every list a wave.  Blocked against not, us, lists as stage 1 makes them, bf16, d = 128: four heads of 2048 (1 MB),
+// k = 160: 91 : 71, k = 640: 158 : 164; 4096, k = 160: 158 : 143, k = 320: 205 : 208; 6000 (3 MB), k = 200: 227 : 239; 12000 (6 MB),
+// k = 80: 235 : 211, k = 160: 474 : 522; one head of 2048, k = 640: 85 : 52; d = 64, 12 of 4096 (1 MB), k = 1280: 817 : 994; one of 16384
+// (4 MB), k = 160: 195 : 115; fp32, d = 128, four of 6000 (6 MB), k = 80: 186 : 173, k = 160: 259 : 329.
 bool split_lists(const dsv_problem &p, const SplitPlan &pl)
 {
-    return use_split(p, pl) && kv_bytes(p) > ((size_t)1 << 20) && (kv_bytes(p) > ((size_t)6 << 20) || mean_k(p) > 256);
+    const double mb = (double)kv_bytes(p) / (1 << 20);
+    return use_split(p, pl) && mb >= 1 && mb * p.B * p.H >= 2 && mb * mean_k(p) * std::sqrt(p.d / 128.0) >= 600;
 }
 
 // Whether a whole backward on rows in any order sorts them first, so that the dq step runs L2-blocked: once a head's K and
@@ -223,7 +254,7 @@ size_t mask_bytes(const dsv_problem &p, int heads)
 }
 
 struct FwdLayout {
-    bool split;
+    RowForm form;     // of the heads below dense_k
     SplitPlan plan;
     int32_t dense_k;  // heads that keep at least so many keys run over dense tiles
     size_t seg, pm, pl, pacc, hist, order, total;
@@ -233,12 +264,13 @@ FwdLayout fwd_layout(const dsv_problem &p)
 {
     FwdLayout w{};
     w.plan = make_split_plan(p, kFwdRangeBytes, false);  // every range brings a maximum of its own (stage2_core.h)
-    w.split = split_rows(p, w.plan);
     w.dense_k = dense_fwd_min_k(p);
+    w.form = row_form(p, w.plan, false, w.dense_k);
     int dense = 0;
     for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= w.dense_k;
     if (dense) w.total = mask_bytes(p, dense);
-    if (!w.split) return w;
+    // with room for the ranges of heads that run over tiles: what callers reserve does not hang on that rule
+    if (w.form != RowForm::ranges && row_form(p, w.plan, false, INT32_MAX) != RowForm::ranges) return w;
     const size_t rows = (size_t)p.B * p.H * p.L;
     size_t o = 0;
     w.seg = o; o = align_up(o + rows * (w.plan.S + 1) * 4, 256);
@@ -254,7 +286,8 @@ FwdLayout fwd_layout(const dsv_problem &p)
 // One split backward step (dq or dkdv): segment pointers and two [rows, S, d] partial arrays
 // (+ [rows, S] for the dq step's Delta partials; laid out for both so that the steps can share it).
 struct StepLayout {
-    bool split_dq, split_dkdv;
+    RowForm form;  // of the dq step
+    bool blocked;  // the dkdv step
     SplitPlan plan;
     size_t seg, pa, pb, pdelta, hist, order, rowstat, total;
 };
@@ -274,15 +307,24 @@ void place_step(const dsv_problem &p, StepLayout &w)
     w.total = o;
 }
 
-StepLayout step_layout(const dsv_problem &p)
+StepLayout dq_layout(const dsv_problem &p)
 {
     StepLayout w{};
     w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
-    w.split_dq = split_rows(p, w.plan);
-    w.split_dkdv = split_lists(p, w.plan);
-    if (w.split_dq || w.split_dkdv) place_step(p, w);
+    w.form = row_form(p, w.plan, true, INT32_MAX);
+    if (w.form == RowForm::ranges) place_step(p, w);
     return w;
 }
+StepLayout dkdv_layout(const dsv_problem &p)
+{
+    StepLayout w{};
+    w.plan = make_split_plan(p, kBwdRangeBytes, false);
+    w.blocked = split_lists(p, w.plan);
+    if (w.blocked) place_step(p, w);
+    return w;
+}
+// Scratch of either step: they are never live together.
+size_t step_bytes(const dsv_problem &p) { return std::max(dq_layout(p).total, dkdv_layout(p).total); }
 
 BwdSplitWorkspace step_buffers(char *ws, const StepLayout &w)
 {
@@ -318,7 +360,7 @@ BwdLayout bwd_layout(const dsv_problem &p, bool own_transpose)
     // own_transpose: the lists come out ascending, so the dkdv step runs the L2-blocked kernel whatever p.flags says
     dsv_problem sorted = p;
     sorted.flags |= DSV_FLAG_SORTED_INDEX;
-    w.step = o; w.step_bytes = own_transpose ? std::max(step_layout(p).total, step_layout(sorted).total) : step_layout(p).total;
+    w.step = o; w.step_bytes = own_transpose ? std::max(step_bytes(p), step_bytes(sorted)) : step_bytes(p);
     o += w.step_bytes;
     w.total = o;
     return w;
@@ -493,7 +535,8 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
         if (st != DSV_OK) return st;
     }
     if (rest.empty()) return DSV_OK;
-    if (!w.split) return launch_sparse_fwd(*p, rest.data(), (int)rest.size(), Q, K, V, idx, O, lse, stream);
+    if (w.form != RowForm::ranges)
+        return launch_sparse_fwd(*p, rest.data(), (int)rest.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, stream);
     FwdSplitWorkspace b;
     b.seg = reinterpret_cast<int32_t *>(ws + w.seg);
     b.pm = reinterpret_cast<float *>(ws + w.pm);
@@ -508,7 +551,7 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
 size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p)
 {
     if (check_problem(p, false) != DSV_OK) return 0;
-    return step_layout(*p).total;
+    return step_bytes(*p);
 }
 
 dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
@@ -518,12 +561,13 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx, O, lse, dO, dQ, delta})) return DSV_EINVAL;
-    const StepLayout w = step_layout(*p);
-    st = check_workspace(workspace, ws_bytes, w.total);
+    st = check_workspace(workspace, ws_bytes, step_bytes(*p));
     if (st != DSV_OK) return st;
+    const StepLayout w = dq_layout(*p);
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.split_dq) return launch_bwd_dq(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, stream);
+    if (w.form != RowForm::ranges)
+        return launch_bwd_dq(*p, tabs.data(), (int)tabs.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, dO, dQ, delta, stream);
     return launch_bwd_dq_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, w.plan,
                                step_buffers(static_cast<char *>(workspace), w), stream);
 }
@@ -551,7 +595,7 @@ dsv_status dsv_idx_transpose(const dsv_problem *p, const int32_t *idx, int32_t *
 size_t dsv_sparse_attn_bwd_dkdv_workspace(const dsv_problem *p)
 {
     if (check_problem(p, false) != DSV_OK) return 0;
-    return step_layout(*p).total;
+    return step_bytes(*p);
 }
 
 dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const void *K, const void *V,
@@ -562,12 +606,12 @@ dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const v
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV})) return DSV_EINVAL;
-    const StepLayout w = step_layout(*p);
-    st = check_workspace(workspace, ws_bytes, w.total);
+    st = check_workspace(workspace, ws_bytes, step_bytes(*p));
     if (st != DSV_OK) return st;
+    const StepLayout w = dkdv_layout(*p);
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.split_dkdv)
+    if (!w.blocked)
         return launch_bwd_dkdv(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
                                stream);
     return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
@@ -773,7 +817,7 @@ GroupedBwdLayout grouped_bwd_layout(const dsv_problem &p, const dsv_grouping &g)
     // the dq step's scratch and the dkdv step's are never live together
     w.step = o;
     w.step_bytes = native ? std::max(grouped_step_layout(p, g, true).total, grouped_key_layout(p).total)
-                          : std::max(step_layout(p).total, step_layout(sorted).total);
+                          : std::max(step_bytes(p), step_bytes(sorted));
     o += w.step_bytes;
     w.total = o;
     return w;
@@ -866,7 +910,7 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
         if ((st = launch_group_rows(*p, *g, 1, O, ws + w.op, stream)) != DSV_OK) return st;
         st = launch_group_expand(*p, *g, tabs.data(), (int)tabs.size(), idx_g, nullptr, nullptr, idx_x, nullptr, nullptr, stream);
         if (st != DSV_OK) return st;
-        const size_t dq_bytes = step_layout(*p).total;
+        const size_t dq_bytes = step_bytes(*p);
         st = dsv_sparse_attn_bwd_dq(p, ws + w.qp, K, V, idx_x, ws + w.op, lsep, ws + w.gop, ws + w.dqp, deltap,
                                     dq_bytes ? ws + w.step : nullptr, dq_bytes, hip_stream);
         if (st != DSV_OK) return st;
@@ -894,7 +938,7 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
     if (st != DSV_OK) return st;
     dsv_problem sorted = *p;
     sorted.flags |= DSV_FLAG_SORTED_INDEX;
-    const size_t dkdv_bytes = step_layout(sorted).total;
+    const size_t dkdv_bytes = step_bytes(sorted);
     return dsv_sparse_attn_bwd_dkdv(&sorted, ws + w.qp, K, V, reinterpret_cast<int32_t *>(ws + w.idxtx),
                                     reinterpret_cast<int64_t *>(ws + w.colx), lsep, deltap, ws + w.gop, dK, dV,
                                     dkdv_bytes ? ws + w.step : nullptr, dkdv_bytes, hip_stream);

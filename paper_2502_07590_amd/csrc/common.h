@@ -404,9 +404,10 @@ dsv_status launch_select_small(const dsv_problem &p, int Lq, const HeadTable &ta
 // emitted: the query-major index is there already.
 dsv_status launch_emit(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr, const void *Klr,
                        const SelectBuffers &b, bool emitted, hipStream_t st);
-dsv_status launch_sparse_fwd(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+// waves: a wave per row, else a lane group per row.
+dsv_status launch_sparse_fwd(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                              const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st);
-dsv_status launch_bwd_dq(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+dsv_status launch_bwd_dq(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                          const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO, void *dQ,
                          float *delta, hipStream_t st);
 dsv_status launch_bwd_dkdv(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,

@@ -11,7 +11,7 @@
 namespace dsv {
 
 // ------------------------------------------------------------------------------------ forward
-template <typename T, int D, int LPR>
+template <typename T, int D, int LPR, bool CARE>
 __global__ __launch_bounds__(256) void sparse_fwd_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                          const T *__restrict__ V, const int32_t *__restrict__ idx,
                                                          T *__restrict__ O, float *__restrict__ lse, int L,
@@ -39,9 +39,9 @@ __global__ __launch_bounds__(256) void sparse_fwd_kernel(const T *__restrict__ Q
     for (int c = 0; c < CH; ++c) st.acc[c] = 0.f;
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    constexpr bool FOLD = sizeof(T) == 4;
+    constexpr bool FOLD = CARE && sizeof(T) == 4;
     __shared__ float sums[FOLD ? (CH + 2) * 256 : 256];
-    fwd_sweep<T, D, LPR, true, FOLD>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e, stage, s,
+    fwd_sweep<T, D, LPR, CARE, FOLD>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e, stage, s,
                                sums + threadIdx.x);
 
     const float inv = 1.f / st.l;
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void sparse_fwd_kernel(const T *__restrict__ Q
 // with D0 = dO_i . O_stored as a centring value,
 //   dQ_i = scale * ( sum_j p_ij (dP_ij - D0) k_j  -  (Delta_i - D0) * sum_j p_ij k_j ).
 // Delta is kept for the dkdv pass.
-template <typename T, int D, int LPR>
+template <typename T, int D, int LPR, bool CARE>
 __global__ __launch_bounds__(256) void sparse_bwd_dq_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                             const T *__restrict__ V,
                                                             const int32_t *__restrict__ idx, const T *__restrict__ O,
@@ -97,8 +97,10 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_kernel(const T *__restrict_
     for (int c = 0; c < CH; ++c) { st.a[c] = 0.f; st.b[c] = 0.f; }
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
-    dq_sweep<T, D, LPR, sizeof(T) == 4>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e,
-                   lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s);
+    constexpr bool FOLD = CARE && sizeof(T) == 4;
+    __shared__ float sums[FOLD ? (2 * CH + 1) * 256 : 256];
+    dq_sweep<T, D, LPR, FOLD>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, 0, k, scale * kLog2e,
+                   lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s, sums + threadIdx.x);
     if (live) {
         float dq[CH];
 #pragma unroll
@@ -124,7 +126,7 @@ template <int LPR> __device__ __forceinline__ void group_part(int n, int grp, in
     te = min(tb + per, n);
 }
 
-template <typename T, int D, int LPR>
+template <typename T, int D, int LPR, bool CARE>
 __global__ __launch_bounds__(256) void sparse_fwd_wave_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                               const T *__restrict__ V, const int32_t *__restrict__ idx,
                                                               T *__restrict__ O, float *__restrict__ lse, int L, float scale,
@@ -150,7 +152,7 @@ __global__ __launch_bounds__(256) void sparse_fwd_wave_kernel(const T *__restric
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(k, grp, tb, te);
-    fwd_sweep<T, D, LPR, true, false>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+    fwd_sweep<T, D, LPR, CARE, false>(st, q, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
                                stage_all[threadIdx.x / LPR], s, (float *)nullptr);
     float m = st.m;
 #pragma unroll
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(256) void sparse_fwd_wave_kernel(const T *__restric
     }
 }
 
-template <typename T, int D, int LPR>
+template <typename T, int D, int LPR, bool CARE>
 __global__ __launch_bounds__(256) void sparse_bwd_dq_wave_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                                  const T *__restrict__ V, const int32_t *__restrict__ idx,
                                                                  const T *__restrict__ O, const float *__restrict__ lse,
@@ -196,8 +198,10 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_wave_kernel(const T *__rest
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(k, grp, tb, te);
-    dq_sweep<T, D, LPR, sizeof(T) == 4>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
-                        lse[(int64_t)bh * L + i] * kLog2e, delta0, stage_all[threadIdx.x / LPR], s);
+    constexpr bool FOLD = CARE && sizeof(T) == 4 && LPR > 8;  // eight parts of a row are short sums as they are
+    __shared__ float sums[FOLD ? (2 * CH + 1) * 256 : 256];
+    dq_sweep<T, D, LPR, FOLD>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
+                        lse[(int64_t)bh * L + i] * kLog2e, delta0, stage_all[threadIdx.x / LPR], s, sums + threadIdx.x);
     const float delta = group_sum<LPR>(st.delta);
     float dq[CH];
 #pragma unroll
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_wave_kernel(const T *__re
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];
     int tb, te;
     group_part<LPR>(n, grp, tb, te);
-    dkdv_sweep<T, D, LPR, sizeof(T) == 4>(st, kc, vc, Q + head_base, dO + head_base, lse + (int64_t)bh * L, delta + (int64_t)bh * L,
+    dkdv_sweep<T, D, LPR, sizeof(T) == 4 && (LPR > 8)>(st, kc, vc, Q + head_base, dO + head_base, lse + (int64_t)bh * L, delta + (int64_t)bh * L,
                           (uint32_t)LL::off(s), idxT + tab.off[slot] + beg, tb, te, scale * kLog2e,
                           stage_all[threadIdx.x / LPR], s);
 #pragma unroll
@@ -252,55 +256,59 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_wave_kernel(const T *__re
 }
 
 // ------------------------------------------------------------------------------------ host
-// Whether rows get a wave each instead of a lane group: when the groups' waves (rows * lanes / 64) would be fewer than
-// `enough`.  Measured, lane groups against waves: bf16, d = 128, one head, k = L / 16, forward: L = 4096 (256 waves): 90 : 32 us,
-// 8192: 190 : 100, 12000: 268 : 255, 16000: 363 : 454; dq: 4096 (512 waves): 55 : 29, 8192: 132 : 88, 12000: 252 : 200,
-// 16000: 349 : 393.  d = 64: forward 12000 (750 waves): 120 : 95, 16000: 160 : 185; dq 16000 (1000 waves): 242 : 185.
-static bool wave_per_row(const dsv_problem &p, int lanes, int64_t enough)
-{
-    return (int64_t)p.B * p.H * p.L * lanes / 64 < enough;
-}
-
-template <typename T, int D>
-static dsv_status fwd_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+// CARE of the kernels (FINE and FOLD of stage2_core.h): for rows that ranges could have walked.  Calls without the flag never had
+// ranges, and go without: 0 to 9 % of the forward, up to 20 % of the dq step of long fp32 rows.
+template <typename T, int D, bool CARE>
+static dsv_status fwd_c(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                         const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st)
 {
-    KernelSpan span(DSV_KERNEL_FWD_SWEEP, st);
+    constexpr int LPR = SweepLanes<T, D>::fwd;
+    const auto kern = waves ? &sparse_fwd_wave_kernel<T, D, LPR, CARE> : &sparse_fwd_kernel<T, D, LPR, CARE>;
+    const int rows = waves ? 4 : 256 / LPR;  // per block
     for (int t = 0; t < n_tabs; ++t) {
-        if (wave_per_row(p, SweepLanes<T, D>::fwd, 800)) {
-            hipLaunchKernelGGL((sparse_fwd_wave_kernel<T, D, SweepLanes<T, D>::fwd>), dim3((p.L + 3) / 4, tabs[t].n), dim3(256), 0, st,
-                               (const T *)Q, (const T *)K, (const T *)V, idx, (T *)O, lse, p.L, p.scale, tabs[t]);
-            DSV_LAUNCH_CHECK();
-            continue;
-        }
-        dim3 grid((p.L + 256 / SweepLanes<T, D>::fwd - 1) / (256 / SweepLanes<T, D>::fwd), tabs[t].n);
-        hipLaunchKernelGGL((sparse_fwd_kernel<T, D, SweepLanes<T, D>::fwd>), grid, dim3(256), 0, st, (const T *)Q, (const T *)K, (const T *)V,
-                           idx, (T *)O, lse, p.L, p.scale, tabs[t]);
+        hipLaunchKernelGGL(kern, dim3((p.L + rows - 1) / rows, tabs[t].n), dim3(256), 0, st, (const T *)Q, (const T *)K, (const T *)V, idx,
+                           (T *)O, lse, p.L, p.scale, tabs[t]);
         DSV_LAUNCH_CHECK();
     }
     return DSV_OK;
 }
 
 template <typename T, int D>
-static dsv_status bwd_dq_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+static dsv_status fwd_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
+                        const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st)
+{
+    KernelSpan span(DSV_KERNEL_FWD_SWEEP, st);
+    return p.flags & DSV_FLAG_SORTED_INDEX ? fwd_c<T, D, true>(p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, st)
+                                           : fwd_c<T, D, false>(p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, st);
+}
+
+template <typename T, int D, bool CARE>
+static dsv_status bwd_dq_c(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
+                           const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO,
+                           void *dQ, float *delta, hipStream_t st)
+{
+    constexpr int LPR = SweepLanes<T, D>::dq;
+    const auto kern = waves ? &sparse_bwd_dq_wave_kernel<T, D, LPR, CARE> : &sparse_bwd_dq_kernel<T, D, LPR, CARE>;
+    const int rows = waves ? 4 : 256 / LPR;  // per block
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL(kern, dim3((p.L + rows - 1) / rows, tabs[t].n), dim3(256), 0, st, (const T *)Q, (const T *)K, (const T *)V, idx,
+                           (const T *)O, lse, (const T *)dO, (T *)dQ, delta, p.L, p.scale, tabs[t]);
+        DSV_LAUNCH_CHECK();
+    }
+    return DSV_OK;
+}
+
+template <typename T, int D>
+static dsv_status bwd_dq_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                            const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO,
                            void *dQ, float *delta, hipStream_t st)
 {
     KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
-    for (int t = 0; t < n_tabs; ++t) {
-        if (wave_per_row(p, SweepLanes<T, D>::dq, 1600)) {
-            hipLaunchKernelGGL((sparse_bwd_dq_wave_kernel<T, D, SweepLanes<T, D>::dq>), dim3((p.L + 3) / 4, tabs[t].n), dim3(256), 0, st,
-                               (const T *)Q, (const T *)K, (const T *)V, idx, (const T *)O, lse, (const T *)dO, (T *)dQ, delta, p.L,
-                               p.scale, tabs[t]);
-            DSV_LAUNCH_CHECK();
-            continue;
-        }
-        dim3 qgrid((p.L + 256 / SweepLanes<T, D>::dq - 1) / (256 / SweepLanes<T, D>::dq), tabs[t].n);
-        hipLaunchKernelGGL((sparse_bwd_dq_kernel<T, D, SweepLanes<T, D>::dq>), qgrid, dim3(256), 0, st, (const T *)Q, (const T *)K,
-                           (const T *)V, idx, (const T *)O, lse, (const T *)dO, (T *)dQ, delta, p.L, p.scale, tabs[t]);
-        DSV_LAUNCH_CHECK();
+    if constexpr (sizeof(T) == 4) {
+        if (p.flags & DSV_FLAG_SORTED_INDEX)
+            return bwd_dq_c<T, D, true>(p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, dO, dQ, delta, st);
     }
-    return DSV_OK;
+    return bwd_dq_c<T, D, false>(p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, dO, dQ, delta, st);
 }
 
 template <typename T, int D>
@@ -330,17 +338,17 @@ static dsv_status bwd_dkdv_t(const dsv_problem &p, const HeadTable *tabs, int n_
         return DSV_EUNSUPPORTED;                                        \
     } while (0)
 
-dsv_status launch_sparse_fwd(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+dsv_status launch_sparse_fwd(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                              const void *V, const int32_t *idx, void *O, float *lse, hipStream_t st)
 {
-    DSV_DISPATCH_TD(fwd_t, p, tabs, n_tabs, Q, K, V, idx, O, lse, st);
+    DSV_DISPATCH_TD(fwd_t, p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, st);
 }
 
-dsv_status launch_bwd_dq(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+dsv_status launch_bwd_dq(const dsv_problem &p, const HeadTable *tabs, int n_tabs, bool waves, const void *Q, const void *K,
                          const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO, void *dQ,
                          float *delta, hipStream_t st)
 {
-    DSV_DISPATCH_TD(bwd_dq_t, p, tabs, n_tabs, Q, K, V, idx, O, lse, dO, dQ, delta, st);
+    DSV_DISPATCH_TD(bwd_dq_t, p, tabs, n_tabs, waves, Q, K, V, idx, O, lse, dO, dQ, delta, st);
 }
 
 dsv_status launch_bwd_dkdv(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,

@@ -301,7 +301,7 @@ template <int LPR> struct StagedIndex {
 
 // positions [tb, te) of `row`; all lanes of the group call with the same arguments.  stage: the
 // group's kStage-entry LDS slot (16-byte aligned); s: this lane's number inside the group.  whole: this thread's column of
-// [D / LPR + 2][256] floats of LDS (FOLD; else unused).
+// [D / LPR + 2][256] floats of LDS (FOLD; else unused; the dq sweep: [2 D / LPR + 1][256]).
 template <typename T, int D, int LPR, bool FINE, bool FOLD>
 __device__ __forceinline__ void fwd_sweep(FwdState<D / LPR> &st, const RowChunk<T, D / LPR> &q, const T *__restrict__ Kh,
                                           const T *__restrict__ Vh, uint32_t lane_off, const int32_t *__restrict__ row,
@@ -333,15 +333,17 @@ template <int CH> struct DqState {
     float delta;
     float a[CH], b[CH];  // a: the centred sum C
 };
-template <int CH> __device__ __forceinline__ void fold(DqState<CH> &whole, DqState<CH> &part)
+template <int CH> __device__ __forceinline__ void fold(float *whole, DqState<CH> &part, bool first)  // as the forward's
 {
-    whole.delta += part.delta;
-    part.delta = 0.f;
+    auto add = [&](float &w, float &x) {
+        w = first ? x : w + x;
+        x = 0.f;
+    };
+    add(whole[0], part.delta);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        whole.a[c] += part.a[c];
-        whole.b[c] += part.b[c];
-        part.a[c] = part.b[c] = 0.f;
+        add(whole[256 * (2 * c + 1)], part.a[c]);
+        add(whole[256 * (2 * c + 2)], part.b[c]);
     }
 }
 
@@ -380,10 +382,10 @@ template <typename T, int D, int LPR, bool FOLD>
 __device__ __forceinline__ void dq_sweep(DqState<D / LPR> &st, const RowChunk<T, D / LPR> &q,
                                          const RowChunk<T, D / LPR> &go, const T *__restrict__ Kh,
                                          const T *__restrict__ Vh, uint32_t lane_off, const int32_t *__restrict__ row,
-                                         int tb, int te, float c2, float lse2, float delta0, int32_t *stage, int s)
+                                         int tb, int te, float c2, float lse2, float delta0, int32_t *stage, int s,
+                                         float *whole)
 {
     if (tb >= te) return;
-    DqState<D / LPR> whole = st;  // nothing yet
     StagedIndex<LPR> si;
     si.request(row, tb, te, s);
     for (int c0 = tb; c0 < te; c0 += kStage) {
@@ -399,11 +401,15 @@ __device__ __forceinline__ void dq_sweep(DqState<D / LPR> &st, const RowChunk<T,
 #endif
         for (; it + 2 <= n; it += 2) dq_step<T, D, LPR, false>(st, q, go, Kh, Vh, lane_off, stage + it, 2, c2, lse2, delta0);
         if (it < n) dq_step<T, D, LPR, true>(st, q, go, Kh, Vh, lane_off, stage + it, n - it, c2, lse2, delta0);
-        if (FOLD && (c0 - tb) % kFold == kFold - kStage) fold(whole, st);
+        if (FOLD && (c0 - tb) % kFold == kFold - kStage) fold(whole, st, c0 - tb < kFold);
     }
-    if constexpr (FOLD) {
-        fold(whole, st);
-        st = whole;
+    if (FOLD && te - tb > kFold - kStage) {  // folded at least once
+        st.delta += whole[0];
+#pragma unroll
+        for (int c = 0; c < D / LPR; ++c) {
+            st.a[c] += whole[256 * (2 * c + 1)];
+            st.b[c] += whole[256 * (2 * c + 2)];
+        }
     }
 }
 

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_split_kernel(const T *__res
     __shared__ __align__(16) int32_t stage_all[256 / LPR][kStage];  // one index staging slot per row group
     int32_t *stage = stage_all[threadIdx.x / LPR];
     dq_sweep<T, D, LPR, false>(st, q, go, K + head_base, V + head_base, (uint32_t)LL::off(s), row, tb, te, scale * kLog2e,
-                   lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s);
+                   lse[(int64_t)bh * L + i] * kLog2e, delta0, stage, s, (float *)nullptr);
     if (live) {
         const int64_t slot_id = ((int64_t)bh * L + i) * pl.S + range;
         store_acc<T, D, LPR>(pa + slot_id * D, s, st.a);
