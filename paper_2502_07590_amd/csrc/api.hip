@@ -770,8 +770,8 @@ GroupedFwdGeneral grouped_fwd_general(const dsv_problem &p)
     return w;
 }
 
-// The key-major step of the group kernels' cases: heads by unions or by the per-query sweep on the lists of groups, as the device
-// finds (launch_union_choice), both with the same ranges of queries -- one where 8192 rows hold them all.
+// The key-major step of the group kernels' cases: by unions or by the per-query sweep on the lists of groups, as the device
+// finds (launch_union_prepare), both with the same ranges of queries -- one where 8192 rows hold them all.
 struct GroupedKeyLayout {
     StepLayout step;
     size_t use, total;
@@ -786,7 +786,7 @@ GroupedKeyLayout grouped_key_layout(const dsv_problem &p)
     }
     place_step(p, w.step);
     w.use = w.step.total;
-    w.total = align_up(w.use + (size_t)p.B * p.H * 4, 256);
+    w.total = w.use + 256;
     return w;
 }
 
@@ -920,15 +920,15 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
         const int G = group_size(*g);
         const GroupedKeyLayout kw = grouped_key_layout(*p);
         const BwdSplitWorkspace b = step_buffers(ws + w.step, kw.step);
-        int32_t *use = reinterpret_cast<int32_t *>(ws + w.step + kw.use);
+        const bool always = union_limit(*p) >= 16;
+        int32_t *use = always ? nullptr : reinterpret_cast<int32_t *>(ws + w.step + kw.use);
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, stream);  // both forms together
-        st = launch_pack_rowstat(lsep, deltap, b.rowstat, (int64_t)p->B * p->H * p->L, stream);
-        if (st != DSV_OK) return st;
-        st = launch_union_choice(*p, G, tabs.data(), (int)tabs.size(), idx_t_g, col_ptr, use, stream);
+        st = launch_union_prepare(*p, G, tabs[0], idx_t_g, col_ptr, lsep, deltap, b.rowstat, use, stream);
         if (st != DSV_OK) return st;
         st = launch_grouped_dkdv(*p, G, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, ws + w.gop, dK, dV, kw.step.plan, b,
                                  use, stream);
         if (st != DSV_OK) return st;
+        if (always) return kw.step.plan.S > 1 ? launch_dkdv_merge_bf16_128(*p, dK, dV, kw.step.plan, b, stream) : DSV_OK;
         return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, lsep, deltap, ws + w.gop, dK, dV,
                                      kw.step.plan, b, stream, G, use);
     }

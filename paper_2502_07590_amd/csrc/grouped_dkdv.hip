@@ -6,7 +6,7 @@
 // the matrix cores with a mask for the (group, key) pairs that are not selected.  Neighbouring keys of the token grid are
 // selected by much the same groups: on spatially smooth inputs the union of 16 keys is 3.2 times a single list, so that
 // a step of 512 (query, key) pairs holds 160 selected ones.  Keys chosen independently of their neighbours (10 times at 6 % kept)
-// are better served by the per-query sweep on the lists of groups; union_choice_kernel looks, head by head.
+// are better served by the per-query sweep on the lists of groups; union_prepare_kernel looks.
 //
 //   S^T = Q_u K^T, dP^T = dO_u V^T   v_mfma_f32_16x16x32_bf16, A = 16 gathered rows as they come from memory (lane = row
 //        l % 16, channels 32 m + 8 (l / 16): one load instruction touches whole 64-byte sectors), B = the keys' K and V rows,
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
     int slot, range, kb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nkb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
-    if (!use[bh]) return;
+    if (use && !*use) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, g4 = lane >> 4;
     UnionWave &sh = sh_all[wave];
@@ -345,20 +345,30 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
     }
 }
 
-// Whether the keys of a head go by unions: use[bh] = 1 where the union of 16 neighbouring lists, measured on kChoiceSamples blocks of
-// 16 keys (of long lists the groups of one window), is at most 5.5 times a list -- in queries per step, of which a group
-// size that does not divide 32 leaves some unused.  Measured, L = 32768, k = 2048, 2 x 2 x 2, per four heads: union 3.2 times a
-// list: 3.5 ms by unions, 5.8 by the per-query sweep on the lists of groups; 10 times (keys chosen independently): 9.5, 5.6.
-// A wave per sample, four lanes per key.
+// Whether a call goes by unions: *use = 1 where the union of 16 neighbouring lists, measured on kChoiceSamples blocks of 16 keys
+// of the call's (first 64) heads (of long lists the groups of one window), is at most `limit` times a list -- in queries per
+// step, of which a group size that does not divide 32 leaves some unused.  One answer for all heads: two forms side by side leave
+// each other's launches short (four heads of 8192, k = 204, two of each: 882 us; all by unions 648, all by the sweep 828).  A wave
+// per sample, four lanes per key, in block 0; the others pack the row statistics meanwhile.
 constexpr int kChoiceSamples = 16;
 constexpr int kChoiceGroups = 8192;
-__global__ __launch_bounds__(64 * kChoiceSamples) void union_choice_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col,
-                                                                           int L, int G, HeadTable tab, int32_t *__restrict__ use)
+__global__ __launch_bounds__(64 * kChoiceSamples) void union_prepare_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col,
+                                                                            int L, int G, HeadTable tab, float limit,
+                                                                            const float *__restrict__ lse,
+                                                                            const float *__restrict__ delta,
+                                                                            float2 *__restrict__ rowstat, int64_t rows,
+                                                                            int32_t *__restrict__ use)
 {
     __shared__ uint32_t bm_all[kChoiceSamples][kChoiceGroups / 32];
     __shared__ int32_t sums[2];  // entries, groups in the unions
-    const int slot = blockIdx.x, bh = tab.bh[slot];
+    const int chooser = use ? 1 : 0;
+    if ((int)blockIdx.x >= chooser) {
+        const int64_t e = (int64_t)(blockIdx.x - chooser) * (64 * kChoiceSamples) + threadIdx.x;
+        if (e < rows) rowstat[e] = make_float2(lse[e] * kLog2e, delta[e]);
+        return;
+    }
     const int lane = threadIdx.x & 63, sample = threadIdx.x >> 6;
+    const int slot = sample % tab.n, bh = tab.bh[slot];
     const int Lq = L / G, blocks = (L + kUnionKeys - 1) / kUnionKeys;
     uint32_t *bm = bm_all[sample];
     for (int w = lane; w < kChoiceGroups / 32; w += 64) bm[w] = 0u;
@@ -397,18 +407,33 @@ __global__ __launch_bounds__(64 * kChoiceSamples) void union_choice_kernel(const
     if (groups) atomicAdd(&sums[1], groups);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const int64_t slots = 32 / G * G;  // queries of a step that are used
-        use[bh] = (int64_t)sums[1] * 16 * 32 * 2 <= 11 * (int64_t)sums[0] * slots;
+        const int slots = 32 / G * G;  // queries of a step that are used
+        *use = (float)sums[1] * 16.f * 32.f <= limit * (float)sums[0] * (float)slots;
     }
 }
 
-dsv_status launch_union_choice(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
-                               int32_t *use, hipStream_t st)
+// Times of the two forms in us, for P pairs and R rows: unions 3.1e-6 (P + 118 R) per list that a union is long, the sweep 1.5e-5 P +
+// 0.0066 R + 39 (segments, row order, more launches).  Fitted to 462 problems (1 to 12 heads of 2048 to 32768 keys, 1 to 16 % kept,
+// groups of 4, 8 and 32, smooth and independent inputs, unions 2.3 to 15 lists long), and a little to the sweep's side of the fit.
+// L = 32768, k = 2730, 2 x 2 x 2, four heads, the whole backward: unions of 3 lists 6.9 ms, sweep 11.0; of 9 lists (keys chosen
+// independently) 13.4, 9.6; L = 16384, 5.7 lists: 4.94, 4.95; one head of 4096, k = 102, 5.8 lists: 125 us, 207; 13.4 lists: 123, 165.  Where
+// any union pays (16 lists), nothing is measured and the sweep is not launched: 25 us.
+double union_limit(const dsv_problem &p)
 {
-    for (int t = 0; t < n_tabs; ++t) {
-        hipLaunchKernelGGL(union_choice_kernel, dim3(tabs[t].n), dim3(64 * kChoiceSamples), 0, st, lists, col, p.L, G, tabs[t], use);
-        DSV_LAUNCH_CHECK();
-    }
+    double pairs = 0;
+    for (int h = 0; h < p.H; ++h) pairs += (double)p.B * p.L * p.k_per_head[h];
+    const double rows = (double)p.B * p.H * p.L;
+    auto limit = [&](double fixed) { return (1.5e-5 * pairs + 0.0066 * rows + fixed) / (3.1e-6 * (pairs + 118 * rows)); };
+    return limit(39 + 25) >= 16 ? 16 : limit(39);
+}
+
+dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable &tab, const int32_t *lists, const int64_t *col, const float *lse,
+                                const float *delta, float2 *rowstat, int32_t *use, hipStream_t st)
+{
+    const int64_t rows = (int64_t)p.B * p.H * p.L, block = 64 * kChoiceSamples;
+    hipLaunchKernelGGL(union_prepare_kernel, dim3((unsigned)((rows + block - 1) / block) + (use ? 1 : 0)), dim3((unsigned)block), 0, st, lists,
+                       col, p.L, G, tab, (float)union_limit(p), lse, delta, rowstat, rows, use);
+    DSV_LAUNCH_CHECK();
     return DSV_OK;
 }
 

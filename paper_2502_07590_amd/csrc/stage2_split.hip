@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
 {
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
-    if (skip && skip[bh]) return;
+    if (skip && *skip) return;
     const int np = pl.S + 1;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (int64_t)L * np) return;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
     int slot, range, kb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
-    if (skip && skip[bh]) return;
+    if (skip && *skip) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / LPR, s = lane % LPR;
     const int64_t jpos = (int64_t)kb * (4 * RPW) + wave * RPW + grp;
@@ -287,14 +287,14 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void sparse_bwd_dkdv_merge_kernel(const float *__restrict__ pdk,
                                                                     const float *__restrict__ pdv,
                                                                     T *__restrict__ dK, T *__restrict__ dV,
-                                                                    int64_t n_rows, int S, float scale, int L,
+                                                                    int64_t n_rows, int S, float scale,
                                                                     const int32_t *__restrict__ skip)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
     const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
-    if (row >= n_rows || (skip && skip[row / L])) return;
+    if (row >= n_rows || (skip && *skip)) return;
     float a[CH], b[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) { a[c] = 0.f; b[c] = 0.f; }
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void seglen_hist_kernel(const int32_t *__restr
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
-    if (skip && skip[bh]) return;
+    if (skip && *skip) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk;
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256) void seglen_scatter_kernel(const int32_t *__re
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
-    if (skip && skip[bh]) return;
+    if (skip && *skip) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk, row1 = min(row0 + kSeglenChunk, L);
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -473,13 +473,6 @@ static dsv_status launch_row_order(const dsv_problem &p, const HeadTable *tabs, 
     return DSV_OK;
 }
 
-dsv_status launch_pack_rowstat(const float *lse, const float *delta, float2 *out, int64_t n, hipStream_t st)
-{
-    hipLaunchKernelGGL(pack_rowstat_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, lse, delta, out, n);
-    DSV_LAUNCH_CHECK();
-    return DSV_OK;
-}
-
 template <typename T, int D>
 static dsv_status fwd_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
                               const void *V, const int32_t *idx, void *O, float *lse, const SplitPlan &pl,
@@ -540,6 +533,17 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
 }
 
 template <typename T, int D>
+static dsv_status dkdv_merge_t(const dsv_problem &p, void *dK, void *dV, const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st,
+                               const int32_t *skip)
+{
+    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
+    hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, w.pa, w.pb,
+                       (T *)dK, (T *)dV, n_rows, pl.S, p.scale, skip);
+    DSV_LAUNCH_CHECK();
+    return DSV_OK;
+}
+
+template <typename T, int D>
 static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
                                    const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                    const float *lse, const float *delta, const void *dO, void *dK, void *dV,
@@ -552,8 +556,10 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
     dsv_status rc = launch_segments(p, tabs, n_tabs, pl, idxT, col, w.seg, st, ge, skip);
     if (rc != DSV_OK) return rc;
     const int64_t nrows = (int64_t)nbh * p.L;
-    if (!skip) rc = launch_pack_rowstat(lse, delta, w.rowstat, nrows, st);
-    if (rc != DSV_OK) return rc;
+    if (!skip) {
+        hipLaunchKernelGGL(pack_rowstat_kernel, dim3((unsigned)((nrows + 255) / 256)), dim3(256), 0, st, lse, delta, w.rowstat, nrows);
+        DSV_LAUNCH_CHECK();
+    }
     rc = launch_row_order(p, tabs, n_tabs, pl, w.seg, w.hist, w.order, st, skip);
     if (rc != DSV_OK) return rc;
     {
@@ -573,11 +579,7 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
             DSV_LAUNCH_CHECK();
         }
     }
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st,
-                       w.pa, w.pb, (T *)dK, (T *)dV, n_rows, pl.S, p.scale, p.L, pl.S > 1 ? nullptr : skip);
-    DSV_LAUNCH_CHECK();
-    return DSV_OK;
+    return dkdv_merge_t<T, D>(p, dK, dV, pl, w, st, pl.S > 1 ? nullptr : skip);
 }
 
 // ---- pieces of the split plan used by the query-grouped kernels as well --------------------------------------
@@ -615,6 +617,12 @@ dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const float *pa, const
                        pdelta, (const bf16_t *)O, (const bf16_t *)dO, (bf16_t *)dQ, delta, n_rows, S, p.scale);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
+}
+
+dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, void *dK, void *dV, const SplitPlan &pl, const BwdSplitWorkspace &w,
+                                      hipStream_t st)
+{
+    return dkdv_merge_t<bf16_t, 128>(p, dK, dV, pl, w, st, nullptr);
 }
 
 #define DSV_DISPATCH_TD(FN, ...)                                        \
