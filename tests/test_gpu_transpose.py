@@ -46,8 +46,10 @@ def test_transpose_is_a_stable_sort_of_the_pairs(L, ks, ascending):
         off += rows.numel()
 
 
-# rows of 512 bytes of K and V: a head passes 3 MB above 6144 keys; from there rows in any order are sorted first
-@pytest.mark.parametrize("dtype,L,d,ks", [("bf16", 6145, 128, [300, 1]), ("f32", 6200, 64, [6200]), ("bf16", 20011, 64, [777])])
+# rows of 512 bytes of K and V: a head passes 3 MB above 6144 keys; from there rows in any order are sorted first, up to 524288
+# keys (a row's bitmap: 64 KB of LDS)
+@pytest.mark.parametrize("dtype,L,d,ks", [("bf16", 6145, 128, [300, 1]), ("f32", 6200, 64, [6200]), ("bf16", 20011, 64, [777]),
+                                          ("bf16", 516097, 64, [5]), ("bf16", 524288, 64, [5])])
 def test_backward_of_rows_in_any_order_equals_that_of_the_sorted_rows(dtype, L, d, ks):
     g = torch.Generator(device="cuda").manual_seed(L)
     td = torch.float32 if dtype == "f32" else torch.bfloat16
