@@ -374,18 +374,20 @@ DSV_API dsv_status dsv_kernel_timing(int32_t enable);
 DSV_API dsv_status dsv_kernel_ms(int32_t span, float *ms);
 
 /* How stage 1 finds every query's threshold score (the k-th largest; paper Sec. "Critical KV Estimation with
- * Kernel Fusion").  Both methods are exact and give identical results; the choice only affects speed.
- *   0  automatic (default): the windowed search -- a key sample brackets the threshold, then two sweeps over
- *      the keys -- for heads with L >= 16384 and k <= L/4 whose sample (2048 to 16384 keys, at most L/8) holds
- *      enough keys on both sides of the threshold; else the radix search (four sweeps, 8 bits each);
+ * Kernel Fusion").  All methods are exact and give identical results; the choice only affects speed.
+ *   0  automatic (default): up to 2048 keys one kernel that forms every score once, finds the threshold among
+ *      them and writes the index (DSV_KERNEL_THRESHOLD and DSV_KERNEL_EMIT both report that one kernel); the
+ *      windowed search -- a key sample brackets the threshold, then two sweeps over the keys -- for heads with
+ *      L >= 16384 and k <= L/4 whose sample (2048 to 16384 keys, at most L/8) holds enough keys on both sides
+ *      of the threshold; else the radix search (four sweeps, 8 bits each);
  *   1  always the radix search;
- *   2  the windowed search for every head it can serve at all (L >= 4096, sample up to L/2 keys).
+ *   2  the windowed search for every head it can serve at all (L >= 4096, sample up to L/2 keys); else as 0.
  * Query tiles the windowed search cannot settle (threshold outside the bracket, massive ties) go through the
  * radix search afterwards, inside the same call.  Process-wide; for tests and measurements.  Returns the
  * previous mode; a mode outside 0..2 changes nothing and returns -1. */
 DSV_API int32_t dsv_threshold_search(int32_t mode);
 /* Which search a head that keeps k of L keys gets under the current mode: the number of keys the windowed
- * search samples for it (a multiple of 32), or 0 when the head takes the radix search.  Host arithmetic only. */
+ * search samples for it (a multiple of 32), or 0 when the head takes another one.  Host arithmetic only. */
 DSV_API int32_t dsv_threshold_sample_keys(int32_t L, int32_t k);
 
 /* Pure-gather probe: the practical ceiling of the vector memory path (L2 -> vector L1 -> registers) for the

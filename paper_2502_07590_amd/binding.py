@@ -509,7 +509,7 @@ KERNEL_SPANS = ("fwd_sweep", "dq_sweep", "dkdv_sweep", "threshold", "emit", "emi
 
 
 def threshold_search(mode: int) -> int:
-    """dsv_threshold_search: 0 automatic, 1 radix search, 2 windowed search wherever it fits; returns the old mode."""
+    """dsv_threshold_search: 0 automatic, 1 always the radix search, 2 windowed search wherever it fits; returns the old mode."""
     old = load_library().dsv_threshold_search(int(mode))
     if old < 0:
         raise ValueError(f"dsv_threshold_search: mode {mode} is not 0, 1 or 2")
@@ -517,7 +517,7 @@ def threshold_search(mode: int) -> int:
 
 
 def threshold_sample_keys(L: int, k: int) -> int:
-    """dsv_threshold_sample_keys: keys the windowed threshold search samples for a head keeping k of L (0: radix search)."""
+    """dsv_threshold_sample_keys: keys the windowed threshold search samples for a head keeping k of L (0: another search)."""
     return int(load_library().dsv_threshold_sample_keys(int(L), int(k)))
 
 

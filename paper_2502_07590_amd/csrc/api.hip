@@ -488,9 +488,10 @@ dsv_status dsv_lowrank_topk_noalloc(const dsv_problem *p, const void *Q, const v
     if (need > kNoallocBytes) return DSV_EWORKSPACE;
     void *ws = noalloc_scratch(&st);
     if (!ws) return st;
-    // every buffer of the layout is written by the kernels of this call before it is read (projections by
-    // project_kernel, thresholds and tie budgets by the first radix pass), so what an earlier call left in
-    // the array does not matter
+    // whatever a kernel of this call reads from the layout, a kernel of this call has written before (projections by
+    // project_kernel, thresholds and tie budgets by the first radix pass or by the windowed search; the kernel for short
+    // sequences writes the thresholds and neither writes nor reads the tie budgets), so what an earlier call left in the
+    // array does not matter
     return lowrank_topk_impl(p, nullptr, Q, K, Wq, Wk, idx, nullptr, nullptr, false, ws, kNoallocBytes, hip_stream);
 }
 

@@ -2,6 +2,8 @@
 score first, lower key on ties), whatever kernels an L, a k and a type lead through, and idx_t its transpose."""
 from __future__ import annotations
 
+import ctypes
+
 import pytest
 import torch
 
@@ -42,6 +44,40 @@ def _check(p, Q, K, Wq, Wk):
 def test_short_sequences(L, ks, dtype, d, r, ties):
     Q, K, Wq, Wk = _inputs(2, L, d, r, dtype, ties, L + r)
     _check(dsv.Problem(1, 2, L, d, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+
+
+def _all_indices(p, grp, Q, K, Wq, Wk):
+    return (dsv.lowrank_topk(p, Q, K, Wq, Wk), *dsv.lowrank_topk_t(p, Q, K, Wq, Wk), *dsv.lowrank_topk_grouped(p, grp, Q, K, Wq, Wk))
+
+
+def _launches(call):
+    """Nodes of the graph that capturing the call gives: its kernel launches."""
+    graph, n = torch.cuda.CUDAGraph(keep_graph=True), ctypes.c_size_t(0)
+    with torch.cuda.graph(graph):
+        call()
+    assert ctypes.CDLL("libamdhip64.so").hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("grid,ks", [((1, 1, 2), [1, 2]), ((1, 5, 10), [49, 3]), ((8, 8, 8), [100, 511]), ((3, 19, 9), [7, 64]),
+                                     ((4, 16, 32), [1, 300])])
+@pytest.mark.parametrize("dtype,d,r", [("f32", 64, 16), ("bf16", 128, 32)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_the_radix_search_is_to_be_had_for_short_sequences(grid, ks, dtype, d, r, ties):
+    """Mode 1 is the radix search at every length.  Where the automatic mode takes one kernel after the projection, the four
+    passes and the emission give the same bits; the launches that a capture records show that they ran."""
+    L = grid[0] * grid[1] * grid[2]
+    Q, K, Wq, Wk = _inputs(2, L, d, r, dtype, ties, L + r)
+    p, grp = dsv.Problem(1, 2, L, d, r, dtype, ks, 0.1), dsv.Grouping(grid, (1, 1, 2 if grid[2] % 2 == 0 else grid[2]))
+    one, launches_one = _all_indices(p, grp, Q, K, Wq, Wk), _launches(lambda: dsv.lowrank_topk(p, Q, K, Wq, Wk))
+    assert dsv.threshold_search(1) == 0
+    try:
+        radix, launches = _all_indices(p, grp, Q, K, Wq, Wk), _launches(lambda: dsv.lowrank_topk(p, Q, K, Wq, Wk))
+    finally:
+        dsv.threshold_search(0)
+    assert launches == launches_one + 4 == 6
+    for a, b in zip(one, radix):
+        assert torch.equal(a, b)
 
 
 # above 2048 keys: radix passes, from 16384 on the windowed search; the emission by blocks below 2048 query tiles (65536
