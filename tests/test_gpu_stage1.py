@@ -220,6 +220,13 @@ def _both_searches(p, Q, K, Wq, Wk):
     return radix, window
 
 
+def _sampled_keys(L, n):
+    """The keys that a sample of n of L takes: one at a scrambled place of each stride of L / n keys."""
+    i, stride = np.arange(n, dtype=np.uint64), L // n
+    place = (((i * 0x9E3779B1) & 0xFFFFFFFF) * stride) >> 32
+    return (i * stride + place).astype(np.int64)
+
+
 @pytest.mark.parametrize("dtype,L,d,r,ks", [("bf16", 16384, 128, 16, [1024, 64, 4096]), ("bf16", 5000, 64, 32, [313, 2500, 1]),
                                             ("f32", 4100, 64, 16, [4100, 4099, 256]), ("bf16", 8192, 128, 64, [512, 7])])
 def test_windowed_search_gives_the_radix_search_result(search_mode, dtype, L, d, r, ks):
@@ -258,14 +265,24 @@ def test_windowed_search_hands_ties_and_bad_samples_to_the_radix_search(search_m
     idx = _run_topk(p1, torch.zeros_like(case.dev["Q"]), case.dev["K"], case.dWq, case.dWk)
     assert np.array_equal(idx.reshape(L, 37), np.tile(np.arange(37, dtype=np.int32), (L, 1)))
 
-    # the sample takes key rows i * stride + stride / 2 (stride = L / 2048): shrink exactly those rows
+    # shrink exactly the sampled keys, whose scores then bracket nothing, and enlarge exactly those: both brackets miss the
+    # thresholds, from below and from above
     case = Case(make_cfg(L, d, r, 2, "bf16", basis_rank=32, scale_num=2.0), [256, 1000], names=("Q", "K"))
     p2 = case.problem(dsv)
-    K = case.dev["K"].clone()
-    stride = L // 2048
-    K[:, :, stride // 2::stride, :] *= 1.0 / 64
-    radix, window = _both_searches(p2, case.dev["Q"], K, case.dWq, case.dWk)
-    assert np.array_equal(radix, window)
+    n = dsv.threshold_sample_keys(L, 256)
+    assert n == dsv.threshold_sample_keys(L, 1000) > 0
+    rows = _sampled_keys(L, n)
+    for factor in (1.0 / 64, 64.0):
+        K = case.dev["K"].clone()
+        K[:, :, torch.from_numpy(rows).cuda(), :] *= factor
+        radix, window = _both_searches(p2, case.dev["Q"], K, case.dWq, case.dWk)
+        assert np.array_equal(radix, window), f"sampled keys times {factor}"
+        for h, k in enumerate((256, 1000)):   # the bracket spans the sample's ranks n k / L - m to n k / L + m
+            mean = n * k / L
+            m = 6.0 * (mean * (1.0 - k / L)) ** 0.5 + 2.0
+            taken = np.isin(case.idx_rows(radix, h), rows).sum(1)
+            outside = taken < mean - m if factor < 1 else taken > mean + m
+            assert outside.mean() > 0.99, f"sampled keys times {factor}, head {h}: {outside.mean()}"
 
 
 def test_windowed_search_with_transposed_and_grouped_emission(search_mode):
