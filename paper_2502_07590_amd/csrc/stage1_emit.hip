@@ -286,10 +286,22 @@ __global__ __launch_bounds__(64) void emit_t_kernel(const T *__restrict__ Qlr, c
 }
 
 // ------------------------------------------------------------------------------------ host
-// Whether the query-major emission takes a block per 32 queries instead of a wave: below two waves per SIMD.  Measured, waves
-// against blocks: 512 query tiles (the groups of four heads of L = 32768), 691 : 180 us; 3804 tiles of r = 32, 813 : 842; 4096
-// tiles of r = 16, 1135 : 1090.
-static bool emit_by_blocks(int64_t tiles) { return tiles < 2048; }
+// Whether the query-major emission takes a block per 32 queries instead of a wave.  A lone wave is bound by latency, and blocks
+// hide it while there are few: up to two tiles per SIMD, three where rows are short (the writes of a block share one
+// barrier loop), one and a half of that where the matrix products take longest.  Measured over 280 pairs of times (tiles, waves :
+// blocks, us): r = 16, L = 16384, k = L / 16, 512 tiles 313 : 81, 2048 338 : 287, 4096 505 : 548; k = L / 64, 2048 300 : 205, 3072
+// 335 : 306; grouped, L = 131072, k = L / 16, 3072 tiles 4016 : 5051.  r = 64, L = 16384, 1024 tiles 383 : 304, 1536 403 : 448.
+// fp32, r = 16, 512 tiles 422 : 269, 1536 718 : 790; r = 64, L = 8192, 256 tiles 393 : 259, 768 690 : 781.  Short rows of keys pay for
+// the barriers sooner (fp32, L = 2080, 520 tiles, 62 : 75).
+template <typename T, int R>
+static bool emit_by_blocks(int L, int qtiles, const HeadTable &tab)
+{
+    const int64_t tiles = (int64_t)qtiles * tab.n;
+    if (sizeof(T) == 4 || R == 64) return tiles <= (int64_t)(sizeof(T) == 4 && R > 16 ? 512 : 1024) * std::min(L, 5120) / 5120;
+    int64_t kept = 0;
+    for (int s = 0; s < tab.n; ++s) kept += tab.k[s];
+    return tiles < 2048 || (tiles <= 3072 && L >= 8192 && kept * 32 <= (int64_t)L * tab.n);
+}
 
 template <typename T, int R>
 static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs, int n_tabs, const void *Qlr,
@@ -304,7 +316,7 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
         KernelSpan span(DSV_KERNEL_EMIT, st);
         for (int t = 0; t < n_tabs; ++t) {
             dim3 grid(qtiles, tabs[t].n);
-            if (emit_by_blocks((int64_t)qtiles * tabs[t].n))
+            if (emit_by_blocks<T, R>(p.L, qtiles, tabs[t]))
                 hipLaunchKernelGGL((emit_block_kernel<T, R>), grid, dim3(64 * kEmitWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem,
                                    b.idx, b.jcut, b.tile_flag);
             else

@@ -80,13 +80,23 @@ def test_the_radix_search_is_to_be_had_for_short_sequences(grid, ks, dtype, d, r
         assert torch.equal(a, b)
 
 
-# above 2048 keys: radix passes, from 16384 on the windowed search; the emission by blocks below 2048 query tiles (65536
-# queries), by waves from there on
+# above 2048 keys: radix passes, from 16384 on the windowed search
 @pytest.mark.parametrize("H,L,ks,r,ties", [(1, 2080, [2080], 16, False), (2, 5001, [5, 900], 64, True), (1, 16411, [1500], 16, False),
                                            (3, 22000, [1100, 2, 5000], 16, False)])
 def test_longer_sequences(H, L, ks, r, ties):
     Q, K, Wq, Wk = _inputs(H, L, 64, r, "bf16", ties, L)
     _check(dsv.Problem(1, H, L, 64, r, "bf16", ks, 0.1), Q, K, Wq, Wk)
+
+
+# the emission by blocks and by waves, on either side of the line between them: query tiles against the length, the type and
+# the rank, and for short rows of bf16 half as many again
+@pytest.mark.parametrize("dtype,H,L,k,r", [("f32", 6, 2080, 130, 16), ("f32", 7, 2080, 130, 16), ("f32", 3, 2080, 40, 64), ("f32", 4, 2080, 40, 64),
+                                           ("f32", 4, 2080, 2080, 32), ("bf16", 6, 2080, 9, 64), ("bf16", 7, 2080, 1040, 64),
+                                           ("bf16", 31, 2080, 65, 32), ("bf16", 32, 2080, 65, 32), ("bf16", 9, 8192, 256, 16), ("bf16", 9, 8192, 257, 16)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_emission(dtype, H, L, k, r, ties):
+    Q, K, Wq, Wk = _inputs(H, L, 64, r, dtype, ties, H + r)
+    _check(dsv.Problem(1, H, L, 64, r, dtype, [k] * H, 0.1), Q, K, Wq, Wk)
 
 
 def test_smooth_inputs_keep_the_windowed_search():
