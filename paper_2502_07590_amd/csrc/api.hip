@@ -398,7 +398,7 @@ static void *noalloc_scratch(dsv_status *err)
 
 extern "C" {
 
-const char *dsv_version(void) { return "dsv 0.5 (gfx950)"; }
+const char *dsv_version(void) { return "dsv 0.6 (gfx950)"; }
 
 const char *dsv_status_string(dsv_status s)
 {
@@ -787,7 +787,7 @@ GroupedKeyLayout grouped_key_layout(const dsv_problem &p)
     }
     place_step(p, w.step);
     w.use = w.step.total;
-    w.total = w.use + 256;
+    w.total = align_up(w.use + (size_t)p.B * p.H * 4, 256);
     return w;
 }
 
@@ -924,7 +924,7 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
         const bool always = union_limit(*p) >= 16;
         int32_t *use = always ? nullptr : reinterpret_cast<int32_t *>(ws + w.step + kw.use);
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, stream);  // both forms together
-        st = launch_union_prepare(*p, G, tabs[0], idx_t_g, col_ptr, lsep, deltap, b.rowstat, use, stream);
+        st = launch_union_prepare(*p, G, tabs.data(), (int)tabs.size(), idx_t_g, col_ptr, lsep, deltap, b.rowstat, use, stream);
         if (st != DSV_OK) return st;
         st = launch_grouped_dkdv(*p, G, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, ws + w.gop, dK, dV, kw.step.plan, b,
                                  use, stream);

@@ -365,8 +365,8 @@ dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, in
                                  const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G = 1,
                                  const int32_t *skip = nullptr);
 // expand_G > 1: idxT / col hold lists of groups of expand_G queries (tabs[].off the offsets of those lists); the sweep
-// runs on the per-query lists they stand for.  Needs p.L < 2^32 / expand_G.  skip (device, or null): with *skip != 0 something
-// else has swept already, into the partial results (with a single range, into dK and dV); w.rowstat is then filled already.
+// runs on the per-query lists they stand for.  Needs p.L < 2^32 / expand_G.  skip (device, [B*H], or null): heads that something else has
+// swept, into the partial results (with a single range, into dK and dV); w.rowstat is then filled already.
 
 // Device buffers of the selection.  idx_t == nullptr skips the key-major emission (then jcut, cnt,
 // col may be null as well).
@@ -455,11 +455,11 @@ dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs
                                      float *lse, int S, hipStream_t st);
 // dK, dV of the group kernels' cases over unions of lists (grouped_dkdv.hip): Q, dO, w.rowstat in group-major order, lists of groups
 // (tabs built for L / G rows per head).  Writes the partial results of every range, or, with a single range, dK and dV.
-// union_limit: the longest union, in lists, that is worth it (16: any).  launch_union_prepare fills rowstat and, below that, *use;
-// with *use == 0 launch_grouped_dkdv does nothing (use null: always works).
+// union_limit: the longest union, in lists, that is worth it (16: any).  launch_union_prepare fills rowstat and, below that, use
+// [B*H]; launch_grouped_dkdv leaves out heads with use[bh] == 0 (use null: none).
 double union_limit(const dsv_problem &p);
-dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable &tab, const int32_t *lists, const int64_t *col, const float *lse,
-                                const float *delta, float2 *rowstat, int32_t *use, hipStream_t st);
+dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
+                                const float *lse, const float *delta, float2 *rowstat, int32_t *use, hipStream_t st);
 dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
                                const void *V, const int32_t *lists, const int64_t *col, const void *dO, void *dK, void *dV,
                                const SplitPlan &plan, const BwdSplitWorkspace &w, const int32_t *use, hipStream_t st);

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
     int slot, range, kb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nkb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
-    if (use && !*use) return;
+    if (use && !use[bh]) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, g4 = lane >> 4;
     UnionWave &sh = sh_all[wave];
@@ -345,15 +345,19 @@ __global__ __launch_bounds__(256, 2) void grouped_dkdv_kernel(const bf16_t *__re
     }
 }
 
-// Whether a call goes by unions: *use = 1 where the union of 16 neighbouring lists, measured on kChoiceSamples blocks of 16 keys
-// of the call's (first 64) heads (of long lists the groups of one window), is at most `limit` times a list -- in queries per
-// step, of which a group size that does not divide 32 leaves some unused.  One answer for all heads: two forms side by side leave
-// each other's launches short (four heads of 8192, k = 204, two of each: 882 us; all by unions 648, all by the sweep 828).  A wave
-// per sample, four lanes per key, in block 0; the others pack the row statistics meanwhile.
+// Which heads go by unions: use[bh] = 1 where the union of 16 neighbouring lists, measured on kChoiceSamples blocks of 16 keys (of
+// long lists the groups of one window), is at most `limit` times a list -- in queries per step, of which a group size that does not
+// divide 32 leaves some unused.  limit == 0: head by head, each against its own limit, a block per head of the table.  Else
+// one answer for all `heads`, from samples of the table's, in block 0.  A wave per sample, four lanes per key; the other blocks
+// pack the row statistics meanwhile.
 constexpr int kChoiceSamples = 16;
 constexpr int kChoiceGroups = 8192;
+__host__ __device__ inline float union_limit_of(float k, float fixed)
+{
+    return (1.5e-5f * k + 0.0066f + fixed) / (3.1e-6f * (k + 118));
+}
 __global__ __launch_bounds__(64 * kChoiceSamples) void union_prepare_kernel(const int32_t *__restrict__ lists, const int64_t *__restrict__ col,
-                                                                            int L, int G, HeadTable tab, float limit,
+                                                                            int L, int G, HeadTable tab, float limit, int heads,
                                                                             const float *__restrict__ lse,
                                                                             const float *__restrict__ delta,
                                                                             float2 *__restrict__ rowstat, int64_t rows,
@@ -361,14 +365,14 @@ __global__ __launch_bounds__(64 * kChoiceSamples) void union_prepare_kernel(cons
 {
     __shared__ uint32_t bm_all[kChoiceSamples][kChoiceGroups / 32];
     __shared__ int32_t sums[2];  // entries, groups in the unions
-    const int chooser = use ? 1 : 0;
-    if ((int)blockIdx.x >= chooser) {
-        const int64_t e = (int64_t)(blockIdx.x - chooser) * (64 * kChoiceSamples) + threadIdx.x;
+    const int choosers = !use ? 0 : limit == 0.f ? tab.n : 1;
+    if ((int)blockIdx.x >= choosers) {
+        const int64_t e = (int64_t)(blockIdx.x - choosers) * (64 * kChoiceSamples) + threadIdx.x;
         if (e < rows) rowstat[e] = make_float2(lse[e] * kLog2e, delta[e]);
         return;
     }
     const int lane = threadIdx.x & 63, sample = threadIdx.x >> 6;
-    const int slot = sample % tab.n, bh = tab.bh[slot];
+    const int slot = limit == 0.f ? blockIdx.x : sample % tab.n, bh = tab.bh[slot];
     const int Lq = L / G, blocks = (L + kUnionKeys - 1) / kUnionKeys;
     uint32_t *bm = bm_all[sample];
     for (int w = lane; w < kChoiceGroups / 32; w += 64) bm[w] = 0u;
@@ -406,9 +410,13 @@ __global__ __launch_bounds__(64 * kChoiceSamples) void union_prepare_kernel(cons
     if (entries) atomicAdd(&sums[0], entries);
     if (groups) atomicAdd(&sums[1], groups);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int slots = 32 / G * G;  // queries of a step that are used
-        *use = (float)sums[1] * 16.f * 32.f <= limit * (float)sums[0] * (float)slots;
+    const int slots = 32 / G * G;  // queries of a step that are used
+    const float most = limit == 0.f ? union_limit_of((float)tab.k[slot], 0.f) : limit;
+    const int32_t by_unions = (float)sums[1] * 16.f * 32.f <= most * (float)sums[0] * (float)slots;
+    if (limit == 0.f) {
+        if (threadIdx.x == 0) use[bh] = by_unions;
+    } else {
+        for (int h = threadIdx.x; h < heads; h += 64 * kChoiceSamples) use[h] = by_unions;
     }
 }
 
@@ -418,22 +426,36 @@ __global__ __launch_bounds__(64 * kChoiceSamples) void union_prepare_kernel(cons
 // L = 32768, k = 2730, 2 x 2 x 2, four heads, the whole backward: unions of 3 lists 6.9 ms, sweep 11.0; of 9 lists (keys chosen
 // independently) 13.4, 9.6; L = 16384, 5.7 lists: 4.94, 4.95; one head of 4096, k = 102, 5.8 lists: 125 us, 207; 13.4 lists: 123, 165.  Where
 // any union pays (16 lists), nothing is measured and the sweep is not launched: 25 us.
-double union_limit(const dsv_problem &p)
+static double pairs_of(const dsv_problem &p)
 {
     double pairs = 0;
     for (int h = 0; h < p.H; ++h) pairs += (double)p.B * p.L * p.k_per_head[h];
-    const double rows = (double)p.B * p.H * p.L;
-    auto limit = [&](double fixed) { return (1.5e-5 * pairs + 0.0066 * rows + fixed) / (3.1e-6 * (pairs + 118 * rows)); };
+    return pairs;
+}
+double union_limit(const dsv_problem &p)
+{
+    const double pairs = pairs_of(p), rows = (double)p.B * p.H * p.L;
+    auto limit = [&](double fixed) { return union_limit_of((float)(pairs / rows), (float)(fixed / rows)); };
     return limit(39 + 25) >= 16 ? 16 : limit(39);
 }
 
-dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable &tab, const int32_t *lists, const int64_t *col, const float *lse,
-                                const float *delta, float2 *rowstat, int32_t *use, hipStream_t st)
+// Whether heads are chosen one by one: from 5e7 pairs on.  Below, two forms side by side leave each other's launches short.
+// Measured over 169 problems with heads of unlike k (2 to 16 heads of 2048 to 65536 keys, keys chosen independently), one by one against one
+// answer: below 3e6 pairs 1.03 (1.36 at worst), 3e6 to 2e7 1.06 (1.40), 2e7 to 4e8 1.00 (0.95 to 1.06), above 0.975 (0.92 to 1.005).
+static bool choose_by_head(const dsv_problem &p) { return pairs_of(p) >= 5e7; }
+
+dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const int32_t *lists, const int64_t *col,
+                                const float *lse, const float *delta, float2 *rowstat, int32_t *use, hipStream_t st)
 {
-    const int64_t rows = (int64_t)p.B * p.H * p.L, block = 64 * kChoiceSamples;
-    hipLaunchKernelGGL(union_prepare_kernel, dim3((unsigned)((rows + block - 1) / block) + (use ? 1 : 0)), dim3((unsigned)block), 0, st, lists,
-                       col, p.L, G, tab, (float)union_limit(p), lse, delta, rowstat, rows, use);
-    DSV_LAUNCH_CHECK();
+    const bool by_head = choose_by_head(p);
+    const int block = 64 * kChoiceSamples;
+    for (int t = 0; t < (use && by_head ? n_tabs : 1); ++t) {
+        const int64_t rows = t ? 0 : (int64_t)p.B * p.H * p.L;
+        const int choosers = !use ? 0 : by_head ? tabs[t].n : 1;
+        hipLaunchKernelGGL(union_prepare_kernel, dim3((unsigned)((rows + block - 1) / block) + choosers), dim3(block), 0, st, lists, col, p.L, G,
+                           tabs[t], by_head ? 0.f : (float)union_limit(p), p.B * p.H, lse, delta, rowstat, rows, use);
+        DSV_LAUNCH_CHECK();
+    }
     return DSV_OK;
 }
 

@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) void segment_ptr_kernel(const int32_t *__restr
 {
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
-    if (skip && *skip) return;
+    if (skip && skip[bh]) return;
     const int np = pl.S + 1;
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (int64_t)L * np) return;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256) void sparse_bwd_dkdv_split_kernel(const T *__r
     int slot, range, kb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, kb)) return;
     const int bh = tab.bh[slot];
-    if (skip && *skip) return;
+    if (skip && skip[bh]) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane / LPR, s = lane % LPR;
     const int64_t jpos = (int64_t)kb * (4 * RPW) + wave * RPW + grp;
@@ -287,14 +287,14 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void sparse_bwd_dkdv_merge_kernel(const float *__restrict__ pdk,
                                                                     const float *__restrict__ pdv,
                                                                     T *__restrict__ dK, T *__restrict__ dV,
-                                                                    int64_t n_rows, int S, float scale,
+                                                                    int64_t n_rows, int S, float scale, int L,
                                                                     const int32_t *__restrict__ skip)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
     const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
-    if (row >= n_rows || (skip && *skip)) return;
+    if (row >= n_rows || (skip && skip[row / L])) return;
     float a[CH], b[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) { a[c] = 0.f; b[c] = 0.f; }
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void seglen_hist_kernel(const int32_t *__restr
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
-    if (skip && *skip) return;
+    if (skip && skip[bh]) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk;
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -389,7 +389,7 @@ __global__ __launch_bounds__(256) void seglen_scatter_kernel(const int32_t *__re
     const int nchunks = (L + kSeglenChunk - 1) / kSeglenChunk;
     const int unit = blockIdx.x / nchunks;  // (head, range)
     const int bh = tab.bh[unit / S], r = unit % S;
-    if (skip && *skip) return;
+    if (skip && skip[bh]) return;
     const int row0 = (blockIdx.x % nchunks) * kSeglenChunk, row1 = min(row0 + kSeglenChunk, L);
     for (int e = threadIdx.x; e < nbins; e += 256) lh[e] = 0;
     __syncthreads();
@@ -538,7 +538,7 @@ static dsv_status dkdv_merge_t(const dsv_problem &p, void *dK, void *dV, const S
 {
     const int64_t n_rows = (int64_t)p.B * p.H * p.L;
     hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, w.pa, w.pb,
-                       (T *)dK, (T *)dV, n_rows, pl.S, p.scale, skip);
+                       (T *)dK, (T *)dV, n_rows, pl.S, p.scale, p.L, skip);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }

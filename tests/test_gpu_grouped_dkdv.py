@@ -21,7 +21,9 @@ pytestmark = pytest.mark.gpu
                                           ((8, 64, 72), (2, 4, 4), [500]),
                                           ((4, 16, 16), (1, 2, 2), [40] * 256),  # one range
                                           ((8, 27, 38), (2, 1, 1), [100] * 16), ((4, 16, 16), (2, 2, 2), [100] * 128),  # two
-                                          ((2, 96, 86), (1, 2, 2), [200, 160, 180, 40])])  # four
+                                          ((2, 96, 86), (1, 2, 2), [200, 160, 180, 40]),  # four
+                                          # and 5e7 pairs, the form head by head: eight ranges, and one
+                                          ((8, 32, 32), (2, 2, 2), [4096, 60, 2048, 60]), ((4, 16, 16), (1, 2, 2), [200] * 256)])
 @pytest.mark.parametrize("near", [(True, True), (False, False), (True, False)])
 def test_grouped_gradients_of_keys_and_values(grid, cube, ks, near):
     L, G, H = math.prod(grid), math.prod(cube), len(ks)
