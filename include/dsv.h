@@ -375,8 +375,9 @@ DSV_API dsv_status dsv_kernel_ms(int32_t span, float *ms);
 
 /* How stage 1 finds every query's threshold score (the k-th largest; paper Sec. "Critical KV Estimation with
  * Kernel Fusion").  All methods are exact and give identical results; the choice only affects speed.
- *   0  automatic (default): up to 2048 keys one kernel that forms every score once, finds the threshold among
- *      them and writes the index (DSV_KERNEL_THRESHOLD and DSV_KERNEL_EMIT both report that one kernel); the
+ *   0  automatic (default): up to 1024 keys, and up to 2048 where it is the faster, one kernel that forms every
+ *      score once, finds the threshold among them and writes the index (DSV_KERNEL_THRESHOLD and
+ *      DSV_KERNEL_EMIT both report that one kernel); the
  *      windowed search -- a key sample brackets the threshold, then two sweeps over the keys -- for heads with
  *      L >= 16384 and k <= L/4 whose sample (2048 to 16384 keys, at most L/8) holds enough keys on both sides
  *      of the threshold; else the radix search (four sweeps, 8 bits each);

@@ -396,9 +396,9 @@ int window_sample_keys(int L, int k, bool forced);
 // 0: automatic; 1: always the four-pass radix search; 2: the windowed search wherever it fits.  Returns the old mode
 // (mode < 0: only that).
 int set_threshold_search(int mode);
-// Threshold search and query-major emission of short sequences in one launch (stage1_small.hip): every head of an L that
-// small_select(L) accepts.  Leaves the same state behind as the search and launch_emit's first part.
-bool small_select(int L);
+// Threshold search and query-major emission of short sequences in one launch (stage1_small.hip): for problems that
+// small_select accepts (Lq queries per head).  Leaves the same state behind as the search and launch_emit's first part.
+bool small_select(const dsv_problem &p, int Lq);
 dsv_status launch_select_small(const dsv_problem &p, int Lq, const HeadTable &tab, const void *Qlr, const void *Klr,
                                const SelectBuffers &b, hipStream_t st);
 // emitted: the query-major index is there already.

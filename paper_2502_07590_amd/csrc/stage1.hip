@@ -368,7 +368,7 @@ static dsv_status select_t(const dsv_problem &p, int Lq, const HeadTable *tabs, 
     const int qtiles = (Lq + 31) / 32;
     const int asked = g_threshold_search.load();
     const int mode = b.win && b.todo ? asked : 1;
-    if (asked != 1 && small_select(p.L)) {  // asked for the radix search: short sequences take it too
+    if (asked != 1 && small_select(p, Lq)) {  // asked for the radix search: short sequences take it too
         {
             KernelSpan search(DSV_KERNEL_THRESHOLD, st), emission(DSV_KERNEL_EMIT, st);  // one kernel does both
             for (int t = 0; t < n_tabs; ++t) {

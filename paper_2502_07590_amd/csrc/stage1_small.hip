@@ -17,7 +17,7 @@
 namespace dsv {
 
 constexpr int kSmallWaves = 16;
-constexpr int kSmallMaxTiles = 4;  // score tiles a wave keeps: 64 accumulators of the 128 registers that 16 waves leave it
+constexpr int kSmallMaxTiles = 4;  // score tiles a wave keeps: 64 accumulators of the 128 registers that 16 waves leave it, some of them in scratch
 constexpr int kSmallCap = 64;      // scores of a query's bin that are ranked in LDS
 constexpr int kSmallMaxKeys = kSmallWaves * kSmallMaxTiles * 32;
 
@@ -178,8 +178,15 @@ __global__ __launch_bounds__(64 * kSmallWaves) void select_small_kernel(const T 
 }
 
 // ------------------------------------------------------------------------------------ host
-// 4 tiles per wave is what the registers hold.
-bool small_select(int L) { return L <= kSmallMaxKeys; }
+// Up to 1024 keys always; up to 2048 (four tiles per wave, of which 68 registers' worth goes through scratch memory) where
+// each CU has one block, or where scores cost most.  Against the four passes and the emission, with the projection, us, k = L / 16:
+// bf16, r = 16, L = 1024, 1 head 18.9 : 30.5, 24 heads 46 : 51, 96 heads 161 : 158; L = 2048, 4 heads (256 blocks) 30 : 40, 12 heads 73 : 69,
+// 96 heads 506 : 388; r = 64, 96 heads 763 : 1120; fp32, r = 16, 1 head 42 : 104, 96 heads 873 : 1936.
+bool small_select(const dsv_problem &p, int Lq)
+{
+    if (p.L <= kSmallMaxKeys / 2 || p.L > kSmallMaxKeys) return p.L <= kSmallMaxKeys;
+    return p.dtype == DSV_F32 || p.r == 64 || (int64_t)p.B * p.H * ((Lq + 31) / 32) <= 256;
+}
 
 template <typename T, int R>
 static dsv_status select_small_t(const dsv_problem &p, int Lq, const HeadTable &tab, const void *Qlr, const void *Klr,

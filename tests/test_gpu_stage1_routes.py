@@ -36,14 +36,15 @@ def _check(p, Q, K, Wq, Wk):
         off += p.L * k
 
 
-# one kernel up to 2048 keys (512, 1024, 2048: 1, 2, 4 score tiles per wave), the radix passes above
+# one kernel up to 2048 keys (512, 1024, 2048: 1, 2, 4 score tiles per wave), the radix passes above (and, in bf16 below rank 64, from
+# 257 blocks of 32 queries and more than 1024 keys on)
 @pytest.mark.parametrize("L,ks", [(1, [1, 1]), (33, [33, 1]), (512, [100, 511]), (513, [7, 64]), (1025, [1025, 200]), (2048, [1, 300]),
-                                  (2049, [150, 2048])])
+                                  (1025, [1025, 200] * 4), (2049, [150, 2048])])
 @pytest.mark.parametrize("dtype,d,r", [("f32", 64, 16), ("bf16", 128, 32), ("bf16", 64, 64)])
 @pytest.mark.parametrize("ties", [False, True])
 def test_short_sequences(L, ks, dtype, d, r, ties):
-    Q, K, Wq, Wk = _inputs(2, L, d, r, dtype, ties, L + r)
-    _check(dsv.Problem(1, 2, L, d, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+    Q, K, Wq, Wk = _inputs(len(ks), L, d, r, dtype, ties, L + r)
+    _check(dsv.Problem(1, len(ks), L, d, r, dtype, ks, 0.1), Q, K, Wq, Wk)
 
 
 def _all_indices(p, grp, Q, K, Wq, Wk):
