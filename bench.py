@@ -32,11 +32,11 @@ VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9   # 256 CUs x 64 fp32 lanes x 2.4 GHz, on
 # (FETCH_SIZE reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0), and the L2 hit rate from
 # TCC_HIT_sum / (TCC_HIT_sum + TCC_MISS_sum).  Source: profiles/config2_pmc_counters.md.  The figures belong to ONE
 # build of the kernels: they are reported only while the library still names that version.
-PMC_LIBRARY_VERSION = "dsv 0.5 (gfx950)"
+PMC_LIBRARY_VERSION = "dsv 0.6 (gfx950)"
 PMC_CONFIG2 = {
-    "sparse_attn_fwd": {"fetch_kib": 85484433, "write_kib": 12786373, "l2_hit_rate": 0.7156},  # mask and dense tiles
-    "sparse_attn_bwd_dq": {"fetch_kib": 48450877, "write_kib": 12976385, "l2_hit_rate": 0.9644},
-    "sparse_attn_bwd_dkdv": {"fetch_kib": 33413195, "write_kib": 12582914, "l2_hit_rate": 0.9740},
+    "sparse_attn_fwd": {"fetch_kib": 88670095, "write_kib": 12783806, "l2_hit_rate": 0.7181},  # mask and dense tiles
+    "sparse_attn_bwd_dq": {"fetch_kib": 48587277, "write_kib": 12976332, "l2_hit_rate": 0.9644},
+    "sparse_attn_bwd_dkdv": {"fetch_kib": 33903656, "write_kib": 12582915, "l2_hit_rate": 0.9738},
 }
 # the gather sweep inside each stage-2 call (the kernel the roofline object is about)
 SWEEP_OF_CALL = {"sparse_attn_fwd": "fwd_sweep", "sparse_attn_bwd_dq": "dq_sweep", "sparse_attn_bwd_dkdv": "dkdv_sweep"}
@@ -511,7 +511,8 @@ def main():
                          "traffic": traffic, "kernel": "mask and dense tile kernels of " + n, "kernel_ms": round(k_ms, 3),
                          "call_ms": round(call_ms[n], 3),
                          "formed": {"achieved": round(formed, 1), "frac": round(formed / MFMA_BF16_PEAK_TFLOPS, 4)},
-                         "note": "achieved = 4 d flops per selected pair / kernel time; formed counts every pair of the tiles"}
+                         "note": "achieved = 4 d flops per selected pair / kernel time; formed counts every pair of the tiles, and the "
+                                 "product with V once, though its weights come as two words"}
     dominant = max(pair_bytes, key=lambda n: kern_ms[SWEEP_OF_CALL[n]])
     roofline = dict(stage2[dominant])
     # Stage 1 is selection work on the plain vector ALUs.  Algorithmic work: per score one compare against the
