@@ -77,8 +77,9 @@ typedef struct dsv_problem {
 /* The caller promises that every idx row, and every idx_t list, is in ascending order -- which is
  * how dsv_lowrank_topk / dsv_lowrank_topk_t write them.  Stage 2 then runs its L2-blocked kernels
  * (the key axis cut into cache-sized ranges, one contiguous segment of each row per range), which
- * need more workspace and are several times faster on long sequences, wherever the problem is large enough for them.  Without the flag stage 2
- * makes no assumption on the order.  Setting it for unsorted indices gives wrong results. */
+ * need more workspace and are several times faster on long sequences, wherever the problem is large enough for them, and
+ * in bf16 its forward over dense tiles for heads that keep many keys.  Without the flag stage 2 makes no
+ * assumption on the order.  Setting it for unsorted indices gives wrong results. */
 #define DSV_FLAG_SORTED_INDEX 1u
 
 DSV_API const char *dsv_version(void);
@@ -155,7 +156,7 @@ DSV_API dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, cons
 
 /* Whole backward with the transposed index supplied by the caller (from dsv_lowrank_topk_t, or
  * from an earlier dsv_idx_transpose): dq step then dkdv step; nothing is built here, so with
- * DSV_FLAG_SORTED_INDEX both steps run L2-blocked.  Same outputs as dsv_sparse_attn_bwd. */
+ * DSV_FLAG_SORTED_INDEX both steps run L2-blocked where that pays.  Same outputs as dsv_sparse_attn_bwd. */
 DSV_API size_t dsv_sparse_attn_bwd_t_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                          const int32_t *idx, const int32_t *idx_t, const int64_t *col_ptr,
@@ -226,8 +227,9 @@ DSV_API dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q,
  *   query returns 0).
  * dsv_sparse_attn_bwd_grouped: gradients of the above (selection held constant).  dQ group by group with
  *   the forward's tiling (K and V rows gathered once per group); dK and dV on queries reordered group by group,
- *   16 keys at a time over the union of their lists of groups where neighbouring keys share them, else key by key: the workspace holds the reordered Q, dO, lse, Delta
- *   besides the steps' scratch.  Needs idx_t_g and col_ptr.  The flag selects the L2-blocked dQ step as in the forward.
+ *   16 keys at a time over the union of their lists of groups where that is short enough, else key by key (the device
+ *   looks at the lists; one answer per call or, in large calls, per head): the workspace holds the reordered Q, dO, lse,
+ *   Delta besides the steps' scratch.  Needs idx_t_g and col_ptr.  The flag selects the L2-blocked dQ step as in the forward.
  *   Cases outside bf16, d = 128, G <= 32: the per-query kernels as described for the forward, with the per-query form of
  *   both indices in the workspace. */
 typedef struct dsv_grouping {

@@ -423,9 +423,10 @@ SplitPlan make_split_plan(const dsv_problem &p, size_t range_bytes, bool few)
     SplitPlan pl;
     // ranges of at most range_bytes and kMaxRangeRows rows (the dkdv sweep parks the range's row statistics in LDS), their
     // number a multiple of 8, so that every XCD gets the same number (a 6-5 split of ranges over XCDs costs ~10 %).  few: two
-    // or four where the size asks for no more and the blocks of 64 rows are still enough; a block lasts as long as its longest
-    // row (three heads of 5280 by groups of 32, k = 116: the layer 1523 us with one range, 654 with eight; lists as stage 1 makes
-    // them, four heads of 16384, k = 1000, dkdv: 2028 with two, 1619 with eight)
+    // or four where the size asks for no more and the blocks of 64 rows are still enough (the dq step where few keys are kept, and
+    // groups); a block lasts as long as its longest row (three heads of 5280 by groups of 32, k = 116: the layer 1523 us with one
+    // range, 654 with eight), which is why the dkdv step, whose lists differ most, does without (lists as stage 1 makes them,
+    // four heads of 16384, k = 1000: 2028 us with two, 1619 with eight)
     const size_t target = std::min<size_t>(kMaxRangeRows, std::max<size_t>(256, range_bytes / row_pair_bytes));
     const int want = (int)((p.L + target - 1) / target);
     pl.S_pad = want <= 2 ? 2 : want <= 4 ? 4 : (want + 7) / 8 * 8;
