@@ -502,7 +502,9 @@ def main():
                      "gather_only_ceiling": {"achieved_by_pure_gather_kernel": GATHER_CEILING_GBS[n], "unit": "GB/s",
                                              "frac_of_it": round(gbs / GATHER_CEILING_GBS[n], 4)},
                      "note": "achieved = algorithmic gather bytes (K row + V row + index entry per pair) / kernel time; the ranges "
-                             "of the split-K plan stay in each XCD's L2, so the bytes cross the L2 -> L1 path, not HBM"}
+                             "of the split-K plan stay in each XCD's L2, so the bytes cross the L2 -> L1 path, not HBM.  Heads that "
+                             "keep about one key in 16 and more run the backward steps over dense tiles: for them achieved is what "
+                             "gathers would have had to bring in that time"}
         if n == "sparse_attn_fwd" and gbs > L1_PEAK_GBS:
             # more than gathers could bring: the heads ran over dense tiles with a mask, on the matrix cores
             formed, kept = (4.0 * cfg.d * pairs / (k_ms * 1e-3) / 1e12 for pairs in (n_scores, nnz))

@@ -230,6 +230,36 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
     return best_k;
 }
 
+// Smallest k whose heads run a backward step over dense tiles with a mask (dense_bwd.hip), INT32_MAX if none should.  (As above, the
+// mask needs a workspace.)
+// Costs in us, bf16.  Gathering, per selected pair, once the chip is full: dq 18.9e-6 at d = 128, 10e-6 at d = 64; dkdv 21.3e-6, 11.3e-6.
+// Dense, per pair of the square: a floor, and more where more pairs are kept (groups of four with a third one).  Whole backward
+// by gathers against both steps dense: d = 128, three heads of 24000, one key in 24: 3461 : 3774, in 16: 4925 : 4442, in 12: 6199 : 4774,
+// in 5: 13724 : 5904; the dkdv step alone, four heads of 6000, one in 16: 238 : 228, in 5: 592 : 283; d = 64, three heads of 24000,
+// dq and dkdv, one in 16: 1279, 1239 : 1293, 1548; in 12: 1423, 1627 : 1332, 1663; in 8: 2055, 2407 : 1547, 1852.
+// 40 us are what launches, the mask and a chip that is not full cost small problems.
+int32_t dense_bwd_min_k(const dsv_problem &p, bool keys)
+{
+    if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
+    const bool wide = p.d == 128;
+    const double pair = wide ? (keys ? 21.3e-6 : 18.9e-6) : keys ? 11.3e-6 : 10e-6;
+    const double formed = wide ? (keys ? 1.2e-6 : 0.95e-6) : keys ? 0.8e-6 : 0.6e-6, more = wide ? 3e-6 : 2.2e-6;
+    std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
+    std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
+    int32_t best_k = INT32_MAX;
+    double best = 0.0, saved = -40.0;  // us saved by the heads with the largest k
+    for (int m = 1; m <= p.H; ++m) {
+        const double k = ks[m - 1], rows = (double)p.B * p.L;
+        saved += rows * (pair * k - (formed + more * k / p.L) * p.L);
+        if (m < p.H && ks[m] == ks[m - 1]) continue;
+        if (saved > best) {
+            best = saved;
+            best_k = ks[m - 1];
+        }
+    }
+    return best_k;
+}
+
 // tabs cut in two: heads of at least min_k, and the others
 void cut_tables(const std::vector<HeadTable> &tabs, int32_t min_k, std::vector<HeadTable> &yes, std::vector<HeadTable> &no)
 {
@@ -289,7 +319,8 @@ struct StepLayout {
     RowForm form;  // of the dq step
     bool blocked;  // the dkdv step
     SplitPlan plan;
-    size_t seg, pa, pb, pdelta, hist, order, rowstat, total;
+    int32_t dense_k;  // heads that keep at least so many keys run over dense tiles
+    size_t seg, pa, pb, pdelta, hist, order, rowstat, mask, mask_bytes, total;
 };
 
 void place_step(const dsv_problem &p, StepLayout &w)
@@ -307,12 +338,31 @@ void place_step(const dsv_problem &p, StepLayout &w)
     w.total = o;
 }
 
+// ... and room for masks, where some heads run over dense tiles in either step (so that both steps reserve the same).
+void place_masks(const dsv_problem &p, StepLayout &w)
+{
+    const int32_t least = std::min(dense_bwd_min_k(p, false), dense_bwd_min_k(p, true));
+    int dense = 0;
+    for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= least;
+    const size_t row = (size_t)bits_pitch(p.L) * 4, all = (size_t)p.B * dense * p.L * row;
+    w.mask = w.total;
+    // whole where they are small beside the partial results; else pieces that fill the chip a few times and that the memory-side
+    // cache holds from their making to their use
+    if (dense) w.mask_bytes = align_up(all <= ((size_t)256 << 20) ? all : std::max((size_t)96 << 20, kDenseMinRows * row), 256);
+    w.total += w.mask_bytes;
+}
+
 StepLayout dq_layout(const dsv_problem &p)
 {
     StepLayout w{};
     w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
-    w.form = row_form(p, w.plan, true, INT32_MAX);
-    if (w.form == RowForm::ranges) place_step(p, w);
+    w.dense_k = dense_bwd_min_k(p, false);
+    w.form = row_form(p, w.plan, true, w.dense_k);
+    // with room for the ranges of heads that run over tiles, as the forward has it
+    if (w.form == RowForm::ranges || w.dense_k != INT32_MAX || row_form(p, w.plan, true, INT32_MAX) == RowForm::ranges) {
+        place_step(p, w);
+        place_masks(p, w);
+    }
     return w;
 }
 StepLayout dkdv_layout(const dsv_problem &p)
@@ -320,7 +370,11 @@ StepLayout dkdv_layout(const dsv_problem &p)
     StepLayout w{};
     w.plan = make_split_plan(p, kBwdRangeBytes, false);
     w.blocked = split_lists(p, w.plan);
-    if (w.blocked) place_step(p, w);
+    w.dense_k = dense_bwd_min_k(p, true);
+    if (w.blocked || w.dense_k != INT32_MAX) {
+        place_step(p, w);
+        place_masks(p, w);
+    }
     return w;
 }
 // Scratch of either step: they are never live together.
@@ -398,7 +452,7 @@ static void *noalloc_scratch(dsv_status *err)
 
 extern "C" {
 
-const char *dsv_version(void) { return "dsv 0.6 (gfx950)"; }
+const char *dsv_version(void) { return "dsv 0.7 (gfx950)"; }
 
 const char *dsv_status_string(dsv_status s)
 {
@@ -567,10 +621,18 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     const StepLayout w = dq_layout(*p);
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (w.form != RowForm::ranges)
-        return launch_bwd_dq(*p, tabs.data(), (int)tabs.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, dO, dQ, delta, stream);
-    return launch_bwd_dq_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx, O, lse, dO, dQ, delta, w.plan,
-                               step_buffers(static_cast<char *>(workspace), w), stream);
+    char *ws = static_cast<char *>(workspace);
+    std::vector<HeadTable> dense, rest;
+    cut_tables(tabs, w.dense_k, dense, rest);
+    const DenseHeads dh{dense.data(), (int)dense.size(), ws + w.mask, w.mask_bytes};
+    std::optional<KernelSpan> span;
+    if (w.form != RowForm::ranges && !rest.empty()) {
+        if (!dense.empty()) span.emplace(DSV_KERNEL_DQ_SWEEP, stream);  // both parts together
+        st = launch_bwd_dq(*p, rest.data(), (int)rest.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, dO, dQ, delta, stream);
+        if (st != DSV_OK || dense.empty()) return st;
+        rest.clear();
+    }
+    return launch_bwd_dq_split(*p, rest.data(), (int)rest.size(), dh, Q, K, V, idx, O, lse, dO, dQ, delta, w.plan, step_buffers(ws, w), stream);
 }
 
 size_t dsv_idx_transpose_workspace(const dsv_problem *p)
@@ -612,11 +674,19 @@ dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const v
     const StepLayout w = dkdv_layout(*p);
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (!w.blocked)
-        return launch_bwd_dkdv(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
-                               stream);
-    return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV,
-                                 w.plan, step_buffers(static_cast<char *>(workspace), w), stream);
+    char *ws = static_cast<char *>(workspace);
+    std::vector<HeadTable> dense, rest;
+    cut_tables(tabs, w.dense_k, dense, rest);
+    const DenseHeads dh{dense.data(), (int)dense.size(), ws + w.mask, w.mask_bytes};
+    std::optional<KernelSpan> span;
+    if (!w.blocked && !rest.empty()) {
+        if (!dense.empty()) span.emplace(DSV_KERNEL_DKDV_SWEEP, stream);  // both parts together
+        st = launch_bwd_dkdv(*p, rest.data(), (int)rest.size(), Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV, stream);
+        if (st != DSV_OK || dense.empty()) return st;
+        rest.clear();
+    }
+    return launch_bwd_dkdv_split(*p, rest.data(), (int)rest.size(), dh, Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV, w.plan, step_buffers(ws, w),
+                                 stream);
 }
 
 size_t dsv_sparse_attn_bwd_workspace(const dsv_problem *p)
@@ -929,8 +999,8 @@ dsv_status dsv_sparse_attn_bwd_grouped(const dsv_problem *p, const dsv_grouping 
         st = launch_grouped_dkdv(*p, G, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, ws + w.gop, dK, dV, kw.step.plan, b,
                                  use, stream);
         if (st != DSV_OK) return st;
-        if (always) return kw.step.plan.S > 1 ? launch_dkdv_merge_bf16_128(*p, dK, dV, kw.step.plan, b, stream) : DSV_OK;
-        return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), ws + w.qp, K, V, idx_t_g, col_ptr, lsep, deltap, ws + w.gop, dK, dV,
+        if (always) return kw.step.plan.S > 1 ? launch_dkdv_merge_bf16_128(*p, tabs.data(), (int)tabs.size(), dK, dV, kw.step.plan, b, stream) : DSV_OK;
+        return launch_bwd_dkdv_split(*p, tabs.data(), (int)tabs.size(), DenseHeads{}, ws + w.qp, K, V, idx_t_g, col_ptr, lsep, deltap, ws + w.gop, dK, dV,
                                      kw.step.plan, b, stream, G, use);
     }
     // dK, dV step: the per-query key-major sweep on the reordered queries

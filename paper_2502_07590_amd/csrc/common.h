@@ -356,10 +356,21 @@ struct BwdSplitWorkspace {
     int32_t *order; // [B*H, S, L]   rows of every (head, range) by descending segment length
     float2 *rowstat;  // [B*H, L]    {lse * log2(e), Delta} per query (dkdv step only)
 };
-dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+// Heads of a ranged backward step that form every pair of a tile (dense_bwd.hip; bf16, scale > 0, L <= kBitsMaxKeys): their
+// partial results take the same places.  mask: scratch, at least kDenseMinRows rows of it.
+struct DenseHeads {
+    const HeadTable *tabs;
+    int n_tabs;
+    char *mask;
+    size_t mask_bytes;
+};
+dsv_status launch_dense_bwd(const dsv_problem &p, const HeadTable &tab, bool keys, const void *Q, const void *K, const void *V, const int32_t *index,
+                            const int64_t *col, const void *O, const float *lse, const void *dO, const SplitPlan &plan,
+                            const BwdSplitWorkspace &w, char *mask, size_t bytes, hipStream_t st);
+dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q, const void *K,
                                const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO,
                                void *dQ, float *delta, const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st);
-dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
+dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q,
                                  const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                  const float *lse, const float *delta, const void *dO, void *dK, void *dV,
                                  const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G = 1,
@@ -463,9 +474,9 @@ dsv_status launch_union_prepare(const dsv_problem &p, int G, const HeadTable *ta
 dsv_status launch_grouped_dkdv(const dsv_problem &p, int G, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
                                const void *V, const int32_t *lists, const int64_t *col, const void *dO, void *dK, void *dV,
                                const SplitPlan &plan, const BwdSplitWorkspace &w, const int32_t *use, hipStream_t st);
-dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, void *dK, void *dV, const SplitPlan &pl, const BwdSplitWorkspace &w,
-                                      hipStream_t st);
-dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const float *pa, const float *pb, const float *pdelta,
+dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, void *dK, void *dV, const SplitPlan &pl,
+                                      const BwdSplitWorkspace &w, hipStream_t st);
+dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const float *pa, const float *pb, const float *pdelta,
                                     const void *O, const void *dO, void *dQ, float *delta, int S, hipStream_t st);
 
 // ---- predictor side (predictor.hip) ---------------------------------------------------------------------
@@ -491,10 +502,11 @@ size_t idx_transpose_bytes(const dsv_problem &p);
 dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const int32_t *idx, bool built,
                                 int32_t *idxT, int64_t *col, void *ws, size_t ws_bytes, hipStream_t st);
 // Rows row0 .. row0 + nrows - 1 of `heads` head slots as a bit matrix [heads, nrows, bits_pitch(L) words]; L <= kBitsMaxKeys.
+// col: the rows are key-major lists (idx: idx_t).
 constexpr int kBitsMaxKeys = 524288;  // a row's bitmap fits 64 KB of LDS
 int bits_pitch(int L);
 dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
-                             int nrows, uint32_t *bits, hipStream_t st);
+                             int nrows, uint32_t *bits, hipStream_t st, const int64_t *col = nullptr);
 // Forward of some heads over dense tiles with a mask (dense.hip; bf16, scale > 0, L <= kBitsMaxKeys); ws: scratch for the
 // mask, at least kDenseMinRows rows of it.
 constexpr int kDenseMinRows = 128;

@@ -869,7 +869,7 @@ dsv_status launch_grouped_dq(const dsv_problem &p, const dsv_grouping &gr, const
             DSV_LAUNCH_CHECK();
         }
     }
-    return launch_dq_merge_bf16_128(p, split->pa, split->pb, split->pc, O, dO, dQ, delta, pl.S, st);
+    return launch_dq_merge_bf16_128(p, tabs, n_tabs, split->pa, split->pb, split->pc, O, dO, dQ, delta, pl.S, st);
 }
 
 }  // namespace dsv

@@ -193,13 +193,14 @@ __global__ __launch_bounds__(256) void sparse_bwd_dq_merge_kernel(const float *_
                                                                   const float *__restrict__ pdelta,
                                                                   const T *__restrict__ O, const T *__restrict__ dO,
                                                                   T *__restrict__ dQ, float *__restrict__ delta_out,
-                                                                  int64_t n_rows, int S, float scale)
+                                                                  int L, HeadTable tab, int S, float scale)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
-    const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
-    if (row >= n_rows) return;
+    const int64_t i = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
+    if (i >= L) return;
+    const int64_t row = (int64_t)tab.bh[blockIdx.y] * L + i;
     float a[CH], b[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) { a[c] = 0.f; b[c] = 0.f; }
@@ -287,14 +288,16 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void sparse_bwd_dkdv_merge_kernel(const float *__restrict__ pdk,
                                                                     const float *__restrict__ pdv,
                                                                     T *__restrict__ dK, T *__restrict__ dV,
-                                                                    int64_t n_rows, int S, float scale, int L,
+                                                                    int L, HeadTable tab, int S, float scale,
                                                                     const int32_t *__restrict__ skip)
 {
     constexpr int CH = D / 16;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int grp = lane >> 4, s = lane & 15;
-    const int64_t row = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
-    if (row >= n_rows || (skip && skip[row / L])) return;
+    const int64_t i = (int64_t)blockIdx.x * 16 + wave * 4 + grp;
+    const int bh = tab.bh[blockIdx.y];
+    if (i >= L || (skip && skip[bh])) return;
+    const int64_t row = (int64_t)bh * L + i;
     float a[CH], b[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) { a[c] = 0.f; b[c] = 0.f; }
@@ -454,6 +457,7 @@ static dsv_status launch_segments(const dsv_problem &p, const HeadTable *tabs, i
 static dsv_status launch_row_order(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const SplitPlan &pl, const int32_t *seg, int32_t *hist,
                                    int32_t *order, hipStream_t st, const int32_t *skip = nullptr)
 {
+    if (!n_tabs) return DSV_OK;
     const int nbh = p.B * p.H;
     // length classes; longer segments (possible only with ranges above 8192 rows) share the last class
     const int nbins = std::min(pl.range_len + 1, 8193);
@@ -504,7 +508,19 @@ static dsv_status fwd_split_t(const dsv_problem &p, const HeadTable *tabs, int n
 }
 
 template <typename T, int D>
-static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
+static dsv_status dq_merge_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *O, const void *dO, void *dQ, float *delta,
+                             const float *pa, const float *pb, const float *pdelta, int S, hipStream_t st)
+{
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL((sparse_bwd_dq_merge_kernel<T, D>), dim3((p.L + 15) / 16, tabs[t].n), dim3(256), 0, st, pa, pb, pdelta, (const T *)O,
+                           (const T *)dO, (T *)dQ, delta, p.L, tabs[t], S, p.scale);
+        DSV_LAUNCH_CHECK();
+    }
+    return DSV_OK;
+}
+
+template <typename T, int D>
+static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q,
                                  const void *K, const void *V, const int32_t *idx, const void *O, const float *lse,
                                  const void *dO, void *dQ, float *delta, const SplitPlan &pl,
                                  const BwdSplitWorkspace &w, hipStream_t st)
@@ -515,6 +531,10 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
+        for (int t = 0; t < dense.n_tabs; ++t) {
+            rc = launch_dense_bwd(p, dense.tabs[t], false, Q, K, V, idx, nullptr, O, lse, dO, pl, w, dense.mask, dense.mask_bytes, st);
+            if (rc != DSV_OK) return rc;
+        }
         for (int t = 0; t < n_tabs; ++t) {
             SplitPlan lp = pl;
             lp.nqb = (p.L + 256 / SweepLanes<T, D>::dq - 1) / (256 / SweepLanes<T, D>::dq);  // row blocks of this kernel's layout
@@ -526,26 +546,25 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
             DSV_LAUNCH_CHECK();
         }
     }
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_bwd_dq_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, w.pa,
-                       w.pb, w.pdelta, (const T *)O, (const T *)dO, (T *)dQ, delta, n_rows, pl.S, p.scale);
-    DSV_LAUNCH_CHECK();
-    return DSV_OK;
+    rc = dq_merge_t<T, D>(p, dense.tabs, dense.n_tabs, O, dO, dQ, delta, w.pa, w.pb, w.pdelta, pl.S, st);
+    if (rc != DSV_OK) return rc;
+    return dq_merge_t<T, D>(p, tabs, n_tabs, O, dO, dQ, delta, w.pa, w.pb, w.pdelta, pl.S, st);
 }
 
 template <typename T, int D>
-static dsv_status dkdv_merge_t(const dsv_problem &p, void *dK, void *dV, const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st,
-                               const int32_t *skip)
+static dsv_status dkdv_merge_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, void *dK, void *dV, const SplitPlan &pl,
+                               const BwdSplitWorkspace &w, hipStream_t st, const int32_t *skip)
 {
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, w.pa, w.pb,
-                       (T *)dK, (T *)dV, n_rows, pl.S, p.scale, p.L, skip);
-    DSV_LAUNCH_CHECK();
+    for (int t = 0; t < n_tabs; ++t) {
+        hipLaunchKernelGGL((sparse_bwd_dkdv_merge_kernel<T, D>), dim3((p.L + 15) / 16, tabs[t].n), dim3(256), 0, st, w.pa, w.pb, (T *)dK, (T *)dV,
+                           p.L, tabs[t], pl.S, p.scale, skip);
+        DSV_LAUNCH_CHECK();
+    }
     return DSV_OK;
 }
 
 template <typename T, int D>
-static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
+static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q,
                                    const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                    const float *lse, const float *delta, const void *dO, void *dK, void *dV,
                                    const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G,
@@ -565,6 +584,10 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
     if (rc != DSV_OK) return rc;
     {
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
+        for (int t = 0; t < dense.n_tabs; ++t) {
+            rc = launch_dense_bwd(p, dense.tabs[t], true, Q, K, V, idxT, col, nullptr, nullptr, dO, pl, w, dense.mask, dense.mask_bytes, st);
+            if (rc != DSV_OK) return rc;
+        }
         for (int t = 0; t < n_tabs; ++t) {
             SplitPlan lp = pl;
             lp.nqb = (p.L + 256 / SweepLanes<T, D>::dkdv - 1) / (256 / SweepLanes<T, D>::dkdv);  // row blocks of this kernel's layout
@@ -580,7 +603,9 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
             DSV_LAUNCH_CHECK();
         }
     }
-    return dkdv_merge_t<T, D>(p, dK, dV, pl, w, st, pl.S > 1 ? nullptr : skip);
+    rc = dkdv_merge_t<T, D>(p, dense.tabs, dense.n_tabs, dK, dV, pl, w, st, nullptr);
+    if (rc != DSV_OK) return rc;
+    return dkdv_merge_t<T, D>(p, tabs, n_tabs, dK, dV, pl, w, st, pl.S > 1 ? nullptr : skip);
 }
 
 // ---- pieces of the split plan used by the query-grouped kernels as well --------------------------------------
@@ -610,20 +635,16 @@ dsv_status launch_fwd_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs
     return DSV_OK;
 }
 
-dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const float *pa, const float *pb, const float *pdelta,
+dsv_status launch_dq_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const float *pa, const float *pb, const float *pdelta,
                                     const void *O, const void *dO, void *dQ, float *delta, int S, hipStream_t st)
 {
-    const int64_t n_rows = (int64_t)p.B * p.H * p.L;
-    hipLaunchKernelGGL((sparse_bwd_dq_merge_kernel<bf16_t, 128>), dim3((unsigned)((n_rows + 15) / 16)), dim3(256), 0, st, pa, pb,
-                       pdelta, (const bf16_t *)O, (const bf16_t *)dO, (bf16_t *)dQ, delta, n_rows, S, p.scale);
-    DSV_LAUNCH_CHECK();
-    return DSV_OK;
+    return dq_merge_t<bf16_t, 128>(p, tabs, n_tabs, O, dO, dQ, delta, pa, pb, pdelta, S, st);
 }
 
-dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, void *dK, void *dV, const SplitPlan &pl, const BwdSplitWorkspace &w,
-                                      hipStream_t st)
+dsv_status launch_dkdv_merge_bf16_128(const dsv_problem &p, const HeadTable *tabs, int n_tabs, void *dK, void *dV, const SplitPlan &pl,
+                                      const BwdSplitWorkspace &w, hipStream_t st)
 {
-    return dkdv_merge_t<bf16_t, 128>(p, dK, dV, pl, w, st, nullptr);
+    return dkdv_merge_t<bf16_t, 128>(p, tabs, n_tabs, dK, dV, pl, w, st, nullptr);
 }
 
 #define DSV_DISPATCH_TD(FN, ...)                                        \
@@ -645,20 +666,20 @@ dsv_status launch_sparse_fwd_split(const dsv_problem &p, const HeadTable *tabs, 
     DSV_DISPATCH_TD(fwd_split_t, p, tabs, n_tabs, Q, K, V, idx, O, lse, pl, w, st);
 }
 
-dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q, const void *K,
+dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q, const void *K,
                                const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO,
                                void *dQ, float *delta, const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st)
 {
-    DSV_DISPATCH_TD(bwd_dq_split_t, p, tabs, n_tabs, Q, K, V, idx, O, lse, dO, dQ, delta, pl, w, st);
+    DSV_DISPATCH_TD(bwd_dq_split_t, p, tabs, n_tabs, dense, Q, K, V, idx, O, lse, dO, dQ, delta, pl, w, st);
 }
 
-dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const void *Q,
+dsv_status launch_bwd_dkdv_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q,
                                  const void *K, const void *V, const int32_t *idxT, const int64_t *col,
                                  const float *lse, const float *delta, const void *dO, void *dK, void *dV,
                                  const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st, int expand_G,
                                  const int32_t *skip)
 {
-    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st, expand_G, skip);
+    DSV_DISPATCH_TD(bwd_dkdv_split_t, p, tabs, n_tabs, dense, Q, K, V, idxT, col, lse, delta, dO, dK, dV, pl, w, st, expand_G, skip);
 }
 
 }  // namespace dsv

@@ -21,19 +21,21 @@ constexpr int kBitsKeys = 512;               // keys per block of the counting a
 constexpr int kBitsRows = 1024;              // queries per block of those kernels: one segment of every list
 constexpr size_t kBitsBytes = (size_t)2 << 30;  // scratch for the bit matrix: larger problems go through it piece by piece
 
-// One block per row at a time: its entries are OR-ed into an LDS bitmap, which is then written out and cleared.
-__global__ __launch_bounds__(256) void bits_build_kernel(const int32_t *__restrict__ idx, int L, HeadTable tab, int slot0,
+// One block per row at a time: its entries are OR-ed into an LDS bitmap, which is then written out and cleared.  col: the rows are
+// key-major lists, whose bits are queries.
+__global__ __launch_bounds__(256) void bits_build_kernel(const int32_t *__restrict__ idx, const int64_t *__restrict__ col, int L, HeadTable tab, int slot0,
                                                          int row0, int nrows, int pitch, uint32_t *__restrict__ bits)
 {
     extern __shared__ __align__(16) uint32_t bm[];  // [pitch]
     const int slot = slot0 + blockIdx.y;
-    const int k = tab.k[slot];
-    const int32_t *base = idx + tab.off[slot] + (int64_t)row0 * k;
+    const int32_t *base = idx + tab.off[slot];
+    const int64_t *cp = col ? col + (int64_t)tab.bh[slot] * (L + 1) + row0 : nullptr;
     uint32_t *out = bits + (int64_t)blockIdx.y * nrows * pitch;
     for (int w = threadIdx.x; w < pitch; w += 256) bm[w] = 0u;
     __syncthreads();
     for (int i = blockIdx.x; i < nrows; i += gridDim.x) {
-        const int32_t *row = base + (int64_t)i * k;
+        const int k = cp ? (int)(cp[i + 1] - cp[i]) : tab.k[slot];
+        const int32_t *row = base + (cp ? cp[i] : (int64_t)(row0 + i) * k);
         for (int t = threadIdx.x; t < k; t += 256) {
             const int v = row[t];
             if (v >= 0 && v < L) atomicOr(&bm[v >> 5], 1u << (v & 31));
@@ -432,10 +434,10 @@ __global__ __launch_bounds__(256) void fill_zero_i32_kernel(int4 *__restrict__ p
 int bits_pitch(int L) { return (L + kBitsKeys - 1) / kBitsKeys * 16; }
 
 dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
-                             int nrows, uint32_t *bits, hipStream_t st)
+                             int nrows, uint32_t *bits, hipStream_t st, const int64_t *col)
 {
     const int pitch = bits_pitch(p.L);
-    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min(nrows, 4096), heads), dim3(256), (size_t)pitch * 4, st, idx, p.L, tab, slot0,
+    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min(nrows, 4096), heads), dim3(256), (size_t)pitch * 4, st, idx, col, p.L, tab, slot0,
                        row0, nrows, pitch, bits);
     DSV_LAUNCH_CHECK();
     return DSV_OK;

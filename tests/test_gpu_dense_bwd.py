@@ -1,0 +1,81 @@
+"""Backward over dense tiles with a selection mask: heads that keep enough of their keys, against the same sums in fp64."""
+import pytest
+import torch
+
+import paper_2502_07590_amd as dsv
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(L, d, ks, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    H = len(ks)
+    Q, K, V, dO = (torch.randn(1, H, L, d, generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    rows, lists, ptrs = [], [], []
+    for h, k in enumerate(ks):
+        # a slope over the keys, so that some lists are several times as long as others
+        score = torch.rand(L, L, generator=g, device="cuda") + torch.linspace(0, 0.2, L, device="cuda")
+        row = score.topk(k, dim=1).indices.sort(dim=1).values.to(torch.int32)
+        rows.append(row)
+        keys = row.reshape(-1)
+        lists.append((torch.sort(keys, stable=True).indices // k).to(torch.int32))
+        ptr = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+        ptr[1:] = torch.bincount(keys, minlength=L).cumsum(0)
+        ptrs.append(ptr)
+    p = dsv.Problem(1, H, L, d, 16, "bf16", ks, 2.0 / d ** 0.5, sorted_index=True)
+    return p, Q, K, V, dO, rows, torch.cat(lists), torch.stack(ptrs)
+
+
+def reference(p, Q, K, V, dO, rows, h):
+    q, k, v, g = (t[0, h].double() for t in (Q, K, V, dO))
+    keep = torch.zeros(p.L, p.L, dtype=torch.bool, device="cuda").scatter_(1, rows[h].long(), True)
+    s = (q @ k.T * p.scale).masked_fill(~keep, float("-inf"))
+    lse = torch.logsumexp(s, dim=1)
+    w = torch.exp(s - lse[:, None])
+    dp = (g @ v.T).masked_fill(~keep, 0.0)
+    ds = w * (dp - (w * dp).sum(1, keepdim=True))
+    return w @ v, lse, ds @ k * p.scale, ds.T @ q * p.scale, w.T @ g, keep
+
+
+def backward(p, Q, K, V, dO, rows, lists, ptrs, refs):
+    O = torch.stack([r[0] for r in refs])[None].to(torch.bfloat16)
+    lse = torch.stack([r[1] for r in refs])[None].float()
+    return dsv.sparse_attn_bwd_t(p, Q, K, V, torch.cat([r.reshape(-1) for r in rows]), lists, ptrs, O, lse, dO)
+
+
+# L around tiles of 32, blocks of 128 and ranges; groups of four with one to four pairs (k = L); heads by gathers beside dense ones
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,ks", [(2977, (2977,)), (2048, (1024, 512, 1500)), (2081, (1900, 60, 1700, 1)), (4100, (820, 1025))])
+def test_backward_over_dense_tiles(L, d, ks):
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, list(ks))
+    refs = [reference(p, Q, K, V, dO, rows, h) for h in range(len(ks))]
+    got = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
+    for name, t, at in zip(("dQ", "dK", "dV"), got, (2, 3, 4)):
+        for h, ref in enumerate(refs):
+            want, err = ref[at], t[0, h].double() - ref[at]
+            # the rounding of the output is 2^-9 of an element at most; the weights' 16 bits and fp32 sums stay far below it,
+            # except where a row's terms nearly cancel (a part of the typical row is allowed for that).  k = 1: dQ and dK are zero, and
+            # fp32 leaves 2^-20 of dP (below 50) there, times a row of norm 8 to 11 and the scale of 0.25 to 0.18: below 1.4e-4
+            size = want.norm(dim=1)
+            assert (err.norm(dim=1) <= 2 ** -8 * size + 2 ** -10 * size.mean() + 1.4e-4).all(), (name, h)
+
+
+def test_rows_that_are_not_finite_reach_only_those_that_select_them():
+    L, d = 2048, 128
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, [1200, 1000])
+    refs = [reference(p, Q, K, V, dO, rows, h) for h in range(2)]
+    j, i = 1027, 777
+    V[0, :, j, 5] = float("inf")   # a key's value row, then a query's gradient row
+    dO[0, :, i, 9] = float("nan")
+    dQ, dK, dV = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
+    for h, ref in enumerate(refs):
+        keep = ref[5]
+        fine = ~keep[:, j]
+        fine[i] = False
+        assert torch.isfinite(dQ[0, h][fine]).all() and not torch.isfinite(dQ[0, h][keep[:, j]]).all()
+        err = (dQ[0, h].double() - ref[2])[fine].norm() / ref[2][fine].norm()
+        assert err < 4e-3  # twice the rounding of the output
+        # dV of a key sums rows of dO only
+        fine = ~keep[i]
+        assert torch.isfinite(dV[0, h][fine]).all()
+        assert (dV[0, h].double() - ref[4])[fine].norm() / ref[4][fine].norm() < 4e-3
