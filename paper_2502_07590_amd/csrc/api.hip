@@ -609,6 +609,28 @@ size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p)
     return step_bytes(*p);
 }
 
+// dense_rows, dense_bits: as in DenseHeads.
+static dsv_status bwd_dq_impl(const dsv_problem *p, const void *Q, const void *K, const void *V, const int32_t *idx, const int32_t *dense_rows,
+                              const uint32_t *dense_bits, const void *O, const float *lse, const void *dO, void *dQ, float *delta, void *workspace,
+                              void *hip_stream)
+{
+    const StepLayout w = dq_layout(*p);
+    const std::vector<HeadTable> tabs = make_tables(*p);
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    char *ws = static_cast<char *>(workspace);
+    std::vector<HeadTable> dense, rest;
+    cut_tables(tabs, w.dense_k, dense, rest);
+    const DenseHeads dh{dense.data(), (int)dense.size(), ws + w.mask, w.mask_bytes, dense_rows, dense_bits};
+    std::optional<KernelSpan> span;
+    if (w.form != RowForm::ranges && !rest.empty()) {
+        if (!dense.empty()) span.emplace(DSV_KERNEL_DQ_SWEEP, stream);  // both parts together
+        const dsv_status st = launch_bwd_dq(*p, rest.data(), (int)rest.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, dO, dQ, delta, stream);
+        if (st != DSV_OK || dense.empty()) return st;
+        rest.clear();
+    }
+    return launch_bwd_dq_split(*p, rest.data(), (int)rest.size(), dh, Q, K, V, idx, O, lse, dO, dQ, delta, w.plan, step_buffers(ws, w), stream);
+}
+
 dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                   const int32_t *idx, const void *O, const float *lse, const void *dO, void *dQ,
                                   float *delta, void *workspace, size_t ws_bytes, void *hip_stream)
@@ -618,21 +640,7 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     if (!ok_ptrs({Q, K, V, idx, O, lse, dO, dQ, delta})) return DSV_EINVAL;
     st = check_workspace(workspace, ws_bytes, step_bytes(*p));
     if (st != DSV_OK) return st;
-    const StepLayout w = dq_layout(*p);
-    const std::vector<HeadTable> tabs = make_tables(*p);
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    char *ws = static_cast<char *>(workspace);
-    std::vector<HeadTable> dense, rest;
-    cut_tables(tabs, w.dense_k, dense, rest);
-    const DenseHeads dh{dense.data(), (int)dense.size(), ws + w.mask, w.mask_bytes};
-    std::optional<KernelSpan> span;
-    if (w.form != RowForm::ranges && !rest.empty()) {
-        if (!dense.empty()) span.emplace(DSV_KERNEL_DQ_SWEEP, stream);  // both parts together
-        st = launch_bwd_dq(*p, rest.data(), (int)rest.size(), w.form == RowForm::waves, Q, K, V, idx, O, lse, dO, dQ, delta, stream);
-        if (st != DSV_OK || dense.empty()) return st;
-        rest.clear();
-    }
-    return launch_bwd_dq_split(*p, rest.data(), (int)rest.size(), dh, Q, K, V, idx, O, lse, dO, dQ, delta, w.plan, step_buffers(ws, w), stream);
+    return bwd_dq_impl(p, Q, K, V, idx, nullptr, nullptr, O, lse, dO, dQ, delta, workspace, hip_stream);
 }
 
 size_t dsv_idx_transpose_workspace(const dsv_problem *p)
@@ -719,10 +727,20 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
     if (sort_rows_first(*p)) {
         // rows in any order: an ascending copy (in the place of the lists, which are built after the dq step) lets the
         // dq step run L2-blocked too; its bitmaps serve the transposition
+        // (heads over dense tiles take their rows as they are, through their bitmaps: 20280, keeping 2028 and 4056 keys, the whole
+        // backward beside two sparser heads 5220 -> 4809 us)
         bits = transpose_matrix(*p, ws + w.cnt);
-        st = launch_sort_rows(*p, tabs.data(), (int)tabs.size(), idx, idx_t, bits, stream);
+        std::vector<HeadTable> dense, rest;
+        cut_tables(tabs, dq_layout(sorted).dense_k, dense, rest);
+        uint32_t *rest_bits = bits;
+        if (bits && !dense.empty()) {  // one table, its first heads
+            st = launch_bits_build(*p, dense[0], 0, dense[0].n, idx, 0, p->L, bits, stream);
+            if (st != DSV_OK) return st;
+            rest_bits += (size_t)dense[0].n * p->L * bits_pitch(p->L);
+        }
+        st = launch_sort_rows(*p, rest.data(), (int)rest.size(), idx, idx_t, rest_bits, stream);
         if (st != DSV_OK) return st;
-        st = dsv_sparse_attn_bwd_dq(&sorted, Q, K, V, idx_t, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
+        st = bwd_dq_impl(&sorted, Q, K, V, idx_t, idx, bits, O, lse, dO, dQ, delta, ws + w.step, hip_stream);
     } else {
         st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
     }

@@ -363,10 +363,12 @@ struct DenseHeads {
     int n_tabs;
     char *mask;
     size_t mask_bytes;
+    const int32_t *rows;   // dq step: their index rows, in any order (null: those of the call)
+    const uint32_t *bits;  // dq step: the masks of all of them [heads, L, bits_pitch(L)], in the order of the (one) table; null: to be built
 };
 dsv_status launch_dense_bwd(const dsv_problem &p, const HeadTable &tab, bool keys, const void *Q, const void *K, const void *V, const int32_t *index,
                             const int64_t *col, const void *O, const float *lse, const void *dO, const SplitPlan &plan,
-                            const BwdSplitWorkspace &w, char *mask, size_t bytes, hipStream_t st);
+                            const BwdSplitWorkspace &w, const DenseHeads &dense, hipStream_t st);
 dsv_status launch_bwd_dq_split(const dsv_problem &p, const HeadTable *tabs, int n_tabs, const DenseHeads &dense, const void *Q, const void *K,
                                const void *V, const int32_t *idx, const void *O, const float *lse, const void *dO,
                                void *dQ, float *delta, const SplitPlan &pl, const BwdSplitWorkspace &w, hipStream_t st);

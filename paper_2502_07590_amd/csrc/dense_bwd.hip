@@ -401,16 +401,15 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
 }
 
 // ------------------------------------------------------------------------------------ host
-// One step over the heads of a table, as many heads and rows at a time as masks fit `bytes` of scratch.  keys: the dkdv step, on
+// One step over the heads of a table, as many heads and rows at a time as masks fit the scratch.  keys: the dkdv step, on
 // key-major lists.
 template <int D>
 static dsv_status dense_bwd_t(const dsv_problem &p, const HeadTable &tab, bool keys, const void *Q, const void *K, const void *V, const int32_t *index,
                               const int64_t *col, const void *O, const float *lse, const void *dO, const SplitPlan &plan,
-                              const BwdSplitWorkspace &w, char *mask, size_t bytes, hipStream_t st)
+                              const BwdSplitWorkspace &w, const DenseHeads &dense, hipStream_t st)
 {
     const int pitch = bits_pitch(p.L);
-    uint32_t *bits = reinterpret_cast<uint32_t *>(mask);
-    const size_t fit = bytes / ((size_t)pitch * 4);  // rows of the mask
+    const size_t fit = dense.bits ? (size_t)tab.n * p.L : dense.mask_bytes / ((size_t)pitch * 4);  // rows of the mask
     const int heads = (int)std::min<size_t>(std::max<size_t>(fit / p.L, 1), (size_t)tab.n);
     // pieces of a head: whole rounds of blocks (two per CU) where that much fits
     const size_t unit = (size_t)kOwn * std::max(1, 512 / plan.S_pad);
@@ -421,8 +420,13 @@ static dsv_status dense_bwd_t(const dsv_problem &p, const HeadTable &tab, bool k
         const int nh = std::min(heads, tab.n - s0);
         for (int r0 = 0; r0 < p.L; r0 += rows) {
             const int nr = std::min(rows, p.L - r0);
-            const dsv_status rc = launch_bits_build(p, tab, s0, nh, index, r0, nr, bits, st, col);
-            if (rc != DSV_OK) return rc;
+            const uint32_t *bits = dense.bits;
+            if (!bits) {
+                uint32_t *mask = reinterpret_cast<uint32_t *>(dense.mask);
+                const dsv_status rc = launch_bits_build(p, tab, s0, nh, index, r0, nr, mask, st, col);
+                if (rc != DSV_OK) return rc;
+                bits = mask;
+            }
             pl.nqb = (nr + kOwn - 1) / kOwn;
             const int64_t blocks = nh * range_items(pl.S_pad, pl.nqb);
             if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
@@ -442,10 +446,10 @@ static dsv_status dense_bwd_t(const dsv_problem &p, const HeadTable &tab, bool k
 
 dsv_status launch_dense_bwd(const dsv_problem &p, const HeadTable &tab, bool keys, const void *Q, const void *K, const void *V, const int32_t *index,
                             const int64_t *col, const void *O, const float *lse, const void *dO, const SplitPlan &plan,
-                            const BwdSplitWorkspace &w, char *mask, size_t bytes, hipStream_t st)
+                            const BwdSplitWorkspace &w, const DenseHeads &dense, hipStream_t st)
 {
-    if (p.dtype == DSV_BF16 && p.d == 64) return dense_bwd_t<64>(p, tab, keys, Q, K, V, index, col, O, lse, dO, plan, w, mask, bytes, st);
-    if (p.dtype == DSV_BF16 && p.d == 128) return dense_bwd_t<128>(p, tab, keys, Q, K, V, index, col, O, lse, dO, plan, w, mask, bytes, st);
+    if (p.dtype == DSV_BF16 && p.d == 64) return dense_bwd_t<64>(p, tab, keys, Q, K, V, index, col, O, lse, dO, plan, w, dense, st);
+    if (p.dtype == DSV_BF16 && p.d == 128) return dense_bwd_t<128>(p, tab, keys, Q, K, V, index, col, O, lse, dO, plan, w, dense, st);
     return DSV_EUNSUPPORTED;
 }
 

@@ -532,7 +532,7 @@ static dsv_status bwd_dq_split_t(const dsv_problem &p, const HeadTable *tabs, in
     {
         KernelSpan span(DSV_KERNEL_DQ_SWEEP, st);
         for (int t = 0; t < dense.n_tabs; ++t) {
-            rc = launch_dense_bwd(p, dense.tabs[t], false, Q, K, V, idx, nullptr, O, lse, dO, pl, w, dense.mask, dense.mask_bytes, st);
+            rc = launch_dense_bwd(p, dense.tabs[t], false, Q, K, V, dense.rows ? dense.rows : idx, nullptr, O, lse, dO, pl, w, dense, st);
             if (rc != DSV_OK) return rc;
         }
         for (int t = 0; t < n_tabs; ++t) {
@@ -585,7 +585,7 @@ static dsv_status bwd_dkdv_split_t(const dsv_problem &p, const HeadTable *tabs, 
     {
         KernelSpan span(DSV_KERNEL_DKDV_SWEEP, st);
         for (int t = 0; t < dense.n_tabs; ++t) {
-            rc = launch_dense_bwd(p, dense.tabs[t], true, Q, K, V, idxT, col, nullptr, nullptr, dO, pl, w, dense.mask, dense.mask_bytes, st);
+            rc = launch_dense_bwd(p, dense.tabs[t], true, Q, K, V, idxT, col, nullptr, nullptr, dO, pl, w, dense, st);
             if (rc != DSV_OK) return rc;
         }
         for (int t = 0; t < n_tabs; ++t) {

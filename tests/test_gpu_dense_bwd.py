@@ -79,3 +79,17 @@ def test_rows_that_are_not_finite_reach_only_those_that_select_them():
         fine = ~keep[i]
         assert torch.isfinite(dV[0, h][fine]).all()
         assert (dV[0, h].double() - ref[4])[fine].norm() / ref[4][fine].norm() < 4e-3
+
+
+def test_rows_in_any_order():
+    """The whole backward on unsorted rows: dense heads take them as they are, the others by an ascending copy."""
+    L, d = 6201, 128
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, [150, 1300, 1000])
+    refs = [reference(p, Q, K, V, dO, rows, h) for h in range(3)]
+    want = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
+    O = torch.stack([r[0] for r in refs])[None].to(torch.bfloat16)
+    lse = torch.stack([r[1] for r in refs])[None].float()
+    loose = dsv.Problem(1, 3, L, d, 16, "bf16", [150, 1300, 1000], p.scale)
+    got = dsv.sparse_attn_bwd(loose, Q, K, V, torch.cat([r.flip(1).reshape(-1) for r in rows]), O, lse, dO)
+    for a, b in zip(got, want):
+        assert (a - b).double().norm() / b.double().norm() < 2 ** -8  # two results within half a unit each
