@@ -78,7 +78,7 @@ typedef struct dsv_problem {
  * how dsv_lowrank_topk / dsv_lowrank_topk_t write them.  Stage 2 then runs its L2-blocked kernels
  * (the key axis cut into cache-sized ranges, one contiguous segment of each row per range), which
  * need more workspace and are several times faster on long sequences, wherever the problem is large enough for them, and
- * in bf16 its forward over dense tiles for heads that keep many keys.  Without the flag stage 2 makes no
+ * in bf16 its forward and backward over dense tiles for heads that keep many keys.  Without the flag stage 2 makes no
  * assumption on the order.  Setting it for unsorted indices gives wrong results. */
 #define DSV_FLAG_SORTED_INDEX 1u
 
@@ -146,7 +146,7 @@ DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, cons
  * and the results are identical, bit for bit, to dsv_sparse_attn_bwd_t on dsv_idx_transpose's output and from run to
  * run.  Without DSV_FLAG_SORTED_INDEX the rows of larger problems are first copied in ascending order (same workspace), so
  * that the dq step is L2-blocked as well; the result is then that of the ascending rows.  Building the transposed index is a
- * tenth of the call (L = 20280, four heads keeping 507 .. 4056 keys: 0.55 ms of 7.6); callers that run stage 1 here can take
+ * tenth of the call (L = 20280, four heads keeping 507 .. 4056 keys: 0.55 ms of 4.8); callers that run stage 1 here can take
  * its transposed index (dsv_lowrank_topk_t) and call dsv_sparse_attn_bwd_t. */
 DSV_API size_t dsv_sparse_attn_bwd_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *K, const void *V,
@@ -185,7 +185,8 @@ DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, co
  *   keys with an empty list get zeros.
  *
  * Workspace of dq and dkdv: none without DSV_FLAG_SORTED_INDEX (query returns 0, null accepted);
- * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked. */
+ * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked; heads that
+ * keep enough of their keys (bf16, scale > 0) run over dense tiles and need a bit per (query, key), 256 MB at a time at most. */
 DSV_API size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                           const int32_t *idx, const void *O, const float *lse, const void *dO,

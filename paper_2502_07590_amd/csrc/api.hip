@@ -240,7 +240,8 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
 // 40 us are what launches, the mask and a chip that is not full cost small problems.
 int32_t dense_bwd_min_k(const dsv_problem &p, bool keys)
 {
-    if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
+    // (the key-major tiles start from lse / scale, which has to be a number)
+    if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 1e-30f)) return INT32_MAX;
     const bool wide = p.d == 128;
     const double pair = wide ? (keys ? 21.3e-6 : 18.9e-6) : keys ? 11.3e-6 : 10e-6;
     const double formed = wide ? (keys ? 1.2e-6 : 0.95e-6) : keys ? 0.8e-6 : 0.6e-6, more = wide ? 3e-6 : 2.2e-6;
