@@ -16,7 +16,7 @@
 // four -- are free of bank conflicts.  Tiles come by direct loads into LDS, two in turn.
 //
 // Measured, L = 32768, four heads, k = 2048 (6 % kept), with the mask (0.43 ms): dq 5.09 ms by gathers -> 4.70, dkdv 5.68 -> 5.77 (which
-// therefore gathers there); L = 20280, two heads of one key in 10 and in 5: whole backward 7.61 -> 5.18 ms.  Matrix cores are busy for
+// therefore gathers there); L = 20280, two of four heads at one key in 10 and in 5: whole backward 7.63 -> 4.78 ms, 0.4 of that the ascending copy that they no longer need.  Matrix cores are busy for
 // 0.47 of the time and the vector units for 0.49: a wave's products and weights wait for each other, and two waves per SIMD --
 // all that 256 registers allow -- overlap them little.  Weights laid beside the products inside a wave gave nothing (dq) or spilled
 // (dkdv, 6.5 ms); fragment reads left to the compiler's order, which puts each right before its use, cost 0.5 ms of dq.
