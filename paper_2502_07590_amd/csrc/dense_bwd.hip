@@ -60,18 +60,19 @@ __device__ __forceinline__ void request_tile(const unsigned char *__restrict__ m
     }
 }
 
-// Written out, because the compiler turns these into two or three instructions each.
+// Plain expressions, because their operands are results of matrix products: the compiler puts the wait that such a read needs before
+// an instruction of its own, and none before one written in inline assembly.  The empty statement only hides from it that a
+// mask is a bit spread out, which it would turn into a compare and a select per use (dq at L = 32768, four heads, k = 2048: 4.65 ms, 4.77
+// without).
 template <int BIT> __device__ __forceinline__ uint32_t bit_mask(uint32_t w)  // all ones where the bit is set, else zero
 {
-    uint32_t m;
-    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(w), "n"(BIT));
+    uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)w, BIT, 1);
+    asm("" : "+v"(m));
     return m;
 }
 __device__ __forceinline__ float pick(uint32_t mask, float a, float b)  // mask all ones: a, zero: b
 {
-    float x;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(x) : "v"(mask), "v"(a), "v"(b));
-    return x;
+    return __uint_as_float((mask & __float_as_uint(a)) | (~mask & __float_as_uint(b)));
 }
 __device__ __forceinline__ float keep(uint32_t mask, float a) { return __uint_as_float(mask & __float_as_uint(a)); }
 
