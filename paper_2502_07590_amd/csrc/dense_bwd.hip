@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "stage2_core.h"
+#include "pair_slots.h"
 
 namespace dsv {
 
@@ -75,37 +76,6 @@ __device__ __forceinline__ float pick(uint32_t mask, float a, float b)  // mask 
     return __uint_as_float((mask & __float_as_uint(a)) | (~mask & __float_as_uint(b)));
 }
 __device__ __forceinline__ float keep(uint32_t mask, float a) { return __uint_as_float(mask & __float_as_uint(a)); }
-
-// The first two selected pairs of every group of four, from the mask word of a lane's row shifted so that accumulator 4 g + i has
-// bit 4 i + 2 (g % 2) + 16 (g / 2).  All groups at once, a bit plane per i.  Slot 0 takes the first of 0, 1, 2 (2 if none), slot
-// 1 the last of the others: their numbers differ and ascend whatever the mask.
-struct PairSlots {
-    uint32_t b0, b1, n2, n3, v0, v1;  // slot 0: b0 ? 0 : b1 ? 1 : 2; slot 1: n3 ? (n2 ? 1 : 2) : 3; v0, v1: a selected pair
-    uint32_t index;                   // the instruction's index operand: slot numbers, two bits each
-    uint32_t r1, r2;                  // pairs number 1 and 2 that are left
-    static constexpr uint32_t M = 0x00050005u;
-    // slot 0 = lo0 + 2 hi0, slot 1 = lo1 + 2 hi1
-    __device__ __forceinline__ static uint32_t index_of(uint32_t lo0, uint32_t hi0, uint32_t lo1, uint32_t hi1)
-    {
-        const uint32_t x = (lo0 & M) | ((hi0 & M) << 1), y = (lo1 & M) | ((hi1 & M) << 1);
-        const uint32_t z = (x & 0x00030003u) | ((x & 0x000C000Cu) << 2) | ((y & 0x00030003u) << 2) | ((y & 0x000C000Cu) << 4);
-        return __builtin_amdgcn_perm(z, z, 0x0C0C0200u);
-    }
-    __device__ __forceinline__ explicit PairSlots(uint32_t w)
-    {
-        b0 = w & M;
-        b1 = (w >> 4) & M;
-        const uint32_t b2 = (w >> 8) & M, b3 = (w >> 12) & M;
-        const uint32_t a = b0 | b1;
-        n3 = a & ~b3;
-        n2 = b0 & ~b2;
-        v0 = a | b2;
-        v1 = (n3 & ((n2 & b1) | (~n2 & b2))) | (~n3 & b3);
-        index = index_of(b1 & ~b0, ~a, ~n3 | n2, ~n3 | ~n2);
-        r1 = b1 & b0 & (b2 | b3);
-        r2 = b2 & a & b3;
-    }
-};
 
 // KEYS: own rows are keys (X, Y = K, V; R1, R2 = Q, dO): a = dK = sum dS q, b = dV = sum p dO, with row statistics stat[query] =
 // {lse * log2(e), Delta}.  Else own rows are queries (X, Y = Q, dO; R1, R2 = K, V): a = C = sum p (dP - D0) k, b = B = sum p k, and
@@ -315,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
                 others(std::integral_constant<int, 1>{});
                 others(std::integral_constant<int, 2>{});
                 others(std::integral_constant<int, 3>{});
-                sums(PairSlots::index_of(ps.r1, ~ps.r1, ~ps.r1, ps.r1));  // 1 and 2, or 2 and 3
+                sums(ps.index_left());
             }
         }
         if (t + 1 < tile1) park(stn);
