@@ -186,7 +186,7 @@ DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, co
  *
  * Workspace of dq and dkdv: none without DSV_FLAG_SORTED_INDEX (query returns 0, null accepted);
  * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked; heads that
- * keep enough of their keys (bf16, scale > 0) run over dense tiles and need a bit per (query, key), 256 MB at a time at most. */
+ * keep enough of their keys (bf16, scale > 1e-30) run over dense tiles and need a bit per (query, key), 256 MB at a time at most. */
 DSV_API size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                           const int32_t *idx, const void *O, const float *lse, const void *dO,
@@ -393,6 +393,11 @@ DSV_API int32_t dsv_threshold_search(int32_t mode);
 /* Which search a head that keeps k of L keys gets under the current mode: the number of keys the windowed
  * search samples for it (a multiple of 32), or 0 when the head takes another one.  Host arithmetic only. */
 DSV_API int32_t dsv_threshold_sample_keys(int32_t L, int32_t k);
+
+/* Which form a stage-2 step takes (DSV_KERNEL_FWD_SWEEP, DSV_KERNEL_DQ_SWEEP or DSV_KERNEL_DKDV_SWEEP): heads that keep at least the
+ * returned number of keys run it over dense tiles, the others gather; 0: no head does (or not a step, or a bad descriptor).
+ * Host arithmetic only. */
+DSV_API int32_t dsv_dense_min_k(const dsv_problem *p, int32_t step);
 
 /* Pure-gather probe: the practical ceiling of the vector memory path (L2 -> vector L1 -> registers) for the
  * stage-2 access pattern, against which the sweeps' achieved gather rate is reported.  K, V: DEVICE bf16

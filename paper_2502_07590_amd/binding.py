@@ -35,7 +35,7 @@ EXPORTED_SYMBOLS = (
     "dsv_group_overlap_workspace", "dsv_group_overlap", "dsv_choose_grouping_workspace", "dsv_choose_grouping",
     "dsv_lowrank_topk_noalloc_max_bytes", "dsv_lowrank_topk_noalloc",
     "dsv_lowrank_project", "dsv_lowrank_scores_rows",
-    "dsv_kernel_timing", "dsv_kernel_ms", "dsv_threshold_search", "dsv_threshold_sample_keys", "dsv_measure_gather_ceiling",
+    "dsv_kernel_timing", "dsv_kernel_ms", "dsv_threshold_search", "dsv_threshold_sample_keys", "dsv_dense_min_k", "dsv_measure_gather_ceiling",
 )
 
 
@@ -151,6 +151,8 @@ def load_library():
     lib.dsv_lowrank_scores_rows.argtypes = [P, vp, vp, i32, i32, vp, i32, vp, vp]
     lib.dsv_threshold_sample_keys.restype = ctypes.c_int32
     lib.dsv_threshold_sample_keys.argtypes = [i32, i32]
+    lib.dsv_dense_min_k.restype = ctypes.c_int32
+    lib.dsv_dense_min_k.argtypes = [P, i32]
     lib.dsv_threshold_search.restype = ctypes.c_int32
     lib.dsv_threshold_search.argtypes = [i32]
     lib.dsv_kernel_timing.restype = ctypes.c_int
@@ -519,6 +521,11 @@ def threshold_search(mode: int) -> int:
 def threshold_sample_keys(L: int, k: int) -> int:
     """dsv_threshold_sample_keys: keys the windowed threshold search samples for a head keeping k of L (0: another search)."""
     return int(load_library().dsv_threshold_sample_keys(int(L), int(k)))
+
+
+def dense_min_k(p: Problem, step: str) -> int:
+    """dsv_dense_min_k: least k whose heads run `step` ("fwd_sweep", "dq_sweep", "dkdv_sweep") over dense tiles, 0 if none do."""
+    return int(load_library().dsv_dense_min_k(p.c, KERNEL_SPANS.index(step)))
 
 
 def kernel_timing(enable: bool):

@@ -1206,6 +1206,13 @@ int32_t dsv_threshold_sample_keys(int32_t L, int32_t k)
     return mode == 1 ? 0 : dsv::window_sample_keys(L, k, mode == 2);
 }
 
+int32_t dsv_dense_min_k(const dsv_problem *p, int32_t step)
+{
+    if (step < DSV_KERNEL_FWD_SWEEP || step > DSV_KERNEL_DKDV_SWEEP || check_problem(p, false) != DSV_OK) return 0;
+    const int32_t k = step == DSV_KERNEL_FWD_SWEEP ? fwd_layout(*p).dense_k : step == DSV_KERNEL_DQ_SWEEP ? dq_layout(*p).dense_k : dkdv_layout(*p).dense_k;
+    return k == INT32_MAX ? 0 : k;
+}
+
 dsv_status dsv_kernel_ms(int32_t span, float *ms)
 {
     dsv::KernelTimer &t = dsv::g_kernel_timer;

@@ -40,12 +40,16 @@ def reference(p, Q, K, V, dO, rows, h):
 def backward(p, Q, K, V, dO, rows, lists, ptrs, refs):
     O = torch.stack([r[0] for r in refs])[None].to(torch.bfloat16)
     lse = torch.stack([r[1] for r in refs])[None].float()
+    # heads that keep a seventh of their keys and more run over dense tiles in both steps, and no sparse one does
+    for step in ("dq_sweep", "dkdv_sweep"):
+        least = dsv.dense_min_k(p, step)
+        assert least and [k >= least for k in p.k_per_head] == [7 * k >= p.L for k in p.k_per_head], (step, least)
     return dsv.sparse_attn_bwd_t(p, Q, K, V, torch.cat([r.reshape(-1) for r in rows]), lists, ptrs, O, lse, dO)
 
 
 # L around tiles of 32, blocks of 128 and ranges; groups of four with one to four pairs (k = L); heads by gathers beside dense ones
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("L,ks", [(2977, (2977,)), (2048, (1024, 512, 1500)), (2081, (1900, 60, 1700, 1)), (4100, (820, 1025))])
+@pytest.mark.parametrize("L,ks", [(2977, (2977,)), (2048, (1024, 512, 1500)), (2081, (1900, 60, 1700, 1)), (4100, (2050, 1640))])
 def test_backward_over_dense_tiles(L, d, ks):
     p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, list(ks))
     refs = [reference(p, Q, K, V, dO, rows, h) for h in range(len(ks))]
