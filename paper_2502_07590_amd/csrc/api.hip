@@ -154,7 +154,11 @@ bool few_ranges(const dsv_problem &p) { return mean_k(p) <= 1280; }
 // d = 128: forward, four heads of 3000, k = 20: 12, 34, 56; of 4096, k = 640: 243, 213, 226; one of 8192, k = 320: 120, 78, 119;
 // dq, four of 24000, k = 1280: 2656, 4271, 2640; fp32, four of 32768, k = 640: 5522, 7896, 3752.
 enum class RowForm { groups, waves, ranges };
-RowForm row_form(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t dense_k)
+struct RowTime {
+    RowForm form;
+    double us;
+};
+RowTime row_time(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t dense_k)
 {
     const double row_bytes = (double)p.d * esize(p.dtype), kv = (double)kv_bytes(p) / (1 << 20);
     const int lanes = (int)std::clamp(row_bytes / (dq ? 32 : 64), 4.0, 16.0), parts = 64 / lanes;  // SweepLanes (stage2_core.h)
@@ -168,7 +172,7 @@ RowForm row_form(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t den
         whole_steps += 4 * parts * std::ceil(k / (4.0 * parts));
         ++n;
     }
-    if (!n) return RowForm::groups;  // nobody asks
+    if (!n) return {RowForm::groups, 0.0};  // nobody asks
     const double heads = (double)p.B * n, rows = heads * p.L, pair = 3.3e-8 * 2 * row_bytes * p.B * p.L;
     auto beside = [](double chain, double all) { return std::sqrt(chain * chain + all * all); };
     auto above = [](double x) { return std::max(0.0, std::log2(x)); };  // doublings past a size
@@ -177,9 +181,10 @@ RowForm row_form(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t den
     const double exchanges = (dq ? 2 * 4e-6 : 9e-6) * (p.d / lanes) * std::log2(parts);
     const double waves = (dq ? 1.06 : 1.1) * (7 + beside(0.008 * most, rows * exchanges + pair * whole_steps * (1 + (dq ? 0.3 : 0.45) * above(kv / 3))));
     const double ranges = 28 + (dq ? 4.4e-6 : 2.5e-6) * p.d * rows * std::max(pl.S_pad, 8) + beside(0.03 * most, pair * sum);
-    if (use_split(p, pl) && ranges < std::min(groups, waves)) return RowForm::ranges;
-    return waves < groups ? RowForm::waves : RowForm::groups;
+    if (use_split(p, pl) && ranges < std::min(groups, waves)) return {RowForm::ranges, ranges};
+    return waves < groups ? RowTime{RowForm::waves, waves} : RowTime{RowForm::groups, groups};
 }
+RowForm row_form(const dsv_problem &p, const SplitPlan &pl, bool dq, int32_t dense_k) { return row_time(p, pl, dq, dense_k).form; }
 
 // Whether the key-major step runs over query ranges.  Lists differ in length: the blocked form also sorts them by it, the other
 // one gives every list a wave.  Blocked against not, us, lists as stage 1 makes them, bf16, d = 128: four heads of 2048 (1 MB),
@@ -236,26 +241,40 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
 // Dense, per pair of the square: a floor, and more where more pairs are kept (groups of four with a third one).  Whole backward
 // by gathers against both steps dense: d = 128, three heads of 24000, one key in 24: 3461 : 3774, in 16: 4925 : 4442, in 12: 6199 : 4774,
 // in 5: 13724 : 5904; the dkdv step alone, four heads of 6000, one in 16: 238 : 228, in 5: 592 : 283; d = 64, three heads of 24000,
-// dq and dkdv, one in 16: 1279, 1239 : 1293, 1548; in 12: 1423, 1627 : 1332, 1663; in 8: 2055, 2407 : 1547, 1852.
+// dq and dkdv, one in 16: 1279, 1239 : 1293, 1548; in 12: 1423, 1627 : 1332, 1663; in 8: 2055, 2407 : 1547, 1852; dq, d = 128, one in 16: one
+// head of 65536 5429 : 4739, of 131072 21485 : 19027.
 // 40 us are what launches, the mask and a chip that is not full cost small problems.
-int32_t dense_bwd_min_k(const dsv_problem &p, bool keys)
+// The dq step's gathers need no partial results where sequences are short, and where few keys are kept only those of two or four
+// ranges; dense tiles have those of eight to write and to merge (and with fewer ranges blocks that last as much longer, of which few
+// rounds fill the chip badly), so there the gathers' own estimate decides.  Gathers against dense, d = 128: 24 heads of 1500,
+// k = 187: 150 : 231; 12 of 3000, k = 250: 185 : 271; 24 of 2048, k = 256: 248 : 341; 12 of 4096, k = 341: 332 : 429; but 4 of 2048, k = 512:
+// 85 : 58; one of 8192, k = 1024: 164 : 114; d = 64, 24 of 3000, k = 375: 292 : 345; 2 of 4096, k = 1024: 90 : 58.  Over 628 dq steps (both
+// d, 1 to 24 heads of 1024 to 131072, 1/24 to 3/4 kept) the form chosen takes 1.003 times the faster one's time in the mean, and dense is
+// chosen where it is slower in two (8 %).  Dkdv gathers cost short sequences more: of the same 628 none where dense is chosen is slower.
+// pl, all: ranges of the dq step, and its form and time without dense tiles.
+int32_t dense_bwd_min_k(const dsv_problem &p, bool keys, const SplitPlan &pl, const RowTime &all)
 {
     // (the key-major tiles start from lse / scale, which has to be a number)
     if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 1e-30f)) return INT32_MAX;
     const bool wide = p.d == 128;
     const double pair = wide ? (keys ? 21.3e-6 : 18.9e-6) : keys ? 11.3e-6 : 10e-6;
     const double formed = wide ? (keys ? 1.2e-6 : 0.95e-6) : keys ? 0.8e-6 : 0.6e-6, more = wide ? 3e-6 : 2.2e-6;
+    const bool same_ranges = keys || (all.form == RowForm::ranges && pl.S_pad >= 8);
     std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
     std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
     int32_t best_k = INT32_MAX;
-    double best = 0.0, saved = -40.0;  // us saved by the heads with the largest k
+    double best = 0.0, rows = 0.0, kept = 0.0;  // us saved by the heads with the largest k; their rows and selected pairs
     for (int m = 1; m <= p.H; ++m) {
-        const double k = ks[m - 1], rows = (double)p.B * p.L;
-        saved += rows * (pair * k - (formed + more * k / p.L) * p.L);
-        if (m < p.H && ks[m] == ks[m - 1]) continue;
+        const int32_t k = ks[m - 1];
+        rows += (double)p.B * p.L;
+        kept += (double)p.B * p.L * k;
+        if (m < p.H && ks[m] == k) continue;
+        const double dense = formed * rows * p.L + more * kept;
+        const double saved = same_ranges ? pair * kept - dense - 40.0
+                                         : all.us - row_time(p, pl, true, k).us - 1.05 * (20.0 + dense + 2.4e-6 * p.d * rows * std::max(pl.S_pad, 8));
         if (saved > best) {
             best = saved;
-            best_k = ks[m - 1];
+            best_k = k;
         }
     }
     return best_k;
@@ -339,10 +358,9 @@ void place_step(const dsv_problem &p, StepLayout &w)
     w.total = o;
 }
 
-// ... and room for masks, where some heads run over dense tiles in either step (so that both steps reserve the same).
-void place_masks(const dsv_problem &p, StepLayout &w)
+// ... and room for the masks of heads that keep at least `least` keys.
+void place_masks(const dsv_problem &p, int32_t least, StepLayout &w)
 {
-    const int32_t least = std::min(dense_bwd_min_k(p, false), dense_bwd_min_k(p, true));
     int dense = 0;
     for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= least;
     const size_t row = (size_t)bits_pitch(p.L) * 4, all = (size_t)p.B * dense * p.L * row;
@@ -353,33 +371,36 @@ void place_masks(const dsv_problem &p, StepLayout &w)
     w.total += w.mask_bytes;
 }
 
-StepLayout dq_layout(const dsv_problem &p)
+// Both steps.  Their scratch is never live together: either reserves `bytes`, what the larger one needs.
+struct StepLayouts {
+    StepLayout dq, dkdv;
+    size_t bytes;
+};
+StepLayouts step_layouts(const dsv_problem &p)
 {
-    StepLayout w{};
-    w.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
-    w.dense_k = dense_bwd_min_k(p, false);
-    w.form = row_form(p, w.plan, true, w.dense_k);
+    StepLayouts s{};
+    s.dq.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
+    s.dkdv.plan = make_split_plan(p, kBwdRangeBytes, false);
+    const RowTime all = row_time(p, s.dq.plan, true, INT32_MAX);
+    s.dq.dense_k = dense_bwd_min_k(p, false, s.dq.plan, all);
+    s.dkdv.dense_k = dense_bwd_min_k(p, true, s.dq.plan, all);
+    s.dq.form = s.dq.dense_k == INT32_MAX ? all.form : row_form(p, s.dq.plan, true, s.dq.dense_k);
+    s.dkdv.blocked = split_lists(p, s.dkdv.plan);
+    // masks: where some heads run over dense tiles in either step, so that both steps reserve the same
+    const int32_t least = std::min(s.dq.dense_k, s.dkdv.dense_k);
     // with room for the ranges of heads that run over tiles, as the forward has it
-    if (w.form == RowForm::ranges || w.dense_k != INT32_MAX || row_form(p, w.plan, true, INT32_MAX) == RowForm::ranges) {
-        place_step(p, w);
-        place_masks(p, w);
+    if (all.form == RowForm::ranges || s.dq.form == RowForm::ranges || s.dq.dense_k != INT32_MAX) {
+        place_step(p, s.dq);
+        place_masks(p, least, s.dq);
     }
-    return w;
-}
-StepLayout dkdv_layout(const dsv_problem &p)
-{
-    StepLayout w{};
-    w.plan = make_split_plan(p, kBwdRangeBytes, false);
-    w.blocked = split_lists(p, w.plan);
-    w.dense_k = dense_bwd_min_k(p, true);
-    if (w.blocked || w.dense_k != INT32_MAX) {
-        place_step(p, w);
-        place_masks(p, w);
+    if (s.dkdv.blocked || s.dkdv.dense_k != INT32_MAX) {
+        place_step(p, s.dkdv);
+        place_masks(p, least, s.dkdv);
     }
-    return w;
+    s.bytes = std::max(s.dq.total, s.dkdv.total);
+    return s;
 }
-// Scratch of either step: they are never live together.
-size_t step_bytes(const dsv_problem &p) { return std::max(dq_layout(p).total, dkdv_layout(p).total); }
+size_t step_bytes(const dsv_problem &p) { return step_layouts(p).bytes; }
 
 BwdSplitWorkspace step_buffers(char *ws, const StepLayout &w)
 {
@@ -611,11 +632,10 @@ size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p)
 }
 
 // dense_rows, dense_bits: as in DenseHeads.
-static dsv_status bwd_dq_impl(const dsv_problem *p, const void *Q, const void *K, const void *V, const int32_t *idx, const int32_t *dense_rows,
+static dsv_status bwd_dq_impl(const dsv_problem *p, const StepLayout &w, const void *Q, const void *K, const void *V, const int32_t *idx, const int32_t *dense_rows,
                               const uint32_t *dense_bits, const void *O, const float *lse, const void *dO, void *dQ, float *delta, void *workspace,
                               void *hip_stream)
 {
-    const StepLayout w = dq_layout(*p);
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     char *ws = static_cast<char *>(workspace);
@@ -639,9 +659,10 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx, O, lse, dO, dQ, delta})) return DSV_EINVAL;
-    st = check_workspace(workspace, ws_bytes, step_bytes(*p));
+    const StepLayouts steps = step_layouts(*p);
+    st = check_workspace(workspace, ws_bytes, steps.bytes);
     if (st != DSV_OK) return st;
-    return bwd_dq_impl(p, Q, K, V, idx, nullptr, nullptr, O, lse, dO, dQ, delta, workspace, hip_stream);
+    return bwd_dq_impl(p, steps.dq, Q, K, V, idx, nullptr, nullptr, O, lse, dO, dQ, delta, workspace, hip_stream);
 }
 
 size_t dsv_idx_transpose_workspace(const dsv_problem *p)
@@ -678,9 +699,10 @@ dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const v
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV})) return DSV_EINVAL;
-    st = check_workspace(workspace, ws_bytes, step_bytes(*p));
+    const StepLayouts steps = step_layouts(*p);
+    st = check_workspace(workspace, ws_bytes, steps.bytes);
     if (st != DSV_OK) return st;
-    const StepLayout w = dkdv_layout(*p);
+    const StepLayout &w = steps.dkdv;
     const std::vector<HeadTable> tabs = make_tables(*p);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     char *ws = static_cast<char *>(workspace);
@@ -732,7 +754,8 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
         // backward beside two sparser heads 5220 -> 4809 us)
         bits = transpose_matrix(*p, ws + w.cnt);
         std::vector<HeadTable> dense, rest;
-        cut_tables(tabs, dq_layout(sorted).dense_k, dense, rest);
+        const StepLayout step = step_layouts(sorted).dq;
+        cut_tables(tabs, step.dense_k, dense, rest);
         uint32_t *rest_bits = bits;
         if (bits && !dense.empty()) {  // one table, its first heads
             st = launch_bits_build(*p, dense[0], 0, dense[0].n, idx, 0, p->L, bits, stream);
@@ -741,7 +764,7 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
         }
         st = launch_sort_rows(*p, rest.data(), (int)rest.size(), idx, idx_t, rest_bits, stream);
         if (st != DSV_OK) return st;
-        st = bwd_dq_impl(&sorted, Q, K, V, idx_t, idx, bits, O, lse, dO, dQ, delta, ws + w.step, hip_stream);
+        st = bwd_dq_impl(&sorted, step, Q, K, V, idx_t, idx, bits, O, lse, dO, dQ, delta, ws + w.step, hip_stream);
     } else {
         st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
     }
@@ -1209,7 +1232,7 @@ int32_t dsv_threshold_sample_keys(int32_t L, int32_t k)
 int32_t dsv_dense_min_k(const dsv_problem *p, int32_t step)
 {
     if (step < DSV_KERNEL_FWD_SWEEP || step > DSV_KERNEL_DKDV_SWEEP || check_problem(p, false) != DSV_OK) return 0;
-    const int32_t k = step == DSV_KERNEL_FWD_SWEEP ? fwd_layout(*p).dense_k : step == DSV_KERNEL_DQ_SWEEP ? dq_layout(*p).dense_k : dkdv_layout(*p).dense_k;
+    const int32_t k = step == DSV_KERNEL_FWD_SWEEP ? fwd_layout(*p).dense_k : step == DSV_KERNEL_DQ_SWEEP ? step_layouts(*p).dq.dense_k : step_layouts(*p).dkdv.dense_k;
     return k == INT32_MAX ? 0 : k;
 }
 
