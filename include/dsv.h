@@ -186,7 +186,8 @@ DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, co
  *
  * Workspace of dq and dkdv: none without DSV_FLAG_SORTED_INDEX (query returns 0, null accepted);
  * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked; heads that
- * keep enough of their keys (bf16, scale > 1e-30) run over dense tiles and need a bit per (query, key), 256 MB at a time at most. */
+ * keep enough of their keys (bf16, scale > 1e-30) run over dense tiles and need a bit per (query, key), 256 MB at a time at most, and the partial sums.
+ * Where gathers alone would need none, a null or smaller workspace is accepted still, and all heads gather. */
 DSV_API size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                           const int32_t *idx, const void *O, const float *lse, const void *dO,

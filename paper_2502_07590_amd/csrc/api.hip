@@ -375,15 +375,16 @@ void place_masks(const dsv_problem &p, int32_t least, StepLayout &w)
 struct StepLayouts {
     StepLayout dq, dkdv;
     size_t bytes;
+    bool spare;  // `bytes` are for dense tiles alone: by gathers the steps need none
 };
-StepLayouts step_layouts(const dsv_problem &p)
+StepLayouts step_layouts(const dsv_problem &p, bool dense = true)
 {
     StepLayouts s{};
     s.dq.plan = make_split_plan(p, kBwdRangeBytes, few_ranges(p));
     s.dkdv.plan = make_split_plan(p, kBwdRangeBytes, false);
     const RowTime all = row_time(p, s.dq.plan, true, INT32_MAX);
-    s.dq.dense_k = dense_bwd_min_k(p, false, s.dq.plan, all);
-    s.dkdv.dense_k = dense_bwd_min_k(p, true, s.dq.plan, all);
+    s.dq.dense_k = dense ? dense_bwd_min_k(p, false, s.dq.plan, all) : INT32_MAX;
+    s.dkdv.dense_k = dense ? dense_bwd_min_k(p, true, s.dq.plan, all) : INT32_MAX;
     s.dq.form = s.dq.dense_k == INT32_MAX ? all.form : row_form(p, s.dq.plan, true, s.dq.dense_k);
     s.dkdv.blocked = split_lists(p, s.dkdv.plan);
     // masks: where some heads run over dense tiles in either step, so that both steps reserve the same
@@ -398,7 +399,14 @@ StepLayouts step_layouts(const dsv_problem &p)
         place_masks(p, least, s.dkdv);
     }
     s.bytes = std::max(s.dq.total, s.dkdv.total);
+    s.spare = all.form != RowForm::ranges && !s.dkdv.blocked;
     return s;
+}
+// ... of a call with this workspace: where gathers need none, one without that of dense tiles gathers.
+StepLayouts step_layouts(const dsv_problem &p, const void *ws, size_t have)
+{
+    const StepLayouts s = step_layouts(p);
+    return s.spare && check_workspace(ws, have, s.bytes) != DSV_OK ? step_layouts(p, false) : s;
 }
 size_t step_bytes(const dsv_problem &p) { return step_layouts(p).bytes; }
 
@@ -419,6 +427,7 @@ BwdSplitWorkspace step_buffers(char *ws, const StepLayout &w)
 // otherwise the caller brings it (dsv_sparse_attn_bwd_t).
 struct BwdLayout {
     size_t delta, cnt, cnt_bytes, col, idxT, step, step_bytes, total;
+    size_t least;  // of `total`, what a call cannot do without
 };
 
 BwdLayout bwd_layout(const dsv_problem &p, bool own_transpose)
@@ -436,9 +445,11 @@ BwdLayout bwd_layout(const dsv_problem &p, bool own_transpose)
     // own_transpose: the lists come out ascending, so the dkdv step runs the L2-blocked kernel whatever p.flags says
     dsv_problem sorted = p;
     sorted.flags |= DSV_FLAG_SORTED_INDEX;
-    w.step = o; w.step_bytes = own_transpose ? std::max(step_bytes(p), step_bytes(sorted)) : step_bytes(p);
+    const StepLayouts steps = step_layouts(own_transpose ? sorted : p);
+    w.step = o; w.step_bytes = steps.bytes;
     o += w.step_bytes;
     w.total = o;
+    w.least = steps.spare ? w.step : w.total;
     return w;
 }
 
@@ -659,7 +670,7 @@ dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const voi
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx, O, lse, dO, dQ, delta})) return DSV_EINVAL;
-    const StepLayouts steps = step_layouts(*p);
+    const StepLayouts steps = step_layouts(*p, workspace, ws_bytes);
     st = check_workspace(workspace, ws_bytes, steps.bytes);
     if (st != DSV_OK) return st;
     return bwd_dq_impl(p, steps.dq, Q, K, V, idx, nullptr, nullptr, O, lse, dO, dQ, delta, workspace, hip_stream);
@@ -699,7 +710,7 @@ dsv_status dsv_sparse_attn_bwd_dkdv(const dsv_problem *p, const void *Q, const v
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV})) return DSV_EINVAL;
-    const StepLayouts steps = step_layouts(*p);
+    const StepLayouts steps = step_layouts(*p, workspace, ws_bytes);
     st = check_workspace(workspace, ws_bytes, steps.bytes);
     if (st != DSV_OK) return st;
     const StepLayout &w = steps.dkdv;
@@ -734,8 +745,9 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx, O, lse, dO, dQ, dK, dV})) return DSV_EINVAL;
     const BwdLayout w = bwd_layout(*p, true);
-    st = check_workspace(workspace, ws_bytes, w.total);
+    st = check_workspace(workspace, ws_bytes, w.least);
     if (st != DSV_OK) return st;
+    const size_t step_have = std::min(w.step_bytes, ws_bytes - w.step);
     char *ws = static_cast<char *>(workspace);
     float *delta = reinterpret_cast<float *>(ws + w.delta);
     int64_t *col = reinterpret_cast<int64_t *>(ws + w.col);
@@ -754,7 +766,7 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
         // backward beside two sparser heads 5220 -> 4809 us)
         bits = transpose_matrix(*p, ws + w.cnt);
         std::vector<HeadTable> dense, rest;
-        const StepLayout step = step_layouts(sorted).dq;
+        const StepLayout step = step_layouts(sorted, ws + w.step, step_have).dq;
         cut_tables(tabs, step.dense_k, dense, rest);
         uint32_t *rest_bits = bits;
         if (bits && !dense.empty()) {  // one table, its first heads
@@ -766,12 +778,12 @@ dsv_status dsv_sparse_attn_bwd(const dsv_problem *p, const void *Q, const void *
         if (st != DSV_OK) return st;
         st = bwd_dq_impl(&sorted, step, Q, K, V, idx_t, idx, bits, O, lse, dO, dQ, delta, ws + w.step, hip_stream);
     } else {
-        st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
+        st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, step_have, hip_stream);
     }
     if (st != DSV_OK) return st;
     st = launch_idx_transpose(*p, tabs.data(), (int)tabs.size(), idx, bits != nullptr, idx_t, col, ws + w.cnt, w.cnt_bytes, stream);
     if (st != DSV_OK) return st;
-    return dsv_sparse_attn_bwd_dkdv(&sorted, Q, K, V, idx_t, col, lse, delta, dO, dK, dV, ws + w.step, w.step_bytes, hip_stream);
+    return dsv_sparse_attn_bwd_dkdv(&sorted, Q, K, V, idx_t, col, lse, delta, dO, dK, dV, ws + w.step, step_have, hip_stream);
 }
 
 size_t dsv_sparse_attn_bwd_t_workspace(const dsv_problem *p)
@@ -789,13 +801,14 @@ dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, const void
     if (st != DSV_OK) return st;
     if (!ok_ptrs({O, dQ, dK, dV, idx_t, col_ptr})) return DSV_EINVAL;
     const BwdLayout w = bwd_layout(*p, false);
-    st = check_workspace(workspace, ws_bytes, w.total);
+    st = check_workspace(workspace, ws_bytes, w.least);
     if (st != DSV_OK) return st;
     char *ws = static_cast<char *>(workspace);
+    const size_t step_have = std::min(w.step_bytes, ws_bytes - w.step);
     float *delta = reinterpret_cast<float *>(ws + w.delta);
-    st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, w.step_bytes, hip_stream);
+    st = dsv_sparse_attn_bwd_dq(p, Q, K, V, idx, O, lse, dO, dQ, delta, ws + w.step, step_have, hip_stream);
     if (st != DSV_OK) return st;
-    return dsv_sparse_attn_bwd_dkdv(p, Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV, ws + w.step, w.step_bytes,
+    return dsv_sparse_attn_bwd_dkdv(p, Q, K, V, idx_t, col_ptr, lse, delta, dO, dK, dV, ws + w.step, step_have,
                                     hip_stream);
 }
 

@@ -98,3 +98,34 @@ def test_rows_in_any_order():
     got = dsv.sparse_attn_bwd(loose, Q, K, V, torch.cat([r.flip(1).reshape(-1) for r in rows]), O, lse, dO)
     for a, b in zip(got, want):
         assert (a - b).double().norm() / b.double().norm() < 2 ** -8  # two results within half a unit each
+
+
+def test_a_call_without_scratch_gathers_where_gathers_need_none():
+    """L = 2048, d = 64: nothing is cut in ranges, so a null workspace is accepted, and one that holds no partial results."""
+    L, d, ks = 2048, 64, [1024, 512, 1500]
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, ks)
+    refs = [reference(p, Q, K, V, dO, rows, h) for h in range(3)]
+    want = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
+    O = torch.stack([r[0] for r in refs])[None].to(torch.bfloat16)
+    lse = torch.stack([r[1] for r in refs])[None].float()
+    idx = torch.cat([r.reshape(-1) for r in rows])
+    lib, stream = dsv.load_library(), torch.cuda.current_stream().cuda_stream
+    assert dsv.sparse_attn_bwd_dq_workspace(p) > 0
+    dQ, dK, dV = (torch.empty_like(Q) for _ in range(3))
+    delta = torch.empty_like(lse)
+    at = [t.data_ptr() for t in (Q, K, V, idx, O, lse, dO, dQ, delta)]
+    assert lib.dsv_sparse_attn_bwd_dq(p.c, *at, None, 0, stream) == 0
+    at = [t.data_ptr() for t in (Q, K, V, lists, ptrs, lse, delta, dO, dK, dV)]
+    assert lib.dsv_sparse_attn_bwd_dkdv(p.c, *at, None, 0, stream) == 0
+    # Delta alone, then the whole backward with all but the steps' scratch
+    small = torch.empty(-(-3 * L * 4 // 256) * 256, dtype=torch.uint8, device="cuda")
+    whole = torch.empty(dsv.sparse_attn_bwd_workspace(p) - dsv.sparse_attn_bwd_dq_workspace(p), dtype=torch.uint8, device="cuda")
+    calls = [(dQ, dK, dV), dsv.sparse_attn_bwd_t(p, Q, K, V, idx, lists, ptrs, O, lse, dO, workspace=small),
+             dsv.sparse_attn_bwd(p, Q, K, V, idx, O, lse, dO, workspace=whole)]
+    for got in calls:
+        for a, b in zip(got, want):
+            assert (a - b).double().norm() / b.double().norm() < 2 ** -8  # two results within half a unit each
+        for a, b in zip(got, calls[0]):
+            assert torch.equal(a, b)  # the same gathers
+    with pytest.raises(dsv.DsvError):
+        dsv.sparse_attn_bwd_t(p, Q, K, V, idx, lists, ptrs, O, lse, dO, workspace=small[:-256])
