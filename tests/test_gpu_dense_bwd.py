@@ -65,25 +65,33 @@ def test_backward_over_dense_tiles(L, d, ks):
             assert (err.norm(dim=1) <= 2 ** -8 * size + 2 ** -10 * size.mean() + 1.4e-4).all(), (name, h)
 
 
-def test_rows_that_are_not_finite_reach_only_those_that_select_them():
-    L, d = 2048, 128
-    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, [1200, 1000])
+@pytest.mark.parametrize("L,d,ks", [(2048, 128, [1200, 1000]), (3000, 64, [1800, 1500])])
+@pytest.mark.parametrize("where", ["Q", "K", "V", "dO"])
+def test_rows_that_are_not_finite_reach_only_those_that_select_them(L, d, ks, where):
+    """Every sum of a dense tile has zero weights on rows that were not selected, and zero times no number is none."""
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, ks)
     refs = [reference(p, Q, K, V, dO, rows, h) for h in range(2)]
-    j, i = 1027, 777
-    V[0, :, j, 5] = float("inf")   # a key's value row, then a query's gradient row
-    dO[0, :, i, 9] = float("nan")
+    r = [777, 1027, L - 1]  # one row at the end of a tile, two beside finite ones
+    for bad, x in zip(r, (float("inf"), float("nan"), float("-inf"))):
+        dict(Q=Q, K=K, V=V, dO=dO)[where][0, :, bad, 5] = x
     dQ, dK, dV = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
     for h, ref in enumerate(refs):
         keep = ref[5]
-        fine = ~keep[:, j]
-        fine[i] = False
-        assert torch.isfinite(dQ[0, h][fine]).all() and not torch.isfinite(dQ[0, h][keep[:, j]]).all()
-        err = (dQ[0, h].double() - ref[2])[fine].norm() / ref[2][fine].norm()
-        assert err < 4e-3  # twice the rounding of the output
-        # dV of a key sums rows of dO only
-        fine = ~keep[i]
-        assert torch.isfinite(dV[0, h][fine]).all()
-        assert (dV[0, h].double() - ref[4])[fine].norm() / ref[4][fine].norm() < 4e-3
+        mine = torch.ones(L, dtype=torch.bool, device="cuda")
+        mine[r] = False
+        if where in ("K", "V"):  # queries that select one of these keys, through Delta all keys of such queries; dV has no V in it
+            hit = keep[:, r].any(1)
+            fine = [~hit, ~keep[hit].any(0), mine if where == "K" else mine | True]
+        else:                    # these queries themselves, and the keys that they select
+            fine = [mine, ~keep[r].any(0), ~keep[r].any(0)]
+        for name, got, want, ok in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref[2:5], fine):
+            if name == "dK" and where in ("K", "V") and not ok.any():
+                continue
+            assert ok.any()
+            assert torch.isfinite(got[0, h][ok]).all(), (name, h)
+            assert (got[0, h].double() - want)[ok].norm() / want[ok].norm() < 4e-3, (name, h)  # twice the rounding of the output
+        broken = dQ[0, h][~fine[0]]
+        assert not torch.isfinite(broken).all(1).any()
 
 
 def test_rows_in_any_order():
