@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
 
     // Accumulator v of a lane: own row 8 (v / 4) + 4 half + v % 4, channel 32 nb + n.
     const int64_t first = (int64_t)bh * L + row0 + rb * kOwn + wave * 32;
-    uint32_t bad = 0;  // own rows with a sum that is not finite
+    uint32_t bad = 0;  // own rows with a sum that is not finite: they are stored below, once
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int o = 8 * (v / 4) + v % 4;
@@ -305,8 +305,9 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) zero = fmaf(a[nb][v], 0.f, fmaf(b[nb][v], 0.f, zero));
         const unsigned long long off = __ballot(zero != 0.f);
-        bad |= ((uint32_t)off ? 1u << o : 0u) | ((uint32_t)(off >> 32) ? 16u << o : 0u);
-        if (rb * kOwn + wave * 32 + o + 4 * half < nrows) {
+        const uint32_t here = ((uint32_t)off ? 1u << o : 0u) | ((uint32_t)(off >> 32) ? 16u << o : 0u);
+        bad |= here;
+        if (rb * kOwn + wave * 32 + o + 4 * half < nrows && !(here >> (o + 4 * half) & 1u)) {
             const int64_t at = ((first + o + 4 * half) * pl.S + range) * D + n;
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
     }
     if constexpr (!KEYS) {
         const float all = delta + __shfl_xor(delta, 32);
-        if (live && half == 0) pdelta[own_row * pl.S + range] = all;
+        if (live && half == 0 && !(bad >> n & 1u)) pdelta[own_row * pl.S + range] = all;
     }
     // Zero times a row that is not finite is no number: such own rows are formed once more from their selected pairs alone.
     constexpr int CH = D / 64;
