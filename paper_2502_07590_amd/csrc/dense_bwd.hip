@@ -77,6 +77,86 @@ __device__ __forceinline__ float pick(uint32_t mask, float a, float b)  // mask 
 }
 __device__ __forceinline__ float keep(uint32_t mask, float a) { return __uint_as_float(mask & __float_as_uint(a)); }
 
+// Zero times a row that is not finite is no number, and the products above multiply rows that are not selected by zero: an own row whose
+// sums came out not finite is formed once more, by its wave, from its selected pairs alone.  16 lanes per pair, eight pairs at a
+// time.  One such row of K sends about half of its range's queries through here, and every key that such a query selects: L = 20280, four
+// heads, k = 2028, the whole backward 5.1 ms on finite rows, 8.6 with one NaN row in a head's K (15.7 with one pair at a time), 11.0 with a head
+// of them (23.1); by gathers 6.9 whatever the rows hold.
+template <int D, bool KEYS>
+__device__ __forceinline__ void exact_row(const bf16_t *__restrict__ xr, const bf16_t *__restrict__ yr, const bf16_t *__restrict__ R1,
+                                          const bf16_t *__restrict__ R2, const uint32_t *__restrict__ mr, int tile0, int tile1, float c2, float l2,
+                                          float dd, const float2 *__restrict__ stat, float *__restrict__ oa, float *__restrict__ ob,
+                                          float *__restrict__ odelta)
+{
+    constexpr int CH = D / 16, U = 2;
+    const int lane = threadIdx.x & 63, grp = lane >> 4, at = (lane & 15) * CH;
+    const RowChunk<bf16_t, CH> x = load_chunk<bf16_t, CH>(xr + at), y = load_chunk<bf16_t, CH>(yr + at);
+    float sa[CH], sb[CH], dsum = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) sa[c] = sb[c] = 0.f;
+    auto words = [&](int t) -> uint64_t { return (t < tile1 ? mr[t] : 0u) | (uint64_t)(t + 1 < tile1 ? mr[t + 1] : 0u) << 32; };
+    uint64_t next = words(tile0);
+    for (int t = tile0; t < tile1; t += 2) {
+        uint64_t w = next;
+        next = words(t + 2);
+        while (w) {  // wave-uniform
+            int j[U];
+            bool has[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {  // group g: the g-th of the next four
+                uint64_t mine = w;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) mine = i < grp ? mine & (mine - 1) : mine;
+                has[u] = mine != 0;
+                j[u] = t * kTile + (has[u] ? __ffsll((unsigned long long)mine) - 1 : 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w &= w - 1;
+            }
+            RowChunk<bf16_t, CH> r1[U], r2[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                r1[u] = load_chunk<bf16_t, CH>(R1 + (int64_t)j[u] * D + at);
+                r2[u] = load_chunk<bf16_t, CH>(R2 + (int64_t)j[u] * D + at);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float s = row_sum<16>(dot_chunk<bf16_t, CH>(x, r1[u])), e = row_sum<16>(dot_chunk<bf16_t, CH>(y, r2[u]));
+                float q, wgt;
+                if constexpr (KEYS) {
+                    const float2 rs = stat[j[u]];
+                    q = fast_exp2(fmaf(s, c2, -rs.x));
+                    wgt = q * (e - rs.y);
+                } else {
+                    q = fast_exp2(fmaf(s, c2, -l2));
+                    wgt = q * (e - dd);
+                }
+                if (has[u]) {
+                    if constexpr (!KEYS) dsum = fmaf(q, e, dsum);
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        const uint32_t v1 = r1[u].w[c / 2], v2 = KEYS ? r2[u].w[c / 2] : v1;
+                        sa[c] = fmaf(wgt, __uint_as_float(c & 1 ? v1 & 0xFFFF0000u : v1 << 16), sa[c]);
+                        sb[c] = fmaf(q, __uint_as_float(c & 1 ? v2 & 0xFFFF0000u : v2 << 16), sb[c]);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        sa[c] = group_sum<16>(sa[c]);
+        sb[c] = group_sum<16>(sb[c]);
+        if (grp == 0) {
+            oa[at + c] = sa[c];
+            ob[at + c] = sb[c];
+        }
+    }
+    if constexpr (!KEYS) {
+        dsum = group_sum<16>(dsum);
+        if (lane == 0) *odelta = dsum;
+    }
+}
+
 // KEYS: own rows are keys (X, Y = K, V; R1, R2 = Q, dO): a = dK = sum dS q, b = dV = sum p dO, with row statistics stat[query] =
 // {lse * log2(e), Delta}.  Else own rows are queries (X, Y = Q, dO; R1, R2 = K, V): a = C = sum p (dP - D0) k, b = B = sum p k, and
 // Delta (dq_sweep in stage2_core.h says what they are).
@@ -320,55 +400,14 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
         const float all = delta + __shfl_xor(delta, 32);
         if (live && half == 0 && !(bad >> n & 1u)) pdelta[own_row * pl.S + range] = all;
     }
-    // Zero times a row that is not finite is no number: such own rows are formed once more from their selected pairs alone.
-    constexpr int CH = D / 64;
     for (; bad; bad &= bad - 1) {
         const int o = __ffs(bad) - 1;
         if (rb * kOwn + wave * 32 + o >= nrows) continue;
         const int64_t row = first + o;
         const uint32_t *mr = bits + ((int64_t)slot * nrows + rb * kOwn + wave * 32 + o) * pitch;
-        const float l2 = __shfl(lse2, o), dd = __shfl(d0, o);
-        float x[CH], y[CH], sa[CH], sb[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            x[c] = bf16_to_f32(X[row * D + lane * CH + c]);
-            y[c] = bf16_to_f32(Y[row * D + lane * CH + c]);
-            sa[c] = sb[c] = 0.f;
-        }
-        float dsum = 0.f;
-        for (int t = tile0; t < tile1; ++t)
-            for (uint32_t w = mr[t]; w; w &= w - 1) {
-                const int64_t j = t * kTile + __ffs(w) - 1, at = hb + j * D + lane * CH;
-                float s = 0.f, e = 0.f;
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    s = fmaf(x[c], bf16_to_f32(R1[at + c]), s);
-                    e = fmaf(y[c], bf16_to_f32(R2[at + c]), e);
-                }
-                s = group_sum<1>(s);
-                e = group_sum<1>(e);
-                float q, wgt;
-                if constexpr (KEYS) {
-                    const float2 rs = stat[(int64_t)bh * L + j];
-                    q = fast_exp2(fmaf(s, c2, -rs.x));
-                    wgt = q * (e - rs.y);
-                } else {
-                    q = fast_exp2(fmaf(s, c2, -l2));
-                    wgt = q * (e - dd);
-                    dsum = fmaf(q, e, dsum);
-                }
-#pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    sa[c] = fmaf(wgt, bf16_to_f32(R1[at + c]), sa[c]);
-                    sb[c] = fmaf(q, bf16_to_f32((KEYS ? R2 : R1)[at + c]), sb[c]);
-                }
-            }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            pa[(row * pl.S + range) * D + lane * CH + c] = sa[c];
-            pb[(row * pl.S + range) * D + lane * CH + c] = sb[c];
-        }
-        if (!KEYS && lane == 0) pdelta[row * pl.S + range] = dsum;
+        exact_row<D, KEYS>(X + row * D, Y + row * D, R1 + hb, R2 + hb, mr, tile0, tile1, c2, __shfl(lse2, o), __shfl(d0, o),
+                           KEYS ? stat + (int64_t)bh * L : nullptr, pa + (row * pl.S + range) * D, pb + (row * pl.S + range) * D,
+                           KEYS ? nullptr : pdelta + row * pl.S + range);
     }
 }
 
