@@ -142,10 +142,12 @@ DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, cons
  * rounding alone would cost more than the output tolerance; O only serves as a centring value
  * (dO . O is within rounding of Delta) that keeps the accumulated weights small.  The workspace holds Delta, the transposed index
  * (as large as idx), its column pointers and the counters of dsv_idx_transpose.  The transposed index built here has
- * ascending lists whatever the order inside the rows of idx is, so the dkdv step may run its L2-blocked kernel
- * and the results are identical, bit for bit, to dsv_sparse_attn_bwd_t on dsv_idx_transpose's output and from run to
- * run.  Without DSV_FLAG_SORTED_INDEX the rows of larger problems are first copied in ascending order (same workspace), so
- * that the dq step is L2-blocked as well; the result is then that of the ascending rows.  Building the transposed index is a
+ * ascending lists whatever the order inside the rows of idx is, so the dkdv step always runs as it does with
+ * DSV_FLAG_SORTED_INDEX.  Bit for bit, the results are the same from run to run, and with the flag those of dsv_sparse_attn_bwd_t on
+ * dsv_idx_transpose's output.  Without it the rows of larger problems (K and V rows of a head above 3 MB) are first copied in ascending
+ * order, or taken as a bit per key (same workspace), so that the dq step runs as with the flag too: the results are those of
+ * dsv_sparse_attn_bwd_t with the flag on the ascending rows.  For smaller problems without the flag dQ is that of dsv_sparse_attn_bwd_dq
+ * without it, dK and dV are those of dsv_sparse_attn_bwd_dkdv with it.  Building the transposed index is a
  * tenth of the call (L = 20280, four heads keeping 507 .. 4056 keys: 0.55 ms of 4.8); callers that run stage 1 here can take
  * its transposed index (dsv_lowrank_topk_t) and call dsv_sparse_attn_bwd_t. */
 DSV_API size_t dsv_sparse_attn_bwd_workspace(const dsv_problem *p);

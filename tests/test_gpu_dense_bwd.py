@@ -94,18 +94,30 @@ def test_rows_that_are_not_finite_reach_only_those_that_select_them(L, d, ks, wh
         assert not torch.isfinite(broken).all(1).any()
 
 
-def test_rows_in_any_order():
-    """The whole backward on unsorted rows: dense heads take them as they are, the others by an ascending copy."""
-    L, d = 6201, 128
-    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, [150, 1300, 1000])
-    refs = [reference(p, Q, K, V, dO, rows, h) for h in range(3)]
+# K and V rows of 3.2 MB: rows sorted first; 0.4 MB and 1 MB: not (dkdv over dense tiles all the same, and by gathers beside them)
+@pytest.mark.parametrize("L,d,ks", [(6201, 128, [150, 1300, 1000]), (1500, 64, [1400] * 6), (4100, 64, [2050, 40, 1640])])
+def test_whole_backward_is_that_of_its_steps(L, d, ks):
+    """The whole backward, which builds the lists itself, bit for bit against the steps on the same lists, with the flag and on
+    rows in any order without it; and the latter against ascending rows."""
+    p, Q, K, V, dO, rows, lists, ptrs = problem(L, d, ks)
+    refs = [reference(p, Q, K, V, dO, rows, h)[:2] for h in range(len(ks))]
     want = backward(p, Q, K, V, dO, rows, lists, ptrs, refs)
     O = torch.stack([r[0] for r in refs])[None].to(torch.bfloat16)
     lse = torch.stack([r[1] for r in refs])[None].float()
-    loose = dsv.Problem(1, 3, L, d, 16, "bf16", [150, 1300, 1000], p.scale)
-    got = dsv.sparse_attn_bwd(loose, Q, K, V, torch.cat([r.flip(1).reshape(-1) for r in rows]), O, lse, dO)
+    idx = torch.cat([r.reshape(-1) for r in rows])
+    for _ in range(2):
+        for a, b in zip(dsv.sparse_attn_bwd(p, Q, K, V, idx, O, lse, dO), want):
+            assert torch.equal(a, b)
+    loose = dsv.Problem(1, len(ks), L, d, 16, "bf16", ks, p.scale)
+    turned = torch.cat([r.flip(1).reshape(-1) for r in rows])
+    got = dsv.sparse_attn_bwd(loose, Q, K, V, turned, O, lse, dO)
     for a, b in zip(got, want):
         assert (a - b).double().norm() / b.double().norm() < 2 ** -8  # two results within half a unit each
+    if L * 4 * d <= 3 << 20:
+        dQ, delta = dsv.sparse_attn_bwd_dq(loose, Q, K, V, turned, O, lse, dO)
+        want = [dQ, *dsv.sparse_attn_bwd_dkdv(p, Q, K, V, lists, ptrs, lse, delta, dO)]
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
 
 
 def test_a_call_without_scratch_gathers_where_gathers_need_none():
