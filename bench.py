@@ -32,13 +32,13 @@ VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9   # 256 CUs x 64 fp32 lanes x 2.4 GHz, on
 # (FETCH_SIZE reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0), and the L2 hit rate from
 # TCC_HIT_sum / (TCC_HIT_sum + TCC_MISS_sum).  Source: profiles/config2_pmc_counters.md.  The figures belong to ONE
 # build of the kernels: they are reported only while the library still names that version.
-PMC_LIBRARY_VERSION = "dsv 0.6 (gfx950)"
+PMC_LIBRARY_VERSION = "dsv 0.8 (gfx950)"
 PMC_CONFIG2 = {
-    "sparse_attn_fwd": {"fetch_kib": 88670095, "write_kib": 12783806, "l2_hit_rate": 0.7181},  # mask and dense tiles
-    "sparse_attn_bwd_dq": {"fetch_kib": 48587277, "write_kib": 12976332, "l2_hit_rate": 0.9644},
-    "sparse_attn_bwd_dkdv": {"fetch_kib": 33903656, "write_kib": 12582915, "l2_hit_rate": 0.9738},
+    "sparse_attn_fwd": {"fetch_kib": 87572678, "write_kib": 12783803, "l2_hit_rate": 0.7130},  # mask and dense tiles
+    "sparse_attn_bwd_dq": {"fetch_kib": 60808786, "write_kib": 25582164, "l2_hit_rate": 0.8245},  # mask and dense tiles
+    "sparse_attn_bwd_dkdv": {"fetch_kib": 33833781, "write_kib": 12582916, "l2_hit_rate": 0.9740},
 }
-# the gather sweep inside each stage-2 call (the kernel the roofline object is about)
+# the sweep inside each stage-2 call, by gathers or over dense tiles (what the roofline object is about)
 SWEEP_OF_CALL = {"sparse_attn_fwd": "fwd_sweep", "sparse_attn_bwd_dq": "dq_sweep", "sparse_attn_bwd_dkdv": "dkdv_sweep"}
 # Vector memory path (L2 -> vector L1 -> registers): 64 bytes per clock per CU, 256 CUs, 2.4 GHz.  The sweeps'
 # gathers are served by it (L2 hit rate 96-98 %); it is what bounds them.
@@ -47,6 +47,8 @@ L1_PEAK_GBS = 256 * 64 * 2.4
 # path: bench.py --gather-ceiling, summary in profiles/gather_ceiling.md (index streamed from memory, 4 MB ranges).
 GATHER_CEILING_GBS = {"sparse_attn_fwd": 34241.5, "sparse_attn_bwd_dq": 33888.4, "sparse_attn_bwd_dkdv": 33888.4}
 MFMA_BF16_PEAK_TFLOPS = 2500.0
+# products of one selected pair, x d: q.k and p v; q.k, dO.v and dS k; q.k, dO.v, dS q and p dO
+FLOPS_PER_PAIR = {"sparse_attn_fwd": 4, "sparse_attn_bwd_dq": 6, "sparse_attn_bwd_dkdv": 8}
 
 
 def pmc_traffic_bytes(call):
@@ -487,34 +489,38 @@ def main():
     pmc_ok = args.config == 2 and not args.unsorted and dsv.version() == PMC_LIBRARY_VERSION
     stage2 = {}
     for n, pb in pair_bytes.items():
-        k_ms = kern_ms[SWEEP_OF_CALL[n]]          # the sweep kernel alone, by HIP events on its own stream
-        gbs = pb * nnz / (k_ms * 1e-3) / 1e9
+        k_ms = kern_ms[SWEEP_OF_CALL[n]]          # the sweep alone, by HIP events on its own stream
         traffic = pmc_traffic_bytes(n) if pmc_ok else None
+        # heads over dense tiles run on the matrix cores, the others gather; where a call has both, its time is that of both and the
+        # record is of the form that holds more of the selected pairs, counting those alone
+        least = dsv.dense_min_k(path.p, SWEEP_OF_CALL[n])
+        dense_ks = [int(k) for k in ks if least and k >= least]
+        dense_nnz = cfg.L * sum(dense_ks)
+        shared = {"traffic": traffic, "heads_over_dense_tiles": len(dense_ks), "kernel_ms": round(k_ms, 3), "call_ms": round(call_ms[n], 3),
+                  # against HBM: the bytes that really crossed the fabric (traffic) per second
+                  "hbm": {"achieved": round(traffic / (k_ms * 1e-3) / 1e9, 1) if traffic else None, "peak": HBM_PEAK_GBS,
+                          "unit": "GB/s", "frac": round(traffic / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
+                          "l2_hit_rate": PMC_CONFIG2[n]["l2_hit_rate"] if pmc_ok else None}}
+        if 2 * dense_nnz > nnz:
+            flops = FLOPS_PER_PAIR[n] * cfg.d
+            kept, formed = (flops * pairs / (k_ms * 1e-3) / 1e12 for pairs in (dense_nnz, len(dense_ks) * cfg.L * cfg.L))
+            stage2[n] = {"bound": "mfma", "bound_name": "matrix cores, dense bf16", "achieved": round(kept, 1),
+                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(kept / MFMA_BF16_PEAK_TFLOPS, 4),
+                         "kernel": "mask and dense tile kernels of " + n, **shared,
+                         "formed": {"achieved": round(formed, 1), "frac": round(formed / MFMA_BF16_PEAK_TFLOPS, 4)},
+                         "note": f"achieved = {FLOPS_PER_PAIR[n]} d flops per selected pair / kernel time; formed counts every pair of the "
+                                 "tiles, and each product once, though weights enter as two words and the backward's sums run on the "
+                                 "sparse instruction"}
+            continue
+        gathered = pb * (nnz - dense_nnz)
+        gbs = gathered / (k_ms * 1e-3) / 1e9
         stage2[n] = {"bound": "l1", "bound_name": "vector memory path, L2 -> vector L1 -> registers (64 B/clk/CU x 256 CUs x 2.4 GHz)",
                      "achieved": round(gbs, 1), "peak": round(L1_PEAK_GBS, 1), "unit": "GB/s", "frac": round(gbs / L1_PEAK_GBS, 4),
-                     "traffic": traffic,
-                     "algorithmic_bytes_per_launch": pb * nnz, "kernel": SWEEP_OF_CALL[n] + " kernel of " + n,
-                     "kernel_ms": round(k_ms, 3), "call_ms": round(call_ms[n], 3),
-                     # the same launch against HBM: the bytes that really crossed the fabric (traffic) per second
-                     "hbm": {"achieved": round(traffic / (k_ms * 1e-3) / 1e9, 1) if traffic else None, "peak": HBM_PEAK_GBS,
-                             "unit": "GB/s", "frac": round(traffic / (k_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                             "l2_hit_rate": PMC_CONFIG2[n]["l2_hit_rate"] if pmc_ok else None},
+                     "algorithmic_bytes_per_launch": gathered, "kernel": SWEEP_OF_CALL[n] + " kernel of " + n, **shared,
                      "gather_only_ceiling": {"achieved_by_pure_gather_kernel": GATHER_CEILING_GBS[n], "unit": "GB/s",
                                              "frac_of_it": round(gbs / GATHER_CEILING_GBS[n], 4)},
                      "note": "achieved = algorithmic gather bytes (K row + V row + index entry per pair) / kernel time; the ranges "
-                             "of the split-K plan stay in each XCD's L2, so the bytes cross the L2 -> L1 path, not HBM.  Heads that "
-                             "keep about one key in 16 and more run the backward steps over dense tiles: for them achieved is what "
-                             "gathers would have had to bring in that time"}
-        if n == "sparse_attn_fwd" and gbs > L1_PEAK_GBS:
-            # more than gathers could bring: the heads ran over dense tiles with a mask, on the matrix cores
-            formed, kept = (4.0 * cfg.d * pairs / (k_ms * 1e-3) / 1e12 for pairs in (n_scores, nnz))
-            stage2[n] = {"bound": "mfma", "bound_name": "matrix cores, dense bf16", "achieved": round(kept, 1),
-                         "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(kept / MFMA_BF16_PEAK_TFLOPS, 4),
-                         "traffic": traffic, "kernel": "mask and dense tile kernels of " + n, "kernel_ms": round(k_ms, 3),
-                         "call_ms": round(call_ms[n], 3),
-                         "formed": {"achieved": round(formed, 1), "frac": round(formed / MFMA_BF16_PEAK_TFLOPS, 4)},
-                         "note": "achieved = 4 d flops per selected pair / kernel time; formed counts every pair of the tiles, and the "
-                                 "product with V once, though its weights come as two words"}
+                             "of the split-K plan stay in each XCD's L2, so the bytes cross the L2 -> L1 path, not HBM"}
     dominant = max(pair_bytes, key=lambda n: kern_ms[SWEEP_OF_CALL[n]])
     roofline = dict(stage2[dominant])
     # Stage 1 is selection work on the plain vector ALUs.  Algorithmic work: per score one compare against the

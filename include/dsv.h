@@ -144,7 +144,7 @@ DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, cons
  * (as large as idx), its column pointers and the counters of dsv_idx_transpose.  The transposed index built here has
  * ascending lists whatever the order inside the rows of idx is, so the dkdv step always runs as it does with
  * DSV_FLAG_SORTED_INDEX.  Bit for bit, the results are the same from run to run, and with the flag those of dsv_sparse_attn_bwd_t on
- * dsv_idx_transpose's output.  Without it the rows of larger problems (K and V rows of a head above 3 MB) are first copied in ascending
+ * dsv_idx_transpose's output.  Without it the rows of larger problems (K and V rows of a head above 3 MB, at most 524288 tokens) are first copied in ascending
  * order, or taken as a bit per key (same workspace), so that the dq step runs as with the flag too: the results are those of
  * dsv_sparse_attn_bwd_t with the flag on the ascending rows.  For smaller problems without the flag dQ is that of dsv_sparse_attn_bwd_dq
  * without it, dK and dV are those of dsv_sparse_attn_bwd_dkdv with it.  Building the transposed index is a
