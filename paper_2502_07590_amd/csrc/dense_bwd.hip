@@ -17,7 +17,7 @@
 //
 // Measured, L = 32768, four heads, k = 2048 (6 % kept), with the mask (0.43 ms): dq 5.09 ms by gathers -> 4.70, dkdv 5.68 -> 5.77 (which
 // therefore gathers there); L = 20280, two of four heads at one key in 10 and in 5: whole backward 7.63 -> 4.78 ms, 0.4 of that the ascending copy that they no longer need.  Matrix cores are busy for
-// 0.47 of the time and the vector units for 0.49: a wave's products and weights wait for each other, and two waves per SIMD --
+// 0.44 to 0.48 of the cycles and the vector units for 0.48 to 0.52: a wave's products and weights wait for each other, and two waves per SIMD --
 // all that 256 registers allow -- overlap them little.  Weights laid beside the products inside a wave gave nothing (dq) or spilled
 // (dkdv, 6.5 ms); fragment reads left to the compiler's order, which puts each right before its use, cost 0.5 ms of dq.
 #include <algorithm>
@@ -256,6 +256,8 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
         if (__any(word != 0u)) {  // wave-uniform
             floatx16_t s, dp;
             if constexpr (KEYS) {
+                // (the additions of the products round at the size of lse / scale and Delta; against 64 bits the gradients are as far off as by
+                // gathers, scales of 1e-6 to 1)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const float4 l4 = *reinterpret_cast<const float4 *>(st + half * 16 + g * 4);
