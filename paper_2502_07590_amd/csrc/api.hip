@@ -244,13 +244,15 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
 // dq and dkdv, one in 16: 1279, 1239 : 1293, 1548; in 12: 1423, 1627 : 1332, 1663; in 8: 2055, 2407 : 1547, 1852; dq, d = 128, one in 16: one
 // head of 65536 5429 : 4739, of 131072 21485 : 19027.
 // 40 us are what launches, the mask and a chip that is not full cost small problems.
-// The dq step's gathers need no partial results where sequences are short, and where few keys are kept only those of two or four
-// ranges; dense tiles have those of eight to write and to merge (and with fewer ranges blocks that last as much longer, of which few
-// rounds fill the chip badly), so there the gathers' own estimate decides.  Gathers against dense, d = 128: 24 heads of 1500,
-// k = 187: 150 : 231; 12 of 3000, k = 250: 185 : 271; 24 of 2048, k = 256: 248 : 341; 12 of 4096, k = 341: 332 : 429; but 4 of 2048, k = 512:
-// 85 : 58; one of 8192, k = 1024: 164 : 114; d = 64, 24 of 3000, k = 375: 292 : 345; 2 of 4096, k = 1024: 90 : 58.  Over 628 dq steps (both
-// d, 1 to 24 heads of 1024 to 131072, 1/24 to 3/4 kept) the form chosen takes 1.003 times the faster one's time in the mean, and dense is
-// chosen where it is slower in two (8 %).  Dkdv gathers cost short sequences more: of the same 628 none where dense is chosen is slower.
+// The dq step's gathers of short sequences need no partial results, or where few keys are kept those of two or four ranges; dense tiles
+// have those of eight to write and to merge (and with fewer ranges blocks that last as much longer, of which few rounds fill the chip
+// badly).  Up to 3 MB of K and V rows per head the gathers' own estimate (row_time) decides therefore, unless it is that of eight ranges
+// and more; above, rows soon miss the L2 without ranges, and that estimate is as far off as what there is to gain.  Gathers against dense,
+// d = 128: 24 heads of 1500, k = 187: 150 : 231; 12 of 3000, k = 250: 185 : 271; 24 of 2048, k = 256: 248 : 341; 12 of 4096, k = 341: 332 : 429;
+// but 4 of 2048, k = 512: 85 : 58; 2 of 3000, k = 750: 95 : 61; d = 64, 24 of 3000, k = 375: 292 : 345; 2 of 4096, k = 1024: 90 : 58.  Over 894
+// dq steps of 30 us and more (both d, 1 to 24 heads of 1000 to 131072, 1/24 to 3/4 kept) the form chosen takes 1.004 times the faster
+// one's time in the mean; dense is chosen where it is more than 5 % slower in 9 (most 14 %), gathers in 14.  Dkdv gathers cost short
+// sequences more: of 1008 steps dense is chosen where it is 5 % slower in none, gathers in 241.
 // pl, all: ranges of the dq step, and its form and time without dense tiles.
 int32_t dense_bwd_min_k(const dsv_problem &p, bool keys, const SplitPlan &pl, const RowTime &all)
 {
@@ -259,7 +261,7 @@ int32_t dense_bwd_min_k(const dsv_problem &p, bool keys, const SplitPlan &pl, co
     const bool wide = p.d == 128;
     const double pair = wide ? (keys ? 21.3e-6 : 18.9e-6) : keys ? 11.3e-6 : 10e-6;
     const double formed = wide ? (keys ? 1.2e-6 : 0.95e-6) : keys ? 0.8e-6 : 0.6e-6, more = wide ? 3e-6 : 2.2e-6;
-    const bool same_ranges = keys || (all.form == RowForm::ranges && pl.S_pad >= 8);
+    const bool flat = keys || (all.form == RowForm::ranges && pl.S_pad >= 8) || kv_bytes(p) > ((size_t)3 << 20);
     std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
     std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
     int32_t best_k = INT32_MAX;
@@ -270,8 +272,8 @@ int32_t dense_bwd_min_k(const dsv_problem &p, bool keys, const SplitPlan &pl, co
         kept += (double)p.B * p.L * k;
         if (m < p.H && ks[m] == k) continue;
         const double dense = formed * rows * p.L + more * kept;
-        const double saved = same_ranges ? pair * kept - dense - 40.0
-                                         : all.us - row_time(p, pl, true, k).us - 1.05 * (20.0 + dense + 2.4e-6 * p.d * rows * std::max(pl.S_pad, 8));
+        const double saved = flat ? pair * kept - dense - 40.0
+                                  : all.us - row_time(p, pl, true, k).us - (20.0 + dense + 2.4e-6 * p.d * rows * std::max(pl.S_pad, 8));
         if (saved > best) {
             best = saved;
             best_k = k;

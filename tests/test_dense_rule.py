@@ -35,7 +35,7 @@ def test_heads_of_long_sequences(L, ks, want):
 @pytest.mark.parametrize("d,H,L,k,gathers,dense", [
     (128, 24, 1500, 187, 150, 231), (128, 12, 3000, 250, 185, 271), (128, 24, 2048, 256, 248, 341), (128, 12, 4096, 341, 332, 429),
     (128, 24, 4096, 341, 673, 821), (64, 24, 3000, 375, 292, 345), (64, 12, 3000, 375, 146, 159), (128, 6, 6000, 500, 354, 385),
-    (128, 4, 2048, 512, 85, 58), (128, 2, 3000, 750, 95, 61), (128, 1, 8192, 1024, 164, 114), (64, 2, 4096, 1024, 90, 58),
+    (128, 6, 21861, 1452, 4403, 3672), (128, 4, 2048, 512, 85, 58), (128, 2, 3000, 750, 95, 61), (128, 1, 8192, 1024, 164, 114), (64, 2, 4096, 1024, 90, 58),
     (128, 4, 6000, 750, 352, 263), (64, 12, 8192, 1024, 1032, 860), (128, 3, 24000, 1500, 2268, 1995), (128, 3, 24000, 1000, 1502, 1777)])
 def test_dq_of_short_and_long_sequences(d, H, L, k, gathers, dense):
     assert (least(L, [k] * H, d=d)[0] > 0) == (dense < gathers)
