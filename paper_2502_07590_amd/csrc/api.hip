@@ -212,7 +212,9 @@ bool sort_rows_first(const dsv_problem &p)
 // 64-key tile a round of blocks takes 2.0 (1.45) with at most one block of 128 queries per CU and 2.9 (2.5) when the CUs
 // hold two (three), and a last round that is partly empty costs a fifth of a full one.  Estimated and measured, d = 128:
 // 12 heads of 2048, 64 : 81; 4 of 4096, 128 : 131; 1 of 8192, 256 : 237; 12 of 8192, 631 : 685; 4 of 16384, 891 : 870; 4 of 32768,
-// 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.
+// 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.  On sparse products, where few
+// pairs are kept (dense_fwd_form in dense.hip), a sixth less, a
+// fifteenth at d = 64: 4 of 32768, k = L / 22: 3170 -> 2670 (gathering 3610), d = 64, k = L / 16: 2220 -> 2070.
 int32_t dense_fwd_min_k(const dsv_problem &p)
 {
     if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
@@ -221,12 +223,14 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
     std::vector<int32_t> ks(p.k_per_head, p.k_per_head + p.H);
     std::sort(ks.begin(), ks.end(), [](int32_t a, int32_t b) { return a > b; });
     int32_t best_k = INT32_MAX;
-    double best = 0.0, gathered = 0.0;  // us saved by the heads with the largest k
+    double best = 0.0, gathered = 0.0, kept = 0.0;  // us saved by the heads with the largest k
     for (int m = 1; m <= p.H; ++m) {
         gathered += pair * (double)p.B * p.L * ks[m - 1];
+        kept += ks[m - 1];
         if (m < p.H && ks[m] == ks[m - 1]) continue;
         const double blocks = (double)p.B * m * ((p.L + 127) / 128), tiles = (p.L + 63) / 64;
-        const double dense = tiles * (blocks <= 256 ? light : full * std::max(1.0, blocks / slots + 0.2));
+        const bool few = blocks > 256 && kept * 14 <= (double)p.L * m;  // on sparse products
+        const double dense = tiles * (blocks <= 256 ? light : (few ? (wide ? 0.83 : 0.93) : 1.0) * full * std::max(1.0, blocks / slots + 0.2));
         if (gathered - 1.1 * dense > best) {
             best = gathered - 1.1 * dense;
             best_k = ks[m - 1];

@@ -16,11 +16,11 @@
 //                     The probabilities go in as bf16 head and tail, 16 significant bits: the result is then as far from the
 //                     64-bit one as its rounding to bf16 puts it (1.66e-3).  One bf16 word saves a fifth of the time
 //                     (2.85 ms) and leaves 1.74e-3, further off than the gathering kernels over ranges (1.68e-3).
-// Per 64 keys and wave: 1536 clocks of matrix work beside about 1450 of vector work, a third of those the exponentials: two waves
-// per SIMD overlap them little (the sum, at the 2 GHz that such work runs at, is the time measured).
+// Per 64 keys and wave: 1536 clocks of matrix work beside about 1450 of vector work, a third of those the exponentials.
 #include <algorithm>
+#include <type_traits>
 
-#include "stage2_core.h"
+#include "dense_tile.h"
 
 namespace dsv {
 
@@ -199,9 +199,232 @@ __global__ __launch_bounds__(256, 2) void dense_fwd_kernel(const bf16_t *__restr
                 make_uint2(pack_bf16x2(o[nb][4 * g] * inv, o[nb][4 * g + 1] * inv), pack_bf16x2(o[nb][4 * g + 2] * inv, o[nb][4 * g + 3] * inv));
 }
 
+// The larger of two numbers, as the middle one of three.  (fmaxf first makes quiet what might be a signalling NaN, an instruction per operand, and
+// the compiler makes fmaxf of a middle one with an infinity that it can see.  A NaN loses here too.)
+__device__ __forceinline__ float larger(float a, float b, float infinity) { return __builtin_amdgcn_fmed3f(a, b, infinity); }
+
+// The same on sparse products, for heads that keep few pairs of a tile, as in the backward (dense_bwd.hip): every lane takes the first two
+// selected of a group of four keys, only those become weights, and v_smfmac_f32_32x32x32_bf16 adds up twice the keys in the time of a
+// dense product; where some group has a third the wave goes over the tile again.  A sum's rows are queries then, its lanes
+// channels: what is known per query goes there through LDS, which the maximum does rarely, as it may lag by 2^8.
+// What bounds it is power: at 1.7 to 1.8 of 2.4 GHz more waves or fewer waits change nothing, fewer operations do.  Per 32 keys and wave 512 clocks
+// of matrix work (768 on dense products) and about 520 of vector work, those of second rounds aside.  L = 32768, four heads, k = 2048, with the
+// mask: 3.28 -> 2.90 ms.  Setting the pairs of second rounds aside for products of their own, sixteen at a time, cost what it gave.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void dense_fwd_pairs_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                                     const bf16_t *__restrict__ V, const uint32_t *__restrict__ bits,
+                                                                     int pitch, bf16_t *__restrict__ O, float *__restrict__ lse, int L,
+                                                                     float scale, HeadTable tab, int slot0, int row0, int nrows)
+{
+    typedef TileLayout<D> TL;
+    constexpr int NM = D / 16, NB = D / 32, CT = 2;
+    // two pairs of tiles in turn, each array a variable of its own: reads of one then need not wait for the loads into the other
+    __shared__ __align__(16) unsigned char t1a[CT * TL::BYTES], t1b[CT * TL::BYTES], t2a[CT * TL::BYTES], t2b[CT * TL::BYTES];
+    __shared__ __align__(16) float by_row[NW * 32];           // a factor per query, from its lanes to the rows of the sums
+    const int bh = tab.bh[slot0 + blockIdx.y];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, half = lane >> 5;
+    const int first = blockIdx.x * (32 * NW) + wave * 32;  // the wave's first row in this piece
+    const bool live = first + n < nrows;
+    const int rc = live ? first + n : nrows - 1;
+    const int64_t hb = (int64_t)bh * L * D;
+    const int64_t qi = row0 + rc;
+    const uint32_t mrow = ((uint32_t)blockIdx.y * nrows + rc) * pitch;  // masks hold less than 2^32 words
+    const unsigned char *m1 = reinterpret_cast<const unsigned char *>(K + hb), *m2 = reinterpret_cast<const unsigned char *>(V + hb);
+    const int tile1 = (L + kTile - 1) / kTile;
+
+    bf16x8_t qf[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) qf[m] = *reinterpret_cast<const bf16x8_t *>(Q + hb + qi * D + m * 16 + half * 8);
+    floatx16_t o[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[nb][v] = 0.f;
+    float mx = -INFINITY, mc = 0.f, l = 0.f;  // maximum that weights are taken against (score units), the same times c2, sum
+    const float c2 = scale * kLog2e;          // > 0
+    float infinity = INFINITY;
+    asm("" : "+v"(infinity));
+    const float lag = 8.f / c2;               // weights reach 2^8 before the maximum follows: head and tail do not depend on it
+
+    const int ar = 4 * (n & 3) + ((n >> 2) & 3) + 16 * (n >> 4);
+    const int ae = TL::base(ar) + ((half ^ (ar & 3)) << 4), ao = TL::base(ar) + (((2 + half) ^ (ar & 3)) << 4);
+    int tr[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        tr[c] = TL::base(16 * half + 4 * ((lane & 15) >> 2) + c) + (((2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ c) << 4) + (lane & 1) * 8;
+    float *mine = by_row + 32 * wave;
+    auto spread = [&](float f, float (&g)[16]) __attribute__((always_inline)) {  // g[v]: the value of query 8 (v / 4) + 4 half + v % 4
+        if (half == 0) mine[n] = f;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 f4 = *reinterpret_cast<const float4 *>(mine + 8 * i + 4 * half);
+            g[4 * i] = f4.x; g[4 * i + 1] = f4.y; g[4 * i + 2] = f4.z; g[4 * i + 3] = f4.w;
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+
+    const TileLoads<D, NW, CT> loads(L, wave, lane);
+    uint2 words;  // the masks of the next tiles
+    auto request = [&](int t, unsigned char *p1, unsigned char *p2) __attribute__((always_inline)) {
+        loads.request(m1, t, p1);
+        loads.request(m2, t, p2);
+        words = *reinterpret_cast<const uint2 *>(bits + mrow + t);
+    };
+    request(0, t1a, t2a);
+    auto tile = [&](uint32_t word, const unsigned char *p1, const unsigned char *p2) __attribute__((always_inline)) {
+        if (!__any(word != 0u)) return;  // wave-uniform
+        // Fragments are read four products before the one that needs them; the order of reads and products is pinned, for left alone the
+        // reads sink to their uses.
+        constexpr int AHEAD = 4;
+        bf16x8_t f1[AHEAD];
+        auto fetch = [&](int m) __attribute__((always_inline)) { f1[m % AHEAD] = *reinterpret_cast<const bf16x8_t *>(p1 + (m & 1 ? ao : ae) + (m >> 1) * 64); };
+#pragma unroll
+        for (int m = 0; m < AHEAD; ++m) fetch(m);
+        __builtin_amdgcn_sched_barrier(0x406);
+        floatx16_t s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[m % AHEAD], qf[m], s, 0, 0, 0);
+            if (m + AHEAD < NM) fetch(m + AHEAD);
+            __builtin_amdgcn_sched_barrier(0x406);
+        }
+        const PairSlots ps(word >> half);
+        const float none = -INFINITY;
+        float x[8], top = none;
+        auto first_two = [&](auto group) __attribute__((always_inline)) {
+            constexpr int g = decltype(group)::value, bit = 2 * (g & 1) + 16 * (g >> 1);
+            const uint32_t k0 = bit_mask<bit>(ps.b0), k1 = bit_mask<bit>(ps.b1), k2 = bit_mask<bit>(ps.n2), k3 = bit_mask<bit>(ps.n3);
+            x[2 * g] = pick(bit_mask<bit>(ps.v0), pick(k0, s[4 * g], pick(k1, s[4 * g + 1], s[4 * g + 2])), none);
+            x[2 * g + 1] = pick(bit_mask<bit>(ps.v1), pick(k3, pick(k2, s[4 * g + 1], s[4 * g + 2]), s[4 * g + 3]), none);
+            top = larger(top, larger(x[2 * g], x[2 * g + 1], infinity), infinity);
+        };
+        first_two(std::integral_constant<int, 0>{});
+        first_two(std::integral_constant<int, 1>{});
+        first_two(std::integral_constant<int, 2>{});
+        first_two(std::integral_constant<int, 3>{});
+        const bool again = __any((ps.r1 | ps.r2) != 0u);  // a third or fourth pair of some group: a second round
+        float y[8];
+        if (again) {
+            auto others = [&](auto group) __attribute__((always_inline)) {
+                constexpr int g = decltype(group)::value, bit = 2 * (g & 1) + 16 * (g >> 1);
+                const uint32_t k1 = bit_mask<bit>(ps.r1), k2 = bit_mask<bit>(ps.r2);
+                y[2 * g] = pick(k1 | k2, pick(k1, s[4 * g + 1], s[4 * g + 2]), none);
+                y[2 * g + 1] = pick(k1 & k2, s[4 * g + 2], none);
+                top = larger(top, larger(y[2 * g], y[2 * g + 1], infinity), infinity);
+            };
+            others(std::integral_constant<int, 0>{});
+            others(std::integral_constant<int, 1>{});
+            others(std::integral_constant<int, 2>{});
+            others(std::integral_constant<int, 3>{});
+        }
+        if (__any(top > mx + lag)) {
+            const float to = fmaxf(mx, fmaxf(top, __shfl_xor(top, 32)));
+            const float f = to > mx ? fast_exp2((mx - to) * c2) : 1.f;  // from -inf: 0
+            mx = to;
+            mc = to > -INFINITY ? to * c2 : 0.f;
+            l *= f;
+            float g[16];
+            spread(f, g);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[nb][v] *= g[v];
+        }
+        bf16x16_t f2[2];
+        auto fetch_rows = [&](int nb) __attribute__((always_inline)) {
+            const unsigned char *p = p2 + nb * 64;
+            const bf16x8_t lo = tr_frag(p + tr[0], p + tr[2]), hi = tr_frag(p + tr[1], p + tr[3]);
+            f2[nb & 1] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+        };
+        auto add = [&](const float (&z)[8], uint32_t index) __attribute__((always_inline)) {
+            fetch_rows(0);
+            fetch_rows(1);
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t ph[4], pt[4];
+            float sum = 0.f;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float q0 = fast_exp2(fmaf(z[2 * g], c2, -mc)), q1 = fast_exp2(fmaf(z[2 * g + 1], c2, -mc));
+                sum += q0 + q1;
+                const SplitWeights w = split_weights(q0, q1);
+                ph[g] = w.head;
+                pt[g] = w.tail;
+            }
+            l += sum;
+            const bf16x8_t fh = __builtin_bit_cast(bf16x8_t, make_uint4(ph[0], ph[1], ph[2], ph[3]));
+            const bf16x8_t ft = __builtin_bit_cast(bf16x8_t, make_uint4(pt[0], pt[1], pt[2], pt[3]));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                o[nb] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(ft, f2[nb & 1], o[nb], (int)index, 0, 0);
+                o[nb] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(fh, f2[nb & 1], o[nb], (int)index, 0, 0);
+                if (nb + 2 < NB) fetch_rows(nb + 2);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        add(x, ps.index);
+        if (again) add(y, ps.index_left());
+    };
+    auto pair = [&](int t, const unsigned char *p1, const unsigned char *p2, unsigned char *n1, unsigned char *n2) __attribute__((always_inline)) {
+        const uint32_t word = live ? words.x : 0u, then = live ? words.y : 0u;
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): a barrier alone does not wait for loads into LDS
+        __syncthreads();                     // these tiles are there, and the other buffer is no longer read
+        if (t + CT < tile1) request(t + CT, n1, n2);
+        tile(word, p1, p2);
+        tile(then, p1 + TL::BYTES, p2 + TL::BYTES);
+    };
+    for (int t = 0; t < tile1; t += 2 * CT) {
+        pair(t, t1a, t2a, t1b, t2b);
+        if (t + CT < tile1) pair(t + CT, t1b, t2b, t1a, t2a);
+    }
+    l += __shfl_xor(l, 32);
+    if (half == 0 && live) lse[(int64_t)bh * L + qi] = (mc + log2f(l)) * kLn2;
+    float inv[16];
+    spread(1.f / l, inv);
+    uint32_t bad = 0;  // queries with a sum that is not finite: formed once more, below
+    bf16_t *Oh = O + hb + (int64_t)(row0 + first) * D;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int at = 8 * (v / 4) + v % 4;
+        float zero = 0.f;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) zero = fmaf(o[nb][v], 0.f, zero);
+        const unsigned long long off = __ballot(zero != 0.f);
+        const uint32_t here = ((uint32_t)off ? 1u << at : 0u) | ((uint32_t)(off >> 32) ? 16u << at : 0u);
+        bad |= here;
+        if (first + at + 4 * half < nrows && !(here >> (at + 4 * half) & 1u)) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) Oh[(at + 4 * half) * D + 32 * nb + n] = f32_to_bf16(o[nb][v] * inv[v]);
+        }
+    }
+    for (; bad; bad &= bad - 1) {
+        const int q = __ffs(bad) - 1;
+        if (first + q >= nrows) continue;
+        dense_fwd_exact<D>(Q + hb + (int64_t)(row0 + first + q) * D, K + hb, V + hb, bits + ((int64_t)blockIdx.y * nrows + first + q) * pitch,
+                           Oh + q * D, L, c2, __shfl(mc, q), __shfl(l, q));
+    }
+}
+
 // ------------------------------------------------------------------------------------ host
 // Scratch of the mask: as many heads and rows at a time as fit `bytes`.
 size_t dense_row_bytes(int L) { return (size_t)bits_pitch(L) * 4; }
+
+// Queries per block of the form on sparse products, 0 for the one on dense products.  Second rounds over tiles cost more than sparse products
+// save where more than one key in 14 is kept, and with one block per CU and fewer the 64 keys between two barriers of the dense form
+// count more.  ms, dense : sparse with 128 : with 256 queries, four heads of 32768, one key in 22: 3.17 : 2.78 : 2.67, in 16: 3.28 : 3.01 :
+// 2.90, in 12: 3.43 : 3.43 : 3.33, in 10: 3.51 : 3.72 : 3.64; d = 64, in 16: 2.16 : 2.04 : 1.98, in 12: 2.29 : 2.35 : 2.29; three heads of 9000, one in 13: 0.288 :
+// 0.298 : 0.386.  Blocks of 256 (one per CU) where they leave their last round nearly full: four heads of 20280, one in 16, 1.25 rounds: 1.51 :
+// 1.43 : 1.68; one head of 131072, two rounds: 13.8 : 12.8 : 12.0.
+static int dense_fwd_form(int L, int heads, int rows, int64_t kept)
+{
+    if (kept * 14 > (int64_t)L * heads || (int64_t)heads * ((rows + 127) / 128) <= 256) return 0;
+    const int64_t blocks = (int64_t)heads * ((rows + 255) / 256), rounds = (blocks + 255) / 256;
+    return blocks * 100 >= rounds * 256 * 85 ? 256 : 128;
+}
 
 template <int D>
 static dsv_status dense_fwd_t(const dsv_problem &p, const HeadTable &tab, const void *Q, const void *K, const void *V,
@@ -219,9 +442,17 @@ static dsv_status dense_fwd_t(const dsv_problem &p, const HeadTable &tab, const 
             const int nr = std::min(rows, p.L - r0);
             const dsv_status rc = launch_bits_build(p, tab, s0, nh, idx, r0, nr, bits, st);
             if (rc != DSV_OK) return rc;
-            hipLaunchKernelGGL((dense_fwd_kernel<D>), dim3((nr + kDenseQueries - 1) / kDenseQueries, nh), dim3(256), 0, st,
-                               (const bf16_t *)Q, (const bf16_t *)K, (const bf16_t *)V, bits, pitch, (bf16_t *)O, lse, p.L, p.scale, tab,
-                               s0, r0, nr);
+            auto run = [&](auto kernel, int queries) {
+                hipLaunchKernelGGL(kernel, dim3((nr + queries - 1) / queries, nh), dim3(2 * queries), 0, st, (const bf16_t *)Q, (const bf16_t *)K,
+                                   (const bf16_t *)V, bits, pitch, (bf16_t *)O, lse, p.L, p.scale, tab, s0, r0, nr);
+            };
+            int64_t kept = 0;
+            for (int s = s0; s < s0 + nh; ++s) kept += tab.k[s];
+            switch (dense_fwd_form(p.L, nh, nr, kept)) {
+            case 256: run(dense_fwd_pairs_kernel<D, 8>, 256); break;
+            case 128: run(dense_fwd_pairs_kernel<D, 4>, 128); break;
+            default: run(dense_fwd_kernel<D>, kDenseQueries);
+            }
             DSV_LAUNCH_CHECK();
         }
     }

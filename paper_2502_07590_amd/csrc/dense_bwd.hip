@@ -23,59 +23,11 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "stage2_core.h"
-#include "pair_slots.h"
+#include "dense_tile.h"
 
 namespace dsv {
 
-constexpr int kTile = 32;          // rows of a tile
 constexpr int kOwn = 128;          // own rows per block, 32 per wave
-constexpr int kChunkPitch = 1088;  // bytes from one kilobyte of a parked tile to the next: 16 banks on
-
-typedef __attribute__((__vector_size__(16 * sizeof(__bf16)))) __bf16 bf16x16_t;
-
-template <int D> struct TileLayout {
-    static constexpr int PPR = D / 8;              // 16-byte pieces per row
-    static constexpr int CHUNKS = kTile * PPR / 64;  // kilobytes, one load instruction of a wave each
-    static constexpr int BYTES = CHUNKS * kChunkPitch;
-    __device__ __forceinline__ static int chunk(int r) { return D == 128 ? r >> 2 : (r >> 2) & 3; }
-    __device__ __forceinline__ static int slot(int r) { return D == 128 ? r & 3 : (r & 3) + 4 * (r >> 4); }
-    __device__ __forceinline__ static int row(int chunk, int slot) { return D == 128 ? 4 * chunk + slot : 4 * chunk + (slot & 3) + 16 * (slot >> 2); }
-    // piece p of row r lies at base(r) + 16 (p ^ r % 4)
-    __device__ __forceinline__ static int base(int r) { return chunk(r) * kChunkPitch + slot(r) * (2 * D); }
-};
-
-// Rows j0 .. j0 + 31 of a [L, D] matrix into a parked tile (rows past the end repeat the last one): this wave's share of the chunks.
-template <int D>
-__device__ __forceinline__ void request_tile(const unsigned char *__restrict__ mat, int j0, int L, unsigned char *tile, int wave, int lane)
-{
-    typedef TileLayout<D> TL;
-#pragma unroll
-    for (int i = 0; i < TL::CHUNKS / 4; ++i) {
-        const int c = wave * (TL::CHUNKS / 4) + i;
-        const int r = TL::row(c, lane / TL::PPR);
-        const int piece = (lane % TL::PPR) ^ (r & 3);
-        const unsigned char *src = mat + ((int64_t)min(j0 + r, L - 1) * TL::PPR + piece) * 16;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                         (__attribute__((address_space(3))) void *)(tile + c * kChunkPitch), 16, 0, 0);
-    }
-}
-
-// Plain expressions, because their operands are results of matrix products: the compiler puts the wait that such a read needs before
-// an instruction of its own, and none before one written in inline assembly.  The empty statement only hides from it that a
-// mask is a bit spread out, which it would turn into a compare and a select per use (dq at L = 32768, four heads, k = 2048: 4.65 ms, 4.77
-// without).
-template <int BIT> __device__ __forceinline__ uint32_t bit_mask(uint32_t w)  // all ones where the bit is set, else zero
-{
-    uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)w, BIT, 1);
-    asm("" : "+v"(m));
-    return m;
-}
-__device__ __forceinline__ float pick(uint32_t mask, float a, float b)  // mask all ones: a, zero: b
-{
-    return __uint_as_float((mask & __float_as_uint(a)) | (~mask & __float_as_uint(b)));
-}
-__device__ __forceinline__ float keep(uint32_t mask, float a) { return __uint_as_float(mask & __float_as_uint(a)); }
 
 // Zero times a row that is not finite is no number, and the products above multiply rows that are not selected by zero: an own row whose
 // sums came out not finite is formed once more, by its wave, from its selected pairs alone.  16 lanes per pair, eight pairs at a
@@ -179,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
     int slot, range, rb;
     if (!decode_range_item(pl.S, pl.S_pad, pl.nqb, blockIdx.x, slot, range, rb)) return;
     const int bh = tab.bh[slot0 + slot];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, half = lane >> 5;
     const int r = rb * kOwn + wave * 32 + n;  // own row in this piece
     const bool live = r < nrows;
@@ -227,9 +179,10 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
     const int sr = threadIdx.x & 31;  // KEYS: query of the tile whose statistics this thread (of the first 32) brings, and its place
     const int sp = (sr & 1) * 16 + (((sr >> 1) & 1) + 2 * (sr >> 4)) * 4 + ((sr >> 2) & 3);
     float2 sn = make_float2(0.f, 0.f);
+    const TileLoads<D, 4, 1> loads(L, wave, lane);
     auto request = [&](int t, unsigned char *p1, unsigned char *p2) {
-        request_tile<D>(m1, t * kTile, L, p1, wave, lane);
-        request_tile<D>(m2, t * kTile, L, p2, wave, lane);
+        loads.request(m1, t, p1);
+        loads.request(m2, t, p2);
         if (KEYS && threadIdx.x < kTile) sn = stat[(int64_t)bh * L + min(t * kTile + sr, L - 1)];
     };
     auto park = [&](float *st) {

@@ -431,7 +431,14 @@ __global__ __launch_bounds__(256) void fill_zero_i32_kernel(int4 *__restrict__ p
 }
 
 // ------------------------------------------------------------------------------------ host
-int bits_pitch(int L) { return (L + kBitsKeys - 1) / kBitsKeys * 16; }
+// Where rows would lie whole kilobytes apart, 64 bytes more: the words that the waves of the chip read together, one of every row, otherwise
+// come from a few of the L2's channels (forward over dense tiles, L = 131072, one head, k = 8192: 12.43 -> 11.99 ms; L = 32768, four heads, k = 2048:
+// 3.04 -> 2.91).  The largest rows stay as long as the bitmap in LDS may be.
+int bits_pitch(int L)
+{
+    const int words = (L + kBitsKeys - 1) / kBitsKeys * 16;
+    return words % 256 == 0 && L <= kBitsMaxKeys / 2 ? words + 16 : words;
+}
 
 dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
                              int nrows, uint32_t *bits, hipStream_t st, const int64_t *col)
@@ -491,7 +498,7 @@ static dsv_status transpose_bits(const dsv_problem &p, const HeadTable &tab, con
 {
     int32_t *tot = reinterpret_cast<int32_t *>(ws + w.tot), *cnt2 = reinterpret_cast<int32_t *>(ws + w.cnt2);
     uint32_t *bits = reinterpret_cast<uint32_t *>(ws + w.mat);
-    const unsigned kb = w.pitch / 16;
+    const unsigned kb = (p.L + kBitsKeys - 1) / kBitsKeys;
     const bool whole = w.rows >= p.L;        // the piece built for counting still stands when the lists are filled
     for (int s0 = 0; s0 < tab.n; s0 += w.heads) {
         const unsigned nh = std::min(w.heads, tab.n - s0);

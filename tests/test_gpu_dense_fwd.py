@@ -46,6 +46,20 @@ def test_dense_and_gathered_heads(d, B, L, near):
     _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 61, device="cuda"), torch.arange(L - 70, L, device="cuda")]))
 
 
+# the form on sparse products, in blocks of 128 queries (24 heads of 2111: 408 of them) and of 256 (24 of 2304: 216), one key in 16 on
+# the mean, so that groups with a third pair come; rows of neighbours leave whole tiles out and crowd others
+@pytest.mark.parametrize("d,H,L,near", [(128, 24, 2111, False), (128, 24, 2304, False), (128, 24, 2304, True), (128, 33, 1985, False),
+                                        (128, 26, 2337, True), (64, 24, 4001, False), (64, 16, 4096, False), (64, 24, 4127, True)])
+def test_heads_that_keep_few_pairs_of_a_tile(d, H, L, near):
+    g = torch.Generator(device="cuda").manual_seed(3 * L + d)
+    ks = [L // 16] * (H - 3) + [L // 9, L // 20, L // 13]
+    Q, K, V = (3 * torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(1, H, L, d, 16, "bf16", ks, d ** -0.5, sorted_index=True)
+    assert 0 < dsv.dense_min_k(p, "fwd_sweep") <= L // 16
+    heads = [_rows(L, k, g, near) for k in ks]
+    _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 97, device="cuda"), torch.arange(L - 40, L, device="cuda")]))
+
+
 def test_mask_in_pieces():
     L, k = 98309, 4000
     g = torch.Generator(device="cuda").manual_seed(7)
@@ -57,14 +71,22 @@ def test_mask_in_pieces():
 # a value row that is not finite belongs to the queries that keep its key, and to no others
 @pytest.mark.parametrize("d,bad", [(64, float("inf")), (128, float("nan"))])
 def test_rows_that_are_not_finite(d, bad):
-    L, k = 2113, 400
+    _rows_that_are_not_finite(d, bad, 12, 2113, 400)
+
+
+@pytest.mark.parametrize("d,L,bad", [(64, 4096, float("nan")), (128, 2304, float("inf"))])
+def test_rows_that_are_not_finite_on_sparse_products(d, L, bad):
+    _rows_that_are_not_finite(d, bad, 24, L, L // 15)
+
+
+def _rows_that_are_not_finite(d, bad, H, L, k):
     g = torch.Generator(device="cuda").manual_seed(d)
-    Q, K, V = (torch.randn(1, 12, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    Q, K, V = (torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
     V[0, :, 700] = bad
     K[0, :, 1500] = bad
     rows = _rows(L, k, g, near=True)
-    idx = torch.cat([rows.reshape(-1)] * 12)
-    p = dsv.Problem(1, 12, L, d, 16, "bf16", [k] * 12, d ** -0.5, sorted_index=True)
+    idx = torch.cat([rows.reshape(-1)] * H)
+    p = dsv.Problem(1, H, L, d, 16, "bf16", [k] * H, d ** -0.5, sorted_index=True)
     assert dsv.sparse_attn_fwd_workspace(p) > 0
     O, _ = dsv.sparse_attn_fwd(p, Q, K, V, idx)
     V[0, :, 700], K[0, :, 1500] = 0, 0
