@@ -93,6 +93,17 @@ __device__ __forceinline__ int half_scan(int x)
     return s;
 }
 
+// The same inside each row of 16 lanes.
+__device__ __forceinline__ int row_scan(int x)
+{
+    int s = x;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+    return s;
+}
+
 // Transposing LDS read (ds_read_b64_tr_b16): inside every block of 16 lanes, lane i receives four halfwords, the
 // e-th being halfword (i % 4) at the address passed by lane 4 e + i / 4 of the block.  So when lane 4 e + q
 // passes the address of channels c0 + 4 q .. + 3 of parked row key(e), lane i ends up with channel c0 + i of rows

@@ -43,6 +43,32 @@ __device__ __forceinline__ Frag<T, R> load_frag(const T *__restrict__ base, int 
     return load_frag_row<T, R>(base, min(row0 + (lane & 31), L - 1), lane);
 }
 
+// The rows of a matrix as a sweep walks them, 32 at a time.  Row operands come in the order that gives a lane 16 rows side by side
+// (accumulator v of half h: row 16 h + v of the tile): its 16 predicates are a halfword then, in order.  Two vector instructions
+// per tile for the address (a head's matrix has less than 2^32 bytes); rows past the end repeat the last one.
+template <typename T, int R> struct TileWalk {
+    uint32_t at, last;
+    __device__ __forceinline__ TileWalk(int L, int lane)
+    {
+        const int r = lane & 31;
+        at = (uint32_t)(16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3)) * (R * (uint32_t)sizeof(T));
+        last = (uint32_t)(L - 1) * (R * (uint32_t)sizeof(T));
+    }
+    __device__ __forceinline__ Frag<T, R> load(const T *__restrict__ base, int tile, int half) const
+    {
+        const T *p = reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + min(at + (uint32_t)tile * (32u * R * (uint32_t)sizeof(T)), last));
+        Frag<T, R> f;
+        if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int m = 0; m < R / 16; ++m) f.v[m] = *reinterpret_cast<const bf16x8_t *>(p + m * 16 + half * 8);
+        } else {
+#pragma unroll
+            for (int m = 0; m < R / 2; ++m) f.v[m] = p[2 * m + half];
+        }
+        return f;
+    }
+};
+
 template <typename T, int R>
 __device__ __forceinline__ floatx16_t score_tile(const Frag<T, R> &rows, const Frag<T, R> &cols)
 {
@@ -94,6 +120,20 @@ __device__ __forceinline__ float key_score(uint32_t key)
         acc_ = __builtin_bitreverse32(acc_) >> 16; /* bit v = sign of d(v) */              \
         acc_ = (acc_ | (acc_ << 8)) & 0x00FF00FFu;                                         \
         (m) = (acc_ | (acc_ << 4)) & 0x0F0F0F0Fu;  /* bit tile_pos(v) */                   \
+    } while (0)
+
+// Bits v of a lane for rows in the order of TileWalk: predicates, and signs (above).
+#define DSV_PRED16(m, pred_expr)                                                             \
+    do {                                                                                   \
+        (m) = 0u;                                                                          \
+        _Pragma("unroll") for (int v = 0; v < 16; ++v) (m) |= (uint32_t)(pred_expr) << v;  \
+    } while (0)
+#define DSV_SIGNS16(m, d_expr)                                                             \
+    do {                                                                                   \
+        uint32_t acc_ = 0u;                                                                \
+        _Pragma("unroll") for (int v = 15; v >= 0; --v)                                    \
+            acc_ = __builtin_amdgcn_alignbit(acc_, __float_as_uint(d_expr), 31);           \
+        (m) = acc_;                                                                        \
     } while (0)
 
 __device__ __forceinline__ uint32_t merge_halves(uint32_t m, int half)

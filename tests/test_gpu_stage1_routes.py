@@ -100,6 +100,17 @@ def test_emission(dtype, H, L, k, r, ties):
     _check(dsv.Problem(1, H, L, 64, r, dtype, [k] * H, 0.1), Q, K, Wq, Wk)
 
 
+# emission in batches of up to 32 key tiles (16 query tiles for the lists) by four waves in turn: one tile over a round, over two, an odd
+# number of tiles; every score twice, so that queries in two take one of two ties, whose places lie batches apart
+@pytest.mark.parametrize("dtype,H,L,ks,r", [("bf16", 8, 4097, [256] * 8, 16), ("bf16", 5, 8193, [2000, 8193, 3, 511, 130], 32), ("bf16", 2, 16385, [1025, 77], 16),
+                                            ("bf16", 4, 4160, [260, 1, 4159, 1000], 64), ("f32", 4, 3007, [189, 3000, 2, 750], 32)])
+def test_emission_in_batches(dtype, H, L, ks, r):
+    Q, K, Wq, Wk = _inputs(H, L, 64, r, dtype, False, L + r)
+    _check(dsv.Problem(1, H, L, 64, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+    K[:, :, L - L // 2:] = K[:, :, :L // 2]
+    _check(dsv.Problem(1, H, L, 64, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+
+
 def test_smooth_inputs_keep_the_windowed_search():
     """Keys that vary slowly along the token grid, whose width the sample's stride divides: the scrambled sample brackets
     the thresholds, and the result is the radix search's."""
