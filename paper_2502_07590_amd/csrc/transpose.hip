@@ -21,32 +21,55 @@ constexpr int kBitsKeys = 512;               // keys per block of the counting a
 constexpr int kBitsRows = 1024;              // queries per block of those kernels: one segment of every list
 constexpr size_t kBitsBytes = (size_t)2 << 30;  // scratch for the bit matrix: larger problems go through it piece by piece
 
-// One block per row at a time: its entries are OR-ed into an LDS bitmap, which is then written out and cleared.  col: the rows are
-// key-major lists, whose bits are queries.
-__global__ __launch_bounds__(256) void bits_build_kernel(const int32_t *__restrict__ idx, const int64_t *__restrict__ col, int L, HeadTable tab, int slot0,
-                                                         int row0, int nrows, int pitch, uint32_t *__restrict__ bits)
+// One wave per row at a time: its entries are OR-ed into a bitmap in LDS, which is then written out and cleared.  col: the rows are
+// key-major lists, whose bits are queries.  Bound by the memory: entries come in 16-byte pieces, eight kilobytes of a row in flight, and no
+// wave waits for another.  L = 32768, four heads, k = 2048 (1.07 GB in, 0.54 out): 289 us, 5.6 TB/s; 408 with a block per row, an entry per lane
+// and load, and three barriers.
+constexpr int kBitsWaves = 4;  // rows per block, at most
+__global__ __launch_bounds__(64 * kBitsWaves) void bits_build_kernel(const int32_t *__restrict__ idx, const int64_t *__restrict__ col, int L, HeadTable tab,
+                                                                     int slot0, int row0, int nrows, int pitch, uint32_t *__restrict__ bits)
 {
-    extern __shared__ __align__(16) uint32_t bm[];  // [pitch]
+    extern __shared__ __align__(16) uint32_t bm_all[];  // [waves][pitch]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    uint32_t *bm = bm_all + wave * pitch;
     const int slot = slot0 + blockIdx.y;
     const int32_t *base = idx + tab.off[slot];
     const int64_t *cp = col ? col + (int64_t)tab.bh[slot] * (L + 1) + row0 : nullptr;
     uint32_t *out = bits + (int64_t)blockIdx.y * nrows * pitch;
-    for (int w = threadIdx.x; w < pitch; w += 256) bm[w] = 0u;
-    __syncthreads();
-    for (int i = blockIdx.x; i < nrows; i += gridDim.x) {
+    for (int w = lane; w < (pitch >> 2); w += 64) reinterpret_cast<uint4 *>(bm)[w] = make_uint4(0u, 0u, 0u, 0u);
+    __builtin_amdgcn_wave_barrier();
+    auto mark = [&](int v) __attribute__((always_inline)) {
+        if ((uint32_t)v < (uint32_t)L) atomicOr(&bm[v >> 5], 1u << (v & 31));
+    };
+    for (int i = blockIdx.x * waves + wave; i < nrows; i += gridDim.x * waves) {
         const int k = cp ? (int)(cp[i + 1] - cp[i]) : tab.k[slot];
         const int32_t *row = base + (cp ? cp[i] : (int64_t)(row0 + i) * k);
-        for (int t = threadIdx.x; t < k; t += 256) {
-            const int v = row[t];
-            if (v >= 0 && v < L) atomicOr(&bm[v >> 5], 1u << (v & 31));
+        const int head = min(k, (int)(-(reinterpret_cast<uintptr_t>(row) >> 2) & 3u));  // entries before the first whole piece
+        if (lane < head) mark(row[lane]);
+        const int4 *piece = reinterpret_cast<const int4 *>(row + head);
+        const int pieces = (k - head) >> 2;
+        constexpr int U = 8;
+        for (int p = lane; p < pieces; p += 64 * U) {
+            int4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = p + 64 * u < pieces ? piece[p + 64 * u] : make_int4(-1, -1, -1, -1);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                mark(v[u].x);
+                mark(v[u].y);
+                mark(v[u].z);
+                mark(v[u].w);
+            }
         }
-        __syncthreads();
+        const int rest = head + 4 * pieces + lane;
+        if (rest < k) mark(row[rest]);
+        __builtin_amdgcn_wave_barrier();
         uint4 *dst = reinterpret_cast<uint4 *>(out + (int64_t)i * pitch);
-        for (int w = threadIdx.x; w < (pitch >> 2); w += 256) {
+        for (int w = lane; w < (pitch >> 2); w += 64) {
             dst[w] = reinterpret_cast<uint4 *>(bm)[w];
             reinterpret_cast<uint4 *>(bm)[w] = make_uint4(0u, 0u, 0u, 0u);
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -444,8 +467,9 @@ dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slo
                              int nrows, uint32_t *bits, hipStream_t st, const int64_t *col)
 {
     const int pitch = bits_pitch(p.L);
-    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min(nrows, 4096), heads), dim3(256), (size_t)pitch * 4, st, idx, col, p.L, tab, slot0,
-                       row0, nrows, pitch, bits);
+    const int waves = std::max(1, std::min(kBitsWaves, (64 << 10) / (pitch * 4)));  // 64 KB of bitmaps
+    hipLaunchKernelGGL(bits_build_kernel, dim3(std::min((nrows + waves - 1) / waves, 8192 / waves), heads), dim3(64 * waves), (size_t)waves * pitch * 4, st, idx,
+                       col, p.L, tab, slot0, row0, nrows, pitch, bits);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }

@@ -46,6 +46,16 @@ def test_transpose_is_a_stable_sort_of_the_pairs(L, ks, ascending):
         off += rows.numel()
 
 
+# bitmaps of four, three and one row per block (up to 131040 keys, up to 174592, above); rows that begin at no multiple of 16 bytes
+@pytest.mark.parametrize("L,k", [(8192, 61), (16384, 1023), (131072, 171), (150001, 198), (300007, 391)])
+def test_bitmaps_of_rows(L, k):
+    rows = _rows(L, k, L, True)
+    p = dsv.Problem(1, 1, L, 64, 16, "bf16", [k], 0.1)
+    idx_t, col = dsv.idx_transpose(p, rows.reshape(-1))
+    want, ptr = _expected(rows, L)
+    assert torch.equal(col[0], ptr) and torch.equal(idx_t, want)
+
+
 # rows of 512 bytes of K and V: a head passes 3 MB above 6144 keys; from there rows in any order are sorted first, up to 524288
 # keys (a row's bitmap: 64 KB of LDS)
 @pytest.mark.parametrize("dtype,L,d,ks", [("bf16", 6145, 128, [300, 1]), ("f32", 6200, 64, [6200]), ("bf16", 20011, 64, [777]),
