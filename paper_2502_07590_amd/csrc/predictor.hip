@@ -15,8 +15,9 @@
 //
 // Both kinds of contraction run on the matrix cores: the Gram matrix in the storage type with fp32 sums over at most
 // 512 tokens (v_mfma_f32_32x32x16_bf16 / 32x32x2_f32), everything behind it in fp64 (v_mfma_f64_16x16x4_f64).
-// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 165 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 46,
-// accum 25 (4.1 ms with the sums over partials in one block per head and the rows' forms on the vector units).
+// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 138 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 44, accum 18; 160 with
+// the weights' products and the loss in kernels and loops of their own, all of M in the rows' forms and half the blocks in accum.
+// L = 3000, one head, 250 rows, d = 64: 66 -> 35 us.
 #include <algorithm>
 
 #include "common.h"
@@ -125,33 +126,33 @@ __global__ __launch_bounds__(256) void gram_partial_kernel(const T *__restrict__
         for (int v = 0; v < 16; ++v) out[(32 * rb + 8 * (v / 4) + 4 * half + v % 4) * D + 32 * (cb0 + j) + n] = sum[j][v];
 }
 
-// M[bh] = sum of the partials, in fp64, in block order.
-__global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ part, int nblk, int DD, double *__restrict__ M)
-{
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int64_t bh = blockIdx.y;
-    const float *p = part + bh * nblk * DD + e;
-    double s = 0.0;
-#pragma unroll 8
-    for (int b = 0; b < nblk; ++b) s += (double)p[(int64_t)b * DD];
-    M[bh * DD + e] = s;
-}
-
-// T1 = M Wk [D, R], then T2 = Wk^T T1 [R, R]: a thread per entry.
+// M[bh] = sum of the partials, in fp64, in block order; of the 256 / D rows of M that a block forms also T1 = M Wk [D, R].
 template <typename T, int D, int R>
-__global__ __launch_bounds__(256) void gram_weights1_kernel(const T *__restrict__ Wk, int H, const double *__restrict__ M,
-                                                            double *__restrict__ T1)
+__global__ __launch_bounds__(256) void gram_sum_kernel(const float *__restrict__ part, int nblk, const T *__restrict__ Wk, int H, double *__restrict__ M,
+                                                       double *__restrict__ T1)
 {
-    const int64_t bh = blockIdx.y;
+    constexpr int ROWS = 256 / D, TPE = 256 / (ROWS * R);  // threads that share an entry of T1
+    __shared__ double m[256];
     const int e = blockIdx.x * 256 + threadIdx.x;
-    const int c = e / R, t = e % R;
-    const T *W = Wk + (bh % H) * D * R;
+    const int64_t bh = blockIdx.y;
+    const float *p = part + bh * nblk * (D * D) + e;
     double s = 0.0;
 #pragma unroll 16
-    for (int c2 = 0; c2 < D; ++c2) s += M[(bh * D + c) * D + c2] * (double)to_f32<T>(W[c2 * R + t]);
-    T1[bh * D * R + e] = s;
+    for (int b = 0; b < nblk; ++b) s += (double)p[(int64_t)b * (D * D)];
+    M[bh * (D * D) + e] = s;
+    m[threadIdx.x] = s;
+    __syncthreads();
+    const int row = threadIdx.x / (TPE * R), t = threadIdx.x / TPE % R;
+    const T *W = Wk + (bh % H) * D * R + t;
+    double x = 0.0;
+#pragma unroll 16
+    for (int c = threadIdx.x % TPE; c < D; c += TPE) x += m[row * D + c] * (double)to_f32<T>(W[c * R]);
+#pragma unroll
+    for (int o = TPE / 2; o; o >>= 1) x += __shfl_xor(x, o);
+    if (threadIdx.x % TPE == 0) T1[(bh * D + blockIdx.x * ROWS + row) * R + t] = x;
 }
 
+// T2 = Wk^T T1 [R, R], a thread per entry: for R = 64; below, every block of the rows' kernel forms its own.
 template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void gram_weights2_kernel(const T *__restrict__ Wk, int H, const double *__restrict__ T1,
                                                             double *__restrict__ T2)
@@ -170,47 +171,84 @@ __global__ __launch_bounds__(256) void gram_weights2_kernel(const T *__restrict_
 // One wave per 16 sampled rows; U = Q_s M, Q_lr = Q_s Wq, V = Q_s T1 and W = Q_lr T2 as fp64 matrix products.  Writes, per
 // row: qlr [R], G [R] (= dAhat_i Klr), the coefficients ca_i, ch_i and the loss terms {1 - cos_i, sum_j (ahat_ij - a_ij)^2}.
 //   ca_i = -0.95 / (n |ahat_i| |a_i|) - 0.1 / (n L),   ch_i = 0.95 <ahat_i, a_i> / (n |ahat_i|^3 |a_i|) + 0.1 / (n L)
-// Bound by the D^2 fp64 multiplications per row (64 clocks per 16 x 16 x 4 product).
+// Bound by the fp64 multiplications, 3 D^2 / 4 per row and more (64 clocks per 16 x 16 x 4 product).
 template <typename T, int D, int R>
-__global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict__ Q, const T *__restrict__ Wq,
+__global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict__ Q, const T *__restrict__ Wq, const T *__restrict__ Wk,
                                                              const int32_t *__restrict__ rows, int n, int L, int H,
                                                              const double *__restrict__ M, const double *__restrict__ T1,
                                                              const double *__restrict__ T2, double *__restrict__ qlr_out,
                                                              double *__restrict__ g_out, double2 *__restrict__ coef,
                                                              double2 *__restrict__ terms)
 {
-    constexpr int CPL = D / 4, RPL = R / 4, NT = R / 16;   // contraction steps: lane group g takes channels g CPL + s
+    constexpr int CPL = D / 4, RPL = R / 4, NT = R / 16;   // contraction steps: lane group g takes channel 4 s + g
+    constexpr bool OWN_T2 = R < 64;                        // (at R = 64 it would take the LDS of a second block)
     __shared__ float xq_all[4][16][D + 1];
     __shared__ double ql_all[4][16][R + 1];
+    __shared__ double t2[OWN_T2 ? R * R : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r16 = lane & 15, g = lane >> 4;
     const int i0 = (blockIdx.x * 4 + wave) * 16;
     const int64_t bh = blockIdx.y;
+    const T *Wh = Wq + (bh % H) * D * R;
+    const double *Mh = M + bh * D * D, *T1h = T1 + bh * D * R;
+    if constexpr (OWN_T2) {  // T2 = Wk^T T1: a tile per wave (R = 32), or a quarter of the contraction (R = 16)
+        const T *Wkh = Wk + (bh % H) * D * R;
+        const int ta = NT == 1 ? 0 : wave / NT, tb = NT == 1 ? 0 : wave % NT, s0 = NT == 1 ? wave * (CPL / 4) : 0;
+        doublex4_t x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < (NT == 1 ? CPL / 4 : CPL); ++s) {
+            const int c = (4 * (s0 + s) + g) * R + r16;
+            x = mfma_f64((double)to_f32<T>(Wkh[c + 16 * ta]), T1h[c + 16 * tb], x);
+        }
+        if constexpr (NT == 1) {
+            double *quarter = &ql_all[0][0][0];  // free until the rows' Q_lr come
+#pragma unroll
+            for (int v = 0; v < 4; ++v) quarter[wave * 256 + (4 * v + g) * 16 + r16] = x[v];
+            __syncthreads();
+            t2[threadIdx.x] = (quarter[threadIdx.x] + quarter[256 + threadIdx.x]) + (quarter[512 + threadIdx.x] + quarter[768 + threadIdx.x]);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t2[(16 * ta + 4 * v + g) * R + 16 * tb + r16] = x[v];
+        }
+        __syncthreads();
+    }
+    const double *T2h = OWN_T2 ? t2 : T2 + bh * R * R;
     if (i0 >= n) return;  // whole wave; nothing below synchronises across waves
     float (*xq)[D + 1] = xq_all[wave];
     double (*ql)[R + 1] = ql_all[wave];
-    const T *Wh = Wq + (bh % H) * D * R;
-    const double *Mh = M + bh * D * D, *T1h = T1 + bh * D * R, *T2h = T2 + bh * R * R;
     const int row = min(max(rows[min(i0 + r16, n - 1)], 0), L - 1);
     const T *qrow = Q + (bh * L + row) * D + g * CPL;
-    double q[CPL];
 #pragma unroll
-    for (int s = 0; s < CPL; ++s) {
-        const float x = to_f32<T>(qrow[s]);
-        xq[r16][g * CPL + s] = x;
-        q[s] = (double)x;
-    }
+    for (int s = 0; s < CPL; ++s) xq[r16][g * CPL + s] = to_f32<T>(qrow[s]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double q[CPL];
+#pragma unroll
+    for (int s = 0; s < CPL; ++s) q[s] = (double)xq[r16][4 * s + g];
     double aa[4] = {0.0, 0.0, 0.0, 0.0}, ah[4] = {0.0, 0.0, 0.0, 0.0}, hh[4] = {0.0, 0.0, 0.0, 0.0};
+    // |a|^2 = q^T M q by four blocks of D / 2 x D / 2 channels: the one above the diagonal twice, the one below it not at all.  (By blocks of 16 the
+    // products are fewer still, but those loops come out slower: 8192 rows of six heads, D = 128, R = 16: 44 us, by blocks of 16 39 with loads where they
+    // are used -- and 61 for 24 where few rows leave a wave alone with them -- or 68 with a column's loads ahead of its products.)
+    const double *col = Mh + g * D + r16;
 #pragma unroll 1
-    for (int nt = 0; nt < D / 16; ++nt) {
+    for (int nt = 0; nt < D / 32; ++nt) {
         doublex4_t u = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int s = 0; s < CPL; ++s) u = mfma_f64(q[s], Mh[(g * CPL + s) * D + 16 * nt + r16], u);
+        for (int s = 0; s < CPL / 2; ++s) u = mfma_f64(q[s], col[4 * s * D + 16 * nt], u);
 #pragma unroll
         for (int v = 0; v < 4; ++v) aa[v] += u[v] * (double)xq[4 * v + g][16 * nt + r16];
+    }
+#pragma unroll 1
+    for (int nt = D / 32; nt < D / 16; ++nt) {
+        doublex4_t u = {0.0, 0.0, 0.0, 0.0}, w = u;
+#pragma unroll
+        for (int s = 0; s < CPL / 2; ++s) {
+            u = mfma_f64(q[s], col[4 * s * D + 16 * nt], u);
+            w = mfma_f64(q[s + CPL / 2], col[4 * (s + CPL / 2) * D + 16 * nt], w);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) aa[v] += (2.0 * u[v] + w[v]) * (double)xq[4 * v + g][16 * nt + r16];
     }
     doublex4_t a[NT], b[NT];  // Q_lr and V
 #pragma unroll
@@ -219,7 +257,7 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
         b[nt] = a[nt];
 #pragma unroll
         for (int s = 0; s < CPL; ++s) {
-            const int e = (g * CPL + s) * R + 16 * nt + r16;
+            const int e = (4 * s + g) * R + 16 * nt + r16;
             a[nt] = mfma_f64(q[s], (double)to_f32<T>(Wh[e]), a[nt]);
             b[nt] = mfma_f64(q[s], T1h[e], b[nt]);
         }
@@ -264,15 +302,15 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
 }
 
 // ---- sums over the sampled rows ---------------------------------------------------------------------------
-// dWq = Q_s^T G [D, R],  N1 = Q_s^T (ca Q_lr) [D, R],  N2 = Q_lr^T (ch Q_lr) [R, R]: every block takes kAccRows sampled rows
+// dWq = Q_s^T G [D, R],  N1 = Q_s^T (ca Q_lr) [D, R],  N2 = Q_lr^T (ch Q_lr) [R, R] and the two loss terms: every block takes kAccRows sampled rows
 // (64 Q rows at a time in LDS) and writes its partial sums; predictor_sum_kernel adds them in block order (deterministic).
 // Waves take the 16-channel row tiles of dWq and N1 (and of N2) in turn.
-constexpr int kAccRows = 128;
+constexpr int kAccRows = 64;
 template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restrict__ Q, const int32_t *__restrict__ rows,
                                                               int n, int L, const double *__restrict__ qlr,
                                                               const double *__restrict__ gm, const double2 *__restrict__ coef,
-                                                              double *__restrict__ part)
+                                                              const double2 *__restrict__ terms, double *__restrict__ part)
 {
     constexpr int NT = R / 16, CT = D / 64;                 // column tiles; row tiles of dWq and N1 per wave
     __shared__ float xq[64][D + 1];
@@ -332,7 +370,19 @@ __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restric
             }
         }
     }
-    double *o = part + (bh * gridDim.x + blockIdx.x) * (2 * D * R + R * R);
+    double *o = part + (bh * gridDim.x + blockIdx.x) * (2 * D * R + R * R + 2);
+    if (wave == 0) {  // the loss terms of the block's rows
+        const int i = blockIdx.x * kAccRows + lane;
+        double2 x = i < i1 ? terms[bh * n + i] : make_double2(0.0, 0.0);
+        for (int d = 32; d; d >>= 1) {
+            x.x += __shfl_xor(x.x, d);
+            x.y += __shfl_xor(x.y, d);
+        }
+        if (lane == 0) {
+            o[2 * D * R + R * R] = x.x;
+            o[2 * D * R + R * R + 1] = x.y;
+        }
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -347,7 +397,7 @@ __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restric
         }
 }
 
-// sums [2 D R + R R] = dWq, N1, N2 over the blocks' partials; dWq is final.
+// sums [2 D R + R R + 2] = dWq, N1, N2, loss terms over the blocks' partials; dWq is final.
 __global__ __launch_bounds__(256) void predictor_sum_kernel(const double *__restrict__ part, int nchunk, int DR, int count,
                                                             double *__restrict__ sums, float *__restrict__ dWq)
 {
@@ -356,50 +406,30 @@ __global__ __launch_bounds__(256) void predictor_sum_kernel(const double *__rest
     if (e >= count) return;
     const double *p = part + bh * nchunk * count + e;
     double s = 0.0;
-#pragma unroll 8
+#pragma unroll 16
     for (int c = 0; c < nchunk; ++c) s += p[(int64_t)c * count];
     if (e < DR) dWq[bh * DR + e] = (float)s;
     else sums[bh * count + e] = s;
 }
 
-// dWk = M (N1 + Wk N2) = M N1 + T1 N2; block 0 of a head also forms the loss {0.95 cos + 0.05 norm, cos, norm}.
+// dWk = M (N1 + Wk N2) = M N1 + T1 N2; block 0 of a head also writes the loss {0.95 cos + 0.05 norm, cos, norm}.
 template <int D, int R>
 __global__ __launch_bounds__(256) void predictor_finish_kernel(const double *__restrict__ M, const double *__restrict__ T1,
-                                                               const double *__restrict__ sums, const double2 *__restrict__ terms,
-                                                               int n, int L, float *__restrict__ loss, float *__restrict__ dWk)
+                                                               const double *__restrict__ sums, int n, int L, float *__restrict__ loss,
+                                                               float *__restrict__ dWk)
 {
-    __shared__ double red[2][256];
     const int64_t bh = blockIdx.y;
-    const double *N1 = sums + bh * (2 * D * R + R * R) + D * R, *N2 = N1 + D * R;
+    const double *N1 = sums + bh * (2 * D * R + R * R + 2) + D * R, *N2 = N1 + D * R, *terms = N2 + R * R;
     const int e = blockIdx.x * 256 + threadIdx.x;
     const int c = e / R, t = e % R;
     double s = 0.0;
-#pragma unroll 16
+#pragma unroll 32
     for (int c2 = 0; c2 < D; ++c2) s += M[(bh * D + c) * D + c2] * N1[c2 * R + t];
 #pragma unroll 16
     for (int t2 = 0; t2 < R; ++t2) s += T1[(bh * D + c) * R + t2] * N2[t2 * R + t];
     dWk[bh * D * R + e] = (float)s;
-    if (blockIdx.x) return;
-    double lc = 0.0, lm = 0.0;
-#pragma unroll 4
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const double2 x = terms[bh * n + i];
-        lc += x.x;
-        lm += x.y;
-    }
-    red[0][threadIdx.x] = lc;
-    red[1][threadIdx.x] = lm;
-    __syncthreads();
-    for (int step = 128; step; step >>= 1) {
-        if ((int)threadIdx.x < step) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + step];
-            red[1][threadIdx.x] += red[1][threadIdx.x + step];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        lc = red[0][0] / (double)n;
-        lm = red[1][0] / ((double)n * (double)L);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const double lc = terms[0] / (double)n, lm = terms[1] / ((double)n * (double)L);
         loss[bh * 3 + 0] = (float)(0.95 * lc + 0.05 * lm);
         loss[bh * 3 + 1] = (float)lc;
         loss[bh * 3 + 2] = (float)lm;
@@ -415,7 +445,7 @@ PredictorLayout predictor_layout(const dsv_problem &p, int n)
     const size_t want = (nbh * p.L + 767) / 768;
     w.tok_per_block = (int)std::min<size_t>(2048, std::max<size_t>(256, align_up(want, 64)));
     w.nblk = (p.L + w.tok_per_block - 1) / w.tok_per_block;
-    w.nchunk = (n + 127) / 128;   // kAccRows sampled rows per partial sum
+    w.nchunk = (n + kAccRows - 1) / kAccRows;
     size_t o = 0;
     w.part = o; o = align_up(o + nbh * w.nblk * D * D * 4, 256);
     w.M = o; o = align_up(o + nbh * D * D * 8, 256);
@@ -425,8 +455,8 @@ PredictorLayout predictor_layout(const dsv_problem &p, int n)
     w.g = o; o = align_up(o + nbh * n * R * 8, 256);
     w.coef = o; o = align_up(o + nbh * n * 16, 256);
     w.terms = o; o = align_up(o + nbh * n * 16, 256);
-    w.acc = o; o = align_up(o + nbh * w.nchunk * (2 * D * R + R * R) * 8, 256);
-    w.sums = o; o = align_up(o + nbh * (2 * D * R + R * R) * 8, 256);
+    w.acc = o; o = align_up(o + nbh * w.nchunk * (2 * D * R + R * R + 2) * 8, 256);
+    w.sums = o; o = align_up(o + nbh * (2 * D * R + R * R + 2) * 8, 256);
     w.total = o;
     return w;
 }
@@ -440,20 +470,19 @@ static dsv_status predictor_t(const dsv_problem &p, const void *Q, const void *K
     float *part = reinterpret_cast<float *>(ws + w.part);
     auto f64 = [&](size_t at) { return reinterpret_cast<double *>(ws + at); };
     double2 *coef = reinterpret_cast<double2 *>(ws + w.coef), *terms = reinterpret_cast<double2 *>(ws + w.terms);
-    constexpr int kSums = 2 * D * R + R * R;
+    constexpr int kSums = 2 * D * R + R * R + 2;
     hipLaunchKernelGGL((gram_partial_kernel<T, D>), dim3(w.nblk, nbh), dim3(256), 0, st, (const T *)K, p.L, w.tok_per_block, part);
-    hipLaunchKernelGGL(gram_sum_kernel, dim3(D * D / 256, nbh), dim3(256), 0, st, part, w.nblk, D * D, f64(w.M));
-    hipLaunchKernelGGL((gram_weights1_kernel<T, D, R>), dim3(D * R / 256, nbh), dim3(256), 0, st, (const T *)Wk, p.H, f64(w.M), f64(w.T1));
-    hipLaunchKernelGGL((gram_weights2_kernel<T, D, R>), dim3(R * R / 256, nbh), dim3(256), 0, st, (const T *)Wk, p.H, f64(w.T1), f64(w.T2));
+    hipLaunchKernelGGL((gram_sum_kernel<T, D, R>), dim3(D * D / 256, nbh), dim3(256), 0, st, part, w.nblk, (const T *)Wk, p.H, f64(w.M), f64(w.T1));
+    if (R == 64)
+        hipLaunchKernelGGL((gram_weights2_kernel<T, D, R>), dim3(R * R / 256, nbh), dim3(256), 0, st, (const T *)Wk, p.H, f64(w.T1), f64(w.T2));
     DSV_LAUNCH_CHECK();
-    hipLaunchKernelGGL((predictor_rows_kernel<T, D, R>), dim3((n + 63) / 64, nbh), dim3(256), 0, st, (const T *)Q, (const T *)Wq, rows, n,
-                       p.L, p.H, f64(w.M), f64(w.T1), f64(w.T2), f64(w.qlr), f64(w.g), coef, terms);
+    hipLaunchKernelGGL((predictor_rows_kernel<T, D, R>), dim3((n + 63) / 64, nbh), dim3(256), 0, st, (const T *)Q, (const T *)Wq, (const T *)Wk, rows,
+                       n, p.L, p.H, f64(w.M), f64(w.T1), f64(w.T2), f64(w.qlr), f64(w.g), coef, terms);
     hipLaunchKernelGGL((predictor_accum_kernel<T, D, R>), dim3(w.nchunk, nbh), dim3(256), 0, st, (const T *)Q, rows, n, p.L, f64(w.qlr),
-                       f64(w.g), coef, f64(w.acc));
+                       f64(w.g), coef, terms, f64(w.acc));
     hipLaunchKernelGGL(predictor_sum_kernel, dim3((kSums + 255) / 256, nbh), dim3(256), 0, st, f64(w.acc), w.nchunk, D * R, kSums,
                        f64(w.sums), dWq);
-    hipLaunchKernelGGL((predictor_finish_kernel<D, R>), dim3(D * R / 256, nbh), dim3(256), 0, st, f64(w.M), f64(w.T1), f64(w.sums), terms,
-                       n, p.L, loss, dWk);
+    hipLaunchKernelGGL((predictor_finish_kernel<D, R>), dim3(D * R / 256, nbh), dim3(256), 0, st, f64(w.M), f64(w.T1), f64(w.sums), n, p.L, loss, dWk);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
 }

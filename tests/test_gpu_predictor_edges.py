@@ -44,3 +44,8 @@ def test_loss_and_gradients_at_tile_edges(L, n, dtype, d, r):
         # rounding of single entries of the Gram matrix reaches, where that is more
         for x, y, z in zip(got, want, reach):
             assert (x[h].double() - y).abs().max() <= max(1e-4 * max(float(y.abs().max()), 1e-2), z)
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 128])
+def test_partial_sums_of_64_rows(n):
+    test_loss_and_gradients_at_tile_edges(300, n, "bf16", 128, 16)
