@@ -30,20 +30,20 @@ namespace dsv {
 constexpr int kBatch = 32;  // words of an owner's batch in the block form below (= lanes of a half-wave)
 constexpr int kWaves = 4;   // waves of a block, a batch each in turn
 
-// OT: owner tiles per wave, W: waves.  Where a wave's batch goes: per owner the next place and the end of its row or list (a correct threshold
+// OT: owner tiles per wave.  Where a wave's batch goes: per owner the next place and the end of its row or list (a correct threshold
 // fills it exactly; the clamp keeps a wrong one from writing out of bounds), in entries after the first owner's start.
-template <int OT, int W> struct EmitShared {
+template <int OT> struct EmitShared {
     static constexpr int TILES = 32 / OT;                // of a batch, at most
-    uint32_t mask[W][TILES][32 * OT + 1];           // [tile in batch][owner], padded: conflict-free both ways
-    int32_t count[2][W][OT][64];                    // entries of a batch by owner tile and lane (owner and half), two rounds in turn
-    int2 place[W][32 * OT];
+    uint32_t mask[kWaves][TILES][32 * OT + 1];           // [tile in batch][owner], padded: conflict-free both ways
+    int32_t count[2][kWaves][OT][64];                    // entries of a batch by owner tile and lane (owner and half), two rounds in turn
+    int2 place[kWaves][32 * OT];
 };
 
 // Tiles per batch: full rounds of the block's waves.
-__device__ __forceinline__ int batch_tiles(int ntiles, int waves, int most)
+__device__ __forceinline__ int batch_tiles(int ntiles, int most)
 {
-    const int rounds = (ntiles + waves * most - 1) / (waves * most);
-    return (ntiles + waves * rounds - 1) / (waves * rounds);
+    const int rounds = (ntiles + kWaves * most - 1) / (kWaves * most);
+    return (ntiles + kWaves * rounds - 1) / (kWaves * rounds);
 }
 
 typedef int32_t entries4_t __attribute__((ext_vector_type(4), aligned(4)));
@@ -52,10 +52,10 @@ typedef int32_t entries2_t __attribute__((ext_vector_type(2), aligned(4)));
 // Expand the parked masks of tiles tile0 .. tile0 + nfilled - 1 for all owners: 64 words at a time, of 2 OT owners.
 // (Compacting an owner's entries in LDS first and writing them out with consecutive lanes on consecutive
 // entries was measured slower -- 24.2 against 21.2 ms for the query-major emission at L = 128k, k = 8192.)
-template <int OT, int W>
-__device__ __forceinline__ void expand_batch(const EmitShared<OT, W> &sh, int wave, int32_t *__restrict__ out, int tile0, int nfilled, int lane)
+template <int OT>
+__device__ __forceinline__ void expand_batch(const EmitShared<OT> &sh, int wave, int32_t *__restrict__ out, int tile0, int nfilled, int lane)
 {
-    constexpr int TILES = EmitShared<OT, W>::TILES, STEP = 64 / TILES;
+    constexpr int TILES = EmitShared<OT>::TILES, STEP = 64 / TILES;
     const int t = lane & (TILES - 1), sub = lane / TILES;
     const int base_val = (tile0 + t) * 32;
     uint32_t next = t < nfilled ? sh.mask[wave][t][sub] : 0u;
@@ -99,14 +99,14 @@ __device__ __forceinline__ void expand_batch(const EmitShared<OT, W> &sh, int wa
 }
 
 // After a round's words are parked and its counts written: the batch's place in its owners' rows.  at, end: of this lane's owners.
-template <int OT, int W>
-__device__ __forceinline__ void place_batch(EmitShared<OT, W> &sh, int buf, int wave, int lane, int (&at)[OT], const int (&end)[OT])
+template <int OT>
+__device__ __forceinline__ void place_batch(EmitShared<OT> &sh, int buf, int wave, int lane, int (&at)[OT], const int (&end)[OT])
 {
 #pragma unroll
     for (int i = 0; i < OT; ++i) {
         int before = 0, all = 0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             const int c = sh.count[buf][w][i][lane & 31] + sh.count[buf][w][i][32 + (lane & 31)];
             before += w < wave ? c : 0;
             all += c;
@@ -120,8 +120,8 @@ __device__ __forceinline__ void place_batch(EmitShared<OT, W> &sh, int buf, int 
 // ------------------------------------------------------------------------------------ query-major
 // Ties that a query does not take: a tile of queries one of which does not take all of its threshold-equal keys counts them beside the
 // selected ones, and a batch that holds more of them than its query may still take (or the last of those) is scored once more to find which.
-template <int W> struct Ties {
-    int32_t count[2][W][64];
+struct Ties {
+    int32_t count[2][kWaves][64];
     int32_t last[32];  // the highest one taken
 };
 
@@ -140,14 +140,14 @@ __device__ __forceinline__ uint32_t equal_word(const T *__restrict__ Kb, const T
 // krem[query] = +-(number of threshold-equal keys to take); negative: that is all of them.
 // jcut (optional) and tile_flag (optional; 1 when all 32 queries of the tile take all their ties)
 // are what the key-major emission needs.
-template <typename T, int R, int W>
-__global__ __launch_bounds__(64 * W, 4) void emit_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq, int L,
+template <typename T, int R>
+__global__ __launch_bounds__(64 * kWaves, 4) void emit_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq, int L,
                                                            HeadTable tab, uint32_t *__restrict__ prefix,
                                                            const int32_t *__restrict__ krem, int32_t *__restrict__ idx,
                                                            int32_t *__restrict__ jcut, int32_t *__restrict__ tile_flag)
 {
-    __shared__ __align__(16) EmitShared<1, W> sh;
-    __shared__ Ties<W> ties;
+    __shared__ __align__(16) EmitShared<1> sh;
+    __shared__ Ties ties;
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
     const int k = tab.k[slot];
@@ -166,13 +166,13 @@ __global__ __launch_bounds__(64 * W, 4) void emit_kernel(const T *__restrict__ Q
     const TileWalk<T, R> walk(L, lane);
     if (!all_simple && threadIdx.x < 32) ties.last[n] = -1;
 
-    const int ntiles = (L + 31) >> 5, batch = batch_tiles(ntiles, W, EmitShared<1, W>::TILES);
+    const int ntiles = (L + 31) >> 5, batch = batch_tiles(ntiles, EmitShared<1>::TILES);
     const uint32_t whole = live ? 0xFFFFu : 0u;
     const int want = kr < 0 ? 0x7FFFFFFF : kr;  // ties to take; taken: those of earlier rounds, whether or not there was room
     int at[1] = {live ? n * k : 0}, taken = 0;
     const int end[1] = {live ? at[0] + k : 0};
     int buf = 0;
-    for (int b0 = 0; b0 < ntiles; b0 += W * batch, buf ^= 1) {
+    for (int b0 = 0; b0 < ntiles; b0 += kWaves * batch, buf ^= 1) {
         const int t0 = min(b0 + wave * batch, ntiles), t1 = min(t0 + batch, ntiles);
         uint16_t *park = reinterpret_cast<uint16_t *>(sh.mask[wave][0]) + 2 * n + half;
         Frag<T, R> kf_next = walk.load(Kb, t0, half);
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(64 * W, 4) void emit_kernel(const T *__restrict__ Q
             // ties that do not fit leave the counts: those of this batch by this wave, for all to see
             int before = taken, here = 0;
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
+            for (int w = 0; w < kWaves; ++w) {
                 const int c = ties.count[buf][w][n] + ties.count[buf][w][32 + n];
                 before += w < wave ? c : 0;
                 here = w == wave ? c : here;
@@ -227,8 +227,8 @@ __global__ __launch_bounds__(64 * W, 4) void emit_kernel(const T *__restrict__ Q
             }
             __syncthreads();
         }
-        place_batch<1, W>(sh, buf, wave, lane, at, end);
-        expand_batch<1, W>(sh, wave, out, t0, t1 - t0, lane);
+        place_batch<1>(sh, buf, wave, lane, at, end);
+        expand_batch<1>(sh, wave, out, t0, t1 - t0, lane);
     }
     if (!all_simple) __syncthreads();
     if (wave == 0 && live && half == 0) {
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
                                                              const int32_t *__restrict__ tile_flag, const int64_t *__restrict__ col,
                                                              int32_t *__restrict__ idxT)
 {
-    __shared__ __align__(16) EmitShared<2, kWaves> sh;
+    __shared__ __align__(16) EmitShared<2> sh;
     __shared__ __align__(16) QueryChunk qc;
     const int slot = blockIdx.y;
     const int bh = tab.bh[slot];
@@ -456,7 +456,7 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
     }
 
     const TileWalk<T, R> walk(Lq, lane);
-    const int batch = batch_tiles(ntiles, kWaves, EmitShared<2, kWaves>::TILES);
+    const int batch = batch_tiles(ntiles, EmitShared<2>::TILES);
     int buf = 0;
     for (int b0 = 0; b0 < ntiles; b0 += kWaves * batch, buf ^= 1) {
         const int t0 = min(b0 + wave * batch, ntiles), t1 = min(t0 + batch, ntiles);
@@ -478,8 +478,8 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
 #pragma unroll
         for (int i = 0; i < 2; ++i) sh.count[buf][wave][i][lane] = count[i];
         __syncthreads();  // (two rounds in turn: what is written next was last read before this barrier)
-        place_batch<2, kWaves>(sh, buf, wave, lane, at, end);
-        expand_batch<2, kWaves>(sh, wave, out, t0, t1 - t0, lane);
+        place_batch<2>(sh, buf, wave, lane, at, end);
+        expand_batch<2>(sh, wave, out, t0, t1 - t0, lane);
     }
 }
 
@@ -487,7 +487,8 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
 // Whether the query-major emission takes the form of 16 waves that write two queries each, instead of that of four that write batches:
 // while there are few tiles of queries.  us, batches : two queries each, r = 16: L = 8192, k = L / 16, 256 tiles 121 : 90, 512 151 : 129, 1024 216 : 215,
 // k = L / 64 106 : 111 and 208 : 202; L = 16384, 512 tiles 210 : 195, 1024 312 : 341, 2048 505 : 629; k = L / 64, 1024 337 : 364.  r = 64, L = 8192,
-// 256 tiles 179 : 179, 512 364 : 345; L = 16384, 512 451 : 454, 1024 847 : 864.  fp32, r = 16, L = 8192, 256 tiles 343 : 324, 512 637 : 623, 1024 1196 : 1218.
+// 256 tiles 179 : 179, 512 364 : 345; L = 16384, 512 451 : 454, 1024 847 : 864.  fp32, r = 16, L = 8192, 256 tiles 216 : 181, 512 333 : 290, 1024 501 : 513;
+// r = 64, 256 tiles 484 : 488, 512 1020 : 980, 1024 1803 : 1917.
 // Short rows of keys pay for the barriers sooner (fp32, L = 2080, 520 tiles, 62 : 75).
 template <typename T, int R>
 static bool emit_by_blocks(int L, int qtiles, const HeadTable &tab)
@@ -506,8 +507,6 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
     const int tiles = (p.L + 31) / 32;    // key tiles
     const int qtiles = (Lq + 31) / 32;    // query (or query-group) tiles
     const float *tau_f = reinterpret_cast<const float *>(b.prefix);
-    // a tile of fp32 products of 64 ranks takes 2048 clocks of matrix work: there lone waves lose nothing (four heads of 16384: 12.0 : 12.4 ms)
-    constexpr int W = sizeof(T) == 4 && R == 64 ? 1 : kWaves;
     if (!emitted) {
         KernelSpan span(DSV_KERNEL_EMIT, st);
         for (int t = 0; t < n_tabs; ++t) {
@@ -516,7 +515,7 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
                 hipLaunchKernelGGL((emit_block_kernel<T, R>), grid, dim3(64 * kEmitWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem,
                                    b.idx, b.jcut, b.tile_flag);
             else
-                hipLaunchKernelGGL((emit_kernel<T, R, W>), grid, dim3(64 * W), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem, b.idx,
+                hipLaunchKernelGGL((emit_kernel<T, R>), grid, dim3(64 * kWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], b.prefix, b.krem, b.idx,
                                    b.jcut, b.tile_flag);
             DSV_LAUNCH_CHECK();
         }

@@ -10,7 +10,8 @@
 //            ties), the block takes the four 8-bit digits of the radix search (stage1.hip) instead.
 //
 // What bounds it: barriers and LDS round trips, about ten in a row.  L = 1024, two heads, fp32, per call with the projection:
-// 128 us in six launches, 32 with the digits, 28.6 with the bins.  Outputs are those of the radix search and of the
+// 128 us in six launches, 32 with the digits, 28.6 with the bins, 22 since fragments come in 16-byte pieces (before, the sixteen waves'
+// loads alone took ten of them).  Outputs are those of the radix search and of the
 // emission (stage1_emit.hip), bit for bit.
 #include "stage1_core.h"
 
