@@ -124,7 +124,8 @@ DSV_API dsv_status dsv_lowrank_topk_t(const dsv_problem *p, const void *Q, const
  * O is written in `dtype`, lse in float.  Workspace: none without DSV_FLAG_SORTED_INDEX (the query
  * returns 0 and a null workspace is accepted); with it, the segment pointers and the per-range
  * partial results, or none where the problem is too small for ranges to pay; heads that keep enough of their keys (bf16,
- * scale > 0) run over dense tiles and need a bit per (query, key), up to 1 GB at a time, in the same place. */
+ * scale > 0) run over dense tiles and need a bit per (query, key), up to 1 GB at a time, in the same place.  Heads near
+ * that line gather where the workspace is enough for gathers only, or null where those need none. */
 DSV_API size_t dsv_sparse_attn_fwd_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                const int32_t *idx, void *O, float *lse,

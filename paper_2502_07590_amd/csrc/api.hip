@@ -215,7 +215,7 @@ bool sort_rows_first(const dsv_problem &p)
 // 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.  On sparse products, where few
 // pairs are kept (dense_fwd_form in dense.hip), a sixth less, a
 // fifteenth at d = 64: 4 of 32768, k = L / 22: 3170 -> 2670 (gathering 3610), d = 64, k = L / 16: 2220 -> 2070.
-int32_t dense_fwd_min_k(const dsv_problem &p)
+int32_t dense_fwd_min_k(const dsv_problem &p, bool sparse = true)
 {
     if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
     const bool wide = p.d == 128;
@@ -229,7 +229,7 @@ int32_t dense_fwd_min_k(const dsv_problem &p)
         kept += ks[m - 1];
         if (m < p.H && ks[m] == ks[m - 1]) continue;
         const double blocks = (double)p.B * m * ((p.L + 127) / 128), tiles = (p.L + 63) / 64;
-        const bool few = blocks > 256 && kept * 14 <= (double)p.L * m;  // on sparse products
+        const bool few = sparse && blocks > 256 && kept * 14 <= (double)p.L * m;  // on sparse products
         const double dense = tiles * (blocks <= 256 ? light : (few ? (wide ? 0.83 : 0.93) : 1.0) * full * std::max(1.0, blocks / slots + 0.2));
         if (gathered - 1.1 * dense > best) {
             best = gathered - 1.1 * dense;
@@ -316,11 +316,12 @@ struct FwdLayout {
     size_t seg, pm, pl, pacc, hist, order, total;
 };
 
-FwdLayout fwd_layout(const dsv_problem &p)
+// sparse: whether sparse products count in the rule for heads over tiles with a mask, which needs scratch.
+FwdLayout fwd_layout(const dsv_problem &p, bool sparse = true)
 {
     FwdLayout w{};
     w.plan = make_split_plan(p, kFwdRangeBytes, false);  // every range brings a maximum of its own (stage2_core.h)
-    w.dense_k = dense_fwd_min_k(p);
+    w.dense_k = dense_fwd_min_k(p, sparse);
     w.form = row_form(p, w.plan, false, w.dense_k);
     int dense = 0;
     for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= w.dense_k;
@@ -614,7 +615,9 @@ dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *
     dsv_status st = check_problem(p, false);
     if (st != DSV_OK) return st;
     if (!ok_ptrs({Q, K, V, idx, O, lse})) return DSV_EINVAL;
-    const FwdLayout w = fwd_layout(*p);
+    FwdLayout w = fwd_layout(*p);
+    // Heads that only sparse products bring to tiles gather where there is no room for their masks.
+    if (check_workspace(workspace, ws_bytes, w.total) != DSV_OK) w = fwd_layout(*p, false);
     st = check_workspace(workspace, ws_bytes, w.total);
     if (st != DSV_OK) return st;
     const std::vector<HeadTable> tabs = make_tables(*p);

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64 * kRadixWaves) void window_hist_kernel(const T *
     // every lo a positive float: a score is at or above lo iff its raw bits are, as signed integers
     // (negative scores are negative integers), and its distance from lo is the difference of the raw bits
     const bool fast = __all((lo & 0x80000000u) != 0u);
-    // 32-bit addresses of wave-uniform tiles, two vector instructions each instead of seven: 647 -> 626 us here and 340 -> 317 in the collecting
+    // 32-bit addresses of wave-uniform tiles, two vector instructions each: 647 -> 626 us here and 340 -> 317 in the collecting
     // sweep (four heads of 32768, r = 16, bf16); vector issue bounds both
     const TileWalk<T, R> walk(L, lane);
     Frag<T, R> kf_next = walk.load(Kb, wave, half);

@@ -60,6 +60,21 @@ def test_heads_that_keep_few_pairs_of_a_tile(d, H, L, near):
     _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 97, device="cuda"), torch.arange(L - 40, L, device="cuda")]))
 
 
+def test_a_call_without_scratch_gathers_where_gathers_need_none():
+    L, d, ks = 2111, 128, [100] * 24  # one key in 21: over tiles for sparse products only
+    g = torch.Generator(device="cuda").manual_seed(1)
+    Q, K, V = (torch.randn(1, 24, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(1, 24, L, d, 16, "bf16", ks, d ** -0.5, sorted_index=True)
+    idx = torch.cat([_rows(L, k, g).reshape(-1) for k in ks])
+    assert dsv.sparse_attn_fwd_workspace(p) > 0
+    want, want_lse = dsv.sparse_attn_fwd(p, Q, K, V, idx)
+    O, lse = torch.empty_like(Q), torch.empty_like(want_lse)
+    lib, stream = dsv.load_library(), torch.cuda.current_stream().cuda_stream
+    assert lib.dsv_sparse_attn_fwd(p.c, *(t.data_ptr() for t in (Q, K, V, idx, O, lse)), None, 0, stream) == 0
+    # both round an output to bf16 once, their sums differ by 2^-16 of sum p |v| and less
+    assert ((O.float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs() + 2.0 ** -9).all() and torch.allclose(lse, want_lse, atol=1e-4)
+
+
 def test_mask_in_pieces():
     L, k = 98309, 4000
     g = torch.Generator(device="cuda").manual_seed(7)
