@@ -34,9 +34,9 @@ VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9   # 256 CUs x 64 fp32 lanes x 2.4 GHz, on
 # build of the kernels: they are reported only while the library still names that version.
 PMC_LIBRARY_VERSION = "dsv 0.8 (gfx950)"
 PMC_CONFIG2 = {
-    "sparse_attn_fwd": {"fetch_kib": 87572678, "write_kib": 12783803, "l2_hit_rate": 0.7130},  # mask and dense tiles
-    "sparse_attn_bwd_dq": {"fetch_kib": 60808786, "write_kib": 25582164, "l2_hit_rate": 0.8245},  # mask and dense tiles
-    "sparse_attn_bwd_dkdv": {"fetch_kib": 33833781, "write_kib": 12582916, "l2_hit_rate": 0.9740},
+    "sparse_attn_fwd": {"fetch_kib": 22152170, "write_kib": 12835465, "l2_hit_rate": 0.8712},  # mask and dense tiles
+    "sparse_attn_bwd_dq": {"fetch_kib": 28284599, "write_kib": 25632575, "l2_hit_rate": 0.9002},  # mask and dense tiles
+    "sparse_attn_bwd_dkdv": {"fetch_kib": 33718040, "write_kib": 12582915, "l2_hit_rate": 0.9739},
 }
 # the sweep inside each stage-2 call, by gathers or over dense tiles (what the roofline object is about)
 SWEEP_OF_CALL = {"sparse_attn_fwd": "fwd_sweep", "sparse_attn_bwd_dq": "dq_sweep", "sparse_attn_bwd_dkdv": "dkdv_sweep"}
