@@ -229,7 +229,9 @@ __global__ __launch_bounds__(64 * NW, 2) void dense_fwd_pairs_kernel(const bf16_
     const int rc = live ? first + n : nrows - 1;
     const int64_t hb = (int64_t)bh * L * D;
     const int64_t qi = row0 + rc;
-    const uint32_t mrow = ((uint32_t)blockIdx.y * nrows + rc) * pitch;  // masks hold less than 2^32 words
+    // the wave's rows of the mask from its first one on; all masks of a launch together may pass 2^32 words
+    const uint32_t *mask = bits + ((int64_t)blockIdx.y * nrows + min(first, nrows - 1)) * pitch;
+    const uint32_t mrow = (uint32_t)((rc - min(first, nrows - 1)) * pitch);
     const unsigned char *m1 = reinterpret_cast<const unsigned char *>(K + hb), *m2 = reinterpret_cast<const unsigned char *>(V + hb);
     const int tile1 = (L + kTile - 1) / kTile;
 
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dense_fwd_pairs_kernel(const bf16_
     auto request = [&](int t, unsigned char *p1, unsigned char *p2) __attribute__((always_inline)) {
         loads.request(m1, t, p1);
         loads.request(m2, t, p2);
-        words = *reinterpret_cast<const uint2 *>(bits + mrow + t);
+        words = *reinterpret_cast<const uint2 *>(mask + mrow + t);
     };
     request(0, t1a, t2a);
     auto tile = [&](uint32_t word, const unsigned char *p1, const unsigned char *p2) __attribute__((always_inline)) {

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256, 2) void dense_bwd_kernel(const bf16_t *__restr
     const int64_t hb = (int64_t)bh * L * D, own_row = (int64_t)bh * L + row0 + rc;
     const int tiles = (L + kTile - 1) / kTile, per = (tiles + pl.S - 1) / pl.S;
     const int tile0 = range * per, tile1 = min(tiles, tile0 + per);
-    const uint32_t mrow = ((uint32_t)slot * nrows + rc) * pitch;  // masks hold less than 2^32 words
+    const uint32_t mrow = ((uint32_t)slot * nrows + rc) * pitch;  // a launch's masks hold less than 2^32 words (checked on the host)
     const unsigned char *m1 = reinterpret_cast<const unsigned char *>(R1 + hb), *m2 = reinterpret_cast<const unsigned char *>(R2 + hb);
 
     const int own_at = wave * ((2 * NM - XR) * 1024) + lane * 16;
@@ -395,7 +395,7 @@ static dsv_status dense_bwd_t(const dsv_problem &p, const HeadTable &tab, bool k
             }
             pl.nqb = (nr + kOwn - 1) / kOwn;
             const int64_t blocks = nh * range_items(pl.S_pad, pl.nqb);
-            if (blocks > 0x7FFFFFFF) return DSV_EUNSUPPORTED;
+            if (blocks > 0x7FFFFFFF || ((uint64_t)nh * nr * pitch) >> 32) return DSV_EUNSUPPORTED;  // never: masks take 2 GB at most
             if (keys)
                 hipLaunchKernelGGL((dense_bwd_kernel<D, true>), dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)K, (const bf16_t *)V,
                                    (const bf16_t *)Q, (const bf16_t *)dO, bits, pitch, (const bf16_t *)nullptr, (const float *)nullptr,

@@ -83,6 +83,20 @@ def test_mask_in_pieces():
     _check(p, Q, K, V, [_rows(L, k, g)], torch.randint(0, L, (200,), generator=g, device="cuda"))
 
 
+# one launch whose masks hold more than 2^32 words: the rows past that, the last ones of the second head
+def test_masks_of_more_than_16_gigabytes():
+    H, L, d = 2, 262144, 128
+    k = L // 20
+    g = torch.Generator(device="cuda").manual_seed(11)
+    Q, K, V = (torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(1, H, L, d, 16, "bf16", [k] * H, d ** -0.5, sorted_index=True)
+    assert 0 < dsv.dense_min_k(p, "fwd_sweep") <= k
+    words = H * L * (L // 32)  # without the space between rows
+    assert words >= 2 ** 32 and dsv.sparse_attn_fwd_workspace(p) > 4 * words
+    rows = _rows(L, k, g, near=True)
+    _check(p, Q, K, V, [rows] * H, torch.cat([torch.arange(0, L, 4099, device="cuda"), torch.arange(L - 60, L, device="cuda")]))
+
+
 # a value row that is not finite belongs to the queries that keep its key, and to no others
 @pytest.mark.parametrize("d,bad", [(64, float("inf")), (128, float("nan"))])
 def test_rows_that_are_not_finite(d, bad):
