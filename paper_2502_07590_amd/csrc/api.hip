@@ -302,11 +302,11 @@ void cut_tables(const std::vector<HeadTable> &tabs, int32_t min_k, std::vector<H
     }
 }
 
-// Scratch for masks: all of them, at most 1 GB at a time (of one head 128 rows at least).
+// Scratch for masks: all of them, at most 1 GB of bits (of one head 128 rows at least).
 size_t mask_bytes(const dsv_problem &p, int heads)
 {
-    const size_t row = (size_t)bits_pitch(p.L) * 4;
-    return align_up(std::max(std::min((size_t)p.B * heads * p.L * row, (size_t)1 << 30), kDenseMinRows * row), 256);
+    const size_t row = (size_t)bits_pitch(p.L) * 4, rows = std::min((size_t)p.B * heads * p.L, bits_rows(p.L, (size_t)1 << 30));
+    return align_up(std::max(rows, (size_t)kDenseMinRows) * row, 256);
 }
 
 struct FwdLayout {
@@ -370,11 +370,12 @@ void place_masks(const dsv_problem &p, int32_t least, StepLayout &w)
 {
     int dense = 0;
     for (int h = 0; h < p.H; ++h) dense += p.k_per_head[h] >= least;
-    const size_t row = (size_t)bits_pitch(p.L) * 4, all = (size_t)p.B * dense * p.L * row;
+    const size_t row = (size_t)bits_pitch(p.L) * 4, all = (size_t)p.B * dense * p.L;
     w.mask = w.total;
     // whole where they are small beside the partial results; else pieces that fill the chip a few times and that the memory-side
     // cache holds from their making to their use
-    if (dense) w.mask_bytes = align_up(all <= ((size_t)256 << 20) ? all : std::max((size_t)96 << 20, kDenseMinRows * row), 256);
+    const size_t most = bits_rows(p.L, (size_t)256 << 20), piece = bits_rows(p.L, (size_t)96 << 20);
+    if (dense) w.mask_bytes = align_up((all <= most ? all : std::max(piece, (size_t)kDenseMinRows)) * row, 256);
     w.total += w.mask_bytes;
 }
 

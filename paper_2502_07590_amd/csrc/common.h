@@ -518,6 +518,7 @@ dsv_status launch_idx_transpose(const dsv_problem &p, const HeadTable *tabs, int
 // col: the rows are key-major lists (idx: idx_t).
 constexpr int kBitsMaxKeys = 524288;  // a row's bitmap fits 64 KB of LDS
 int bits_pitch(int L);
+size_t bits_rows(int L, size_t bytes);  // rows whose bits take that much, the space between rows (bits_pitch) not counted
 dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
                              int nrows, uint32_t *bits, hipStream_t st, const int64_t *col = nullptr);
 // Forward of some heads over dense tiles with a mask (dense.hip; bf16, scale > 0, L <= kBitsMaxKeys); ws: scratch for the

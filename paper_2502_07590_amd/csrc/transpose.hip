@@ -19,7 +19,7 @@ namespace dsv {
 // that the 512 keys of a block are whole 64-byte pieces of every row.
 constexpr int kBitsKeys = 512;               // keys per block of the counting and filling kernels (16 words)
 constexpr int kBitsRows = 1024;              // queries per block of those kernels: one segment of every list
-constexpr size_t kBitsBytes = (size_t)2 << 30;  // scratch for the bit matrix: larger problems go through it piece by piece
+constexpr size_t kBitsBytes = (size_t)2 << 30;  // bits of the matrix: larger problems go through it piece by piece
 
 // One wave per row at a time: its entries are OR-ed into a bitmap in LDS, which is then written out and cleared.  col: the rows are
 // key-major lists, whose bits are queries.  Bound by the memory: entries come in 16-byte pieces, eight kilobytes of a row in flight, and no
@@ -457,11 +457,16 @@ __global__ __launch_bounds__(256) void fill_zero_i32_kernel(int4 *__restrict__ p
 // Where rows would lie whole kilobytes apart, 64 bytes more: the words that the waves of the chip read together, one of every row, otherwise
 // come from a few of the L2's channels (forward over dense tiles, L = 131072, one head, k = 8192: 12.43 -> 11.99 ms; L = 32768, four heads, k = 2048:
 // 3.04 -> 2.91).  The largest rows stay as long as the bitmap in LDS may be.
+static int bits_words(int L) { return (L + kBitsKeys - 1) / kBitsKeys * 16; }
 int bits_pitch(int L)
 {
-    const int words = (L + kBitsKeys - 1) / kBitsKeys * 16;
+    const int words = bits_words(L);
     return words % 256 == 0 && L <= kBitsMaxKeys / 2 ? words + 16 : words;
 }
+// Limits of scratch hold for the bits alone: rows with space between them are those of lengths that fill such a limit exactly (131072 keys
+// and queries: 2 GB), and would come in a piece more.  That length, one head, transposed, k = 512 : 8192: 2.81 : 5.80 ms in two pieces, 2.30 : 4.51
+// in one; its forward, d = 64, k = 8192: 10.8 ms in three, 7.9 in two.
+size_t bits_rows(int L, size_t bytes) { return bytes / ((size_t)bits_words(L) * 4); }
 
 dsv_status launch_bits_build(const dsv_problem &p, const HeadTable &tab, int slot0, int heads, const int32_t *idx, int row0,
                              int nrows, uint32_t *bits, hipStream_t st, const int64_t *col)
@@ -501,7 +506,7 @@ static TransposePlan transpose_plan(const dsv_problem &p)
     if (w.bits) {
         w.pitch = bits_pitch(p.L);
         const size_t row = (size_t)w.pitch * 4;
-        const size_t fit = kBitsBytes / row;  // rows
+        const size_t fit = bits_rows(p.L, kBitsBytes);
         if (fit >= (size_t)p.L) {
             w.heads = (int)std::min<size_t>({fit / p.L, nbh, (size_t)kMaxSlots});
             w.rows = p.L;

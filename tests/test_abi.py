@@ -128,6 +128,19 @@ def test_workspace_sizes_follow_the_documented_layout(dsv):
     assert 2 * rows * cfg.r * 2 < s1 < 2 * rows * cfg.r * 2 + rows * 4 * 8
 
 
+def test_masks_that_fill_a_limit_exactly_come_in_one_piece(dsv):
+    """Rows of a bit mask lie 64 bytes further apart where they would be whole kilobytes; the limits count the bits."""
+    for H, L in ((1, 131072), (4, 65536), (16, 32768)):  # 2 GB of bits: the whole matrix of the transposition
+        p = dsv.Problem(1, H, L, 64, 16, "bf16", [L // 64] * H, 0.1)
+        assert dsv.idx_transpose_workspace(p) >= H * L * (L // 8 + 64) + 4 * H * L * (1 + L // 1024)
+    # 256 MB: the masks of a backward step, whole, beside what the gathers of a call with fewer keys take
+    step = [dsv.sparse_attn_bwd_dq_workspace(dsv.Problem(1, 2, 32768, 128, 16, "bf16", [k] * 2, 0.1, sorted_index=True)) for k in (1300, 3276)]
+    assert step[1] - step[0] >= 2 * 32768 * (32768 // 8 + 64)
+    # 1 GB: half of the masks of a head
+    p = dsv.Problem(1, 1, 131072, 64, 16, "bf16", [8192], 0.1, sorted_index=True)
+    assert dsv.sparse_attn_fwd_workspace(p) >= 65536 * (131072 // 8 + 64)
+
+
 def test_measurement_aid_rejects_what_has_not_run(dsv):
     lib = dsv.load_library()
     ms = ctypes.c_float(-1.0)
