@@ -17,6 +17,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4_t;
 
 constexpr int kWave = 64;
+constexpr int64_t kMaxKeys = (1 << 25) - 1;  // keys of a head: its matrix is below 4 GB, the shortest row (bf16, d = 64) has 128 bytes
 constexpr int kMaxSlots = 64;  // (batch, head) pairs described by one kernel launch
 
 // Per-launch table of the (batch, head) pairs a grid works on, passed by value as a kernel

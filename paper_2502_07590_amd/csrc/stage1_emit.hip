@@ -31,7 +31,7 @@ constexpr int kBatch = 32;  // words of an owner's batch in the block form below
 constexpr int kWaves = 4;   // waves of a block, a batch each in turn
 
 // OT: owner tiles per wave.  Where a wave's batch goes: per owner the next place and the end of its row or list (a correct threshold
-// fills it exactly; the clamp keeps a wrong one from writing out of bounds), in entries after the first owner's start.
+// fills it exactly; the clamp keeps a wrong one from writing out of bounds), in entries after the start of its tile's first owner.
 template <int OT> struct EmitShared {
     static constexpr int TILES = 32 / OT;                // of a batch, at most
     uint32_t mask[kWaves][TILES][32 * OT + 1];           // [tile in batch][owner], padded: conflict-free both ways
@@ -49,12 +49,14 @@ __device__ __forceinline__ int batch_tiles(int ntiles, int most)
 typedef int32_t entries4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t entries2_t __attribute__((ext_vector_type(2), aligned(4)));
 
-// Expand the parked masks of tiles tile0 .. tile0 + nfilled - 1 for all owners: 64 words at a time, of 2 OT owners.
+// Expand the parked masks of tiles tile0 .. tile0 + nfilled - 1 for all owners: 64 words at a time, of 2 OT owners.  out, out_last: where the
+// rows or lists of the first and of the last owner tile begin.  Offsets from there have 32 bits: 32 lists of every query are less than 2^32 bytes (64 are not).
 // (Compacting an owner's entries in LDS first and writing them out with consecutive lanes on consecutive
 // entries was measured slower -- 24.2 against 21.2 ms for the query-major emission at L = 128k, k = 8192.)
 template <int OT>
-__device__ __forceinline__ void expand_batch(const EmitShared<OT> &sh, int wave, int32_t *__restrict__ out, int tile0, int nfilled, int lane)
+__device__ __forceinline__ void expand_batch(const EmitShared<OT> &sh, int wave, int32_t *out, int32_t *out_last, int tile0, int nfilled, int lane)
 {
+    static_assert(32 * kMaxKeys * (int64_t)sizeof(int32_t) < 1ll << 32, "offsets inside an owner tile's rows or lists");
     constexpr int TILES = EmitShared<OT>::TILES, STEP = 64 / TILES;
     const int t = lane & (TILES - 1), sub = lane / TILES;
     const int base_val = (tile0 + t) * 32;
@@ -74,8 +76,8 @@ __device__ __forceinline__ void expand_batch(const EmitShared<OT> &sh, int wave,
             while (__popc(m) > room) m &= ~(0x80000000u >> __clz(m));
             c = __popc(m);
         }
-        char *to = reinterpret_cast<char *>(out);
-        uint32_t off = (uint32_t)pos * 4u;  // 64 rows have less than 2^32 bytes
+        char *to = reinterpret_cast<char *>(STEP * i < 32 ? out : out_last);
+        uint32_t off = (uint32_t)pos * 4u;
         auto take = [&]() __attribute__((always_inline)) {
             const int e = base_val + (__ffs(m) - 1);
             m &= m - 1;
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void emit_kernel(const T *__restric
             __syncthreads();
         }
         place_batch<1>(sh, buf, wave, lane, at, end);
-        expand_batch<1>(sh, wave, out, t0, t1 - t0, lane);
+        expand_batch<1>(sh, wave, out, out, t0, t1 - t0, lane);
     }
     if (!all_simple) __syncthreads();
     if (wave == 0 && live && half == 0) {
@@ -436,22 +438,23 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
 
     const Frag<T, R> kf[2] = {load_frag<T, R>(Kb, j0, L, lane), load_frag<T, R>(Kb, j0 + 32, L, lane)};
     // col comes from the counting pass over the same predicate, so the lists fill the head's block of
-    // L * k entries exactly; the clamps (to [0, cap], ascending, and the block's 64 lists to 64 * Lq entries) only keep an
+    // L * k entries exactly; the clamps (to [0, cap], ascending, and a tile's 32 lists to 32 * Lq entries) only keep an
     // inconsistent col from sending writes out of it
     const int64_t cap = (int64_t)Lq * tab.k[slot];
     const int64_t *cp = col + (int64_t)bh * (L + 1);
     auto clamped = [&](int64_t x, int64_t lo, int64_t hi) { return x < lo ? lo : x < hi ? x : hi; };
-    const int64_t origin = clamped(cp[j0], 0, cap), far = clamped(origin + 64ll * Lq, 0, cap);
-    int32_t *out = idxT + tab.off[slot] + origin;
+    const int64_t origin[2] = {clamped(cp[j0], 0, cap), clamped(cp[min(j0 + 32, L)], 0, cap)};
+    int32_t *out = idxT + tab.off[slot] + origin[0], *out_last = idxT + tab.off[slot] + origin[1];
     int at[2], end[2];
     uint32_t whole[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int j = min(j0 + 32 * i + n, L - 1);
         const bool live = j0 + 32 * i + n < L;
-        const int64_t c0 = clamped(cp[j], origin, far), c1 = clamped(cp[j + 1], c0, far);
-        at[i] = (int)(c0 - origin);
-        end[i] = live ? (int)(c1 - origin) : at[i];
+        const int64_t far = clamped(origin[i] + 32ll * Lq, 0, cap);
+        const int64_t c0 = clamped(cp[j], origin[i], far), c1 = clamped(cp[j + 1], c0, far);
+        at[i] = (int)(c0 - origin[i]);
+        end[i] = live ? (int)(c1 - origin[i]) : at[i];
         whole[i] = live ? 0xFFFFu : 0u;
     }
 
@@ -479,7 +482,7 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
         for (int i = 0; i < 2; ++i) sh.count[buf][wave][i][lane] = count[i];
         __syncthreads();  // (two rounds in turn: what is written next was last read before this barrier)
         place_batch<2>(sh, buf, wave, lane, at, end);
-        expand_batch<2>(sh, wave, out, t0, t1 - t0, lane);
+        expand_batch<2>(sh, wave, out, out_last, t0, t1 - t0, lane);
     }
 }
 

@@ -141,6 +141,13 @@ def test_masks_that_fill_a_limit_exactly_come_in_one_piece(dsv):
     assert dsv.sparse_attn_fwd_workspace(p) >= 65536 * (131072 // 8 + 64)
 
 
+def test_the_longest_head(dsv):
+    """2^25 - 1 keys of 128 bytes: what offsets of 32 bits inside the kernels are laid out for."""
+    for L, ok in ((2 ** 25 - 1, True), (2 ** 25, False)):
+        p = dsv.Problem(1, 1, L, 64, 16, "bf16", [64], 0.1)
+        assert (dsv.lowrank_topk_t_workspace(p) > 0) == ok
+
+
 def test_measurement_aid_rejects_what_has_not_run(dsv):
     lib = dsv.load_library()
     ms = ctypes.c_float(-1.0)
