@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "grid.h"
 #include "stage1_core.h"
 
 namespace dsv {
@@ -132,10 +133,11 @@ __global__ __launch_bounds__((64 * kProfWaves)) void profile_kernel(const T *__r
     extern __shared__ __align__(16) unsigned char lds[];
     ProfShared<G> &sh = *reinterpret_cast<ProfShared<G> *>(lds);
     // consecutive blocks land on consecutive XCDs: each takes a stretch of the (head, queries) pairs, so that its L2 sees one head or two
-    const int nblk = (n + 31) >> 5, per_xcd = gridDim.x >> 3, item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    const int bh = item / nblk;
-    if (bh >= nbh) return;
-    const int q0 = (item - bh * nblk) * 32;
+    const int nblk = (n + 31) >> 5;
+    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, per_xcd = (int64_t)gridDim.x * gridDim.y >> 3;
+    const int64_t item = (block & 7) * per_xcd + (block >> 3);
+    if (item >= (int64_t)nblk * nbh) return;
+    const int bh = (int)(item / nblk), q0 = (int)(item % nblk) * 32;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = lane & 31;                        // the query that a thread searches for
     const int ql = lane & 15, g = lane >> 4;         // in the sweeps: a lane's queries are ql and 16 + ql
@@ -435,7 +437,8 @@ static dsv_status profile_t(const dsv_problem &p, const void *Q, const void *K, 
     constexpr size_t lds = sizeof(ProfShared<threads / 32>);  // above the default of 64 KB
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     DSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&profile_kernel<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL((profile_kernel<T, D>), dim3((((n + 31) / 32) * nbh + 7) / 8 * 8), dim3(threads), lds, st, (const T *)Q, (const T *)K, rows, n, p.L, nbh,
+    const GridXY grid = grid_of((int64_t)((n + 31) / 32) * nbh);
+    hipLaunchKernelGGL((profile_kernel<T, D>), dim3(grid.x, grid.y), dim3(threads), lds, st, (const T *)Q, (const T *)K, rows, n, p.L, nbh,
                        p.scale * 1.4426950408889634f, mass, counts);
     DSV_LAUNCH_CHECK();
     hipLaunchKernelGGL(profile_finish_kernel, dim3(nbh), dim3(256), 0, st, counts, n, p.L, sparsity, ema, alpha);

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "dsv.h"
+#include "grid.h"
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed: %s (line %d)\n", #c, __LINE__); std::exit(1); } } while (0)
 
@@ -111,6 +112,14 @@ int main()
         CHECK(dsv_predictor_loss_workspace(&f32p, 64) > 0 && dsv_predictor_loss_workspace(&f32p, 0) == 0);
         CHECK(dsv_profile_sparsity_workspace(&f32p, 2000) == 0);        // more rows than tokens
     }
+    // grids of the sparsity profiler, up to 65535 heads and every query sampled: within what a launch takes
+    for (int64_t heads : {1, 3, 24, 65535})
+        for (int64_t rows : {1, 32, 33, 513, 4097, 131072, (1 << 25) - 1}) {
+            const int64_t blocks = heads * ((rows + 31) / 32);
+            const dsv::GridXY g = dsv::grid_of(blocks);
+            CHECK(g.x % 8 == 0 && (uint64_t)g.x * 512 < 1ull << 32 && g.y >= 1 && g.y <= 65535);
+            CHECK((int64_t)g.x * g.y >= blocks && (int64_t)g.x * (g.y - 1) < blocks);
+        }
     std::printf("host checks sanitizer run ok\n");
     return 0;
 }

@@ -83,3 +83,15 @@ def test_a_mass_next_to_one_counts_no_key_twice():
     _, counts = dsv.profile_sparsity(p, Q, K, rows, mass=mass)
     least, _ = _counts(Q[0, 0, :n], K[0, 0], p.scale, mass - 8e-6)  # the bound on the cumulative mass above
     assert (counts[0] <= L).all() and (counts[0] >= least).all()
+
+
+# more blocks than one dimension of a grid takes (2^32 work items): the same three heads many times over
+def test_many_heads_and_rows():
+    B, H, L, d = 21845, 3, 4097, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    K = torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16()
+    rows = torch.randperm(L, generator=g, device="cuda").to(torch.int32)
+    want, want_counts = dsv.profile_sparsity(dsv.Problem(1, H, L, d, 16, "bf16", [1] * H, 0.3), K, K, rows)
+    K = K.repeat(B, 1, 1, 1)
+    sparsity, counts = dsv.profile_sparsity(dsv.Problem(B, H, L, d, 16, "bf16", [1] * H, 0.3), K, K, rows)
+    assert (counts.view(B, H, L) == want_counts.view(1, H, L)).all() and (sparsity.view(B, H) == want.view(1, H)).all()

@@ -45,7 +45,7 @@ def test_library_host_code_under_address_and_undefined_sanitizers(tmp_path):
     with ThreadPoolExecutor(max_workers=4) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     main_o = str(tmp_path / "main.o")
-    _run([hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", *san, "-I", os.path.join(ROOT, "include"), "-c",
+    _run([hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", *san, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c",
           "-x", "c++", os.path.join(SAN, "host_checks_main.cpp"), "-o", main_o])
     exe = str(tmp_path / "host_san")
     _run([hipcc, "--offload-arch=gfx950", *san, "-o", exe, main_o, *objs])
