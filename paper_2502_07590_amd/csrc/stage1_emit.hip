@@ -39,6 +39,8 @@ template <int OT> struct EmitShared {
     int2 place[kWaves][32 * OT];
 };
 
+typedef uint16_t __attribute__((may_alias)) halfword_t;  // half of a parked word, which is read whole
+
 // Tiles per batch: full rounds of the block's waves.
 __device__ __forceinline__ int batch_tiles(int ntiles, int most)
 {
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void emit_kernel(const T *__restric
     int buf = 0;
     for (int b0 = 0; b0 < ntiles; b0 += kWaves * batch, buf ^= 1) {
         const int t0 = min(b0 + wave * batch, ntiles), t1 = min(t0 + batch, ntiles);
-        uint16_t *park = reinterpret_cast<uint16_t *>(sh.mask[wave][0]) + 2 * n + half;
+        halfword_t *park = reinterpret_cast<halfword_t *>(sh.mask[wave][0]) + 2 * n + half;
         Frag<T, R> kf_next = walk.load(Kb, t0, half);
         int count = 0, equal = 0;
 #pragma unroll 1
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
     int buf = 0;
     for (int b0 = 0; b0 < ntiles; b0 += kWaves * batch, buf ^= 1) {
         const int t0 = min(b0 + wave * batch, ntiles), t1 = min(t0 + batch, ntiles);
-        uint16_t *park = reinterpret_cast<uint16_t *>(sh.mask[wave][0]) + 2 * n + half;
+        halfword_t *park = reinterpret_cast<halfword_t *>(sh.mask[wave][0]) + 2 * n + half;
         int count[2] = {0, 0};
         walk_queries<T, R>(qc, Qb, walk, kf, tau_b, jcut_b, tile_flag + (int64_t)bh * ntiles, Lq, t0, t1, wave, lane,
                            [&](const int32_t *cuts, int i, const floatx16_t &acc, const float (&tq)[16], bool simple) __attribute__((always_inline)) {
