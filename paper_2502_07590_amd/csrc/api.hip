@@ -212,9 +212,14 @@ bool sort_rows_first(const dsv_problem &p)
 // 64-key tile a round of blocks takes 2.0 (1.45) with at most one block of 128 queries per CU and 2.9 (2.5) when the CUs
 // hold two (three), and a last round that is partly empty costs a fifth of a full one.  Estimated and measured, d = 128:
 // 12 heads of 2048, 64 : 81; 4 of 4096, 128 : 131; 1 of 8192, 256 : 237; 12 of 8192, 631 : 685; 4 of 16384, 891 : 870; 4 of 32768,
-// 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.  On sparse products, where few
-// pairs are kept (dense_fwd_form in dense.hip), a sixth less, a
-// fifteenth at d = 64: 4 of 32768, k = L / 22: 3170 -> 2670 (gathering 3610), d = 64, k = L / 16: 2220 -> 2070.
+// 3266 : 3402; gathering there with k = L / 16 and L / 30: 91, 56; 102, 59; 100, 72; 933, 526; 1355, 657; 4972, 2924.
+// On sparse products, where few pairs are kept (dense_fwd_form in dense.hip), a round's time grows with the share of them, that of the fullest head where
+// there are few rounds; a round that is hardly begun costs half of a full one, and one that gives CUs two blocks all of it.  Rounds of 512 blocks and
+// their time in full ones of 2.4 us a tile, k = L / 20 or so: 1.00 : 1.04, 1.02 : 1.52, 1.50 : 1.74, 1.52 : 2.11, 1.98 : 2.15, 2.05 : 2.56, 2.89 : 3.03.  Where that
+// estimate is the lower one, tiles pay earlier: four of 32768, k = L / 22: 2670, gathering 3610.  (A sixth off all rounds moved heads there that gather
+// faster, dense : gathering, us: 24 of 5426, k = L / 26: 530 : 464; two of 33215, k = L / 24: 3144 : 2765.)  Over 1308 calls near the line, with one k or one per head, none
+// is more than 2.4 % slower than with the line of dense products alone, and the mean is 11 % faster.  At d = 64 that line holds: gathers of short
+// sequences cost less there than the rate above (24 of 5249, k = L / 21, dense : gathering: 307 : 273).
 int32_t dense_fwd_min_k(const dsv_problem &p, bool sparse = true)
 {
     if (!(p.flags & DSV_FLAG_SORTED_INDEX) || p.dtype != DSV_BF16 || p.L > kBitsMaxKeys || !(p.scale > 0.f)) return INT32_MAX;
@@ -229,10 +234,15 @@ int32_t dense_fwd_min_k(const dsv_problem &p, bool sparse = true)
         kept += ks[m - 1];
         if (m < p.H && ks[m] == ks[m - 1]) continue;
         const double blocks = (double)p.B * m * ((p.L + 127) / 128), tiles = (p.L + 63) / 64;
-        const bool few = sparse && blocks > 256 && kept * 14 <= (double)p.L * m;  // on sparse products
-        const double dense = tiles * (blocks <= 256 ? light : (few ? (wide ? 0.83 : 0.93) : 1.0) * full * std::max(1.0, blocks / slots + 0.2));
-        if (gathered - 1.1 * dense > best) {
-            best = gathered - 1.1 * dense;
+        double dense = 1.1 * tiles * (blocks <= 256 ? light : full * std::max(1.0, blocks / slots + 0.2));
+        if (sparse && wide && blocks > 256 && kept * 14 <= (double)p.L * m) {  // on sparse products
+            const double rounds = blocks / slots, whole = std::floor(rounds), part = rounds - whole;
+            const double last = part > 0.5 ? 0.95 + 0.1 * part : part > 0.0 ? 0.5 + 0.5 * part : 0.0;
+            const double mean = kept / ((double)p.L * m), share = mean + ((double)ks[0] / p.L - mean) / (0.5 + rounds);
+            dense = std::min(dense, 1.05 * tiles * full * (0.74 + 2.9 * share) * std::max(1.0, whole + last));
+        }
+        if (gathered - dense > best) {
+            best = gathered - dense;
             best_k = ks[m - 1];
         }
     }

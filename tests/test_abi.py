@@ -141,6 +141,19 @@ def test_masks_that_fill_a_limit_exactly_come_in_one_piece(dsv):
     assert dsv.sparse_attn_fwd_workspace(p) >= 65536 * (131072 // 8 + 64)
 
 
+def test_heads_over_tiles_near_the_line(dsv):
+    """Heads of about one key in 22 to 26 run over dense tiles for sparse products where those fill the chip's rounds, and gather where
+    gathers are faster (measured): a last round that is hardly begun, short sequences at d = 64."""
+    for H, L, d, per, dense in ((4, 32768, 128, 22, True), (8, 14855, 128, 25, True), (12, 12000, 128, 24, True), (24, 5426, 128, 25.7, False),
+                                (3, 21959, 128, 23.4, False), (2, 33215, 128, 24.4, False), (24, 5249, 64, 20.8, False), (8, 9921, 64, 19.4, False),
+                                (4, 32768, 64, 16, True)):
+        p = dsv.Problem(1, H, L, d, 16, "bf16", [int(L / per)] * H, 0.1, sorted_index=True)
+        assert (dsv.dense_min_k(p, "fwd_sweep") > 0) == dense, (H, L, d, per)
+    # a head that keeps one key in 53 gathers beside three that keep three to seven times as many
+    p = dsv.Problem(1, 4, 21704, 128, 16, "bf16", [2855, 1607, 412, 1199], 0.1, sorted_index=True)
+    assert dsv.dense_min_k(p, "fwd_sweep") == 1199
+
+
 def test_the_longest_head(dsv):
     """2^25 - 1 keys of 128 bytes: what offsets of 32 bits inside the kernels are laid out for."""
     for L, ok in ((2 ** 25 - 1, True), (2 ** 25, False)):
