@@ -28,9 +28,9 @@
 
 namespace dsv {
 
-// Waves per block: 16 where the registers allow it (the fragments of two key tiles and a query tile beside the scores).
-// Waves per block: what the registers and, for their key tiles, LDS allow.
-constexpr int kProfWaves = 8;
+// Waves per block (a block per CU): as many as LDS holds key tiles for, and the registers the operands of a tile.  bf16, d = 64, 5 heads of 30134, 893 rows each,
+// 8 : 16 waves: 866 : 564 us (711 before tiles went through LDS), also with the few spills that 16 of them cost.
+template <typename T, int D> constexpr int kProfWaves = D * sizeof(T) <= 128 ? 16 : 8;
 
 constexpr int kMassBits = 39;  // low bits of a counter: mass in units of 2^-38 (at most 1 + rounding); above them the count
                                // (L < 2^25 wherever a head's matrix is below 4 GB)
@@ -125,11 +125,11 @@ __device__ __forceinline__ void cross_bin(ProfShared<G> &sh, unsigned long long 
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__((64 * kProfWaves)) void profile_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+__global__ __launch_bounds__((64 * kProfWaves<T, D>)) void profile_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                                   const int32_t *__restrict__ rows, int n, int L, int nbh,
                                                                   float c2, float target, int32_t *__restrict__ counts)
 {
-    constexpr int WAVES = kProfWaves, THREADS = 64 * WAVES, G = THREADS / 32;
+    constexpr int WAVES = kProfWaves<T, D>, THREADS = 64 * WAVES, G = THREADS / 32;
     extern __shared__ __align__(16) unsigned char lds[];
     ProfShared<G> &sh = *reinterpret_cast<ProfShared<G> *>(lds);
     // consecutive blocks land on consecutive XCDs: each takes a stretch of the (head, queries) pairs, so that its L2 sees one head or two
@@ -153,6 +153,7 @@ __global__ __launch_bounds__((64 * kProfWaves)) void profile_kernel(const T *__r
     // row lie in an order of the row's own, so that neither side meets bank conflicts.  (Rows of 512 bytes do not fit.)
     constexpr int RB = D * (int)sizeof(T), PPR = RB / 16;
     constexpr bool STAGED = RB <= 256;
+    static_assert(!STAGED || WAVES * 32 * RB <= (int)std::min(sizeof(sh.cand), sizeof(sh.hist)), "a tile per wave");
     auto sweep = [&](void *stage, auto f) {
         auto visit = [&](int tile, const Rows16<T, D> (&kf)[2]) __attribute__((always_inline)) {
             floatx4_t acc[2][2];
@@ -433,7 +434,7 @@ static dsv_status profile_t(const dsv_problem &p, const void *Q, const void *K, 
                             int32_t *counts, float *sparsity, float *ema, float alpha, hipStream_t st)
 {
     const int nbh = p.B * p.H;
-    constexpr int threads = 64 * kProfWaves;
+    constexpr int threads = 64 * kProfWaves<T, D>;
     constexpr size_t lds = sizeof(ProfShared<threads / 32>);  // above the default of 64 KB
     static_assert(lds <= 160 * 1024, "LDS of a CU");
     DSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&profile_kernel<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
