@@ -24,7 +24,8 @@ constexpr size_t kBitsBytes = (size_t)2 << 30;  // bits of the matrix: larger pr
 // One wave per row at a time: its entries are OR-ed into a bitmap in LDS, which is then written out and cleared.  col: the rows are
 // key-major lists, whose bits are queries.  Bound by the memory: entries come in 16-byte pieces, eight kilobytes of a row in flight, and no
 // wave waits for another.  L = 32768, four heads, k = 2048 (1.07 GB in, 0.54 out): 289 us, 5.6 TB/s; 408 with a block per row, an entry per lane
-// and load, and three barriers.
+// and load, and three barriers.  Long rows leave a CU few bitmaps, and are faster that way too: the transposition of one head of 262144, k = 8192,
+// 23.3 -> 16.2 ms; of 524288, two waves per CU, k = 1024 : 8192, 46.7 : 84.4 -> 43.5 : 61.5.
 constexpr int kBitsWaves = 4;  // rows per block, at most
 __global__ __launch_bounds__(64 * kBitsWaves) void bits_build_kernel(const int32_t *__restrict__ idx, const int64_t *__restrict__ col, int L, HeadTable tab,
                                                                      int slot0, int row0, int nrows, int pitch, uint32_t *__restrict__ bits)
@@ -49,7 +50,15 @@ __global__ __launch_bounds__(64 * kBitsWaves) void bits_build_kernel(const int32
         const int4 *piece = reinterpret_cast<const int4 *>(row + head);
         const int pieces = (k - head) >> 2;
         constexpr int U = 8;
-        for (int p = lane; p < pieces; p += 64 * U) {
+        if (pieces <= 64) {  // a path of few instructions: fetching those below takes longer than a short row (L = 511, two heads, k = 51: 4.0 -> 3.3 us; 2336, three, 116: 5.7 -> 4.5)
+            if (lane < pieces) {
+                const int4 v = piece[lane];
+                mark(v.x);
+                mark(v.y);
+                mark(v.z);
+                mark(v.w);
+            }
+        } else for (int p = lane; p < pieces; p += 64 * U) {
             int4 v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = p + 64 * u < pieces ? piece[p + 64 * u] : make_int4(-1, -1, -1, -1);
