@@ -51,6 +51,36 @@ __device__ __forceinline__ int batch_tiles(int ntiles, int most)
 typedef int32_t entries4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t entries2_t __attribute__((ext_vector_type(2), aligned(4)));
 
+// One word's entries, base_val + its bits, at entries pos on from `to`; no more of them than fit before `end`.
+__device__ __forceinline__ void write_word(char *to, uint32_t m, int c, int pos, int end, int base_val)
+{
+    if (pos + c > end) {  // entries past the row's capacity are dropped, highest first
+        const int room = max(end - pos, 0);
+        while (__popc(m) > room) m &= ~(0x80000000u >> __clz(m));
+        c = __popc(m);
+    }
+    uint32_t off = (uint32_t)pos * 4u;
+    auto take = [&]() __attribute__((always_inline)) {
+        const int e = base_val + (__ffs(m) - 1);
+        m &= m - 1;
+        return e;
+    };
+    for (; c >= 4; c -= 4, off += 16) {
+        entries4_t e;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = take();
+        *reinterpret_cast<entries4_t *>(to + off) = e;
+    }
+    if (c & 2) {
+        entries2_t e;
+        e[0] = take();
+        e[1] = take();
+        *reinterpret_cast<entries2_t *>(to + off) = e;
+        off += 8;
+    }
+    if (c & 1) *reinterpret_cast<int32_t *>(to + off) = take();
+}
+
 // Expand the parked masks of tiles tile0 .. tile0 + nfilled - 1 for all owners: 64 words at a time, of 2 OT owners.  out, out_last: where the
 // rows or lists of the first and of the last owner tile begin.  Offsets from there have 32 bits: 32 lists of every query are less than 2^32 bytes (64 are not).
 // (Compacting an owner's entries in LDS first and writing them out with consecutive lanes on consecutive
@@ -66,39 +96,36 @@ __device__ __forceinline__ void expand_batch(const EmitShared<OT> &sh, int wave,
     int2 next_at = sh.place[wave][sub];
 #pragma unroll 2
     for (int i = 0; i < 16; ++i) {
-        uint32_t m = next;
+        const uint32_t m = next;
         const int2 at = next_at;
         const int o = STEP * min(i + 1, 15) + sub;
         next = t < nfilled ? sh.mask[wave][t][o] : 0u;
         next_at = sh.place[wave][o];
-        int c = __popc(m);
-        const int pos = at.x + (OT == 1 ? half_scan(c) : row_scan(c)) - c;
-        if (pos + c > at.y) {  // entries past the row's capacity are dropped, highest first
-            const int room = max(at.y - pos, 0);
-            while (__popc(m) > room) m &= ~(0x80000000u >> __clz(m));
-            c = __popc(m);
+        const int c = __popc(m);
+        write_word(reinterpret_cast<char *>(STEP * i < 32 ? out : out_last), m, c, at.x + (OT == 1 ? half_scan(c) : row_scan(c)) - c, at.y, base_val);
+    }
+}
+
+// The same where one round is not full and all there is: a wave takes 16 of the 64 owners and the words that all waves have parked, 16 tiles
+// at a time, in 4 steps for every 16 tiles where its own tiles' words take 16 (few queries to a head, as where they come in groups: 24 heads of 3360 keys, 210
+// groups, k = L / 14: 17.1 -> 10.4 us; a wave per 32 keys that takes all tiles: 13.4).
+constexpr int kFewTiles = 48;
+__device__ __forceinline__ void expand_few(const EmitShared<2> &sh, int wave, int32_t *out, int32_t *out_last, int batch, int ntiles, int lane)
+{
+    static_assert(kFewTiles <= kWaves * EmitShared<2>::TILES, "one round");
+    const uint32_t per = 65536u / (uint32_t)batch + 1u;  // tile / batch for tiles below 64
+    char *to = reinterpret_cast<char *>(wave < 2 ? out : out_last);
+#pragma unroll 1
+    for (int o = 16 * wave + (lane >> 4); o < 16 * wave + 16; o += 4) {
+        int2 at = sh.place[wave][o];
+#pragma unroll 1
+        for (int t = lane & 15; t < ntiles + (lane & 15); t += 16) {  // the same steps for all lanes
+            const int w = (int)((uint32_t)t * per >> 16);
+            const uint32_t m = t < ntiles ? sh.mask[w][t - w * batch][o] : 0u;
+            const int c = __popc(m), sum = row_scan(c);
+            write_word(to, m, c, at.x + sum - c, at.y, t * 32);
+            at.x += __shfl(sum, lane | 15);
         }
-        char *to = reinterpret_cast<char *>(STEP * i < 32 ? out : out_last);
-        uint32_t off = (uint32_t)pos * 4u;
-        auto take = [&]() __attribute__((always_inline)) {
-            const int e = base_val + (__ffs(m) - 1);
-            m &= m - 1;
-            return e;
-        };
-        for (; c >= 4; c -= 4, off += 16) {
-            entries4_t e;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = take();
-            *reinterpret_cast<entries4_t *>(to + off) = e;
-        }
-        if (c & 2) {
-            entries2_t e;
-            e[0] = take();
-            e[1] = take();
-            *reinterpret_cast<entries2_t *>(to + off) = e;
-            off += 8;
-        }
-        if (c & 1) *reinterpret_cast<int32_t *>(to + off) = take();
     }
 }
 
@@ -394,7 +421,10 @@ __global__ __launch_bounds__(64 * kWaves) void count_t_kernel(const T *__restric
     const int half = lane >> 5, j = j0 + (lane & 31);
     const Frag<T, R> kf[2] = {load_frag<T, R>(Kb, j0, L, lane), load_frag<T, R>(Kb, j0 + 32, L, lane)};
     const TileWalk<T, R> walk(Lq, lane);
-    const int per = (ntiles + kWaves * QueryChunk::kTiles - 1) / (kWaves * QueryChunk::kTiles) * QueryChunk::kTiles;
+    constexpr int CHUNKS = kWaves * QueryChunk::kTiles;
+    // few tiles: every wave some, unless the operands of the two key tiles, which each of them reads, are most of the work (24 heads of 3360 keys, 7 tiles,
+    // r = 16: 7.2 -> 4.6 us; of 1536, 3 tiles, r = 64: 4.9, 6.6 by four waves)
+    const int per = R * sizeof(T) != 128 && ntiles <= CHUNKS ? (ntiles + kWaves - 1) / kWaves : (ntiles + CHUNKS - 1) / CHUNKS * QueryChunk::kTiles;
     int taken[2] = {0, 0};
     walk_queries<T, R>(qc, Qb, walk, kf, tau_b, jcut_b, tile_flag + (int64_t)bh * ntiles, Lq, min(wave * per, ntiles), min((wave + 1) * per, ntiles), wave, lane,
                        [&](const int32_t *cuts, int i, const floatx16_t &acc, const float (&tq)[16], bool simple) __attribute__((always_inline)) {
@@ -419,8 +449,9 @@ __global__ __launch_bounds__(64 * kWaves) void count_t_kernel(const T *__restric
 }
 
 // The lists, starting at col[bh, j].
+// (Rows of 128 bytes: a third wave per SIMD for 6 registers less; 24 heads of 2304, 6 query tiles, the selection 129 -> 124 us together with expand_few.)
 template <typename T, int R>
-__global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq, int L, HeadTable tab,
+__global__ __launch_bounds__(64 * kWaves, R * sizeof(T) == 128 ? 3 : 1) void emit_t_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq, int L, HeadTable tab,
                                                              const float *__restrict__ tau_f, const int32_t *__restrict__ jcut,
                                                              const int32_t *__restrict__ tile_flag, const int64_t *__restrict__ col,
                                                              int32_t *__restrict__ idxT)
@@ -483,6 +514,14 @@ __global__ __launch_bounds__(64 * kWaves) void emit_t_kernel(const T *__restrict
 #pragma unroll
         for (int i = 0; i < 2; ++i) sh.count[buf][wave][i][lane] = count[i];
         __syncthreads();  // (two rounds in turn: what is written next was last read before this barrier)
+        if (ntiles <= kFewTiles) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (lane < 32) sh.place[wave][32 * i + lane] = make_int2(at[i], end[i]);
+            __builtin_amdgcn_wave_barrier();
+            expand_few(sh, wave, out, out_last, batch, ntiles, lane);
+            return;
+        }
         place_batch<2>(sh, buf, wave, lane, at, end);
         expand_batch<2>(sh, wave, out, out_last, t0, t1 - t0, lane);
     }

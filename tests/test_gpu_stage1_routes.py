@@ -111,6 +111,16 @@ def test_emission_in_batches(dtype, H, L, ks, r):
     _check(dsv.Problem(1, H, L, 64, r, dtype, ks, 0.1), Q, K, Wq, Wk)
 
 
+# lists of up to 48 query tiles are written by owners, 16 tiles at a time, and of up to 32 counted by all waves: one tile, a few, 15 to 17, 32 and 33, 48 and 49
+@pytest.mark.parametrize("dtype,r", [("bf16", 16), ("bf16", 64), ("f32", 32)])
+@pytest.mark.parametrize("L", [31, 97, 160, 480, 512, 513, 1024, 1025, 1536, 1537])
+@pytest.mark.parametrize("ties", [False, True])
+def test_lists_of_few_queries(dtype, r, L, ties):
+    ks = [1, L, max(1, L // 3)]
+    Q, K, Wq, Wk = _inputs(3, L, 64, r, dtype, ties, L + r)
+    _check(dsv.Problem(1, 3, L, 64, r, dtype, ks, 0.1), Q, K, Wq, Wk)
+
+
 def test_smooth_inputs_keep_the_windowed_search():
     """Keys that vary slowly along the token grid, whose width the sample's stride divides: the scrambled sample brackets
     the thresholds, and the result is the radix search's."""
