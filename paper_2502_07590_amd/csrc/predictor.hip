@@ -15,7 +15,7 @@
 //
 // Both kinds of contraction run on the matrix cores: the Gram matrix in the storage type with fp32 sums over at most
 // 512 tokens (v_mfma_f32_32x32x16_bf16 / 32x32x2_f32), everything behind it in fp64 (v_mfma_f64_16x16x4_f64).
-// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 138 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 44, accum 18; 160 with
+// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 136 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 41, accum 18; 160 with
 // the weights' products and the loss in kernels and loops of their own, all of M in the rows' forms and half the blocks in accum.
 // L = 3000, one head, 250 rows, d = 64: 66 -> 35 us.
 #include <algorithm>
@@ -171,7 +171,9 @@ __global__ __launch_bounds__(256) void gram_weights2_kernel(const T *__restrict_
 // One wave per 16 sampled rows; U = Q_s M, Q_lr = Q_s Wq, V = Q_s T1 and W = Q_lr T2 as fp64 matrix products.  Writes, per
 // row: qlr [R], G [R] (= dAhat_i Klr), the coefficients ca_i, ch_i and the loss terms {1 - cos_i, sum_j (ahat_ij - a_ij)^2}.
 //   ca_i = -0.95 / (n |ahat_i| |a_i|) - 0.1 / (n L),   ch_i = 0.95 <ahat_i, a_i> / (n |ahat_i|^3 |a_i|) + 0.1 / (n L)
-// Bound by the fp64 multiplications, 3 D^2 / 4 per row and more (64 clocks per 16 x 16 x 4 product).
+// Bound by the fp64 multiplications, 3 D^2 / 4 per row and more (64 clocks per 16 x 16 x 4 product); with few rows, by the way to M, T1 and Wq.  A lane group
+// takes channels side by side: in steps of four rows of these every load has an address of its own (six heads, 57 rows each, R = 64: 64 -> 55 us; R = 16, 8192 rows:
+// 44 -> 41).
 template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict__ Q, const T *__restrict__ Wq, const T *__restrict__ Wk,
                                                              const int32_t *__restrict__ rows, int n, int L, int H,
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
                                                              double *__restrict__ g_out, double2 *__restrict__ coef,
                                                              double2 *__restrict__ terms)
 {
-    constexpr int CPL = D / 4, RPL = R / 4, NT = R / 16;   // contraction steps: lane group g takes channel 4 s + g
+    constexpr int CPL = D / 4, RPL = R / 4, NT = R / 16;   // contraction steps: lane group g takes CPL / 2 channels in a row of either half
     constexpr bool OWN_T2 = R < 64;                        // (at R = 64 it would take the LDS of a second block)
     __shared__ float xq_all[4][16][D + 1];
     __shared__ double ql_all[4][16][R + 1];
@@ -217,25 +219,29 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
     float (*xq)[D + 1] = xq_all[wave];
     double (*ql)[R + 1] = ql_all[wave];
     const int row = min(max(rows[min(i0 + r16, n - 1)], 0), L - 1);
-    const T *qrow = Q + (bh * L + row) * D + g * CPL;
+    const int c0 = g * (CPL / 2);
+    auto channel = [&](int s) __attribute__((always_inline)) { return c0 + (s < CPL / 2 ? s : D / 2 + s - CPL / 2); };
+    const T *qrow = Q + (bh * L + row) * D;
+    double q[CPL];
 #pragma unroll
-    for (int s = 0; s < CPL; ++s) xq[r16][g * CPL + s] = to_f32<T>(qrow[s]);
+    for (int s = 0; s < CPL; ++s) {
+        const float x = to_f32<T>(qrow[channel(s)]);
+        xq[r16][channel(s)] = x;
+        q[s] = (double)x;
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    double q[CPL];
-#pragma unroll
-    for (int s = 0; s < CPL; ++s) q[s] = (double)xq[r16][4 * s + g];
     double aa[4] = {0.0, 0.0, 0.0, 0.0}, ah[4] = {0.0, 0.0, 0.0, 0.0}, hh[4] = {0.0, 0.0, 0.0, 0.0};
     // |a|^2 = q^T M q by four blocks of D / 2 x D / 2 channels: the one above the diagonal twice, the one below it not at all.  (By blocks of 16 the
-    // products are fewer still, but those loops come out slower: 8192 rows of six heads, D = 128, R = 16: 44 us, by blocks of 16 39 with loads where they
+    // products are fewer still, but those loops come out slower, with four-row steps of channels: 8192 rows of six heads, D = 128, R = 16: 44 us, by blocks of 16 39 with loads where they
     // are used -- and 61 for 24 where few rows leave a wave alone with them -- or 68 with a column's loads ahead of its products.)
-    const double *col = Mh + g * D + r16;
+    const double *col = Mh + c0 * D + r16;  // rows s and D / 2 + s from there
 #pragma unroll 1
     for (int nt = 0; nt < D / 32; ++nt) {
         doublex4_t u = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int s = 0; s < CPL / 2; ++s) u = mfma_f64(q[s], col[4 * s * D + 16 * nt], u);
+        for (int s = 0; s < CPL / 2; ++s) u = mfma_f64(q[s], col[s * D + 16 * nt], u);
 #pragma unroll
         for (int v = 0; v < 4; ++v) aa[v] += u[v] * (double)xq[4 * v + g][16 * nt + r16];
     }
@@ -244,8 +250,8 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
         doublex4_t u = {0.0, 0.0, 0.0, 0.0}, w = u;
 #pragma unroll
         for (int s = 0; s < CPL / 2; ++s) {
-            u = mfma_f64(q[s], col[4 * s * D + 16 * nt], u);
-            w = mfma_f64(q[s + CPL / 2], col[4 * (s + CPL / 2) * D + 16 * nt], w);
+            u = mfma_f64(q[s], col[s * D + 16 * nt], u);
+            w = mfma_f64(q[s + CPL / 2], col[(D / 2 + s) * D + 16 * nt], w);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) aa[v] += (2.0 * u[v] + w[v]) * (double)xq[4 * v + g][16 * nt + r16];
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
         b[nt] = a[nt];
 #pragma unroll
         for (int s = 0; s < CPL; ++s) {
-            const int e = (4 * s + g) * R + 16 * nt + r16;
+            const int e = channel(s) * R + 16 * nt + r16;
             a[nt] = mfma_f64(q[s], (double)to_f32<T>(Wh[e]), a[nt]);
             b[nt] = mfma_f64(q[s], T1h[e], b[nt]);
         }
