@@ -28,9 +28,9 @@
 
 namespace dsv {
 
-// Waves per block (a block per CU): as many as LDS holds key tiles for, and the registers the operands of a tile.  bf16, d = 64, 5 heads of 30134, 893 rows each,
-// 8 : 16 waves: 866 : 564 us (711 before tiles went through LDS), also with the few spills that 16 of them cost.
-template <typename T, int D> constexpr int kProfWaves = D * sizeof(T) <= 128 ? 16 : 8;
+// Waves per block (a block per CU): as many as LDS holds key tiles for, and the registers the operands of a tile.
+constexpr int kProfWaves = 8;
+template <typename T, int D> constexpr int kProfWavesMost = D * sizeof(T) <= 128 ? 16 : kProfWaves;
 
 constexpr int kMassBits = 39;  // low bits of a counter: mass in units of 2^-38 (at most 1 + rounding); above them the count
                                // (L < 2^25 wherever a head's matrix is below 4 GB)
@@ -124,12 +124,12 @@ __device__ __forceinline__ void cross_bin(ProfShared<G> &sh, unsigned long long 
     __syncthreads();
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__((64 * kProfWaves<T, D>)) void profile_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+template <typename T, int D, int WAVES>
+__global__ __launch_bounds__((64 * WAVES)) void profile_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                                   const int32_t *__restrict__ rows, int n, int L, int nbh,
                                                                   float c2, float target, int32_t *__restrict__ counts)
 {
-    constexpr int WAVES = kProfWaves<T, D>, THREADS = 64 * WAVES, G = THREADS / 32;
+    constexpr int THREADS = 64 * WAVES, G = THREADS / 32;
     extern __shared__ __align__(16) unsigned char lds[];
     ProfShared<G> &sh = *reinterpret_cast<ProfShared<G> *>(lds);
     // consecutive blocks land on consecutive XCDs: each takes a stretch of the (head, queries) pairs, so that its L2 sees one head or two
@@ -429,19 +429,32 @@ __global__ __launch_bounds__(256) void profile_finish_kernel(const int32_t *__re
 }
 
 // ------------------------------------------------------------------------------------ host
+template <typename T, int D, int WAVES>
+static dsv_status profile_waves(const dsv_problem &p, const void *Q, const void *K, const int32_t *rows, int n, float mass,
+                                int32_t *counts, hipStream_t st)
+{
+    const int nbh = p.B * p.H;
+    constexpr int threads = 64 * WAVES;
+    constexpr size_t lds = sizeof(ProfShared<threads / 32>);  // above the default of 64 KB
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    DSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&profile_kernel<T, D, WAVES>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    const GridXY grid = grid_of((int64_t)((n + 31) / 32) * nbh);
+    hipLaunchKernelGGL((profile_kernel<T, D, WAVES>), dim3(grid.x, grid.y), dim3(threads), lds, st, (const T *)Q, (const T *)K, rows, n, p.L, nbh,
+                       p.scale * 1.4426950408889634f, mass, counts);
+    DSV_LAUNCH_CHECK();
+    return DSV_OK;
+}
+
+// Sixteen waves spill a few registers: they pay where each has a few tiles.  bf16, d = 64, us before tiles went through LDS, with 8, with 16 waves: four heads of 800,
+// 60 rows each: 30.1, 25.6, 28.4; of 1200, 100 rows: 36.0, 32.5, 32.8; of 2000, 160: 49.9, 44.7, 41.6; five of 30134, 893: 711, 866, 564.
 template <typename T, int D>
 static dsv_status profile_t(const dsv_problem &p, const void *Q, const void *K, const int32_t *rows, int n, float mass,
                             int32_t *counts, float *sparsity, float *ema, float alpha, hipStream_t st)
 {
     const int nbh = p.B * p.H;
-    constexpr int threads = 64 * kProfWaves<T, D>;
-    constexpr size_t lds = sizeof(ProfShared<threads / 32>);  // above the default of 64 KB
-    static_assert(lds <= 160 * 1024, "LDS of a CU");
-    DSV_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&profile_kernel<T, D>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const GridXY grid = grid_of((int64_t)((n + 31) / 32) * nbh);
-    hipLaunchKernelGGL((profile_kernel<T, D>), dim3(grid.x, grid.y), dim3(threads), lds, st, (const T *)Q, (const T *)K, rows, n, p.L, nbh,
-                       p.scale * 1.4426950408889634f, mass, counts);
-    DSV_LAUNCH_CHECK();
+    const dsv_status rc = p.L > 1280 ? profile_waves<T, D, kProfWavesMost<T, D>>(p, Q, K, rows, n, mass, counts, st)
+                                     : profile_waves<T, D, kProfWaves>(p, Q, K, rows, n, mass, counts, st);
+    if (rc != DSV_OK) return rc;
     hipLaunchKernelGGL(profile_finish_kernel, dim3(nbh), dim3(256), 0, st, counts, n, p.L, sparsity, ema, alpha);
     DSV_LAUNCH_CHECK();
     return DSV_OK;
