@@ -46,16 +46,27 @@ def test_dense_and_gathered_heads(d, B, L, near):
     _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 61, device="cuda"), torch.arange(L - 70, L, device="cuda")]))
 
 
-# the form on sparse products, in blocks of 128 queries (24 heads of 2111: 408 of them) and of 256 (24 of 2304: 216), one key in 16 on
+def _queries_per_block(p, rows):
+    """Of the launch that takes `rows` rows of all heads over tiles: 128 or 256 on sparse products, 0 on dense ones."""
+    heads = [k for k in p.k_per_head if k >= dsv.dense_min_k(p, "fwd_sweep")] if dsv.dense_min_k(p, "fwd_sweep") else []
+    if sum(heads) * 14 > p.L * len(heads) or len(heads) * -(-rows // 128) <= 256:
+        return 0
+    blocks = len(heads) * -(-rows // 256)
+    return 256 if blocks * 100 >= -(-blocks // 256) * 256 * 85 else 128
+
+
+# the form on sparse products, in blocks of 128 queries and of 256 (one a CU, nearly all of them), the last one whole and not, one key in 16 on
 # the mean, so that groups with a third pair come; rows of neighbours leave whole tiles out and crowd others
-@pytest.mark.parametrize("d,H,L,near", [(128, 24, 2111, False), (128, 24, 2304, False), (128, 24, 2304, True), (128, 33, 1985, False),
-                                        (128, 26, 2337, True), (64, 24, 4001, False), (64, 16, 4096, False), (64, 24, 4127, True)])
-def test_heads_that_keep_few_pairs_of_a_tile(d, H, L, near):
+@pytest.mark.parametrize("d,H,L,near,block", [(128, 24, 2111, False, 128), (128, 24, 2304, False, 128), (128, 24, 2304, True, 128), (128, 33, 1985, False, 256),
+                                              (128, 26, 2337, True, 128), (64, 24, 4001, False, 128), (64, 16, 4096, False, 256), (64, 24, 4127, True, 128),
+                                              (128, 25, 2337, False, 256), (128, 25, 2337, True, 256), (128, 25, 2559, False, 256), (64, 16, 4001, False, 256),
+                                              (64, 16, 4001, True, 256)])
+def test_heads_that_keep_few_pairs_of_a_tile(d, H, L, near, block):
     g = torch.Generator(device="cuda").manual_seed(3 * L + d)
     ks = [L // 16] * (H - 3) + [L // 9, L // 20, L // 13]
     Q, K, V = (3 * torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
     p = dsv.Problem(1, H, L, d, 16, "bf16", ks, d ** -0.5, sorted_index=True)
-    assert 0 < dsv.dense_min_k(p, "fwd_sweep") <= L // 16
+    assert 0 < dsv.dense_min_k(p, "fwd_sweep") <= L // 16 and _queries_per_block(p, L) == block
     heads = [_rows(L, k, g, near) for k in ks]
     _check(p, Q, K, V, heads, torch.cat([torch.arange(0, L, 97, device="cuda"), torch.arange(L - 40, L, device="cuda")]))
 
@@ -75,12 +86,20 @@ def test_a_call_without_scratch_gathers_where_gathers_need_none():
     assert ((O.float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs() + 2.0 ** -9).all() and torch.allclose(lse, want_lse, atol=1e-4)
 
 
-def test_mask_in_pieces():
-    L, k = 98309, 4000
+# a mask in as many rows at a time as the scratch holds: all of them beside the partial results of d = 128; pieces at d = 64, the last one no whole block,
+# on dense and on sparse products
+@pytest.mark.parametrize("d,L,k,pieces,block", [(128, 98309, 6000, 1, 128), (64, 98309, 20000, 2, 0), (64, 150001, 9375, 3, 128)])
+def test_mask_in_pieces(d, L, k, pieces, block):
     g = torch.Generator(device="cuda").manual_seed(7)
-    Q, K, V = (torch.randn(1, 1, L, 128, generator=g, device="cuda").bfloat16() for _ in range(3))
-    p = dsv.Problem(1, 1, L, 128, 16, "bf16", [k], 128 ** -0.5, sorted_index=True)
-    _check(p, Q, K, V, [_rows(L, k, g)], torch.randint(0, L, (200,), generator=g, device="cuda"))
+    Q, K, V = (torch.randn(1, 1, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
+    p = dsv.Problem(1, 1, L, d, 16, "bf16", [k], d ** -0.5, sorted_index=True)
+    words = -(-L // 512) * 16  # of a row; neither length leaves space between rows
+    assert words % 256
+    rows = min(dsv.sparse_attn_fwd_workspace(p) // (4 * words) // 128 * 128, L)
+    assert dsv.dense_min_k(p, "fwd_sweep") > 0 and -(-L // rows) == pieces
+    assert _queries_per_block(p, L - (pieces - 1) * rows) == block  # the last piece
+    ends = [torch.arange(max(r - 20, 0), min(r + 20, L), device="cuda") for r in range(0, L, rows)] + [torch.arange(L - 20, L, device="cuda")]
+    _check(p, Q, K, V, [_rows(L, k, g)], torch.cat(ends + [torch.randint(0, L, (100,), generator=g, device="cuda")]))
 
 
 # one launch whose masks hold more than 2^32 words: the rows past that, the last ones of the second head
@@ -103,12 +122,13 @@ def test_rows_that_are_not_finite(d, bad):
     _rows_that_are_not_finite(d, bad, 12, 2113, 400)
 
 
-@pytest.mark.parametrize("d,L,bad", [(64, 4096, float("nan")), (128, 2304, float("inf"))])
-def test_rows_that_are_not_finite_on_sparse_products(d, L, bad):
-    _rows_that_are_not_finite(d, bad, 24, L, L // 15)
+@pytest.mark.parametrize("d,H,L,bad,block", [(64, 24, 4096, float("nan"), 128), (128, 24, 2304, float("inf"), 128), (64, 16, 4001, float("inf"), 256),
+                                             (128, 25, 2437, float("nan"), 256)])
+def test_rows_that_are_not_finite_on_sparse_products(d, H, L, bad, block):
+    _rows_that_are_not_finite(d, bad, H, L, L // 15, block)
 
 
-def _rows_that_are_not_finite(d, bad, H, L, k):
+def _rows_that_are_not_finite(d, bad, H, L, k, block=0):
     g = torch.Generator(device="cuda").manual_seed(d)
     Q, K, V = (torch.randn(1, H, L, d, generator=g, device="cuda").bfloat16() for _ in range(3))
     V[0, :, 700] = bad
@@ -116,7 +136,7 @@ def _rows_that_are_not_finite(d, bad, H, L, k):
     rows = _rows(L, k, g, near=True)
     idx = torch.cat([rows.reshape(-1)] * H)
     p = dsv.Problem(1, H, L, d, 16, "bf16", [k] * H, d ** -0.5, sorted_index=True)
-    assert dsv.sparse_attn_fwd_workspace(p) > 0
+    assert dsv.sparse_attn_fwd_workspace(p) > 0 and _queries_per_block(p, L) == block
     O, _ = dsv.sparse_attn_fwd(p, Q, K, V, idx)
     V[0, :, 700], K[0, :, 1500] = 0, 0
     keeps = ((rows == 700) | (rows == 1500)).any(1)

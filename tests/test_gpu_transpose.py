@@ -46,8 +46,9 @@ def test_transpose_is_a_stable_sort_of_the_pairs(L, ks, ascending):
         off += rows.numel()
 
 
-# bitmaps of four, three and one row per block (up to 131040 keys, up to 174592, above); rows that begin at no multiple of 16 bytes
-@pytest.mark.parametrize("L,k", [(8192, 61), (16384, 1023), (131072, 171), (150001, 198), (300007, 391)])
+# bitmaps of four, three, two rows and one per block (up to 130560 keys, up to 174592, up to 261632, above); rows that begin at no multiple of 16 bytes,
+# of up to 256 entries and more
+@pytest.mark.parametrize("L,k", [(8192, 61), (16384, 1023), (131072, 171), (150001, 198), (200003, 263), (200003, 1031), (300007, 391)])
 def test_bitmaps_of_rows(L, k):
     rows = _rows(L, k, L, True)
     p = dsv.Problem(1, 1, L, 64, 16, "bf16", [k], 0.1)
