@@ -309,9 +309,9 @@ __global__ __launch_bounds__(256) void predictor_rows_kernel(const T *__restrict
 
 // ---- sums over the sampled rows ---------------------------------------------------------------------------
 // dWq = Q_s^T G [D, R],  N1 = Q_s^T (ca Q_lr) [D, R],  N2 = Q_lr^T (ch Q_lr) [R, R] and the two loss terms: every block takes kAccRows sampled rows
-// (64 Q rows at a time in LDS) and writes its partial sums; predictor_sum_kernel adds them in block order (deterministic).
+// (their Q rows in LDS) and writes its partial sums; predictor_sum_kernel adds them in block order (deterministic).
 // Waves take the 16-channel row tiles of dWq and N1 (and of N2) in turn.
-constexpr int kAccRows = 64;
+constexpr int kAccRows = 64;  // a lane per row for the loss terms
 template <typename T, int D, int R>
 __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restrict__ Q, const int32_t *__restrict__ rows,
                                                               int n, int L, const double *__restrict__ qlr,
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restric
                                                               const double2 *__restrict__ terms, double *__restrict__ part)
 {
     constexpr int NT = R / 16, CT = D / 64;                 // column tiles; row tiles of dWq and N1 per wave
-    __shared__ float xq[64][D + 1];
+    __shared__ float xq[kAccRows][D + 1];
     const int64_t bh = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r16 = lane & 15, g = lane >> 4;
@@ -331,54 +331,51 @@ __global__ __launch_bounds__(256) void predictor_accum_kernel(const T *__restric
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) { s1[ct][nt] = zero; s2[ct][nt] = zero; }
     }
-    const int i1 = min((int)(blockIdx.x + 1) * kAccRows, n);
-    for (int i0 = blockIdx.x * kAccRows; i0 < i1; i0 += 64) {
-        __syncthreads();
-        constexpr int EPP = 16 / (int)sizeof(T), PPR = D / EPP;  // elements per 16-byte piece, pieces per row
+    const int i0 = blockIdx.x * kAccRows, i1 = min(i0 + kAccRows, n);
+    constexpr int EPP = 16 / (int)sizeof(T), PPR = D / EPP;  // elements per 16-byte piece, pieces per row
 #pragma unroll
-        for (int u = 0; u < 64 * PPR / 256; ++u) {
-            const int e = threadIdx.x + 256 * u;
-            const int i = e / PPR, c = e % PPR * EPP;
-            const int row = min(max(rows[min(i0 + i, i1 - 1)], 0), L - 1);
-            const RowChunk<T, EPP> x = load_chunk<T, EPP>(Q + (bh * L + row) * D + c);  // rows past the end meet zero weights
+    for (int u = 0; u < kAccRows * PPR / 256; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        const int i = e / PPR, c = e % PPR * EPP;
+        const int row = min(max(rows[min(i0 + i, i1 - 1)], 0), L - 1);
+        const RowChunk<T, EPP> x = load_chunk<T, EPP>(Q + (bh * L + row) * D + c);  // rows past the end meet zero weights
 #pragma unroll
-            for (int m = 0; m < EPP; ++m) {
-                if constexpr (sizeof(T) == 4) xq[i][c + m] = __uint_as_float(x.w[m]);
-                else xq[i][c + m] = __uint_as_float(m & 1 ? x.w[m / 2] & 0xFFFF0000u : x.w[m / 2] << 16);
-            }
+        for (int m = 0; m < EPP; ++m) {
+            if constexpr (sizeof(T) == 4) xq[i][c + m] = __uint_as_float(x.w[m]);
+            else xq[i][c + m] = __uint_as_float(m & 1 ? x.w[m / 2] & 0xFFFF0000u : x.w[m / 2] << 16);
         }
-        __syncthreads();
+    }
+    __syncthreads();
 #pragma unroll 4
-        for (int s = 0; s < 16; ++s) {
-            const int i = i0 + 4 * s + g;
-            const bool ok = i < i1;
-            const int64_t r = bh * n + (ok ? i : i1 - 1);
-            const double2 cf = ok ? coef[r] : make_double2(0.0, 0.0);
-            double vg[NT], vl[NT], x[CT];
+    for (int s = 0; s < kAccRows / 4; ++s) {
+        const int i = i0 + 4 * s + g;
+        const bool ok = i < i1;
+        const int64_t r = bh * n + (ok ? i : i1 - 1);
+        const double2 cf = ok ? coef[r] : make_double2(0.0, 0.0);
+        double vg[NT], vl[NT], x[CT];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                vg[nt] = ok ? gm[r * R + 16 * nt + r16] : 0.0;
-                vl[nt] = qlr[r * R + 16 * nt + r16];
+        for (int nt = 0; nt < NT; ++nt) {
+            vg[nt] = ok ? gm[r * R + 16 * nt + r16] : 0.0;
+            vl[nt] = qlr[r * R + 16 * nt + r16];
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) x[ct] = (double)xq[4 * s + g][16 * (wave + 4 * ct) + r16];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                s1[ct][nt] = mfma_f64(x[ct], vg[nt], s1[ct][nt]);
+                s2[ct][nt] = mfma_f64(x[ct], ok ? cf.x * vl[nt] : 0.0, s2[ct][nt]);
             }
+        if (wave < NT) {  // row tile `wave` of N2
+            const double xl = qlr[r * R + 16 * wave + r16];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) x[ct] = (double)xq[4 * s + g][16 * (wave + 4 * ct) + r16];
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    s1[ct][nt] = mfma_f64(x[ct], vg[nt], s1[ct][nt]);
-                    s2[ct][nt] = mfma_f64(x[ct], ok ? cf.x * vl[nt] : 0.0, s2[ct][nt]);
-                }
-            if (wave < NT) {  // row tile `wave` of N2
-                const double xl = qlr[r * R + 16 * wave + r16];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) s3[nt] = mfma_f64(xl, ok ? cf.y * vl[nt] : 0.0, s3[nt]);
-            }
+            for (int nt = 0; nt < NT; ++nt) s3[nt] = mfma_f64(xl, ok ? cf.y * vl[nt] : 0.0, s3[nt]);
         }
     }
     double *o = part + (bh * gridDim.x + blockIdx.x) * (2 * D * R + R * R + 2);
     if (wave == 0) {  // the loss terms of the block's rows
-        const int i = blockIdx.x * kAccRows + lane;
+        const int i = i0 + lane;
         double2 x = i < i1 ? terms[bh * n + i] : make_double2(0.0, 0.0);
         for (int d = 32; d; d >>= 1) {
             x.x += __shfl_xor(x.x, d);
