@@ -32,11 +32,11 @@ VALU_LANE_OPS_PER_S = 256 * 64 * 2.4e9   # 256 CUs x 64 fp32 lanes x 2.4 GHz, on
 # (FETCH_SIZE reads 0.5 GiB for it: factor 2.0; WRITE_SIZE reads 1 GiB: factor 1.0), and the L2 hit rate from
 # TCC_HIT_sum / (TCC_HIT_sum + TCC_MISS_sum).  Source: profiles/config2_pmc_counters.md.  The figures belong to ONE
 # build of the kernels: they are reported only while the library still names that version.
-PMC_LIBRARY_VERSION = "dsv 0.8 (gfx950)"
+PMC_LIBRARY_VERSION = "dsv 0.9 (gfx950)"
 PMC_CONFIG2 = {
-    "sparse_attn_fwd": {"fetch_kib": 22152170, "write_kib": 12835465, "l2_hit_rate": 0.8712},  # mask and dense tiles
-    "sparse_attn_bwd_dq": {"fetch_kib": 28284599, "write_kib": 25632575, "l2_hit_rate": 0.9002},  # mask and dense tiles
-    "sparse_attn_bwd_dkdv": {"fetch_kib": 33718040, "write_kib": 12582915, "l2_hit_rate": 0.9739},
+    "sparse_attn_fwd": {"fetch_kib": 22224569, "write_kib": 12835475, "l2_hit_rate": 0.8719},  # mask and dense tiles
+    "sparse_attn_bwd_dq": {"fetch_kib": 28335641, "write_kib": 25632444, "l2_hit_rate": 0.9004},  # mask and dense tiles
+    "sparse_attn_bwd_dkdv": {"fetch_kib": 33518529, "write_kib": 12582914, "l2_hit_rate": 0.9738},
 }
 # the sweep inside each stage-2 call, by gathers or over dense tiles (what the roofline object is about)
 SWEEP_OF_CALL = {"sparse_attn_fwd": "fwd_sweep", "sparse_attn_bwd_dq": "dq_sweep", "sparse_attn_bwd_dkdv": "dkdv_sweep"}

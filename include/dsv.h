@@ -124,8 +124,8 @@ DSV_API dsv_status dsv_lowrank_topk_t(const dsv_problem *p, const void *Q, const
  * O is written in `dtype`, lse in float.  Workspace: none without DSV_FLAG_SORTED_INDEX (the query
  * returns 0 and a null workspace is accepted); with it, the segment pointers and the per-range
  * partial results, or none where the problem is too small for ranges to pay; heads that keep enough of their keys (bf16,
- * scale > 0) run over dense tiles and need a bit per (query, key), up to 1 GB at a time, in the same place.  Heads near
- * that line gather where the workspace is enough for gathers only, or null where those need none. */
+ * scale > 0) run over dense tiles and need a bit per (query, key): the query asks for up to 1 GB of them, in the same place, and a call
+ * takes as many rows at a time as fit its workspace.  Heads near that line gather where the workspace is enough for gathers only, or null where those need none. */
 DSV_API size_t dsv_sparse_attn_fwd_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_fwd(const dsv_problem *p, const void *Q, const void *K, const void *V,
                                const int32_t *idx, void *O, float *lse,
@@ -182,14 +182,14 @@ DSV_API dsv_status dsv_sparse_attn_bwd_t(const dsv_problem *p, const void *Q, co
  *   order inside the rows of idx is, and the output is the same from run to run; for rows as stage 1 writes them
  *   it equals dsv_lowrank_topk_t's idx_t.  Workspace: int32 counters per (b, h, key) and per (b, h, chunk of
  *   query rows, key) -- chunks of 1024 rows, or at most 256 of them -- and, unless the rows keep very few of the keys, a
- *   bit per (query, key) of up to 2 GB of (b, h)s at a time.
+ *   bit per (query, key), 2 GB of them at a time.
  *
  * dsv_sparse_attn_bwd_dkdv: key-major sweep over idx_t.  Writes dK, dV [B, H, L, d] (`dtype`);
  *   keys with an empty list get zeros.
  *
  * Workspace of dq and dkdv: none without DSV_FLAG_SORTED_INDEX (query returns 0, null accepted);
  * with it, segment pointers and per-range partial sums, or none for problems too small for either step to be blocked; heads that
- * keep enough of their keys (bf16, scale > 1e-30) run over dense tiles and need a bit per (query, key), 256 MB at a time at most, and the partial sums.
+ * keep enough of their keys (bf16, scale > 1e-30) run over dense tiles and need a bit per (query, key), 256 MB of them at a time at most, and the partial sums.
  * Where gathers alone would need none, a null or smaller workspace is accepted still, and all heads gather. */
 DSV_API size_t dsv_sparse_attn_bwd_dq_workspace(const dsv_problem *p);
 DSV_API dsv_status dsv_sparse_attn_bwd_dq(const dsv_problem *p, const void *Q, const void *K, const void *V,

@@ -503,7 +503,7 @@ static void *noalloc_scratch(dsv_status *err)
 
 extern "C" {
 
-const char *dsv_version(void) { return "dsv 0.8 (gfx950)"; }
+const char *dsv_version(void) { return "dsv 0.9 (gfx950)"; }
 
 const char *dsv_status_string(dsv_status s)
 {

@@ -420,7 +420,8 @@ size_t dense_row_bytes(int L) { return (size_t)bits_pitch(L) * 4; }
 // count more.  ms, dense : sparse with 128 : with 256 queries, four heads of 32768, one key in 22: 3.17 : 2.78 : 2.67, in 16: 3.28 : 3.01 :
 // 2.90, in 12: 3.43 : 3.43 : 3.33, in 10: 3.51 : 3.72 : 3.64; d = 64, in 16: 2.16 : 2.04 : 1.98, in 12: 2.29 : 2.35 : 2.29; three heads of 9000, one in 13: 0.288 :
 // 0.298 : 0.386.  Blocks of 256 (one per CU) where they leave their last round nearly full: four heads of 20280, one in 16, 1.25 rounds: 1.51 :
-// 1.43 : 1.68; one head of 131072, two rounds: 13.8 : 12.8 : 12.0.
+// 1.43 : 1.68; one head of 131072, two rounds: 13.8 : 12.8 : 12.0.  Where heads differ their mean decides: of 31 mixes none was slower than on dense products
+// alone (eight heads of 32768, one key in 4 in one of them and in 26 in seven: 6.39 -> 5.85).
 static int dense_fwd_form(int L, int heads, int rows, int64_t kept)
 {
     if (kept * 14 > (int64_t)L * heads || (int64_t)heads * ((rows + 127) / 128) <= 256) return 0;

@@ -23,10 +23,11 @@ namespace dsv {
 // writing them as they appear makes every store a partial cache line (measured: 5x write
 // amplification), and appending them one by one to a per-owner buffer costs a serial loop per tile
 // that runs as long as the fullest of the 32 owners needs.  Instead a wave parks each tile's 32-bit
-// mask per owner in LDS and, every batch of up to kBatch tiles, expands owner by owner: the 32 lanes of a half-wave
-// take the owner's 32 parked words (one tile each), a prefix sum of their popcounts gives every lane its
+// mask per owner in LDS and, every batch of tiles, expands owner by owner: lanes side by side take the owner's
+// parked words (one tile each), a prefix sum of their popcounts gives every lane its
 // place in the owner's row, and the lanes write their entries side by side -- one store instruction
-// covers a contiguous stretch of the row.  Two owners are expanded at a time (one per half-wave).
+// covers a contiguous stretch of the row.  Query-major a wave has 32 owners and up to 32 tiles a batch, and expands two owners at a time (one
+// per half-wave); key-major it has 64 and up to 16, and expands four (one per 16 lanes).
 constexpr int kBatch = 32;  // words of an owner's batch in the block form below (= lanes of a half-wave)
 constexpr int kWaves = 4;   // waves of a block, a batch each in turn
 
