@@ -134,10 +134,10 @@ __global__ __launch_bounds__((64 * WAVES)) void profile_kernel(const T *__restri
     ProfShared<G> &sh = *reinterpret_cast<ProfShared<G> *>(lds);
     // consecutive blocks land on consecutive XCDs: each takes a stretch of the (head, queries) pairs, so that its L2 sees one head or two
     const int nblk = (n + 31) >> 5;
-    const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, per_xcd = (int64_t)gridDim.x * gridDim.y >> 3;
-    const int64_t item = (block & 7) * per_xcd + (block >> 3);
-    if (item >= (int64_t)nblk * nbh) return;
-    const int bh = (int)(item / nblk), q0 = (int)(item % nblk) * 32;
+    // (less than 2^32 of them: every 32 sampled rows come with K rows of 4096 bytes and more)
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x, per_xcd = gridDim.x * gridDim.y >> 3, item = (block & 7u) * per_xcd + (block >> 3);
+    const int bh = (int)(item / (uint32_t)nblk), q0 = (int)(item - (uint32_t)bh * nblk) * 32;
+    if (bh >= nbh) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int nq = lane & 31;                        // the query that a thread searches for
     const int ql = lane & 15, g = lane >> 4;         // in the sweeps: a lane's queries are ql and 16 + ql
