@@ -450,8 +450,9 @@ __global__ __launch_bounds__(64 * kWaves) void count_t_kernel(const T *__restric
 }
 
 // The lists, starting at col[bh, j].
-// (Rows of 128 bytes: a third wave per SIMD for 6 registers less; 24 heads of 2304, 6 query tiles, the selection 129 -> 124 us together with expand_few.)
-template <typename T, int R>
+// FEW: at most kFewTiles query tiles.  (Rows of 128 bytes: a third wave per SIMD for 6 registers less; 24 heads of 2304, 6 query tiles, the selection
+// 129 -> 124 us together with expand_few.)
+template <typename T, int R, bool FEW>
 __global__ __launch_bounds__(64 * kWaves, R * sizeof(T) == 128 ? 3 : 1) void emit_t_kernel(const T *__restrict__ Qlr, const T *__restrict__ Klr, int Lq, int L, HeadTable tab,
                                                              const float *__restrict__ tau_f, const int32_t *__restrict__ jcut,
                                                              const int32_t *__restrict__ tile_flag, const int64_t *__restrict__ col,
@@ -515,7 +516,7 @@ __global__ __launch_bounds__(64 * kWaves, R * sizeof(T) == 128 ? 3 : 1) void emi
 #pragma unroll
         for (int i = 0; i < 2; ++i) sh.count[buf][wave][i][lane] = count[i];
         __syncthreads();  // (two rounds in turn: what is written next was last read before this barrier)
-        if (ntiles <= kFewTiles) {
+        if constexpr (FEW) {  // one round
 #pragma unroll
             for (int i = 0; i < 2; ++i)
                 if (lane < 32) sh.place[wave][32 * i + lane] = make_int2(at[i], end[i]);
@@ -582,8 +583,11 @@ static dsv_status emit_all_t(const dsv_problem &p, int Lq, const HeadTable *tabs
         KernelSpan span(DSV_KERNEL_EMIT_T_WRITE, st);
         for (int t = 0; t < n_tabs; ++t) {
             dim3 grid((tiles + 1) / 2, tabs[t].n);
-            hipLaunchKernelGGL((emit_t_kernel<T, R>), grid, dim3(64 * kWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], tau_f, b.jcut, b.tile_flag,
-                               b.col, b.idx_t);
+            auto lists = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), 0, st, Ql, Kl, Lq, p.L, tabs[t], tau_f, b.jcut, b.tile_flag, b.col, b.idx_t);
+            };
+            if (qtiles <= kFewTiles) lists(emit_t_kernel<T, R, true>);
+            else lists(emit_t_kernel<T, R, false>);
             DSV_LAUNCH_CHECK();
         }
     }
