@@ -15,7 +15,7 @@
 //
 // Both kinds of contraction run on the matrix cores: the Gram matrix in the storage type with fp32 sums over at most
 // 512 tokens (v_mfma_f32_32x32x16_bf16 / 32x32x2_f32), everything behind it in fp64 (v_mfma_f64_16x16x4_f64).
-// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 136 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 41, accum 18; 160 with
+// L = 131072, 6 heads, 8192 rows each, bf16, r = 16: 143 us in all, of them gram_partial 48 (K at 4.2 TB/s), rows 41, accum 18; 167 with
 // the weights' products and the loss in kernels and loops of their own, all of M in the rows' forms and half the blocks in accum.
 // L = 3000, one head, 250 rows, d = 64: 66 -> 35 us.
 #include <algorithm>

@@ -17,7 +17,7 @@
 // order of arrival.
 // Sweeps were bound by accesses to the vector cache, one per 16 bytes where lanes read an operand's rows: key tiles go through LDS now, whole
 // lines at a time, and the sweeps are vector work (the exponentials and a bin per score) and matrix work again.  L = 32768, four heads, 2048
-// rows each, bf16: 800 -> 550 us; two heads of 20280, 1000 rows: 490 -> 315; fp32, d = 128, two heads of 10000, 700 rows (4-byte loads of 32 rows
+// rows each, bf16: 800 -> 515 us; two heads of 20280, 1000 rows: 490 -> 315; fp32, d = 128, two heads of 10000, 700 rows (4-byte loads of 32 rows
 // before, 16-byte ones of 16 rows now): 1750 -> 700.  A count differs from that in 64 bits in 25 of 82000 rows (37 before the sum of
 // exponentials kept what its additions lose), by one.
 #include <algorithm>
